@@ -21,12 +21,7 @@
  *   - Functions returning int / int64_t return a negative monet_status on
  *     failure; monet_last_error() then holds a message naming the violated
  *     constraint or the failing call.  No C++ exception crosses this boundary.
- *   - A plan is not re-entrant: one monet_step at a time per plan.  Beyond that, one step at a
- *     time per process and GPU: convolution launches whose last round of tiles is cut count
- *     their arrivals in one table inside the library, so two steps (of one plan or of two) that
- *     overlap in time on different streams of one GPU would corrupt each other's results.
- *     monet_step zeroes that table at its start, so a step that was broken off by an error
- *     leaves nothing behind for the next one.
+ *   - A plan is not re-entrant: one monet_step at a time per plan.
  *   - A BatchNorm backward implementation 'from_output' recovers the normalised input as
  *     (y - beta) / gamma (Section 4, "Backward Operator Optimization"): every gamma of such a layer
  *     must be non-zero, otherwise its gradients are not finite.  The library does not check the

@@ -26,22 +26,19 @@ extern "C" {
  * for layers whose result is small, at the price of workspace (device memory, contents irrelevant before and
  * after the call).  The partial results are always added in range order, so a result depends on `splits` and
  * the workspace size only.
- *   splits > 1: ws >= splits * |result| floats; a second kernel adds the partial results.
- *   fwd, dgrad with splits == 1 and a workspace: only the tiles of the ragged last round (beyond a multiple of
- *     the 256 CUs) are cut, as far as the workspace allows (monet_conv_workspace_bytes gives the useful size);
- *     their partial tiles wait in ws and the workgroup that finishes a tile last adds them.  Arrival counts live
- *     in a table inside the library: convolution calls that overlap in time on one GPU (different streams) must
- *     not both pass such a workspace.  With ws == NULL nothing is cut.
+ *   splits > 1: ws >= splits * |result| floats; a second kernel adds the partial results.  A launch uses fewer ranges than
+ *     it is given where more would only cost partial results.
+ *   splits == 1: the reduction is not cut; a workspace is accepted and left alone.
+ * Products are exact fp32 products to about 2^-25 (three bf16 pieces per operand on the matrix cores), sums are fp32; infinities and
+ * NaNs come out as the fp32 product's.
  * Appendix D's workspace / speed trade-off of convolution algorithms is this choice.
  *
  * y[N,P,Q,K] = cross-correlation of x[N,H,W,C] with w[K,R,S,C], zero padding, no bias. */
 int monet_conv_fwd(void *stream, const float *x, const float *w, float *y,
                    int N, int H, int W, int C, int K, int R, int S, int stride, int pad,
                    int splits, float *ws, size_t ws_bytes);
-/* Puts the arrival table of the cut tiles back to zero (one small kernel on `stream`).  The convolution kernels leave
- * every entry at zero when they finish; a caller whose sequence of launches was broken off by an error (or by a reset of
- * the stream) calls this before the next monet_conv_fwd / monet_conv_dgrad that passes a workspace with splits == 1.
- * monet_step does it at the start of every step. */
+/* Kept for callers of earlier versions, whose convolution kernels counted arrivals in a table inside the library: there is
+ * nothing to reset any more.  Always 0. */
 int monet_conv_reset_arrivals(void *stream);
 /* monet_conv_fwd followed by monet_bn_stats of its output, with the statistics' first level computed in the
  * convolution's epilogue instead of a pass over y (the largest of the fusions the executor applies between a
@@ -147,7 +144,7 @@ int monet_conv_winograd_wgrad(void *stream, const float *x, const float *dy, flo
                               int m, float *ws, size_t ws_bytes);
 int64_t monet_conv_winograd_wgrad_workspace_bytes(int N, int H, int W, int C, int K, int m);
 /* Workspace bytes for monet_conv_fwd (which = 0) / monet_conv_dgrad (which = 1) of this shape with `splits` ranges;
- * for splits == 1 the size that lets the ragged last round be cut as far as it pays (0: nothing to gain).
+ * for splits == 1 the size that earlier versions used for the ragged last round of tiles (0: none; it is no longer needed).
  * Negative: error code. */
 int64_t monet_conv_workspace_bytes(int which, int N, int H, int W, int C, int K, int R, int S, int stride, int pad, int splits);
 /* dx[N,H,W,C] (+)= gradient of the above wrt x, from dy[N,P,Q,K]. */

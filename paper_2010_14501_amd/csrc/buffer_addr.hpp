@@ -13,6 +13,12 @@ typedef float bf4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000);
 }
+// The same for a tensor of `bytes` bytes: a load at an offset beyond them reads zero and touches no memory (the hardware's
+// range check of raw buffers); BUFFER_ABSENT is such an offset for every tensor below 4 GiB - 16 bytes.
+constexpr unsigned BUFFER_ABSENT = 0xfffffff0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
 __device__ __forceinline__ float buffer_load(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));
 }

@@ -1,5 +1,5 @@
-// Convolution forward, input-gradient and weight-gradient as implicit GEMMs on the fp32
-// matrix cores of gfx950 (v_mfma_f32_32x32x2_f32), NHWC activations, KRSC filters.
+// Convolution forward, input-gradient and weight-gradient as implicit GEMMs on the matrix cores of gfx950, NHWC fp32
+// activations, KRSC fp32 filters; fp32 products from bf16 instructions (v_mfma_f32_32x32x16_bf16), see below.
 //
 //   forward : Y[m, k]   = sum_{r,s,c} X[n, p*st+r-pad, q*st+s-pad, c] * W[k, r, s, c]     m = (n,p,q)
 //   dgrad   : dX[m, c]  = sum_{r,s,k} dY[n, (h+pad-r)/st, (w+pad-s)/st, k] * W[k, r, s, c] m = (n,h,w)
@@ -11,14 +11,16 @@
 // time trade-off the schedule chooses between (Section 4, "Forward/Backward Operator
 // Optimization").
 //
-// One workgroup computes a (64*WM) x (64*WN) tile with WM*WN waves, each wave a 64x64 sub-tile
-// as 2x2 MFMA blocks.  The reduction runs in steps of 16, double-buffered through LDS: global
-// loads for step t+1 are issued into registers before step t's MFMAs and written to the other
-// LDS buffer afterwards.  An operand whose reduction index is contiguous in memory is kept
-// [row][16+4] in LDS and read as one 128-bit load per lane (lane group g = lane/32 takes
-// reduction indices 8h+4g..8h+4g+3); the MFMA pairs index 8h+4g+j of both operands, so the
-// order of the sum inside a step is permuted but complete.  An operand contiguous along its
-// row/column index is kept [16][cols+4] and read with 32-bit loads under the same pairing.
+// One workgroup computes a (64*WM) x (32*WN) tile with WM*WN waves, each wave a 64x32 sub-tile as two 32x32 MFMA blocks.  The
+// reduction runs in steps of 16, double-buffered through LDS: while step t is multiplied, step t+1 is split and written
+// to the other LDS buffer, and the loads of step t+2 (t+3) are issued into the registers it leaves.  LDS holds each operand as three
+// planes of bf16 pieces, two neighbouring reduction indices per 32-bit word; an operand contiguous along its row / column index
+// in memory is paired on the way in.
+//
+// What bounds it: on large layers the power limit (3x3, 256 -> 256, 56x56, batch 176: 205 TFLOP/s = 1.23 PFLOP/s of bf16
+// instructions at 1.4 - 1.7 GHz; torch's own bf16 matmul of 8192 reaches 1.14, of 16384 1.36), against 134 TFLOP/s with the fp32
+// instruction; on small ones the length of one step (0.7 - 0.8 us from load to barrier), so that half of the peak needs two
+// workgroups per CU; on layers with few channels memory.
 //
 // The position of a reduction step -- (r, s, c0) forward, (tap, k0) dgrad, (n, p, q) of each
 // staged row for wgrad -- is carried from step to step by increments; no integer division is
@@ -47,8 +49,58 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 namespace {
 
 constexpr int BK = 16;        // reduction step
-constexpr int KC_LD = BK + 4; // row stride of a reduction-contiguous operand in LDS (floats)
 constexpr int NUM_XCD = 8;
+
+// ---- fp32 products on the bf16 matrix cores
+// A float is the sum of three bf16 numbers (8 + 8 + 8 significant bits, each remainder is exact in fp32): x = h + m + l.  A
+// product keeps the six terms h*h, h*m, m*h, m*m, h*l, l*h; the three left out are below 2^-25 of it.  Every term is exact
+// in the matrix unit and the sums are fp32, so the result is as close to 64 bits as the fp32 matrix instruction's (fewer
+// roundings: six per 16 products instead of one per product; measured side by side, normwise error of one layer).
+// Six bf16 instructions take 192 cycles for what the fp32 instruction does in 512.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+struct Pieces { unsigned h, m, l; };     // two neighbouring reduction indices: low half first
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {       // to nearest
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
+__device__ __forceinline__ Pieces split_pair(float a, float b) {
+    Pieces p;
+    p.h = pack_bf16(a, b);
+    const float a1 = a - __uint_as_float(p.h << 16), b1 = b - __uint_as_float(p.h & 0xffff0000u);
+    p.m = pack_bf16(a1, b1);
+    p.l = pack_bf16(a1 - __uint_as_float(p.m << 16), b1 - __uint_as_float(p.m & 0xffff0000u));
+    return p;
+}
+// The same for operands that hold infinities, NaNs or values that round to infinity in bf16 (taken only after a first pass
+// has left an infinity or a NaN in the result).  All pieces are truncated, so they have the number's sign and the six terms of an
+// overflowing product agree; an infinity or a NaN travels in the piece that meets only the other operand's h, and stands
+// as +-1 where the other operand's infinity meets it.
+__device__ __forceinline__ void split_special(float x, unsigned &h, unsigned &m, unsigned &l) {
+    const unsigned u = __float_as_uint(x);
+    const bool bad = (u & 0x7f800000u) == 0x7f800000u;
+    const float hf = __uint_as_float(bad ? (u & 0x80000000u) | 0x3f800000u : u & 0xffff0000u);
+    const float r = bad ? 0.0f : x - hf;
+    const float mf = __uint_as_float(__float_as_uint(r) & 0xffff0000u);
+    h = __float_as_uint(hf) >> 16;
+    m = __float_as_uint(mf) >> 16;
+    l = bad ? (u >> 16) | ((u & 0x007fffffu) ? 0x40u : 0u) : __float_as_uint(r - mf) >> 16;
+}
+__device__ __forceinline__ Pieces split_pair_special(float a, float b) {
+    unsigned h0, m0, l0, h1, m1, l1;
+    split_special(a, h0, m0, l0);
+    split_special(b, h1, m1, l1);
+    return {h0 | h1 << 16, m0 | m1 << 16, l0 | l1 << 16};
+}
+// LDS tile of one operand: three planes (h, m, l) of 32-bit words that hold two neighbouring reduction indices.
+//   reduction contiguous in memory: [k / 8][row][(k % 8) / 2], one 16-byte read per lane; the second half 64 bytes further on, so that the
+//     four lanes that write one row's 16 indices do not meet in a bank
+//   row / column contiguous: [k / 2][column], four 4-byte reads per lane
+constexpr int kc_half(int rows) { return rows * 4 + 16; }
+constexpr int rc_row(int cols) { return cols + 4; }
+constexpr int plane_words(bool kc, int n) { return kc ? 2 * kc_half(n) : 8 * rc_row(n); }
 
 enum ConvMode { FWD = 0, DGRAD = 1, WGRAD = 2 };
 
@@ -65,14 +117,9 @@ struct TileArgs {
     int splits;                // reduction splits (>= 1); split z writes partial result z
     int64_t out_elems;         // elements of one (partial) result
     int accumulate;            // FWD/DGRAD, whole result only: add into the output
-    // Split tiles that meet inside the kernel (FWD/DGRAD): tiles [main_tiles, total_tiles) are cut into
-    // meet_splits reduction ranges, each workgroup leaves its partial tile in `part`, and the one that
-    // arrives last adds the parts in range order and writes the result.  Tiles below main_tiles are whole.
-    int64_t main_tiles;        // multiple of 8
-    int meet_splits;           // <= 1: off
-    float *part;               // (class, tile - main_tiles, range) x 64 x threads floats, register order
     float *stats_part;         // FWD, whole results only: BatchNorm partial statistics of the output (tile_stats.hpp), or null
     BnAffine affine;           // FWD, whole results only: BatchNorm apply step of the output in the epilogue (gamma == null: off)
+    unsigned a_bytes, b_bytes;             // operand sizes for the aligned loaders' descriptors: an element that does not exist is a load beyond them and reads zero
     int64_t batch_a, batch_b, batch_out;   // FWD / WGRAD with gridDim.z > 1: z-th GEMM of a batch, operands and result this many floats apart
     // decoding a row index into (image, row, column) without a division: floor(n / Q) = umulhi(n, q_mul) >> q_shift for
     // n < 2^31 (Q >= 2), likewise P (forward rows, the filter gradient's reduction rows) and W, H (input-gradient rows at
@@ -80,41 +127,35 @@ struct TileArgs {
     unsigned q_mul, q_shift, p_mul, p_shift, w_mul, w_shift, h_mul, h_shift;
 };
 
-// arrivals per split tile; zero whenever no convolution kernel is running (the last arrival puts its entry back)
-constexpr int MEET_SLOTS = 1 << 16;
-__device__ unsigned g_meet_arrivals[MEET_SLOTS];
-
-// puts every entry back to zero (a step that ended in an error may have left counts behind)
-__global__ __launch_bounds__(256) void meet_reset_kernel() { g_meet_arrivals[blockIdx.x * 256 + threadIdx.x] = 0; }
-
 __device__ inline float4 ld4(const float *p) { return *(const float4 *)p; }
 
 // TAG only names the use in profiles: 0 a convolution, 1 / 2 / 3 the batched GEMMs of a Winograd forward / input gradient /
 // filter gradient
 // FAST: 0 element-wise loaders, 1 aligned loaders, 2 aligned loaders of a 1x1 layer whose last reduction step is partly
-// empty (a kernel of its own: the two tests per step would cost the other layers 2 %, measured on ResNet-50)
+// empty (a kernel of its own: the two tests per step would cost the other layers 2 %, measured on ResNet-50), 3 aligned
+// loaders of a larger filter over channels that are a multiple of 4 but not of 16: a step straddles filter taps, every
+// lane carries the tap and channel of its four reduction indices, 4 as 1 for reductions of at most six steps (5x5 filter, 24 -> 64 channels, 14x14 maps, batch 320:
+// 160 -> 38 us forward, 134 -> 82 us input gradient against the element-wise loaders)
 template <int MODE, int WM, int WN, int FAST, int TAG = 0>
-__global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN == 4 ? 3 : 2))) void conv_tile_kernel(TileArgs ta) {
-    // The square four-wave tile runs four workgroups per CU (4 x 40 KiB of LDS, 128 registers per lane) and
-    // prefetches one reduction step; the other tiles keep two register stages (loads two steps ahead) at three
-    // (256x64, 64x256: 50 KiB of LDS) or two waves per SIMD.  Measured on the ResNet-50 layer set: 4 waves /
-    // 1 stage beats 3 waves / 2 stages by 2-3 % for the square tile.
-    constexpr int STAGES = (WM == 2 && WN == 2) ? 1 : 2;
-    constexpr int BM = 64 * WM, BN = 64 * WN, NT = 64 * WM * WN;
+__global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 4 ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
+    // Register stages of the aligned variants: loads run this many steps ahead of the split.  The tiles of at most four waves take
+    // two at three waves per SIMD (1x1, 1024 -> 256, 14x14, batch 184: 123 against 142 us with one), the larger ones, and short
+    // reductions, which live from many workgroups at once (64 -> 256, 56x56: 214 against 245 us), one at four (128 registers).
+    constexpr int STAGES = (FAST == 1 || FAST == 3) && WM * WN <= 4 ? 2 : 1;
+    constexpr int BM = 64 * WM, BN = 32 * WN, NT = 64 * WM * WN;
     constexpr bool A_KC = (MODE != WGRAD);          // A operand reduction-contiguous?
     constexpr bool B_KC = (MODE == FWD);
-    constexpr int A_LD = A_KC ? KC_LD : BM + 4;
-    constexpr int B_LD = B_KC ? KC_LD : BN + 4;
-    constexpr int A_SZ = A_KC ? BM * KC_LD : BK * (BM + 4);
-    constexpr int B_SZ = B_KC ? BN * KC_LD : BK * (BN + 4);
-    constexpr int LA = BM * 4 / NT;                 // float4 slots per thread, A tile
-    constexpr int LB = BN * 4 / NT;
-    __shared__ float As[2][A_SZ];
-    __shared__ float Bs[2][B_SZ];
+    constexpr int A_PL = plane_words(A_KC, BM), B_PL = plane_words(B_KC, BN);
+    constexpr int A_SZ = 3 * A_PL, B_SZ = 3 * B_PL;
+    // float4 slots of an operand's tile per thread; a tile with fewer slots than threads is loaded twice (same value, same place)
+    constexpr int SA = BM * 4, SB = BN * 4, LA = SA >= NT ? SA / NT : 1, LB = SB >= NT ? SB / NT : 1;
+    __shared__ __attribute__((aligned(16))) unsigned As[2][A_SZ];
+    __shared__ __attribute__((aligned(16))) unsigned Bs[2][B_SZ];
+    __shared__ int redo;     // a first pass left an infinity or a NaN: once more with the special split
     // First layers (3 input channels): the element-wise forward loader looks the (r, s, c) of a reduction index up
-    // instead of dividing (measured 925 -> 815 us on the ResNet-50 stem).  Only the four-wave non-square tiles have
+    // instead of dividing (measured 925 -> 815 us on the ResNet-50 stem).  Only the 64 columns wide tiles have
     // the LDS to spare (2 KiB), and those are the ones results up to 64 channels wide, i.e. every first layer, use.
-    constexpr bool HAS_KTAB = !FAST && MODE == FWD && WM * WN == 4 && !(WM == 2 && WN == 2);
+    constexpr bool HAS_KTAB = !FAST && MODE == FWD && BN == 64;
     constexpr int KTAB = 256;
     __shared__ int2 ktab[HAS_KTAB ? KTAB : 1];   // x = ((r*W + s)*C + c), y = r | s << 8, or y < 0 beyond the reduction
     // Aligned filter gradient: the BK output positions a reduction step covers, decoded once per step by 16 lanes for
@@ -132,39 +173,19 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, g = lane >> 5;
+    const int tid_a = SA < NT ? tid % SA : tid, tid_b = SB < NT ? tid % SB : tid;
 
     // XCD-aware order of the (tile, split) work items
-    int nsplit = ta.splits, split;
-    int64_t logical;
-    bool meet = false;
-    if (MODE != WGRAD && ta.meet_splits > 1) {
-        // every XCD takes its share of the whole tiles first, then its share of the split ones, so the short
-        // items come last everywhere and fill the ragged end of the launch
-        const int64_t xcd = blockIdx.x % NUM_XCD, idx = blockIdx.x / NUM_XCD;
-        const int64_t pm = ta.main_tiles / NUM_XCD;
-        if (idx < pm) {
-            logical = xcd * pm + idx;
-            split = 0;
-            nsplit = 1;
-        } else {
-            const int64_t nt = (ta.total_tiles - ta.main_tiles) * ta.meet_splits;
-            const int64_t pt = (nt + NUM_XCD - 1) / NUM_XCD;
-            const int64_t j = xcd * pt + (idx - pm);
-            if (idx - pm >= pt || j >= nt) return;
-            logical = ta.main_tiles + j / ta.meet_splits;
-            split = (int)(j % ta.meet_splits);
-            nsplit = ta.meet_splits;
-            meet = true;
-        }
-    } else {
-        const int64_t per_xcd = gridDim.x / NUM_XCD;
-        const int64_t item = (int64_t)(blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
-        if (item >= ta.total_tiles * nsplit) return;
-        split = (int)(item / ta.total_tiles);
-        logical = item - (int64_t)split * ta.total_tiles;
-    }
-    const int tile_n = (int)((unsigned)logical % (unsigned)ta.tiles_n);      // the host bounds the tile count below 2^31
-    const int64_t tile_m = (unsigned)logical / (unsigned)ta.tiles_n;
+    const int nsplit = ta.splits;
+    // all indices of work items and reduction steps are 32 bits wide (bounded by the host): a 64-bit division is 150 scalar
+    // instructions, and four of them per wave were a microsecond of every tile
+    const unsigned tiles = (unsigned)ta.total_tiles;
+    const unsigned item = blockIdx.x % NUM_XCD * (gridDim.x / NUM_XCD) + blockIdx.x / NUM_XCD;
+    if (item >= tiles * (unsigned)nsplit) return;
+    const int split = nsplit > 1 ? (int)(item / tiles) : 0;
+    const unsigned logical = item - (unsigned)split * tiles;
+    const int64_t tile_m = logical / (unsigned)ta.tiles_n;
+    const int tile_n = (int)(logical - (unsigned)tile_m * (unsigned)ta.tiles_n);
     const int64_t row0 = tile_m * BM;
     const int col0 = tile_n * BN;
     const int RSC = (int)cs.RSC();
@@ -194,23 +215,25 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
 
     // reduction range of this workgroup: split z takes steps [z*sps, (z+1)*sps) (possibly none: it
     // then contributes zeros to its partial result)
-    int64_t kt0 = 0, kt1 = (Kg + BK - 1) / BK;
+    int kt0 = 0, kt1 = (int)(((unsigned)Kg + BK - 1) / BK);
     if (nsplit > 1) {
-        const int64_t sps = (kt1 + nsplit - 1) / nsplit;
-        kt0 = split * sps;
-        int64_t e = kt0 + sps;
-        kt1 = e < kt1 ? e : kt1;
+        const int sps = (int)(((unsigned)kt1 + (unsigned)nsplit - 1) / (unsigned)nsplit);
+        kt0 = min(split * sps, kt1);       // split * sps < steps + splits * splits / 16: far below 2^31
+        kt1 = min(kt0 + sps, kt1);
     }
 
     // ---------------- per-slot constants of the A loader
     // reduction-contiguous A (FWD / DGRAD): slot = (row, float4 j): idx = tid + s*NT, row = idx/4, j = idx%4
-    // row-contiguous A (WGRAD)            : slot = (red row, float4 along k): red = idx/(BM/4), k4 = idx%(BM/4)
+    // row-contiguous operand (L slots per thread, n rows or columns): slots 2u, 2u + 1 are the float4 at the same column of two
+    // neighbouring reduction indices, which share a word in LDS; with one slot per thread the neighbour sits n / 4 lanes away
+    auto rc_red = [&](int t, int s, int L, int n) { return L == 1 ? t / (n / 4) : 2 * ((t + (s >> 1) * NT) / (n / 4)) + (s & 1); };
+    auto rc_col4 = [&](int t, int s, int L, int n) { return L == 1 ? t % (n / 4) : (t + (s >> 1) * NT) % (n / 4); };
     int64_t a_base[LA];   // FWD/DGRAD: image base + j4; WGRAD: unused
     int a_h0[LA], a_w0[LA];
     bool a_ok[LA];
 #pragma unroll
     for (int s = 0; s < LA; ++s) {
-        int idx = tid + s * NT;
+        int idx = tid_a + s * NT;
         if (A_KC) {
             int64_t m = row0 + idx / 4;
             a_ok[s] = m < Mg;
@@ -243,8 +266,8 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 a_base[s] = (int64_t)n * cs.P * cs.Q * cs.K + (idx % 4) * 4;
             }
         } else {
-            int k4 = idx % (BM / 4);
-            a_h0[s] = idx / (BM / 4);                       // red row within the step
+            int k4 = rc_col4(tid_a, s, LA, BM);
+            a_h0[s] = rc_red(tid_a, s, LA, BM);                    // red row within the step
             a_w0[s] = (int)(row0 + k4 * 4);                 // first out-channel of the float4
             a_ok[s] = a_w0[s] < cs.K;
             a_base[s] = 0;
@@ -257,7 +280,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
     int w_n[LB], w_p[LB], w_q[LB];
 #pragma unroll
     for (int s = 0; s < LB; ++s) {
-        int idx = tid + s * NT;
+        int idx = tid_b + s * NT;
         w_n[s] = w_p[s] = w_q[s] = 0;
         if (B_KC) {          // FWD: slot = (filter k, float4 j)
             b_i0[s] = col0 + idx / 4;
@@ -265,9 +288,9 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
             b_i1[s] = (idx % 4) * 4;
             b_i2[s] = 0;
         } else {             // slot = (red row, float4 along the column index)
-            int c4 = idx % (BN / 4);
+            int c4 = rc_col4(tid_b, s, LB, BN);
             int col = col0 + c4 * 4;
-            b_i0[s] = idx / (BN / 4);                       // red row within the step
+            b_i0[s] = rc_red(tid_b, s, LB, BN);                    // red row within the step
             if (MODE == DGRAD) {
                 b_i1[s] = col;                              // input channel c
                 b_ok[s] = col < cs.C;
@@ -281,14 +304,6 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 // tap (r, s) packed for the bounds test
                 b_i1[s] |= (rs / cs.S) << 24;
                 b_i2[s] |= (rs % cs.S) << 24;
-                if (!FAST) {
-                    int64_t m = kt0 * BK + b_i0[s];
-                    int64_t mm = m < Kg ? m : 0;
-                    const unsigned m32 = (unsigned)mm, t = m32 / (unsigned)cs.Q;
-                    w_q[s] = (int)(m32 % (unsigned)cs.Q);
-                    w_p[s] = (int)(t % (unsigned)cs.P);
-                    w_n[s] = (int)(t / (unsigned)cs.P);
-                }
             }
         }
     }
@@ -319,11 +334,11 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 if (MODE == FWD ? (unsigned)(a_w0[s] + c) < (unsigned)cs.W : (unsigned)(a_w0[s] - c) < (unsigned)cs.Q) cols |= 1u << c;
             for (int r = 0; r < tr; ++r)
                 if ((rows >> r) & 1) taps |= cols << (r * ts);
-            a_taps[s] = a_ok[s] ? taps : 0u;
+            a_taps[s] = a_ok[s] ? taps : 0u;      // a row beyond the tensor has no tap
         }
 #pragma unroll
         for (int s = 0; s < LB; ++s)
-            b_voff[s] = b_ok[s] ? (unsigned)(((int64_t)b_i0[s] * RSC + b_i1[s]) * 4) : 0u;      // an absent filter row reads the tensor's start
+            b_voff[s] = b_ok[s] ? (unsigned)(((int64_t)b_i0[s] * RSC + b_i1[s]) * 4) : BUFFER_ABSENT;
     }
     // Aligned filter gradient: dy rows advance by a scalar offset; the window of an output position comes from the
     // row table, the slot adds its tap and channel and tests its tap's bit.  The input descriptor starts b_shift floats
@@ -333,7 +348,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
     if (FAST && MODE == WGRAD) {
         b_shift = ((int64_t)cs.pad * cs.W + cs.pad) * cs.C;
 #pragma unroll
-        for (int s = 0; s < LA; ++s) a_voff[s] = a_ok[s] ? (unsigned)(((int64_t)a_h0[s] * cs.K + a_w0[s]) * 4) : 0u;
+        for (int s = 0; s < LA; ++s) a_voff[s] = a_ok[s] ? (unsigned)(((int64_t)a_h0[s] * cs.K + a_w0[s]) * 4) : BUFFER_ABSENT;
 #pragma unroll
         for (int s = 0; s < LB; ++s) {
             const int r = b_i1[s] >> 24, ss = b_i2[s] >> 24;
@@ -341,18 +356,24 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
             w_tapbit[s] = b_ok[s] ? 1u << (r * cs.S + ss) : 0u;
         }
     }
-    const __amdgpu_buffer_rsrc_t ra = buffer_of(ta.a - a_shift), rb = buffer_of(ta.b - b_shift);
+    // FAST == 3: reduction index of this lane's float4 (A; FWD's B has the same) or filter row (DGRAD's B) in the step to load, as
+    // (tap, channel), and the tap's offset
+    struct LaneTap { int at, c, row, col; unsigned bit, off; };
+    constexpr int UB3 = LB == 1 ? 1 : LB / 2;
+    LaneTap la3, lb3[UB3];
+    __amdgpu_buffer_rsrc_t ra = buffer_of(ta.a - a_shift, ta.a_bytes + (unsigned)a_shift * 4u),
+                           rb = buffer_of(ta.b - b_shift, ta.b_bytes + (unsigned)b_shift * 4u);
     int w_slot = 0;   // row table entry the next load_tiles reads
     // Decodes the output positions of reduction step `step`: the last wave alone, every lane the entry lane % BK (four
     // lanes write the same value), and no lane switched off on the way (the branch is uniform over the wave, the
     // rest are selects).  Measured: a version in which only 16 lanes ran this code, under a narrowed execution mask
     // while the step's loads were still in flight, now and then lost one row of a step on the two-wave tile shapes
     // when several workgroups shared a compute unit; this version does not (kernel test with many short ranges).
-    auto fill_rows = [&](int64_t step, int slot) {
+    auto fill_rows = [&](int step, int slot) {
         if (ROWTAB && __builtin_amdgcn_readfirstlane(tid >> 6) == NT / 64 - 1) {
             const int e = tid & (BK - 1);
-            const int64_t m = step * BK + e;
-            const bool in = m < Kg;
+            const int m = step * BK + e;
+            const bool in = m < (int)Kg;
             const unsigned m32 = in ? (unsigned)m : 0u;
             const unsigned t = cs.Q == 1 ? m32 : __umulhi(m32, ta.q_mul) >> ta.q_shift;
             const unsigned q = m32 - t * (unsigned)cs.Q;
@@ -370,15 +391,46 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
     };
 
     // ---------------- position of the next step to load (uniform over the workgroup)
-    int64_t kk0 = kt0 * BK;
-    int u_r = 0, u_s = 0, u_c = 0;   // FWD: (r, s, c0); DGRAD: (tap row, tap column, k0)
-    if (MODE != WGRAD && kt0 > 0) {  // a later reduction split starts in the middle: locate it once
-        const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns;
-        int tap = (int)(kk0 / inner);
-        u_c = (int)(kk0 % inner);
-        u_r = tap / cols;
-        u_s = tap % cols;
-    }
+    int kk0;
+    int u_r, u_s, u_c;   // FWD: (r, s, c0); DGRAD: (tap row, tap column, k0)
+    auto to_start = [&] {
+        kk0 = kt0 * BK;
+        u_r = u_s = u_c = 0;
+        if (MODE != WGRAD && kt0 > 0) {  // a later reduction split starts in the middle: locate it once
+            const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns;
+            const int tap = (int)((unsigned)kk0 / (unsigned)inner);
+            u_c = kk0 - tap * inner;
+            u_r = tap / cols;
+            u_s = tap % cols;
+        }
+        if constexpr (FAST == 3) {
+            auto place = [&](LaneTap &t, int at) {
+                const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : max(ns, 1), taps = MODE == FWD ? cs.R * cs.S : nr * ns;
+                const int tap = at / inner;
+                t.at = at;
+                t.c = at - tap * inner;
+                t.row = tap / cols;
+                t.col = tap - t.row * cols;
+                t.bit = tap < taps ? 1u << tap : 0u;
+            };
+            place(la3, kk0 + (tid % 4) * 4);
+            if (MODE == DGRAD) {
+#pragma unroll
+                for (int u = 0; u < UB3; ++u) place(lb3[u], kk0 + b_i0[LB == 1 ? 0 : 2 * u]);
+            }
+        }
+        if (MODE == WGRAD && !FAST) {
+#pragma unroll
+            for (int s = 0; s < LB; ++s) {
+                const int64_t m = kk0 + b_i0[s];
+                const unsigned m32 = m < Kg ? (unsigned)m : 0u, t = m32 / (unsigned)cs.Q;
+                w_q[s] = (int)(m32 % (unsigned)cs.Q);
+                w_p[s] = (int)(t % (unsigned)cs.P);
+                w_n[s] = (int)(t / (unsigned)cs.P);
+            }
+        }
+    };
+    to_start();
 
     const bool use_ktab = HAS_KTAB && (ta.Kg + BK - 1) / BK * BK <= KTAB;
     if (HAS_KTAB && use_ktab) {
@@ -394,38 +446,47 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
         __syncthreads();
     }
 
-    float4 a_set0[LA], b_set0[LB], a_set1[LA], b_set1[LB];   // two register stages: loads run two steps ahead
+    float4 a_regs[STAGES][LA], b_regs[STAGES][LB];
+    unsigned long long w_row[LB];       // aligned filter gradient: the table entries of this lane's B slots
 
-    // In the aligned variants every load is issued unconditionally (an out-of-range slot reads the
-    // tensor's first 16 bytes instead) and zeroed when it is written to LDS: without branches around
-    // the loads the compiler can count outstanding loads exactly and wait only for the older stage.
-    // pm: which slots hold data (lane masks, kept in scalar registers).
-    struct Present { bool a[LA], b[LB]; };
-    auto load_tiles = [&](float4 (&a_reg)[LA], float4 (&b_reg)[LB], Present &pm, int &full) {
-        bool every = FAST;      // every slot of this lane holds data
+    // In the aligned variants every load is issued unconditionally: one of an absent element (padding, rows beyond the tensor) goes
+    // to an offset beyond the descriptor and reads zero, so neither a branch around it nor a select behind it is needed.
+    int left;                           // reduction indices of the step being loaded (BK but for the last one of some layers)
+    bool part_step;
+    auto begin_load = [&] {
+        if constexpr (FAST == 3) {
+            // the tap's offset from the slot's: FWD forwards in the image, DGRAD backwards (the descriptor starts a_shift floats early)
+            la3.off = MODE == FWD ? (unsigned)(((la3.row * cs.W + la3.col) * cs.C + la3.c) * 4)
+                                  : (unsigned)(((int)a_shift - (la3.row * cs.Q + la3.col) * cs.K + la3.c) * 4);
+            if (MODE == DGRAD) {
+#pragma unroll
+                for (int u = 0; u < UB3; ++u)
+                    lb3[u].off = ((unsigned)lb3[u].c * (unsigned)RSC + (unsigned)(((r0 + cs.stride * lb3[u].row) * cs.S + s0 + cs.stride * lb3[u].col) * cs.C)) * 4u;
+            }
+        }
         // 1x1 layers whose reduction length is a multiple of 4 only: the last step holds `left` < 16 reduction indices
         // (uniform over the workgroup; every other step, and every step of the other layers, is whole)
-        const int left = (int)(Kg - kk0 < BK ? Kg - kk0 : BK);
-        const bool part_step = FAST == 2 && MODE != WGRAD && left < BK;
-        // aligned filter gradient: the table entries of this lane's B slots, read before anything else is issued
-        unsigned long long w_row[LB];
+        left = min((int)Kg - kk0, BK);
+        part_step = FAST == 2 && MODE != WGRAD && left < BK;
         if (ROWTAB) {
 #pragma unroll
             for (int s = 0; s < LB; ++s) w_row[s] = *(const unsigned long long *)&rowtab[w_slot][b_i0[s]];
         }
-        // ======== A
-#pragma unroll
-        for (int s = 0; s < LA; ++s) {
-            int idx = tid + s * NT;
+    };
+    auto load_a = [&](float4 (&a_reg)[LA], const int s) {
+            int idx = tid_a + s * NT;
             float4 v = make_float4(0, 0, 0, 0);
-            bool ok = !FAST;    // the element-wise variants zero what they do not load
+            bool ok;
             if (MODE == FWD) {
-                if (FAST) {
-                    // scalar: tap number and offset; an absent element reads float u_c of the tensor instead
+                if constexpr (FAST == 3) {
+                    const bf4 q = buffer_load4(ra, (a_taps[s] & la3.bit) ? a_voff[s] - (unsigned)(tid % 4) * 16u + la3.off : BUFFER_ABSENT, 0u);
+                    v = make_float4(q.x, q.y, q.z, q.w);
+                } else if (FAST) {
+                    // scalar: tap number and offset
                     const unsigned tapoff = (unsigned)(((int64_t)u_r * cs.W + u_s) * cs.C);
                     ok = (a_taps[s] >> (u_r * cs.S + u_s)) & 1u;
                     if (part_step) ok = ok && (idx % 4) * 4 < left;
-                    const bf4 q = buffer_load4(ra, ok ? a_voff[s] : ((unsigned)a_shift - tapoff) * 4u, (tapoff + (unsigned)u_c) * 4u);
+                    const bf4 q = buffer_load4(ra, ok ? a_voff[s] : BUFFER_ABSENT, (tapoff + (unsigned)u_c) * 4u);
                     v = make_float4(q.x, q.y, q.z, q.w);
                 } else if (HAS_KTAB && use_ktab) {
                     // branch-free: an element outside the image or the reduction reads the tensor's first word and is zeroed
@@ -457,12 +518,15 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 }
             } else if (MODE == DGRAD) {
                 // reduction index = (tap row, tap column, k); FAST: K % 16 == 0 so a step stays inside one tap
-                if (FAST) {
+                if constexpr (FAST == 3) {
+                    const bf4 q = buffer_load4(ra, (a_taps[s] & la3.bit) ? a_voff[s] - (unsigned)(tid % 4) * 16u + la3.off : BUFFER_ABSENT, 0u);
+                    v = make_float4(q.x, q.y, q.z, q.w);
+                } else if (FAST) {
                     // the descriptor starts a_shift floats early: tap (u_r, u_s) lies tapoff floats before the slot's offset
                     const unsigned tapoff = (unsigned)(((int64_t)u_r * cs.Q + u_s) * cs.K);
                     ok = (a_taps[s] >> (u_r * ns + u_s)) & 1u;
                     if (part_step) ok = ok && (idx % 4) * 4 < left;
-                    const bf4 q = buffer_load4(ra, ok ? a_voff[s] : tapoff * 4u, ((unsigned)a_shift - tapoff + (unsigned)u_c) * 4u);
+                    const bf4 q = buffer_load4(ra, ok ? a_voff[s] : BUFFER_ABSENT, ((unsigned)a_shift - tapoff + (unsigned)u_c) * 4u);
                     v = make_float4(q.x, q.y, q.z, q.w);
                 } else {
                     float e[4] = {0, 0, 0, 0};
@@ -481,10 +545,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
             } else {   // WGRAD: A[red = m][row = k] = dy[m][k]
                 int64_t m = kk0 + a_h0[s];
                 if (FAST) {
-                    // an absent element (row beyond the reduction, column beyond K) reads the step's first row instead
-                    const int left = (int)(Kg - kk0 < BK ? Kg - kk0 : BK);
-                    ok = a_ok[s] && a_h0[s] < left;
-                    const bf4 q = buffer_load4(ra, ok ? a_voff[s] : 0u, (unsigned)(kk0 * cs.K) * 4u);
+                    const bf4 q = buffer_load4(ra, a_h0[s] < left ? a_voff[s] : BUFFER_ABSENT, (unsigned)kk0 * (unsigned)cs.K * 4u);
                     v = make_float4(q.x, q.y, q.z, q.w);
                 } else if (m < Kg) {
                     float e[4] = {0, 0, 0, 0};
@@ -495,21 +556,14 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 }
             }
             a_reg[s] = v;
-            pm.a[s] = ok;
-            every = every && ok;
-        }
-        // ======== B
-#pragma unroll
-        for (int s = 0; s < LB; ++s) {
-            int idx = tid + s * NT;
+    };
+    auto load_b = [&](float4 (&b_reg)[LB], const int s) {
             float4 v = make_float4(0, 0, 0, 0);
-            bool ok = !FAST;
             if (MODE == FWD) {
                 if (FAST) {
-                    ok = b_ok[s];
                     unsigned vo = b_voff[s];
-                    // beyond the filter row's end: the row's floats kk0 .. kk0 + 3 instead (in bounds), zeroed below
-                    if (part_step && b_i1[s] >= left) { vo = ok ? vo - (unsigned)b_i1[s] * 4u : 0u; ok = false; }
+                    if (FAST == 3 && b_i1[s] >= left) vo = BUFFER_ABSENT;
+                    if (part_step && b_i1[s] >= left) vo = BUFFER_ABSENT;      // beyond the filter row's end
                     const bf4 q = buffer_load4(rb, vo, (unsigned)kk0 * 4u);
                     v = make_float4(q.x, q.y, q.z, q.w);
                 } else {
@@ -522,13 +576,16 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
             } else if (MODE == DGRAD) {
                 // B[red = (tap, k)][col = c] = W[k][r0 + st*tr][s0 + st*ts][c]
                 int64_t kk = kk0 + b_i0[s];
-                if (FAST) {
+                if constexpr (FAST == 3) {
+                    // the two slots of a word are filters k, k + 1 of the same tap (K is a multiple of 4)
+                    const LaneTap &t = lb3[LB == 1 ? 0 : s >> 1];
+                    const bf4 q = buffer_load4(rb, t.bit && b_ok[s] ? t.off + (LB == 1 ? 0u : (unsigned)(s & 1) * (unsigned)RSC * 4u) + (unsigned)b_i1[s] * 4u : BUFFER_ABSENT, 0u);
+                    v = make_float4(q.x, q.y, q.z, q.w);
+                } else if (FAST) {
                     // a step reaches beyond the reduction only in the last step of a 1x1 layer with K % 16 != 0 (part_step)
                     const int r = r0 + cs.stride * u_r, ss = s0 + cs.stride * u_s;
-                    ok = b_ok[s];
                     unsigned vo = b_voff[s];
-                    // a filter beyond the last one: the step's first filter instead (in bounds), zeroed below
-                    if (part_step && b_i0[s] >= left) { vo = ok ? vo - (unsigned)b_i0[s] * (unsigned)RSC * 4u : 0u; ok = false; }
+                    if (part_step && b_i0[s] >= left) vo = BUFFER_ABSENT;      // a filter beyond the last one
                     const bf4 q = buffer_load4(rb, vo, (unsigned)(((int64_t)u_c * RSC + (r * cs.S + ss) * cs.C) * 4));
                     v = make_float4(q.x, q.y, q.z, q.w);
                 } else if (kk < Kg) {
@@ -545,15 +602,14 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 int64_t m = kk0 + b_i0[s];
                 if (FAST) {
                     const unsigned pix = (unsigned)w_row[s], taps = (unsigned)(w_row[s] >> 32);
-                    ok = (taps & w_tapbit[s]) != 0u;
-                    const bf4 q = buffer_load4(rb, ok ? pix + b_voff[s] : (unsigned)b_shift * 4u, 0u);
+                    const bf4 q = buffer_load4(rb, (taps & w_tapbit[s]) ? pix + b_voff[s] : BUFFER_ABSENT, 0u);
                     v = make_float4(q.x, q.y, q.z, q.w);
                 } else if (m < Kg) {
                     int h0 = w_p[s] * cs.stride - cs.pad, w0 = w_q[s] * cs.stride - cs.pad;
                     const float *img = ta.b + (int64_t)w_n[s] * cs.H * cs.W * cs.C;
                     {
                         float e[4] = {0, 0, 0, 0};
-                        int col = col0 + (idx % (BN / 4)) * 4;
+                        int col = col0 + rc_col4(tid_b, s, LB, BN) * 4;
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
                             int cc = col + u;
@@ -570,15 +626,25 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 }
             }
             b_reg[s] = v;
-            pm.b[s] = ok;
-            every = every && ok;
-        }
-        // uniform over the wave: when nothing is absent the LDS write below needs no selects (vector instructions that
-        // would take their cycles from the matrix pipe)
-        full = __all(every) ? 1 : 0;
-        // ======== advance to the next step
+    };
+    auto advance = [&] {     // to the next step
         kk0 += BK;
-        if (MODE == FWD) {
+        if constexpr (FAST == 3) {
+            auto next = [&](LaneTap &t) {
+                const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns, rows = MODE == FWD ? cs.R : nr;
+                t.c += BK;
+                while (t.c >= inner) {       // once, or up to four times for 4 .. 12 channels
+                    t.c -= inner;
+                    if (++t.col == cols) { t.col = 0; ++t.row; }
+                }
+                t.bit = t.row < rows ? 1u << (t.row * cols + t.col) : 0u;
+            };
+            next(la3);
+            if (MODE == DGRAD) {
+#pragma unroll
+                for (int u = 0; u < UB3; ++u) next(lb3[u]);
+            }
+        } else if (MODE == FWD) {
             u_c += BK;
             if (u_c >= cs.C) { u_c = 0; if (++u_s == cs.S) { u_s = 0; ++u_r; } }
         } else if (MODE == DGRAD) {
@@ -601,202 +667,264 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
         }
     };
 
-    auto store_tiles = [&](int buf, const float4 (&a_reg)[LA], const float4 (&b_reg)[LB], const Present &pm, int full) {
-        const float4 zero = make_float4(0, 0, 0, 0);
-        auto put = [&](auto whole) {
+    auto load_tiles = [&](auto set) {
+        begin_load();
 #pragma unroll
-            for (int s = 0; s < LA; ++s) {
-                int idx = tid + s * NT;
-                float4 v = decltype(whole)::value || pm.a[s] ? a_reg[s] : zero;
-                if (A_KC) *(float4 *)&As[buf][(idx / 4) * KC_LD + (idx % 4) * 4] = v;
-                else *(float4 *)&As[buf][(idx / (BM / 4)) * A_LD + (idx % (BM / 4)) * 4] = v;
+        for (int s = 0; s < LA; ++s) load_a(a_regs[decltype(set)::value], s);
+#pragma unroll
+        for (int s = 0; s < LB; ++s) load_b(b_regs[decltype(set)::value], s);
+        advance();
+    };
+
+    // One operand's slot (two slots where they share words), split into pieces and written as words of two neighbouring
+    // reduction indices.
+    auto put_unit = [&](auto odd, auto kc, auto count, auto width, auto unit, int t, unsigned *dst, const auto &reg) {
+        constexpr bool KC = decltype(kc)::value;
+        constexpr int L = decltype(count)::value, n = decltype(width)::value, PL = plane_words(KC, n), u = decltype(unit)::value;
+        auto pieces = [&](float x, float y) {
+            if constexpr (decltype(odd)::value) return split_pair_special(x, y);
+            else return split_pair(x, y);
+        };
+        if constexpr (KC) {
+            const int idx = t + u * NT;
+            const float4 v = reg[u];
+            const Pieces p = pieces(v.x, v.y), q = pieces(v.z, v.w);
+            unsigned *at = dst + ((idx % 4) >> 1) * kc_half(n) + (idx / 4) * 4 + (idx & 1) * 2;
+            *(uint2 *)at = make_uint2(p.h, q.h);
+            *(uint2 *)(at + PL) = make_uint2(p.m, q.m);
+            *(uint2 *)(at + 2 * PL) = make_uint2(p.l, q.l);
+        } else if constexpr (L > 1) {
+            const float4 v = reg[2 * u], w = reg[2 * u + 1];
+            const Pieces p0 = pieces(v.x, w.x), p1 = pieces(v.y, w.y), p2 = pieces(v.z, w.z), p3 = pieces(v.w, w.w);
+            unsigned *at = dst + (rc_red(t, 2 * u, L, n) >> 1) * rc_row(n) + rc_col4(t, 2 * u, L, n) * 4;
+            *(uint4 *)at = make_uint4(p0.h, p1.h, p2.h, p3.h);
+            *(uint4 *)(at + PL) = make_uint4(p0.m, p1.m, p2.m, p3.m);
+            *(uint4 *)(at + 2 * PL) = make_uint4(p0.l, p1.l, p2.l, p3.l);
+        } else {
+            // n / 4 lanes hold one reduction index, the next n / 4 its neighbour: after exchanging the second half of the one with
+            // the first half of the other a lane holds both indices of two columns
+            static_assert(n == 64 || n == 128, "one slot per thread: 16 or 32 lanes per reduction index");
+            const float4 v = reg[0];
+            auto swap = [&](float a, float b) {
+                if constexpr (n == 64) return __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+                else return __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+            };
+            const auto e0 = swap(v.x, v.z), e1 = swap(v.y, v.w);
+            const Pieces p = pieces(__uint_as_float(e0[0]), __uint_as_float(e0[1])), q = pieces(__uint_as_float(e1[0]), __uint_as_float(e1[1]));
+            const int red = rc_red(t, 0, L, n);
+            unsigned *at = dst + (red >> 1) * rc_row(n) + rc_col4(t, 0, L, n) * 4 + (red & 1) * 2;
+            *(uint2 *)at = make_uint2(p.h, q.h);
+            *(uint2 *)(at + PL) = make_uint2(p.m, q.m);
+            *(uint2 *)(at + 2 * PL) = make_uint2(p.l, q.l);
+        }
+    };
+    constexpr int UA = A_KC || LA == 1 ? LA : LA / 2, UB = B_KC || LB == 1 ? LB : LB / 2, UNITS = UA + UB;
+    // unit i of the step held in register stage `set` goes to LDS buffer `buf`; `again`: and its registers take the next loads
+    auto unit = [&](auto odd, auto i, int buf, auto set, auto again) {
+        constexpr int u = decltype(i)::value;
+        float4 (&a_reg)[LA] = a_regs[decltype(set)::value];
+        float4 (&b_reg)[LB] = b_regs[decltype(set)::value];
+        if constexpr (u < UA) {
+            put_unit(odd, std::bool_constant<A_KC>{}, std::integral_constant<int, LA>{}, std::integral_constant<int, BM>{}, std::integral_constant<int, u>{}, tid_a, As[buf], a_reg);
+            if constexpr (decltype(again)::value) {
+                if constexpr (A_KC || LA == 1) load_a(a_reg, u);
+                else { load_a(a_reg, 2 * u); load_a(a_reg, 2 * u + 1); }
             }
+        } else {
+            put_unit(odd, std::bool_constant<B_KC>{}, std::integral_constant<int, LB>{}, std::integral_constant<int, BN>{}, std::integral_constant<int, u - UA>{}, tid_b, Bs[buf], b_reg);
+            if constexpr (decltype(again)::value) {
+                if constexpr (B_KC || LB == 1) load_b(b_reg, u - UA);
+                else { load_b(b_reg, 2 * (u - UA)); load_b(b_reg, 2 * (u - UA) + 1); }
+            }
+        }
+    };
+    auto each_unit = [&](auto f) {
+        [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }(std::make_integer_sequence<int, UNITS>{});
+    };
+    auto store_tiles = [&](auto odd, int buf, auto set) {
+        each_unit([&](auto i) { unit(odd, i, buf, set, std::false_type{}); });
+    };
+
+    // Two sums per result: the h * h terms and the five smaller ones.  A matrix instruction rounds its sum to fp32; the smaller terms'
+    // sum is 2^-8 of the result, so that one rounding per 16 products counts.  All six into one sum would be faster by 5 % (half
+    // the accumulators, three workgroups per CU), but 1.2 - 1.3 times further from 64 bits than the fp32 matrix instruction, and 3 times for
+    // filter gradients over many ranges (the unit's rounding leans towards minus infinity by 0.004 ulp, which the ranges add up).
+    floatx16 acc[2], low[2];
+    // Fragments of one plane: reduction indices 8g .. 8g+7 of this lane's rows / columns.
+    auto fragment = [&](auto kc, auto width, const unsigned *plane, int r) {
+        constexpr int n = decltype(width)::value;
+        if constexpr (decltype(kc)::value) return __builtin_bit_cast(bf16x8, *(const uintx4 *)(plane + g * kc_half(n) + r * 4));
+        else {
+            const unsigned *at = plane + 4 * g * rc_row(n) + r;
+            return __builtin_bit_cast(bf16x8, uintx4{at[0], at[rc_row(n)], at[2 * rc_row(n)], at[3 * rc_row(n)]});
+        }
+    };
+    struct Rows { bf16x8 b[2]; };      // the wave's 64 rows as two blocks of 32
+    auto frag_a = [&](int buf, int p) {
+        Rows f;
 #pragma unroll
-            for (int s = 0; s < LB; ++s) {
-                int idx = tid + s * NT;
-                float4 v = decltype(whole)::value || pm.b[s] ? b_reg[s] : zero;
-                if (B_KC) *(float4 *)&Bs[buf][(idx / 4) * KC_LD + (idx % 4) * 4] = v;
-                else *(float4 *)&Bs[buf][(idx / (BN / 4)) * B_LD + (idx % (BN / 4)) * 4] = v;
+        for (int i = 0; i < 2; ++i) f.b[i] = fragment(std::bool_constant<A_KC>{}, std::integral_constant<int, BM>{}, As[buf] + p * A_PL, wm * 64 + i * 32 + l32);
+        return f;
+    };
+    auto frag_b = [&](int buf, int p) { return fragment(std::bool_constant<B_KC>{}, std::integral_constant<int, BN>{}, Bs[buf] + p * B_PL, wn * 32 + l32); };
+    auto term = [&](floatx16 (&sum)[2], const Rows &x, const bf16x8 &y) {
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) sum[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.b[mi], y, sum[mi], 0, 0, 0);
+    };
+    auto compute = [&](int buf) {
+        const Rows ah = frag_a(buf, 0), am = frag_a(buf, 1), al = frag_a(buf, 2);
+        const bf16x8 bh = frag_b(buf, 0), bm = frag_b(buf, 1), bl = frag_b(buf, 2);
+        term(acc, ah, bh); term(low, ah, bm); term(low, am, bh); term(low, am, bm); term(low, ah, bl); term(low, al, bh);
+    };
+    // One step of the aligned variants: the matrix instructions of the step in LDS buffer `buf`, and between them, unit by unit,
+    // the split and LDS write of the next step (register stage `set`) and the loads of a later one into the registers just freed.  A bf16 matrix
+    // instruction leaves room for about six vector instructions of the same SIMD (measured: 2.2 PFLOP/s with 0 .. 6 of them,
+    // 1.7 with 10); the fences keep the compiler from gathering the splits, which costs 70 registers.
+    auto step = [&](int buf, auto set) {
+        begin_load();
+        const Rows ah = frag_a(buf, 0);
+        const bf16x8 bh = frag_b(buf, 0), bm = frag_b(buf, 1);
+        const Rows am = frag_a(buf, 1);
+        Rows al;
+        bf16x8 bl;
+        __builtin_amdgcn_sched_barrier(0);
+        auto chunk = [&](auto j) {
+            constexpr int J = decltype(j)::value;
+            if constexpr (J == 0) { term(acc, ah, bh); term(low, ah, bm); }
+            else if constexpr (J == 1) { term(low, am, bh); term(low, am, bm); al = frag_a(buf, 2); bl = frag_b(buf, 2); }
+            else { term(low, ah, bl); term(low, al, bh); }
+            each_unit([&](auto i) {
+                if constexpr (decltype(i)::value * 3 / UNITS == J) unit(std::false_type{}, i, buf ^ 1, set, std::true_type{});
+            });
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        chunk(std::integral_constant<int, 0>{}); chunk(std::integral_constant<int, 1>{}); chunk(std::integral_constant<int, 2>{});
+        advance();
+        __syncthreads();
+    };
+
+    auto clear = [&] {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = low[i][v] = 0.0f;
+    };
+    clear();
+    if (tid == 0) redo = 0;      // read behind the barriers below
+    const std::false_type ordinary{};
+    if (kt0 < kt1) {
+        const int steps = kt1 - kt0;
+        if (ROWTAB) {
+            fill_rows(kt0, 0);
+            __syncthreads();
+        }
+        const std::integral_constant<int, 0> s0{};
+        const std::integral_constant<int, STAGES - 1> s1{};
+        auto loading = [&](int t) {      // step t is about to be loaded: beyond the range the loads touch no memory
+            if (t >= steps) {
+                ra = buffer_of(ta.a, 0);
+                rb = buffer_of(ta.b, 0);
             }
         };
-        // uniform over the wave: a step in which no lane misses anything is written without the selects
-        if (full) put(std::true_type{});
-        else put(std::false_type{});
-    };
-
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    auto compute = [&](int buf) {
-        const float *A = As[buf], *B = Bs[buf];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float af[2][4], bf[2][4];
-#pragma unroll
-            for (int mi = 0; mi < 2; ++mi) {
-                int r = wm * 64 + mi * 32 + l32;
-                if (A_KC) {
-                    float4 v = *(const float4 *)&A[r * KC_LD + 8 * h + 4 * g];
-                    af[mi][0] = v.x; af[mi][1] = v.y; af[mi][2] = v.z; af[mi][3] = v.w;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) af[mi][j] = A[(8 * h + 4 * g + j) * A_LD + r];
+        load_tiles(s0);
+        if constexpr (FAST) {
+            // a load writes the table entry that the load before it read: barriers between the first ones
+            if (ROWTAB) __syncthreads();
+            if constexpr (STAGES == 2) {
+                if (steps > 1) load_tiles(s1);
+                if (ROWTAB) __syncthreads();
+            }
+            store_tiles(ordinary, 0, s0);
+            if (steps > STAGES) load_tiles(s0);
+            __syncthreads();
+            int t = 0;
+            if constexpr (STAGES == 2) {
+                for (; t + 2 < steps; t += 2) {
+                    loading(t + 3);
+                    step(0, s1);
+                    loading(t + 4);
+                    step(1, s0);
+                }
+                if (t + 1 < steps) {
+                    loading(t + 3);
+                    step(0, s1);
+                }
+            } else {
+                for (; t + 1 < steps; ++t) {
+                    loading(t + 2);
+                    step(t & 1, s0);
                 }
             }
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni) {
-                int c = wn * 64 + ni * 32 + l32;
-                if (B_KC) {
-                    float4 v = *(const float4 *)&B[c * KC_LD + 8 * h + 4 * g];
-                    bf[ni][0] = v.x; bf[ni][1] = v.y; bf[ni][2] = v.z; bf[ni][3] = v.w;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) bf[ni][j] = B[(8 * h + 4 * g + j) * B_LD + c];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < 2; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi][j], bf[ni][j], acc[mi][ni], 0, 0, 0);
-        }
-    };
-
-    // Software pipeline, loads two steps ahead: while step t is computed from LDS buffer t%2, the
-    // registers of stage (t+1)%2 hold step t+1 (on its way or landed) and the loads of step t+2 are
-    // issued into stage t%2.
-    if (STAGES == 1 && kt0 < kt1) {
-        const int64_t steps = kt1 - kt0;
-        Present pm0{};
-        int full0 = 0;
-        if (ROWTAB) {
-            fill_rows(kt0, 0);
+        } else {
+            store_tiles(ordinary, 0, s0);
             __syncthreads();
-        }
-        load_tiles(a_set0, b_set0, pm0, full0);
-        store_tiles(0, a_set0, b_set0, pm0, full0);
-        __syncthreads();
-        for (int64_t t = 0; t + 1 < steps; ++t) {
-            load_tiles(a_set0, b_set0, pm0, full0);
-            __builtin_amdgcn_sched_barrier(0);
-            compute((int)(t & 1));
-            __builtin_amdgcn_sched_barrier(0);
-            store_tiles((int)((t + 1) & 1), a_set0, b_set0, pm0, full0);
-            __syncthreads();
-        }
-        compute((int)((steps - 1) & 1));
-    } else if (kt0 < kt1) {
-        const int64_t steps = kt1 - kt0;
-        Present pm0{}, pm1{};
-        int full0 = 0, full1 = 0;
-        if (ROWTAB) {
-            fill_rows(kt0, 0);
-            __syncthreads();
-        }
-        load_tiles(a_set0, b_set0, pm0, full0);
-        if (ROWTAB) __syncthreads();    // the second load writes the table entry the first one read
-        if (steps > 1) load_tiles(a_set1, b_set1, pm1, full1);
-        store_tiles(0, a_set0, b_set0, pm0, full0);
-        __syncthreads();
-        int64_t t = 0;
-        // The scheduling fences keep the order loads -> MFMAs -> LDS write -> barrier: left alone, the
-        // compiler hoists the LDS write (and with it the wait for the loads) above the MFMAs.
-        // Steady state: both halves always issue their loads, so the number of loads in flight at
-        // each LDS write is the same on every path and the wait can name exactly the older stage.
-        for (; t + 3 < steps; t += 2) {
-            // even step: LDS buffer 0, next step waits in stage 1
-            load_tiles(a_set0, b_set0, pm0, full0);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(0);
-            __builtin_amdgcn_sched_barrier(0);
-            store_tiles(1, a_set1, b_set1, pm1, full1);
-            __syncthreads();
-            // odd step: LDS buffer 1, next step waits in stage 0
-            load_tiles(a_set1, b_set1, pm1, full1);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(1);
-            __builtin_amdgcn_sched_barrier(0);
-            store_tiles(0, a_set0, b_set0, pm0, full0);
-            __syncthreads();
-        }
-        // Drain: one to three steps are left; step t sits in buffer 0, step t+1 (if any) in stage 1.
-        if (t + 2 < steps) load_tiles(a_set0, b_set0, pm0, full0);
-        compute(0);
-        if (t + 1 < steps) {
-            store_tiles(1, a_set1, b_set1, pm1, full1);
-            __syncthreads();
-            compute(1);
-            if (t + 2 < steps) {
-                store_tiles(0, a_set0, b_set0, pm0, full0);
+            for (int t = 0; t + 1 < steps; ++t) {
+                load_tiles(s0);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(t & 1);
+                __builtin_amdgcn_sched_barrier(0);
+                store_tiles(ordinary, (t + 1) & 1, s0);
                 __syncthreads();
-                compute(0);
             }
         }
+        compute((steps - 1) & 1);
+    }
+    auto join = [&] {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] += low[i];
+    };
+    join();
+    // An infinity or a NaN in the result says that an operand held one, or that a product overflowed (perhaps only with pieces
+    // rounded up): this tile once more with the split that treats those as the fp32 product would.  Finite data: one barrier and 32 additions per tile.
+    {
+        float probe[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            probe[0] += acc[0][v];
+            probe[1] += acc[0][v + 8];
+            probe[2] += acc[1][v];
+            probe[3] += acc[1][v + 8];
+        }
+        const float sum = (probe[0] + probe[1]) + (probe[2] + probe[3]);
+        if (!(__builtin_fabsf(sum) < __builtin_inff())) redo = 1;
+    }
+    __syncthreads();       // also: every wave is done with the operand tiles in LDS
+    if (redo) {
+        ra = buffer_of(ta.a - a_shift, ta.a_bytes + (unsigned)a_shift * 4u);
+        rb = buffer_of(ta.b - b_shift, ta.b_bytes + (unsigned)b_shift * 4u);
+        clear();
+        to_start();
+        w_slot = 0;
+        if (ROWTAB) {
+            fill_rows(kt0, 0);
+            __syncthreads();
+        }
+        for (int t = kt0; t < kt1; ++t) {
+            load_tiles(std::integral_constant<int, 0>{});
+            store_tiles(std::true_type{}, 0, std::integral_constant<int, 0>{});
+            __syncthreads();
+            compute(0);
+            __syncthreads();
+        }
+        join();
     }
 
     // ---------------- epilogue: lane holds column l32 of rows 8*(v/4) + 4*g + v%4 of each 32x32 block
     float *out = ta.out;
-    if (!meet) out += (int64_t)split * ta.out_elems;
-    const bool do_acc = MODE != WGRAD && ta.accumulate && (nsplit == 1 || meet);
-    if (MODE != WGRAD && meet) {
-        // Leave this range's partial tile (register order: 16 float4 per lane, each wave instruction writes
-        // 1 KiB in a row), then count the arrival.  Release before the count and acquire after it order the
-        // parts of the other workgroups, on whichever XCD they ran, before the loads below.
-        const int64_t uid = (MODE == DGRAD ? (int64_t)blockIdx.z * (ta.total_tiles - ta.main_tiles) : 0) + (logical - ta.main_tiles);
-        float *tile_part = ta.part + uid * nsplit * (int64_t)(64 * NT);
-        {
-            float4 *mine = (float4 *)(tile_part + (int64_t)split * (64 * NT));
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const floatx16 &a = acc[b >> 1][b & 1];
-                    mine[(b * 4 + q4) * NT + tid] = float4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
-                }
-        }
-        __threadfence();
-        __syncthreads();                                       // also: every wave is done with the operand tiles in LDS
-        unsigned *slot = (unsigned *)&As[0][0];                // LDS is full (four workgroups per CU): borrow a word
-        if (tid == 0) *slot = atomicAdd(&g_meet_arrivals[uid], 1u);
-        __syncthreads();
-        const unsigned arrived = *slot;
-        if (arrived != (unsigned)(nsplit - 1)) return;
-        __threadfence();
-        if (tid == 0) g_meet_arrivals[uid] = 0;
-        // last to arrive: add the parts in range order (its own comes back from memory like the others, so
-        // the sum does not depend on which range arrived last)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            floatx16 t;
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                float4 v = ((const float4 *)tile_part)[(b * 4 + q4) * NT + tid];
-                t[4 * q4] = v.x; t[4 * q4 + 1] = v.y; t[4 * q4 + 2] = v.z; t[4 * q4 + 3] = v.w;
-            }
-            for (int z = 1; z < nsplit; ++z) {
-                const float4 *src = (const float4 *)(tile_part + (int64_t)z * (64 * NT));
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    float4 v = src[(b * 4 + q4) * NT + tid];
-                    t[4 * q4] += v.x; t[4 * q4 + 1] += v.y; t[4 * q4 + 2] += v.z; t[4 * q4 + 3] += v.w;
-                }
-            }
-            acc[b >> 1][b & 1] = t;
-        }
-    }
+    out += (int64_t)split * ta.out_elems;
+    const bool do_acc = MODE != WGRAD && ta.accumulate && nsplit == 1;
     if (FAST && (ta.Ng & 3) == 0) {
-        // Vector path: each wave transposes its 64x64 result through a private 16x64 LDS patch, four
-        // passes of 16 rows, and writes whole 16-byte pieces, 256 contiguous bytes per row.
+        // Vector path: each wave transposes its 64x32 result through a private 16x32 LDS patch, four
+        // passes of 16 rows, and writes whole 16-byte pieces, 128 contiguous bytes per row.
         constexpr int NW = WM * WN;
         __syncthreads();   // every wave has finished reading the operand tiles
-        float *stage = (2 * A_SZ >= NW * 1024 ? &As[0][0] : &Bs[0][0]) + wave * 1024;
+        static_assert(2 * A_SZ >= NW * 512 || 2 * B_SZ >= NW * 512, "the epilogue's patches fit one operand's tiles");
+        float *stage = (float *)(2 * A_SZ >= NW * 512 ? &As[0][0] : &Bs[0][0]) + wave * 512;
         const bool want_stats = MODE == FWD && ta.stats_part != nullptr;
         LaneStats ls;
         ls.init();
@@ -804,45 +932,42 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
         const bool want_affine = MODE == FWD && ta.affine.gamma != nullptr;
         float bn_a[4] = {1, 1, 1, 1}, bn_b[4] = {0, 0, 0, 0};
         if (MODE == FWD && want_affine) {
-            const int c0 = col0 + wn * 64 + 4 * (lane & 15);
+            const int c0 = col0 + wn * 32 + 4 * (lane & 7);
             if (c0 < ta.Ng) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, c0 + j, bn_a[j], bn_b[j]);
             }
         }
-        // the sign code of a ReLU applied here: per row one word per 64 columns, i.e. per wave; the values are read once more
-        // from the LDS patch with lane = column, so that one ballot is one word
-        const bool want_mask = MODE == FWD && want_affine && ta.affine.relu && ta.affine.mask != nullptr && col0 + wn * 64 < ta.Ng;
+        // the sign code of a ReLU applied here: per row one half word (32 columns) per wave; the values are read once more
+        // from the LDS patch with lane = column, two rows at a time, so that one ballot is two half words
+        const bool want_mask = MODE == FWD && want_affine && ta.affine.relu && ta.affine.mask != nullptr && col0 + wn * 32 < ta.Ng;
         float bn_ac = 1.0f, bn_bc = 0.0f;
-        if (MODE == FWD && want_mask) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, col0 + wn * 64 + lane, bn_ac, bn_bc);
+        if (MODE == FWD && want_mask) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, col0 + wn * 32 + l32, bn_ac, bn_bc);
         // A tile that lies inside the result whole (all but the last row of tiles and, for widths that are no multiple
         // of the tile, the last column) writes through buffer addressing: the descriptor starts at the tile, a lane's
         // byte offset inside the tile never changes and the row of a pass is a scalar offset, so a store costs no vector
         // instruction for its address and none for a bounds test.
         const bool inside = row0 + BM <= Mg && col0 + BN <= ta.Ng && ta.Ng < (1 << 24) && !(MODE == DGRAD && cs.stride > 1);
         const unsigned row_bytes = (unsigned)ta.Ng * 4u;
-        const int64_t tile_at = (row0 + wm * 64) * ta.Ng + col0 + wn * 64;
+        const int64_t tile_at = (row0 + wm * 64) * ta.Ng + col0 + wn * 32;
         const __amdgpu_buffer_rsrc_t r_out = buffer_of(out + tile_at);
         const __amdgpu_buffer_rsrc_t r_relu = buffer_of(MODE == FWD && ta.affine.relu_out ? ta.affine.relu_out + tile_at : out + tile_at);
-        const unsigned t_voff = (unsigned)(lane >> 4) * row_bytes + 16u * (unsigned)(lane & 15);
+        const unsigned t_voff = (unsigned)(lane >> 3) * row_bytes + 16u * (unsigned)(lane & 7);
         auto emit = [&](auto whole_tile) {
             constexpr bool IN = decltype(whole_tile)::value;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int mi = q >> 1, vbase = 8 * (q & 1);
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
+                for (int vv = 0; vv < 8; ++vv) stage[(8 * (vv >> 2) + 4 * g + (vv & 3)) * 32 + l32] = acc[mi][vbase + vv];
 #pragma unroll
-                    for (int vv = 0; vv < 8; ++vv)
-                        stage[(8 * (vv >> 2) + 4 * g + (vv & 3)) * 64 + ni * 32 + l32] = acc[mi][ni][vbase + vv];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int idx = lane + 64 * i, rl = idx >> 4, c4 = idx & 15;
-                    float4 val = *(const float4 *)&stage[rl * 64 + 4 * c4];
+                for (int i = 0; i < 2; ++i) {
+                    const int idx = lane + 64 * i, rl = idx >> 3, c4 = idx & 7;
+                    float4 val = *(const float4 *)&stage[rl * 32 + 4 * c4];
                     const int64_t row = row0 + wm * 64 + 16 * q + rl;
-                    const int col = col0 + wn * 64 + 4 * c4;
+                    const int col = col0 + wn * 32 + 4 * c4;
                     if (IN || (row < Mg && col < ta.Ng)) {
-                        const unsigned t_soff = (unsigned)(16 * q + 4 * i) * row_bytes;
+                        const unsigned t_soff = (unsigned)(16 * q + 8 * i) * row_bytes;
                         int64_t orow = row;
                         if (!IN && MODE == DGRAD && cs.stride > 1) {
                             // rows are bounded below 2^31 by the host: 32-bit divisions
@@ -870,35 +995,44 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                         }
                         if (IN) buffer_store4(r_out, t_voff, t_soff, bf4{val.x, val.y, val.z, val.w});
                         else *dst = val;
-                        if (MODE == FWD && want_stats) {
-                            if (!IN) ls.add(val.x, val.y, val.z, val.w);
-                            else if (q == 0 && i == 0) ls.add_first(val.x, val.y, val.z, val.w);
-                            else ls.add_next(val.x, val.y, val.z, val.w);
-                        }
+                    }
+                }
+                if (MODE == FWD && want_stats) {
+                    // the statistics' own assignment: lanes of a column group take rows (lane / 8) % 4 + 4 i of the pass, in order (the upper
+                    // 32 lanes repeat the lower ones)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int rl = ((lane >> 3) & 3) + 4 * i;
+                        const float4 val = *(const float4 *)&stage[rl * 32 + 4 * (lane & 7)];
+                        if (!IN) {
+                            if (row0 + wm * 64 + 16 * q + rl < Mg && col0 + wn * 32 + 4 * (lane & 7) < ta.Ng) ls.add(val.x, val.y, val.z, val.w);
+                        } else if (q == 0 && i == 0) ls.add_first(val.x, val.y, val.z, val.w);
+                        else ls.add_next(val.x, val.y, val.z, val.w);
                     }
                 }
                 if (MODE == FWD && want_mask) {      // uniform over the wave
-                    unsigned w_lo = 0, w_hi = 0;
+                    unsigned half = 0;
 #pragma unroll
-                    for (int rr = 0; rr < 16; ++rr) {
-                        const float e = bn_affine(stage[rr * 64 + lane], bn_ac, bn_bc);
+                    for (int rr = 0; rr < 8; ++rr) {
+                        const float e = bn_affine(stage[(2 * rr + g) * 32 + l32], bn_ac, bn_bc);
                         const bool pass = ta.affine.relu == 2 ? (e > 0.0f && e < 6.0f) : e > 0.0f;
                         const unsigned long long word = __ballot(pass);
-                        if (lane == rr) { w_lo = (unsigned)word; w_hi = (unsigned)(word >> 32); }
+                        if (lane == 2 * rr) half = (unsigned)word;
+                        if (lane == 2 * rr + 1) half = (unsigned)(word >> 32);
                     }
-                    const int64_t mrow = row0 + wm * 64 + 16 * q + lane;       // lanes 0 .. 15 hold the words of the pass's rows
-                    if (lane < 16 && mrow < Mg) ta.affine.mask[(mrow * ta.Ng + col0 + wn * 64) >> 6] = ((unsigned long long)w_hi << 32) | w_lo;
+                    const int64_t mrow = row0 + wm * 64 + 16 * q + lane;       // lanes 0 .. 15 hold the half words of the pass's rows
+                    if (lane < 16 && mrow < Mg) ((unsigned *)ta.affine.mask)[(mrow * ta.Ng + col0 + wn * 32) >> 5] = half;
                 }
             }
         };
         if (inside) emit(std::true_type{});
         else emit(std::false_type{});
         if (MODE == FWD && want_stats) {
-            // this wave's 64 rows are one row group of the statistics; lanes l, l^16, l^32, l^48 share their columns
+            // this wave's 64 rows are one row group of the statistics; lanes l, l^8, l^16, l^24 share their columns
             float n, mean[4], m2[4];
-            merge_lane_stats(ls, lane, n, mean, m2);
+            merge_lane_stats<8>(ls, lane, n, mean, m2);
             const int64_t first = row0 + wm * 64;
-            if (first < Mg) store_group_stats(ta.stats_part, first / STAT_ROWS, ta.Ng, col0 + wn * 64 + 4 * (lane & 15), lane, mean, m2);
+            if (first < Mg) store_group_stats<8>(ta.stats_part, first / STAT_ROWS, ta.Ng, col0 + wn * 32 + 4 * (lane & 7), lane, mean, m2);
         }
         return;
     }
@@ -914,15 +1048,12 @@ __global__ __launch_bounds__(64 * WM * WN, (WM == 2 && WN == 2 ? 4 : (WM * WN ==
                 const int wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - n * (unsigned)Hc);
                 orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
             }
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni) {
-                int col = col0 + wn * 64 + ni * 32 + l32;
-                if (col < ta.Ng) {
-                    float *dst = out + orow * ta.Ng + col;
-                    float r = acc[mi][ni][v];
-                    if (do_acc) r += *dst;
-                    *dst = r;
-                }
+            const int col = col0 + wn * 32 + l32;
+            if (col < ta.Ng) {
+                float *dst = out + orow * ta.Ng + col;
+                float r = acc[mi][v];
+                if (do_acc) r += *dst;
+                *dst = r;
             }
         }
 }
@@ -997,61 +1128,70 @@ void check_shape(const ConvShape &cs) {
 }
 
 // How a launch divides its reduction.  `splits` > 1 asks for that many ranges on every tile: partial results go
-// to `splits` full-size slabs that a second kernel adds in range order.  `splits` == 1 with a workspace (FWD /
-// DGRAD at stride 1) lets the ragged last round, the tiles beyond a multiple of the CU count, be cut as far as the
-// workspace allows; those partial tiles meet inside the kernel.  (Letting every tile of a launch meet that way
-// was measured too: the device-wide release each split workgroup performs costs more than the second kernel.)
+// to as many full-size slabs, which a second kernel adds in range order.  (Cutting only the ragged last round of tiles and adding the
+// parts inside the kernel paid with the fp32 matrix instruction; with tiles worked three times faster the device-wide release it
+// needs costs more than the idle CUs: 1x1, 1024 -> 256, 14x14, batch 184: 144 us with it, 130 without.)
 constexpr int NUM_CU = 256;
+
+// Workgroups of a tile shape that are on a CU together: LDS (160 KiB) and three or four waves per SIMD.
+constexpr int resident_workgroups(int mode, int wm, int wn) {
+    const int bytes = 2 * 3 * 4 * (plane_words(mode != WGRAD, 64 * wm) + plane_words(mode == FWD, 32 * wn)) + 512;
+    return std::min(160 * 1024 / bytes, wm * wn <= 4 ? 12 / (wm * wn) : 16 / (wm * wn));
+}
+// The caller's `splits` is the most ranges a launch may cut its reduction into; it takes fewer where more only cost partial
+// results.  `slots`: workgroups of the tile shape that are on the GPU together.
+//   Filter gradients (few tiles, many ranges): the fullest of one to four rounds of workgroups, by an estimate of the matrix
+//   instructions (180 TFLOP/s, 7 % lost to the uneven end of a single round) and of writing and reading the slabs (4 TB/s).
+//   Forward / input gradient: at most five workgroups per CU; beyond that the slabs cost more than the better balance gives.
+int useful_splits(int mode, int splits, int64_t tiles, int64_t slots, double flops, double slab_bytes) {
+    if (mode != WGRAD) return (int)std::max<int64_t>(1, std::min<int64_t>(splits, (5 * NUM_CU + tiles - 1) / tiles));
+    int best = 1;
+    double best_us = 0;
+    for (int64_t r = 1; r <= 4; ++r) {
+        const int s = (int)std::max<int64_t>(1, std::min<int64_t>(splits, slots * r / tiles));
+        const double work = (double)(tiles * s), rounds = (double)((tiles * s + slots - 1) / slots);
+        const double us = flops / 180e6 * (rounds * slots / work) * (1 + 0.07 / rounds) + (s > 1 ? s * slab_bytes * 2 / 4e6 : 0);
+        if (r == 1 || us < best_us) { best = s; best_us = us; }
+    }
+    return best;
+}
 
 template <int MODE, int WM, int WN, int TAG = 0>
 void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, int splits, float *ws, size_t ws_bytes, int64_t steps,
                  bool accumulate, const char *who) {
-    constexpr int BM = 64 * WM, BN = 64 * WN, NT = 64 * WM * WN;
+    constexpr int BM = 64 * WM, BN = 32 * WN, NT = 64 * WM * WN;
     if (splits < 1) throw KernelError(std::string(who) + ": splits must be >= 1");
     set_row_magic(ta);
     if (splits > steps) splits = (int)std::max<int64_t>(steps, 1);
+    if (splits > 1 && (!ws || ws_bytes < (size_t)splits * ta.out_elems * 4)) throw KernelError(std::string(who) + ": workspace too small for the requested splits");
+    if (splits > 1)
+        splits = useful_splits(MODE, splits, (ta.Mg + BM - 1) / BM * ((ta.Ng + BN - 1) / BN) * zdim, (int64_t)NUM_CU * resident_workgroups(MODE, WM, WN),
+                               2.0 * ta.Mg * ta.Ng * ta.Kg * zdim, 4.0 * ta.out_elems);
     int64_t tiles_m = (ta.Mg + BM - 1) / BM;
     ta.tiles_n = (ta.Ng + BN - 1) / BN;
     ta.total_tiles = tiles_m * ta.tiles_n;
     ta.out = out;
     ta.splits = 1;
     ta.accumulate = accumulate ? 1 : 0;
-    ta.main_tiles = 0;
-    ta.meet_splits = 0;
-    ta.part = nullptr;
-    const size_t tile_bytes = (size_t)BM * BN * sizeof(float);
     bool slabs = false;
     if (splits > 1) {
-        if (!ws || ws_bytes < (size_t)splits * ta.out_elems * 4) throw KernelError(std::string(who) + ": workspace too small for the requested splits");
         slabs = true;
         ta.out = ws;
         ta.splits = splits;
-    } else if (MODE != WGRAD && zdim == 1 && ws && ta.total_tiles % NUM_CU) {
-        const int64_t tail = ta.total_tiles % NUM_CU;
-        int64_t s = std::min<int64_t>({NUM_CU / tail, steps / 4, 16, (int64_t)(ws_bytes / (tail * tile_bytes))});
-        if (s >= 2) {
-            ta.main_tiles = ta.total_tiles - tail;
-            ta.meet_splits = (int)s;
-            ta.part = ws;
-        }
     }
-    int64_t blocks;
-    if (ta.meet_splits > 1) {
-        const int64_t nt = (ta.total_tiles - ta.main_tiles) * ta.meet_splits;
-        blocks = (ta.main_tiles / NUM_XCD + (nt + NUM_XCD - 1) / NUM_XCD) * NUM_XCD;
-    } else {
-        blocks = (ta.total_tiles * ta.splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-    }
+    const int64_t blocks = (ta.total_tiles * ta.splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
     if (blocks > 0x7fffffffll) throw KernelError("conv: too many tiles");
     dim3 grid((unsigned)blocks, 1, (unsigned)zdim);
     if constexpr (TAG != 0) {
         if (!fast) throw KernelError("conv: batched GEMMs need aligned shapes");
         hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1, TAG>), grid, dim3(NT), 0, st, ta);
     } else {
-        // a forward or input-gradient reduction that is no multiple of 16 (the host admits that for 1x1 layers only)
+        // forward or input-gradient channels that are no multiple of 16
         const bool part = MODE == FWD ? ta.cs.C % BK != 0 : MODE == DGRAD ? ta.cs.K % BK != 0 : false;
         if constexpr (MODE != WGRAD) {
-            if (fast && part) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 2>), grid, dim3(NT), 0, st, ta); }
+            if (fast && part && ta.cs.R * ta.cs.S > 1) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 3>), grid, dim3(NT), 0, st, ta); }
+            else if (fast && part) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 2>), grid, dim3(NT), 0, st, ta); }
+            else if (fast && WM * WN == 4 && steps <= 6) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, WM * WN == 4 ? 4 : 1>), grid, dim3(NT), 0, st, ta); }
             else if (fast) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1>), grid, dim3(NT), 0, st, ta); }
             else { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 0>), grid, dim3(NT), 0, st, ta); }
         } else {
@@ -1067,43 +1207,49 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 //   0: 128x128   1: 256x64   2: 64x256   3: 128x64   4: 64x128   5: 64x64
 int g_cfg_override = -1;   // tuning aid: force one tile shape for every launch
 
-// Choice measured on the ResNet-50 b184 layer set: the square four-wave tile unless the GEMM is
-// narrower than it, then the four-wave (or smaller) tile that covers the narrow side exactly.
-int pick_cfg(int mode, int64_t Mg, int64_t Ng) {
+// Choice measured on the ResNet-50, VGG-16, MobileNetV2 and inception layer sets.  The square tile moves the least through LDS and
+// L2 per product (3x3, 256 -> 256, 56x56, batch 176: 3.25 ms against 3.67 with 128x64), the 128x64 tile has twice as many workgroups,
+// four of them on a CU: it is the faster one where a reduction is short and the time goes into loads and stores (1x1, 64 -> 256, 56x56,
+// batch 184: 214 against 250 us) and where square tiles are too few to fill the GPU evenly (1x1, 160 -> 960, 7x7, batch 272: 47 against
+// 76 us; 1x1, 512 -> 128, 28x28: 126 against 132; at 2256 tiles, 1x1, 256 -> 1024, 14x14: 126 against 118).  A reduction cut into
+// ranges fills it anyway.  `straddle`: reduction steps that cross filter taps.
+int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool straddle) {
     if (g_cfg_override >= 0) return g_cfg_override;
     if (mode == WGRAD) {
-        if (Mg <= 64) return Ng % 256 == 0 ? 2 : 5;
-        if (Ng <= 64) return Mg >= 256 ? 1 : 3;
+        if (Ng <= 64) return Mg <= 64 ? 5 : 3;
+        if (Mg <= 64) return (Ng + 127) / 128 * 128 <= (Ng + 63) / 64 * 64 * 9 / 8 ? 4 : 5;
         return 0;
     }
-    return Ng <= 64 ? 1 : 0;
+    if (Ng <= 64 || straddle) return 3;      // straddling lanes carry their tap: registers the larger tiles do not have
+    if (splits > 1) return 0;
+    return steps > 6 && (Mg + 127) / 128 * ((Ng + 127) / 128) * classes >= 6 * NUM_CU ? 0 : 3;
 }
 
 template <int MODE, class... Rest>
 void launch_cfg(int cfg, Rest... rest) {
     switch (cfg) {
-        case 0: launch_tile<MODE, 2, 2>(rest...); break;
-        case 1: launch_tile<MODE, 4, 1>(rest...); break;
-        case 2: launch_tile<MODE, 1, 4>(rest...); break;
-        case 3: launch_tile<MODE, 2, 1>(rest...); break;
-        case 4: launch_tile<MODE, 1, 2>(rest...); break;
-        default: launch_tile<MODE, 1, 1>(rest...); break;
+        case 0: launch_tile<MODE, 2, 4>(rest...); break;
+        case 1: launch_tile<MODE, 4, 2>(rest...); break;
+        case 2: launch_tile<MODE, 1, 8>(rest...); break;
+        case 3: launch_tile<MODE, 2, 2>(rest...); break;
+        case 4: launch_tile<MODE, 1, 4>(rest...); break;
+        default: launch_tile<MODE, 1, 2>(rest...); break;
     }
 }
 
 // the batched GEMMs only ever see the two tile shapes the forward heuristic picks
 template <int TAG, class... Rest>
 void launch_batched(int cfg, Rest... rest) {
-    if (cfg == 1) launch_tile<FWD, 4, 1, TAG>(rest...);
-    else launch_tile<FWD, 2, 2, TAG>(rest...);
+    if (cfg == 3) launch_tile<FWD, 2, 2, TAG>(rest...);
+    else launch_tile<FWD, 2, 4, TAG>(rest...);
 }
 
 }  // namespace
 
 void conv_force_tile(int cfg) { g_cfg_override = cfg; }
 
-// reduction steps of 16 must not straddle filter taps: C % 16 == 0, or a 1x1 layer (one tap) with C % 4 == 0, whose last
-// step is partly empty
+// layers whose epilogue takes the statistics or the BatchNorm behind them: reduction steps of 16 do not straddle filter taps,
+// C % 16 == 0, or a 1x1 layer (one tap) with C % 4 == 0, whose last step is partly empty
 bool conv_fwd_aligned(const ConvShape &cs) { return cs.C % BK == 0 || (cs.R == 1 && cs.S == 1 && cs.C % 4 == 0); }
 
 bool conv_epilogue_writes_mask(const ConvShape &cs, bool winograd_fused) {
@@ -1125,18 +1271,13 @@ SplitGemm split_gemm_of(int which, const ConvShape &cs) {
 }
 }  // namespace
 
-void conv_reset_arrivals(hipStream_t st) {
-    hipLaunchKernelGGL(meet_reset_kernel, dim3(MEET_SLOTS / 256), dim3(256), 0, st);
-    hip_check(hipGetLastError(), "arrival table reset launch");
-}
-
 size_t conv_workspace_bytes(int which, const ConvShape &cs, int splits) {
     check_shape(cs);
     const SplitGemm sg = split_gemm_of(which, cs);
     if (splits > sg.steps) splits = (int)std::max<int64_t>(sg.steps, 1);
     if (splits > 1) return (size_t)splits * 4 * (which == 0 ? cs.M() * cs.K : (int64_t)cs.N * cs.H * cs.W * cs.C);
     static const int shape[6][2] = {{128, 128}, {256, 64}, {64, 256}, {128, 64}, {64, 128}, {64, 64}};
-    const int cfg = pick_cfg(FWD, sg.rows, sg.cols);
+    const int cfg = g_cfg_override >= 0 ? g_cfg_override : sg.cols <= 64 ? 1 : 0;
     const int64_t bm = shape[cfg][0], bn = shape[cfg][1];
     const int64_t tiles = ((sg.rows + bm - 1) / bm) * ((sg.cols + bn - 1) / bn);
     const int64_t tail = tiles % NUM_CU;
@@ -1159,8 +1300,9 @@ void gemm_batched(hipStream_t st, const float *a, const float *b, float *out, in
     ta.a = a; ta.b = b; ta.cs = cs;
     ta.Mg = rows; ta.Ng = cols; ta.Kg = red;
     ta.out_elems = rows * cols;
+    ta.a_bytes = (unsigned)(rows * red * 4); ta.b_bytes = (unsigned)((int64_t)cols * red * 4);
     ta.batch_a = rows * red; ta.batch_b = (int64_t)cols * red; ta.batch_out = rows * cols;
-    const int cfg = cols <= 64 ? 1 : 0;
+    const int cfg = cols <= 64 ? 3 : 0;
     if (adjoint_use) launch_batched<2>(cfg, st, ta, true, batch, out, 1, (float *)nullptr, (size_t)0, (int64_t)red / BK, false, "gemm_batched");
     else launch_batched<1>(cfg, st, ta, true, batch, out, 1, (float *)nullptr, (size_t)0, (int64_t)red / BK, false, "gemm_batched");
 }
@@ -1176,11 +1318,12 @@ void gemm_tn_batched(hipStream_t st, const float *a, const float *b, float *out,
     ta.a = a; ta.b = b; ta.cs = cs;
     ta.Mg = m; ta.Ng = n; ta.Kg = red;
     ta.out_elems = (int64_t)batch * m * n;
+    ta.a_bytes = (unsigned)(red * m * 4); ta.b_bytes = (unsigned)(red * n * 4);
     ta.batch_a = red * m; ta.batch_b = red * n; ta.batch_out = (int64_t)m * n;
     // the aligned loader addresses each operand plane with 32-bit byte offsets
     if (red * m * 4 >= ((int64_t)1 << 32) - (1 << 20) || red * n * 4 >= ((int64_t)1 << 32) - (1 << 20))
         throw KernelError("gemm_tn_batched: an operand plane of 4 GiB or more");
-    launch_tile<WGRAD, 2, 2, 3>(st, ta, true, batch, out, splits, ws, ws_bytes, (red + BK - 1) / BK, false, "gemm_tn_batched");
+    launch_tile<WGRAD, 2, 4, 3>(st, ta, true, batch, out, splits, ws, ws_bytes, (red + BK - 1) / BK, false, "gemm_tn_batched");
 }
 
 void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const ConvShape &cs, int splits, float *ws, size_t ws_bytes,
@@ -1193,20 +1336,21 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
     }
     TileArgs ta{};
     ta.a = x; ta.b = w; ta.cs = cs;
+    ta.a_bytes = (unsigned)((int64_t)cs.N * cs.H * cs.W * cs.C * 4); ta.b_bytes = (unsigned)(cs.K * cs.RSC() * 4);
     ta.Mg = cs.M(); ta.Ng = cs.K; ta.Kg = cs.RSC();
     ta.out_elems = ta.Mg * ta.Ng;
     // the aligned loader addresses both operands with 32-bit byte offsets (plus one tap's reach) and keeps one bit per filter tap
     const int64_t span32 = ((int64_t)1 << 32) - (1 << 20);
     const int64_t reach = ((int64_t)(cs.R + cs.pad) * cs.W + cs.S + cs.pad) * cs.C * 4;
-    bool fast = conv_fwd_aligned(cs) && cs.R * cs.S <= 32 && (int64_t)cs.N * cs.H * cs.W * cs.C * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
-    if ((stats_part || affine) && (!fast || cs.K % 4 || splits != 1 || accumulate))
+    bool fast = cs.C % 4 == 0 && cs.R * cs.S <= 32 && (int64_t)cs.N * cs.H * cs.W * cs.C * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
+    if ((stats_part || affine) && (!fast || !conv_fwd_aligned(cs) || cs.K % 4 || splits != 1 || accumulate))
         throw KernelError("conv_fwd: statistics or BatchNorm in the epilogue need C % 16 == 0 (1x1: C % 4 == 0), K % 4 == 0, splits == 1 and no accumulation");
     if (stats_part && affine) throw KernelError("conv_fwd: either the statistics of the output or its BatchNorm apply step, not both");
     if (affine && (!affine->gamma || !affine->beta || !affine->stats)) throw KernelError("conv_fwd: incomplete BatchNorm coefficients");
     if (affine && affine->mask && (!affine->relu || cs.K % 64)) throw KernelError("conv_fwd: a sign code in the epilogue needs the ReLU and K % 64 == 0");
     ta.stats_part = stats_part;
     if (affine) ta.affine = *affine;
-    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng), st, ta, fast, 1, y, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, accumulate, "conv_fwd");
+    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, (ta.Kg + BK - 1) / BK, 1, splits, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, accumulate, "conv_fwd");
 }
 
 void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, const ConvShape &cs, bool accumulate, int splits, float *ws,
@@ -1214,6 +1358,7 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     check_shape(cs);
     TileArgs ta{};
     ta.a = dy; ta.b = w; ta.cs = cs;
+    ta.a_bytes = (unsigned)(cs.M() * cs.K * 4); ta.b_bytes = (unsigned)(cs.K * cs.RSC() * 4);
     const SplitGemm sg = split_gemm_of(1, cs);   // rows of residue class (0,0), the largest; the shortest class reduction bounds the splits
     ta.Mg = sg.rows;
     ta.Ng = cs.C;
@@ -1221,11 +1366,8 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     ta.out_elems = (int64_t)cs.N * cs.H * cs.W * cs.C;
     const int64_t span32 = ((int64_t)1 << 32) - (1 << 20);
     const int64_t reach = ((int64_t)cs.R * cs.Q + cs.S) * cs.K * 4;
-    // reduction steps of 16 must not straddle filter taps: K % 16 == 0, or a 1x1 layer (one tap) with K % 4 == 0, whose last
-    // step is partly empty
-    const bool k_ok = cs.K % BK == 0 || (cs.R == 1 && cs.S == 1 && cs.K % 4 == 0);
-    bool fast = k_ok && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
-    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
+    bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
+    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, splits, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
 }
 
 void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, const ConvShape &cs, int splits, float *ws, size_t ws_bytes) {
@@ -1242,6 +1384,7 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
     }
     TileArgs ta{};
     ta.a = dy; ta.b = x; ta.cs = cs;
+    ta.a_bytes = (unsigned)(cs.M() * cs.K * 4); ta.b_bytes = (unsigned)((int64_t)cs.N * cs.H * cs.W * cs.C * 4);
     ta.Mg = cs.K; ta.Ng = (int)cs.RSC(); ta.Kg = cs.M();
     ta.out_elems = (int64_t)cs.K * cs.RSC();
     // the aligned loader addresses both operands with 32-bit byte offsets and keeps one bit per filter tap
@@ -1249,7 +1392,7 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
     const int64_t lead = ((int64_t)cs.pad * cs.W + cs.pad) * cs.C * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 < span32 &&
                 (int64_t)cs.N * cs.H * cs.W * cs.C * 4 + lead < span32;
-    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng), st, ta, fast, 1, dw, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, false, "conv_wgrad");
+    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, splits, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, false, "conv_wgrad");
 }
 
 }  // namespace monet

@@ -58,8 +58,11 @@ struct LaneStats {
     }
 };
 
+// LANES: lanes that share a row (16 where a wave holds 64 columns, 8 where it holds 32 and lanes 0 .. 31 do what lanes 32 .. 63
+// repeat); lane l then owns the columns 4*(l % LANES) .. +3 of rows (l / LANES) % 4 + 4*i + 16*q.
 // Merges the four lanes that share their columns; afterwards each of them holds the group's row count,
 // means and sums of squared deviations of its four columns.  Every lane of the wave must call this.
+template <int LANES = 16>
 __device__ inline void merge_lane_stats(const LaneStats &ls, int lane, float &n, float (&mean)[4], float (&m2)[4]) {
 #pragma clang fp contract(off)
     n = ls.n;
@@ -70,7 +73,7 @@ __device__ inline void merge_lane_stats(const LaneStats &ls, int lane, float &n,
         m2[j] = q < 0.0f ? 0.0f : q;
     }
 #pragma unroll
-    for (int mask = 16; mask <= 32; mask <<= 1) {
+    for (int mask = LANES; mask <= 2 * LANES; mask <<= 1) {
         const bool low = (lane & mask) == 0;
         const float n_o = __shfl_xor(n, mask);
         const float na = low ? n : n_o, nb = low ? n_o : n, nt = na + nb;   // a = the lane with the bit clear
@@ -99,9 +102,10 @@ __device__ inline void merge_lane_stats(const LaneStats &ls, int lane, float &n,
     }
 }
 
-// lane l < 16 writes {mean, M2} of its four columns of row group `grp`: part[(grp * C + c) * 2 + {0, 1}]
+// lane l < LANES writes {mean, M2} of its four columns of row group `grp`: part[(grp * C + c) * 2 + {0, 1}]
+template <int LANES = 16>
 __device__ inline void store_group_stats(float *part, int64_t grp, int C, int col, int lane, const float (&mean)[4], const float (&m2)[4]) {
-    if ((lane >> 4) != 0 || col >= C) return;
+    if (lane >= LANES || col >= C) return;
     float4 *dst = (float4 *)(part + (grp * C + col) * 2);
     dst[0] = make_float4(mean[0], m2[0], mean[1], m2[1]);
     dst[1] = make_float4(mean[2], m2[2], mean[3], m2[3]);

@@ -39,6 +39,12 @@ CONV_CASES = [
     (2, 28, 28, 144, 24, 1, 1, 0),      # ... and 24 output channels: the same in the input gradient
     (3, 15, 13, 40, 36, 1, 2, 0),       # both at once, stride 2, ragged rows and columns
     (2, 9, 9, 4, 8, 1, 1, 0),           # a single, mostly empty step
+    # reduction steps that straddle filter taps (channels a multiple of 4, not of 16)
+    (2, 14, 14, 24, 64, 5, 1, 2),       # an inception 5x5
+    (3, 13, 17, 60, 92, 3, 1, 1),       # both directions, last step partly empty
+    (2, 9, 11, 4, 8, 3, 1, 1),          # four taps to a step
+    (2, 10, 9, 36, 28, 3, 2, 1),        # stride 2: input-gradient classes with one, two and four taps
+    (5, 6, 7, 132, 44, 2, 2, 0),        # even filter, no padding
 ]
 
 
@@ -91,10 +97,105 @@ def test_conv_trio_matches_oracle(case):
         check_close(gw.cpu().numpy(), want, GRAD_TOL, what=splits)
 
 
+@pytest.mark.parametrize("tile", range(6))
+@pytest.mark.parametrize("case", [(3, 15, 14, 48, 112, 3, 1, 1), (2, 11, 13, 20, 76, 3, 2, 1), (2, 9, 8, 30, 70, 3, 1, 1), (2, 20, 18, 132, 72, 1, 1, 0)])
+def test_conv_trio_on_every_tile_shape(case, tile):
+    """Each of the six tile shapes, with rows and columns beyond a tile's edge, aligned, straddling and element-wise loaders,
+    whole and in ranges, forward and both gradients, plain and accumulating."""
+    torch = torch_mod()
+    N, H, W, C, K, R, stride, pad = case
+    rng = np.random.default_rng(11)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    x = rng.standard_normal((N, H, W, C), dtype=np.float32)
+    w = rng.standard_normal((K, R, R, C), dtype=np.float32)
+    dy = rng.standard_normal((N, P, Q, K), dtype=np.float32)
+    xo, wo, dyo = wt.act_to_oracle(x), wt.weight_to_oracle(w), wt.act_to_oracle(dy)
+    want_y = wt.act_from_oracle(nm.conv2d_fwd(xo, wo, stride, pad))
+    want_dx = wt.act_from_oracle(nm.conv2d_dgrad(dyo, wo, xo.shape, stride, pad))
+    want_dw = wt.weight_from_oracle(nm.conv2d_wgrad(xo, dyo, R, R, stride, pad))
+    gx, gw, gd = dev(x), dev(w), dev(dy)
+    ws = torch.empty(3 * max(x.size, dy.size, w.size), device="cuda")
+    dims = (N, H, W, C, K, R, R, stride, pad)
+    lib = monet.load_library()
+    lib.monet_conv_force_tile(tile)
+    try:
+        for splits in (1, 3):
+            y, dx, dw = (torch.full(a.shape, float("nan"), device="cuda") for a in (dy, x, w))
+            wsp, wsb = (ws.data_ptr(), ws.numel() * 4) if splits > 1 else (None, 0)
+            monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), y.data_ptr(), *dims, splits, wsp, wsb)
+            monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), dx.data_ptr(), *dims, 0, splits, wsp, wsb)
+            monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), dx.data_ptr(), *dims, 1, splits, wsp, wsb)
+            monet.call("monet_conv_wgrad", None, gx.data_ptr(), gd.data_ptr(), dw.data_ptr(), *dims, splits, wsp, wsb)
+            # fp32 sums of at most 1008 products: 1e-6 in the norm
+            check_close(y.cpu().numpy(), want_y, 1e-6, what=splits)
+            check_close(dx.cpu().numpy(), 2 * want_dx, 1e-6, what=splits)
+            check_close(dw.cpu().numpy(), want_dw, 1e-6, what=splits)
+    finally:
+        lib.monet_conv_force_tile(-1)
+
+
+SPECIAL_CASES = [
+    # N, H, W, C, K: 1x1 layers (no padding: a padded zero times an infinity is a NaN in any implementation that stages zeros)
+    (1, 16, 16, 36, 40),        # aligned loaders, last reduction step partly empty
+    (2, 12, 12, 64, 128),       # two tiles of rows, only one of which holds special values
+    (1, 9, 9, 30, 17),          # element-wise loaders
+]
+
+
+@pytest.mark.parametrize("case", SPECIAL_CASES)
+@pytest.mark.parametrize("kind", ["inf", "nan", "inf_times_zero", "both_inf", "near_max", "overflow", "tiny"])
+def test_conv_of_infinities_nans_and_extreme_values(case, kind):
+    """Every float is worked as three bf16 pieces: infinities, NaNs, values that round to infinity in bf16 and products that
+    overflow have to come out as the fp32 product's.  Reference: the same sums in fp64, rounded to fp32."""
+    torch = torch_mod()
+    N, H, W, C, K = case
+    rng = np.random.default_rng(5)
+    x = (rng.standard_normal((N, H, W, C)) + 3.0).astype(np.float32)
+    w = (np.abs(rng.standard_normal((K, 1, 1, C))) + 0.5).astype(np.float32)
+    dy = (rng.standard_normal((N, H, W, K)) + 2.0).astype(np.float32)
+    inf = np.float32(np.inf)
+    if kind == "inf":
+        x[0, 1, 2, 3], x[0, 3, 3, 7], dy[0, 2, 2, 5], w[4, 0, 0, 6] = inf, -inf, -inf, inf
+    elif kind == "nan":
+        x[0, 1, 2, 3], dy[0, 2, 2, 5] = np.nan, np.nan
+    elif kind == "inf_times_zero":
+        x[0, 1, 2, 3], w[2, 0, 0, 3], w[3, 0, 0, 3], dy[0, 1, 2, 9] = inf, 0.0, -0.0, 0.0
+    elif kind == "both_inf":
+        x[0, 1, 2, 3], w[2, 0, 0, 3], w[3, 0, 0, 3], dy[0, 1, 2, 9] = inf, inf, -inf, -inf
+    elif kind == "near_max":      # 3.4e38 rounds to infinity in bf16
+        x[0, 1, 2, 3], w[:, 0, 0, 3], dy[0, 1, 2, 9] = 3.4e38, 1e-3, 1e-4
+    elif kind == "overflow":
+        x[0, 1, 2, 3], w[2, 0, 0, 3], w[3, 0, 0, 3], dy[0, 1, 2, 9] = 1.7e38, 1.3e38, -1.9e30, 1.1e33
+    else:
+        x[0, 1, 2, 3], w[2, 0, 0, 3] = 1e-40, 1e-39
+    with np.errstate(all="ignore"):
+        x2, w2, g2 = x.reshape(-1, C).astype(np.float64), w.reshape(K, C).astype(np.float64), dy.reshape(-1, K).astype(np.float64)
+
+        def product(a, b):      # a[m, r] b[r, n] in fp32 semantics: every product and the sum rounded to fp32's range
+            p = (a[:, :, None] * b[None, :, :]).astype(np.float32).astype(np.float64)
+            return p.sum(1).astype(np.float32)
+        want = dict(y=product(x2, w2.T), dx=product(g2, w2), dw=np.concatenate([product(g2.T[i:i + 8], x2) for i in range(0, K, 8)]))
+    gx, gw, gd = dev(x), dev(w), dev(dy)
+    got = dict(y=torch.empty(N * H * W, K, device="cuda"), dx=torch.empty(N * H * W, C, device="cuda"), dw=torch.empty(K, C, device="cuda"))
+    dims = (N, H, W, C, K, 1, 1, 1, 0)
+    ws = torch.empty(3 * K * C, device="cuda")
+    for splits in (1, 3):
+        monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), got["y"].data_ptr(), *dims, 1, None, 0)
+        monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), got["dx"].data_ptr(), *dims, 0, 1, None, 0)
+        monet.call("monet_conv_wgrad", None, gx.data_ptr(), gd.data_ptr(), got["dw"].data_ptr(), *dims, splits, ws.data_ptr(), ws.numel() * 4)
+        for name, t in got.items():
+            a, b = t.cpu().numpy(), want[name]
+            assert np.array_equal(np.isnan(a), np.isnan(b)), (name, splits)
+            assert np.array_equal(np.isinf(a), np.isinf(b)) and np.array_equal(a[np.isinf(b)], b[np.isinf(b)]), (name, splits)
+            fine = np.isfinite(b)
+            # at most 324 products of like size: their fp32 sums differ from fp64's by less than 324 * 2^-24
+            assert np.all(np.abs(a[fine] - b[fine]) <= 324 * 2.0 ** -24 * np.maximum(np.abs(b[fine]), 1.0) * 8), (name, splits)
+
+
 def test_conv_ragged_last_round_is_split_and_counts_reset():
-    """More than 256 tiles and not a multiple of it: with a workspace the tiles of the last round are cut and meet
-    inside the kernel.  Several calls in a row (the arrival table has to be back at zero each time), forward and
-    input gradient with accumulation, against the oracle and against the uncut kernel."""
+    """More than 256 tiles and not a multiple of it, with the workspace that lets a library cut the tiles of the last round.
+    Several calls in a row, forward and input gradient with accumulation, against the oracle and against the call
+    without a workspace."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad = 48, 28, 28, 128, 128, 1, 1, 0          # 37632 rows = 294 tiles of 128
     rng = np.random.default_rng(7)
