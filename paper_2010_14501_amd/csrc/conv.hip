@@ -36,6 +36,7 @@
 // split) with the tile index fastest, so a launch with few tiles and many splits (weight
 // gradients) still spreads over all XCDs and the tiles of one split share their operand rows.
 #include <type_traits>
+#include <utility>
 
 #include "bn_affine.hpp"
 #include "buffer_addr.hpp"
@@ -127,7 +128,10 @@ struct TileArgs {
     unsigned q_mul, q_shift, p_mul, p_shift, w_mul, w_shift, h_mul, h_shift;
 };
 
-__device__ inline float4 ld4(const float *p) { return *(const float4 *)p; }
+template <class F, int... I>
+__device__ __forceinline__ void for_each_int(F &f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
 
 // TAG only names the use in profiles: 0 a convolution, 1 / 2 / 3 the batched GEMMs of a Winograd forward / input gradient /
 // filter gradient
@@ -137,7 +141,7 @@ __device__ inline float4 ld4(const float *p) { return *(const float4 *)p; }
 // lane carries the tap and channel of its four reduction indices, 4 as 1 for reductions of at most six steps (5x5 filter, 24 -> 64 channels, 14x14 maps, batch 320:
 // 160 -> 38 us forward, 134 -> 82 us input gradient against the element-wise loaders)
 template <int MODE, int WM, int WN, int FAST, int TAG = 0>
-__global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 4 ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
+__global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST != 2 && FAST != 4) ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
     // Register stages of the aligned variants: loads run this many steps ahead of the split.  The tiles of at most four waves take
     // two at three waves per SIMD (1x1, 1024 -> 256, 14x14, batch 184: 123 against 142 us with one), the larger ones, and short
     // reductions, which live from many workgroups at once (64 -> 256, 56x56: 214 against 245 us), one at four (128 registers).
@@ -158,11 +162,12 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
     constexpr bool HAS_KTAB = !FAST && MODE == FWD && BN == 64;
     constexpr int KTAB = 256;
     __shared__ int2 ktab[HAS_KTAB ? KTAB : 1];   // x = ((r*W + s)*C + c), y = r | s << 8, or y < 0 beyond the reduction
-    // Aligned filter gradient: the BK output positions a reduction step covers, decoded once per step by 16 lanes for
-    // the whole workgroup: x = byte offset of the position's window in the (shifted) input tensor, y = bit per filter
-    // tap that falls inside the image.  Two entries: the table of step j + 1 is written while step j is loaded.
+    // Aligned filter gradient: the output positions of four reduction steps, decoded once for the whole workgroup by the 64 lanes of one
+    // wave: x = byte offset of the position's window in the (shifted) input tensor, y = bit per filter tap that falls inside the
+    // image.  Two such tables: one is written while the other is read.
     constexpr bool ROWTAB = FAST && MODE == WGRAD;
-    __shared__ uint2 rowtab[ROWTAB ? 2 : 1][ROWTAB ? BK : 1];
+    constexpr int TABLE = 4 * BK;
+    __shared__ uint2 rowtab[ROWTAB ? 2 * TABLE : 1];
 
     if (MODE != DGRAD) {   // batched GEMMs (the 16 products of a Winograd convolution) share one launch
         ta.a += (int64_t)blockIdx.z * ta.batch_a;
@@ -363,15 +368,15 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
     LaneTap la3, lb3[UB3];
     __amdgpu_buffer_rsrc_t ra = buffer_of(ta.a - a_shift, ta.a_bytes + (unsigned)a_shift * 4u),
                            rb = buffer_of(ta.b - b_shift, ta.b_bytes + (unsigned)b_shift * 4u);
-    int w_slot = 0;   // row table entry the next load_tiles reads
-    // Decodes the output positions of reduction step `step`: the last wave alone, every lane the entry lane % BK (four
-    // lanes write the same value), and no lane switched off on the way (the branch is uniform over the wave, the
-    // rest are selects).  Measured: a version in which only 16 lanes ran this code, under a narrowed execution mask
-    // while the step's loads were still in flight, now and then lost one row of a step on the two-wave tile shapes
-    // when several workgroups shared a compute unit; this version does not (kernel test with many short ranges).
-    auto fill_rows = [&](int step, int slot) {
+    int w_t = 0;      // step, counted from the start of the range, that the next load reads
+    // Decodes the output positions of reduction steps `step` .. `step` + 3: the last wave alone, no lane switched off on the way
+    // (the branch is uniform over the wave, the rest are selects).  Measured: a version in which only 16 lanes ran this code, under
+    // a narrowed execution mask while the step's loads were still in flight, now and then lost one row of a step on the two-wave
+    // tile shapes when several workgroups shared a compute unit; whole waves do not (kernel test with many short ranges).  With a table
+    // per step every step waited for the wave that wrote it (3x3, 256 -> 256, 56x56, batch 176: 4.06 against 3.81 ms).
+    auto fill_rows = [&](int step, int table) {
         if (ROWTAB && __builtin_amdgcn_readfirstlane(tid >> 6) == NT / 64 - 1) {
-            const int e = tid & (BK - 1);
+            const int e = lane;
             const int m = step * BK + e;
             const bool in = m < (int)Kg;
             const unsigned m32 = in ? (unsigned)m : 0u;
@@ -386,7 +391,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
             unsigned taps = 0;
             for (int r = 0; r < cs.R; ++r) taps |= ((rows >> r) & 1u) ? cols << (r * cs.S) : 0u;
             const unsigned pix = (unsigned)((((int64_t)n * cs.H + h0) * cs.W + w0) * cs.C + b_shift) * 4u;
-            rowtab[slot][e] = make_uint2(in ? pix : 0u, in ? taps : 0u);
+            rowtab[table * TABLE + e] = make_uint2(in ? pix : 0u, in ? taps : 0u);
         }
     };
 
@@ -470,7 +475,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
         part_step = FAST == 2 && MODE != WGRAD && left < BK;
         if (ROWTAB) {
 #pragma unroll
-            for (int s = 0; s < LB; ++s) w_row[s] = *(const unsigned long long *)&rowtab[w_slot][b_i0[s]];
+            for (int s = 0; s < LB; ++s) w_row[s] = *(const unsigned long long *)&rowtab[(w_t & 7) * BK + b_i0[s]];
         }
     };
     auto load_a = [&](float4 (&a_reg)[LA], const int s) {
@@ -651,10 +656,10 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
             u_c += BK;
             if (u_c >= cs.K) { u_c = 0; if (++u_s == ns) { u_s = 0; ++u_r; } }
         } else if (FAST) {
-            // kk0 now names the step after the one just loaded: its table goes into the entry that step's loads will
-            // read; every wave finished reading that entry before the barrier that ended the previous step
-            fill_rows(kk0 / BK, w_slot ^ 1);
-            w_slot ^= 1;
+            // kk0 now names the step after the one just loaded: if it is the first of a table, the table is written now; every wave
+            // finished reading that table four steps ago, and a barrier follows before the next load
+            ++w_t;
+            if ((w_t & 3) == 0) fill_rows(kk0 / BK, (w_t >> 2) & 1);
         } else {
 #pragma unroll
             for (int s = 0; s < LB; ++s) {
@@ -739,7 +744,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
         }
     };
     auto each_unit = [&](auto f) {
-        [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }(std::make_integer_sequence<int, UNITS>{});
+        for_each_int(f, std::make_integer_sequence<int, UNITS>{});
     };
     auto store_tiles = [&](auto odd, int buf, auto set) {
         each_unit([&](auto i) { unit(odd, i, buf, set, std::false_type{}); });
@@ -833,11 +838,8 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
         };
         load_tiles(s0);
         if constexpr (FAST) {
-            // a load writes the table entry that the load before it read: barriers between the first ones
-            if (ROWTAB) __syncthreads();
             if constexpr (STAGES == 2) {
                 if (steps > 1) load_tiles(s1);
-                if (ROWTAB) __syncthreads();
             }
             store_tiles(ordinary, 0, s0);
             if (steps > STAGES) load_tiles(s0);
@@ -899,7 +901,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 && FAST != 2 && FAST != 
         rb = buffer_of(ta.b - b_shift, ta.b_bytes + (unsigned)b_shift * 4u);
         clear();
         to_start();
-        w_slot = 0;
+        w_t = 0;
         if (ROWTAB) {
             fill_rows(kt0, 0);
             __syncthreads();
