@@ -29,6 +29,11 @@ __device__ __forceinline__ void buffer_store4(__amdgpu_buffer_rsrc_t r, unsigned
     typedef unsigned int word4 __attribute__((__vector_size__(16)));
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(word4, v), r, (int)voff, (int)soff, 0);
 }
+// the same past the caches (non-temporal)
+__device__ __forceinline__ void buffer_store4_stream(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, bf4 v) {
+    typedef unsigned int word4 __attribute__((__vector_size__(16)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(word4, v), r, (int)voff, (int)soff, 2);
+}
 __device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)voff, (int)soff, 0);
 }

@@ -118,6 +118,11 @@ struct TileArgs {
     int splits;                // reduction splits (>= 1); split z writes partial result z
     int64_t out_elems;         // elements of one (partial) result
     int accumulate;            // FWD/DGRAD, whole result only: add into the output
+    // whole result only: its stores pass the caches by.  For results of at least 256 MiB, what the last-level cache holds: whoever
+    // reads such a result next starts with a part that has left the cache, and the stores then only push out the operands
+    // (1x1, 64 -> 256, 56x56, batch 184: 237 -> 202 us; its input gradient's mirror 226 -> 191).  Smaller results are found in the
+    // cache by the next kernel: streaming them too cost MobileNetV2's step 1 %.
+    int stream;
     float *stats_part;         // FWD, whole results only: BatchNorm partial statistics of the output (tile_stats.hpp), or null
     BnAffine affine;           // FWD, whole results only: BatchNorm apply step of the output in the epilogue (gamma == null: off)
     unsigned a_bytes, b_bytes;             // operand sizes for the aligned loaders' descriptors: an element that does not exist is a load beyond them and reads zero
@@ -955,6 +960,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         const __amdgpu_buffer_rsrc_t r_out = buffer_of(out + tile_at);
         const __amdgpu_buffer_rsrc_t r_relu = buffer_of(MODE == FWD && ta.affine.relu_out ? ta.affine.relu_out + tile_at : out + tile_at);
         const unsigned t_voff = (unsigned)(lane >> 3) * row_bytes + 16u * (unsigned)(lane & 7);
+        const bool past_caches = MODE != WGRAD && ta.stream;
+        auto put4 = [&](__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, bf4 v) {
+            if (past_caches) buffer_store4_stream(r, voff, soff, v);      // uniform over the launch
+            else buffer_store4(r, voff, soff, v);
+        };
         auto emit = [&](auto whole_tile) {
             constexpr bool IN = decltype(whole_tile)::value;
 #pragma unroll
@@ -991,11 +1001,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
                             const float4 rv = float4{relu_clamp(val.x, ta.affine.relu), relu_clamp(val.y, ta.affine.relu),
                                                      relu_clamp(val.z, ta.affine.relu), relu_clamp(val.w, ta.affine.relu)};
                             if (ta.affine.relu_out) {
-                                if (IN) buffer_store4(r_relu, t_voff, t_soff, bf4{rv.x, rv.y, rv.z, rv.w});
+                                if (IN) put4(r_relu, t_voff, t_soff, bf4{rv.x, rv.y, rv.z, rv.w});
                                 else *(float4 *)(ta.affine.relu_out + orow * ta.Ng + col) = rv;
                             } else val = rv;
                         }
-                        if (IN) buffer_store4(r_out, t_voff, t_soff, bf4{val.x, val.y, val.z, val.w});
+                        if (IN) put4(r_out, t_voff, t_soff, bf4{val.x, val.y, val.z, val.w});
                         else *dst = val;
                     }
                 }
@@ -1175,6 +1185,7 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
     ta.out = out;
     ta.splits = 1;
     ta.accumulate = accumulate ? 1 : 0;
+    ta.stream = MODE != WGRAD && TAG == 0 && splits == 1 && ta.out_elems * 4 >= (256ll << 20);
     bool slabs = false;
     if (splits > 1) {
         slabs = true;
