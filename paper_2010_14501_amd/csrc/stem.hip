@@ -18,14 +18,20 @@
 // one row.  Workgroups loop over tiles.
 //
 // Filter gradient: dw[k][r][j] = sum_m dy[m][k] * x_row(m, r)[j]: A = dy (positions are the reduction index now, read
-// from memory in the instruction's layout: lane (k, h) loads dy[m + h][k]), B = lane (col, h) reads
-// LDS[off(m + h) + r(col) * rowlen + j(col)] with col = (r, j) flattened.  Wave kb of a workgroup owns the 32 output
+// from memory in the layout of v_mfma_f32_32x32x16_bf16: lane (k, h) loads dy[m + 8 h + i][k], i < 8), B = lane (col, h) reads
+// LDS[off(m + 8 h + i) + r(col) * rowlen + j(col)] with col = (r, j) flattened; both are split into bf16 pieces in registers
+// (bf16_pieces.hpp), 44 vector instructions per operand beside six matrix instructions per 32 columns.  7x7, 64 channels, 224x224,
+// batch 184: 581 -> 497 us (75 -> 87 TFLOP/s), error against 64 bits 8.5e-7 -> 3.1e-7; bound by the chain of LDS reads, splits and
+// matrix instructions of two waves per SIMD (256 registers).  The 3x3 filters keep the fp32 instruction, and so does the forward pass,
+// whose eight-value windows cost it more in LDS reads and registers than the instruction saves (529 -> 842 us).  Wave kb of a workgroup owns the 32 output
 // channels 32 kb .. 32 kb + 31 and all R * 3 S columns; the workgroups' partial results are added in a fixed order by
 // split_reduce.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
+#include "bf16_pieces.hpp"
 #include "buffer_addr.hpp"
 #include "kernels.hpp"
 
@@ -213,6 +219,134 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const float *__restric
 // block of dw of its output channels in registers (NBC column blocks of 32) over all its tiles and leaves it in
 // part[workgroup] at the end.
 template <int R, int S, int ST>
+__global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, StemGeom gm) {
+    extern __shared__ float lds[];
+    constexpr int RUN = 3 * S, COLS = R * RUN, NBC = (COLS + 31) / 32;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int kb = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nthreads = blockDim.x;
+    // LDS offset of this lane's column (r, j) in every column block relative to a position's window; a column beyond
+    // R * 3 S reads the window's first float into a result column that is never written
+    int coloff[NBC];
+#pragma unroll
+    for (int c = 0; c < NBC; ++c) {
+        int col = 32 * c + l32;
+        if (col >= COLS) col = 0;
+        coloff[c] = (col / RUN) * gm.rowlen + col % RUN;
+    }
+    floatx16 acc[NBC], low[NBC];      // the h * h terms and the smaller ones
+    const int total4 = gm.rows_in * (gm.rowlen / 4);
+    __shared__ int redo;              // an infinity or a NaN in the result: all tiles once more with the split that carries them
+    auto all_tiles = [&](auto special) {
+#pragma unroll
+    for (int c = 0; c < NBC; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][i] = low[c][i] = 0.0f;
+    for (int64_t tile = blockIdx.x; tile < gm.tiles; tile += gridDim.x) {
+        int n, p0, q0;
+        tile_origin(gm, tile, n, p0, q0);
+        __syncthreads();      // the previous tile has been read
+        for (int k0 = 0; k0 * nthreads < total4; k0 += FILL) {
+            float4 staged[FILL];
+            stem_fill_load<ST>(staged, x, gm, n, p0, q0, tid, nthreads, k0);
+            stem_fill_write(lds, staged, gm, tid, nthreads, k0);
+        }
+        __syncthreads();
+        const int rows_here = min(gm.nrow, gm.P - p0), cols_here = min(gm.qn, gm.Q - q0);
+        const int npos = gm.nrow == 1 ? cols_here : rows_here * gm.qn;      // positions of the tile that exist: m * K floats apart in dy
+        const __amdgpu_buffer_rsrc_t rdy = buffer_of(dy + (((int64_t)n * gm.P + p0) * gm.Q + q0) * gm.K);
+        const unsigned kbytes = (unsigned)gm.K * 4u, lbytes = (unsigned)(kb * 32 + l32) * 4u;
+        // groups of 16 positions, two register sets: the dy loads of the next group are issued before the matrix
+        // instructions of the current one.  A position beyond the tile contributes zero (its window in LDS is the image's).
+        struct Set { float a[8]; };
+        auto load = [&](Set &t, int m0) {      // this lane takes positions m0 + 8 h .. m0 + 8 h + 7
+            const int m = m0 + 8 * h;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float got = buffer_load(rdy, (m + i < npos ? (unsigned)(m + i) * kbytes : 0u) + lbytes, 0u);      // in bounds either way
+                t.a[i] = m + i < npos ? got : 0.0f;
+            }
+        };
+        auto compute = [&](const Set &t, int m0) {
+            int po[8];
+            {
+                const int m = m0 + 8 * h;
+                int pr = gm.nrow == 1 ? 0 : m / gm.qn, qq = m - pr * gm.qn;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const bool in = pr < gm.nrow && qq < gm.qn;      // a nominal position: its window lies in the staged rows
+                    po[i] = in ? pr * ST * gm.rowlen + qq * ST * 3 + gm.xlead : gm.xlead;
+                    ++qq;
+                    if (gm.nrow > 1 && qq >= gm.qn) { qq -= gm.qn; ++pr; }
+                }
+            }
+            const PieceRow a = split_row<decltype(special)::value>(t.a);
+            float v[8], next[8];
+            auto read = [&](int c, float (&o)[8]) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) o[i] = lds[po[i] + coloff[c]];
+            };
+            read(0, v);
+#pragma unroll
+            for (int c = 0; c < NBC; ++c) {
+                if (c + 1 < NBC) read(c + 1, next);
+                __builtin_amdgcn_sched_barrier(0);
+                const PieceRow b = split_row<decltype(special)::value>(v);
+                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc[c], 0, 0, 0);
+                low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, low[c], 0, 0, 0);
+                low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, low[c], 0, 0, 0);
+                low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, low[c], 0, 0, 0);
+                low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, low[c], 0, 0, 0);
+                low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, low[c], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);      // the splits of several columns gathered ahead would not fit the registers
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = next[i];
+            }
+        };
+        const int groups = (npos + 15) / 16;
+        Set s0, s1;
+        if (groups > 0) load(s0, 0);
+        for (int g = 0; g < groups; g += 2) {
+            if (g + 1 < groups) load(s1, (g + 1) * 16);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(s0, g * 16);
+            if (g + 2 < groups) load(s0, (g + 2) * 16);
+            __builtin_amdgcn_sched_barrier(0);
+            if (g + 1 < groups) compute(s1, (g + 1) * 16);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NBC; ++c) acc[c] += low[c];
+    };
+    if (tid == 0) redo = 0;
+    __syncthreads();
+    all_tiles(std::false_type{});
+    {
+        float sum = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NBC; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += acc[c][i];
+        if (!(__builtin_fabsf(sum) < __builtin_inff())) redo = 1;
+    }
+    __syncthreads();
+    if (redo) all_tiles(std::true_type{});
+    // this workgroup's partial result, laid out as dw[k][r][s][c]: lane holds column l32 of rows 8 (i / 4) + 4 h + i % 4
+    float *mine = part + (int64_t)blockIdx.x * gm.K * COLS;
+#pragma unroll
+    for (int c = 0; c < NBC; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int row = kb * 32 + 8 * (i / 4) + 4 * h + (i % 4), col = 32 * c + l32;
+            if (col < COLS) mine[row * COLS + col] = acc[c][i];
+        }
+}
+
+// The same with the fp32 matrix instruction, for the 3x3 filters: 27 columns, bound by reading dy, which groups of 16 positions
+// in place of 32 slowed down (stride 1, 64 channels, 224x224, batch 176: 755 against 866 us).  A workgroup of K / 32 waves walks tiles; wave kb keeps the 32 x (R * 3 S)
+// block of dw of its output channels in registers (NBC column blocks of 32) over all its tiles and leaves it in
+// part[workgroup] at the end.
+template <int R, int S, int ST>
 __global__ __launch_bounds__(256, 2) void stem_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, StemGeom gm) {
     extern __shared__ float lds[];
     constexpr int RUN = 3 * S, COLS = R * RUN, NBC = (COLS + 31) / 32, U = NBC >= 4 ? 8 : 16;
@@ -342,7 +476,8 @@ int stem_wgrad_groups(const StemPlan &sp, int splits) { return (int)std::min<int
 
 template <int R, int S, int ST>
 void launch_stem_wgrad(hipStream_t st, const float *x, const float *dy, float *ws, const StemPlan &sp, int groups) {
-    hipLaunchKernelGGL((stem_wgrad_kernel<R, S, ST>), dim3((unsigned)groups), dim3(64u * (unsigned)(sp.gm.K / 32)), sp.lds_bytes, st, x, dy, ws, sp.gm);
+    if constexpr (R == 7) hipLaunchKernelGGL((stem7_wgrad_kernel<R, S, ST>), dim3((unsigned)groups), dim3(64u * (unsigned)(sp.gm.K / 32)), sp.lds_bytes, st, x, dy, ws, sp.gm);
+    else hipLaunchKernelGGL((stem_wgrad_kernel<R, S, ST>), dim3((unsigned)groups), dim3(64u * (unsigned)(sp.gm.K / 32)), sp.lds_bytes, st, x, dy, ws, sp.gm);
     hip_check(hipGetLastError(), "stem_wgrad launch");
 }
 

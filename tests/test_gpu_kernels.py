@@ -673,6 +673,44 @@ def test_first_layer_forward_and_filter_gradient_from_rows_staged_in_lds(case):
     check_close(got[0], wt.weight_from_oracle(nm.conv2d_wgrad(xo, dyo, R, R, stride, pad)), GRAD_TOL, what="filter gradient")
 
 
+@pytest.mark.parametrize("kind", ["finite", "inf", "nan", "near_max"])
+@pytest.mark.parametrize("case", [(2, 40, 38, 64), (1, 24, 24, 32), (1, 31, 29, 96)])
+def test_first_layer_filter_gradient_of_infinities_and_nans(case, kind):
+    """7x7 / stride 2 filter gradient (bf16 pieces): special values at positions whose windows lie inside the image come out
+    as the fp32 products' sums."""
+    torch = torch_mod()
+    N, H, W, K = case
+    rng = np.random.default_rng(3)
+    P, Q = (H - 1) // 2 + 1, (W - 1) // 2 + 1
+    x = (np.abs(rng.standard_normal((N, H, W, 3))) + 0.5).astype(np.float32)
+    dy = (np.abs(rng.standard_normal((N, P, Q, K))) + 0.5).astype(np.float32)
+    if kind == "inf":
+        dy[0, 5, 5, 3], x[0, 12, 9, 1] = -np.inf, np.inf
+    elif kind == "nan":
+        dy[0, 5, 5, 3], x[0, 12, 9, 1] = np.nan, np.nan
+    elif kind == "near_max":      # rounds to infinity in bf16
+        dy[0, 5, 5, 3] = 3.4e38
+        x[0, 7:14, 7:14] *= 1e-4
+    pad = np.zeros((N, H + 6, W + 6, 3), np.float64)
+    pad[:, 3:3 + H, 3:3 + W] = x
+    want = np.empty((K, 7, 7, 3))
+    with np.errstate(all="ignore"):
+        for r in range(7):
+            for s in range(7):
+                win = pad[:, r:r + 2 * P - 1:2, s:s + 2 * Q - 1:2].reshape(-1, 3)
+                want[:, r, s] = (dy.reshape(-1, K, 1).astype(np.float64) * win[:, None, :]).sum(0)
+    splits = 4
+    ws = torch.empty(splits * K * 147, device="cuda")
+    gx, gd, dw = dev(x), dev(dy), torch.empty((K, 7, 7, 3), device="cuda")
+    monet.call("monet_conv_stem_wgrad", None, gx.data_ptr(), gd.data_ptr(), dw.data_ptr(), N, H, W, K, 7, 7, 2, 3, splits, ws.data_ptr(), ws.numel() * 4)
+    got, want = dw.cpu().numpy(), want.astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)]) and np.array_equal(np.isinf(got), np.isinf(want))
+    fine = np.isfinite(want)
+    # at most 760 products of one sign: fp32 sums within 760 * 2^-24 of fp64's
+    assert np.all(np.abs(got[fine] - want[fine]) <= 760 * 2.0 ** -24 * np.abs(want[fine]))
+
+
 def test_first_layer_kernels_refuse_what_they_are_not_for():
     torch = torch_mod()
     t = torch.zeros(1 << 20, device="cuda")
