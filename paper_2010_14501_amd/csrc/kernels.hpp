@@ -45,7 +45,7 @@ struct BnAffine {
 // which convolution kernels can write the sign code from their epilogue
 bool conv_epilogue_writes_mask(const ConvShape &cs, bool winograd_fused);
 
-// ---- convolution (implicit GEMM on fp32 MFMA)
+// ---- convolution (implicit GEMM; fp32 products as sums of bf16 matrix instructions)
 // Every variant can cut its reduction into `splits` ranges: partial results go to ws (splits * |output|
 // floats) and are added in range order.  splits == 1 needs no workspace.
 // y (+)= conv(x, w)
@@ -124,8 +124,8 @@ void pointwise_wgrad(hipStream_t st, const float *x, const float *dy, float *dw,
 
 // tuning aid: cfg 0..5 forces tile shape (2x2, 4x1, 1x4, 2x1, 1x2, 1x1 waves of 64x64); -1 restores the heuristic
 void conv_force_tile(int cfg);
-// workspace bytes of conv_fwd (which = 0) / conv_dgrad (which = 1) for `splits` ranges; for splits = 1 the bytes
-// with which the ragged last round of tiles is cut as far as it pays (0 if there is nothing to gain)
+// workspace bytes of conv_fwd (which = 0) / conv_dgrad (which = 1) for `splits` ranges; for splits = 1 a size
+// that callers' saved plans declare and the kernels leave alone (0 where none was ever declared)
 size_t conv_workspace_bytes(int which, const ConvShape &cs, int splits);
 
 // ---- BatchNorm over rows x C (rows = N*H*W), training mode, biased variance

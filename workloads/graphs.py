@@ -419,10 +419,9 @@ def conv_split_plan(rows, cols, reduction, classes=1, out_elems=None):
       * fewer than two tiles per CU (or fewer than eight with stride > 1): cut every tile into the number of
         ranges s (at most 16, at least 128 reduction elements each) that minimises rounds / s, with 1 % per range
         for the slabs of partial results a second kernel adds;
-      * otherwise, stride 1, at least 48 reduction steps of 16: `splits` stays 1 and a workspace lets the library
-        cut only the tiles beyond a multiple of 256, into as many ranges as keep them within one round (their
-        parts are added inside the kernel; with a short reduction the device-wide release this needs costs
-        more than the idle CUs);
+      * otherwise, stride 1, at least 48 reduction steps of 16: `splits` stays 1 and the graph declares the small
+        workspace with which earlier kernels cut the tiles beyond a multiple of 256 (the kernels now leave it
+        alone; it stays declared, so that graphs, cost tables and stored schedules keep their sizes);
       * otherwise: plain."""
     bm, bn = (256, 64) if cols <= 64 else (128, 128)
     tiles = math.ceil(rows / bm) * math.ceil(cols / bn)
