@@ -27,7 +27,8 @@ struct BnGeom {
     int64_t slab;
 };
 
-BnGeom bn_geom(int64_t rows, int C, int64_t scratch_floats, int per_slab_floats_per_channel) {
+// small: slabs of two sweeps instead of eight where those leave CUs without a workgroup (stream_grid's reason)
+BnGeom bn_geom(int64_t rows, int C, int64_t scratch_floats, int per_slab_floats_per_channel, bool small = false) {
     if (C % 4) throw KernelError("BatchNorm: C must be a multiple of 4");
     BnGeom g;
     g.C4 = C / 4;
@@ -36,6 +37,7 @@ BnGeom bn_geom(int64_t rows, int C, int64_t scratch_floats, int per_slab_floats_
     g.RPP = 256 / g.TPR;
     g.CB = (g.C4 + g.TPR - 1) / g.TPR;
     int64_t want = (rows + (int64_t)g.RPP * 8 - 1) / ((int64_t)g.RPP * 8);
+    if (small) want = std::max<int64_t>(want, std::min<int64_t>((rows + (int64_t)g.RPP * 2 - 1) / ((int64_t)g.RPP * 2), 256 / g.CB));
     int64_t cap = scratch_floats / ((int64_t)per_slab_floats_per_channel * C);
     if (cap < 1) throw KernelError("BatchNorm: reduction scratch too small");
     g.G = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, 1024), cap));
@@ -365,12 +367,6 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const float *x, float *y,
     }
 }
 
-// one workgroup per 2048 float4 (32 KiB), up to 64 Ki workgroups
-static int stream_grid(int64_t total4) {
-    int64_t want = (total4 + 2047) / 2048;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(want, 65536));
-}
-
 void bn_apply(hipStream_t st, const float *x, float *y, const float *gamma, const float *beta, const float *stats, int64_t rows, int C) {
     if (C % 4) throw KernelError("BatchNorm: C must be a multiple of 4");
     int64_t total4 = rows * (C / 4);
@@ -675,7 +671,7 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
         else throw KernelError("BatchNorm backward: unknown ReLU mode");
     }
     int64_t floats = (int64_t)(scratch_bytes / 4) - 2 * C;    // tail of the scratch holds the two coefficient vectors
-    BnGeom g = bn_geom(rows, C, floats, 2);
+    BnGeom g = bn_geom(rows, C, floats, 2, true);
     float *coef = scratch + (int64_t)g.G * C * 2;
     const int64_t total4 = rows * (C / 4);
     const int grid = stream_grid(total4);

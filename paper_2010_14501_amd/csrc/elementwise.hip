@@ -884,7 +884,13 @@ void softmaxce_bwd(hipStream_t st, const float *logits, const int32_t *labels, f
 __global__ __launch_bounds__(256) void partial_sum_kernel(const float *__restrict__ x, float *__restrict__ part, int64_t n) {
     __shared__ float sh[8];
     float s = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) s += x[i];
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (; i + 3 * step < n; i += 4 * step) {             // four loads in flight
+        const float a = x[i], b = x[i + step], c = x[i + 2 * step], d = x[i + 3 * step];
+        s += a; s += b; s += c; s += d;
+    }
+    for (; i < n; i += step) s += x[i];
     s = block_sum(s, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
@@ -913,6 +919,8 @@ void linear_bias_grad(hipStream_t st, const float *dy, float *db, int N, int out
 void sumloss_fwd(hipStream_t st, const float *x, float *loss, int64_t n, float *scratch, size_t scratch_bytes) {
     int grid = grid_for(n, 256 * 16, 1024);
     if ((size_t)grid * 4 > scratch_bytes) throw KernelError("sumloss: scratch too small");
+    // small inputs: four elements per thread instead of sixteen, as far as the scratch holds the partial sums
+    grid = std::max(grid, (int)std::min<size_t>(grid_for(n, 256 * 4, 256), scratch_bytes / 4));
     hipLaunchKernelGGL(partial_sum_kernel, dim3(grid), dim3(256), 0, st, x, scratch, n);
     hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st, (const float *)scratch, loss, (int64_t)grid, 1.0f);
     hip_check(hipGetLastError(), "sumloss_fwd launch");

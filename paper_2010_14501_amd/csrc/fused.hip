@@ -104,13 +104,6 @@ __global__ __launch_bounds__(256) void fwd_chain_kernel(const float *x, const fl
     }
 }
 
-// one workgroup per 2048 float4 (32 KiB) up to 64 Ki workgroups: many short contiguous streams measured
-// fastest for a plain copy on this chip
-int chain_grid(int64_t total4) {
-    int64_t want = (total4 + 2047) / 2048;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(want, 65536));
-}
-
 }  // namespace
 
 void fwd_chain(hipStream_t st, const float *x, const float *x2, const float *gamma, const float *beta, const float *stats, int C,
@@ -121,7 +114,7 @@ void fwd_chain(hipStream_t st, const float *x, const float *x2, const float *gam
     if (bn && C % 4) throw KernelError("fused forward: C must be a multiple of 4");
     if (!bn && out_bn) throw KernelError("fused forward: BatchNorm output requested without BatchNorm");
     const int64_t total4 = n / 4;
-    const int grid = chain_grid(total4);
+    const int grid = stream_grid(total4);
 #define FC(BN, ADD, SIX, MK) \
     hipLaunchKernelGGL((fwd_chain_kernel<BN, ADD, SIX, MK>), dim3(grid), dim3(256), 0, st, x, x2, gamma, beta, stats, C, out_bn, out_pre, out, mask, total4)
 #define FC_MK(BN, ADD, SIX) do { if (mk) FC(BN, ADD, SIX, true); else FC(BN, ADD, SIX, false); } while (0)
@@ -194,7 +187,7 @@ void relu_bwd_fanout(hipStream_t st, const float *dz, const void *t, int mode, f
     if (n <= 0) return;
     if (n % 4) throw KernelError("fused ReLU backward: element count must be a multiple of 4");
     const int64_t total4 = n / 4;
-    const int grid = chain_grid(total4);
+    const int grid = stream_grid(total4);
 #define RF(MODE, SIX) hipLaunchKernelGGL((relu_bwd_fanout_kernel<MODE, SIX>), dim3(grid), dim3(256), 0, st, dz, t, d0, acc0 ? 1 : 0, d1, acc1 ? 1 : 0, total4)
     if (mode == RELU_FROM_MASK) RF(RELU_FROM_MASK, false);
     else if (mode == RELU_FROM_INPUT || mode == RELU_FROM_OUTPUT) { if (six) RF(RELU_FROM_INPUT, true); else RF(RELU_FROM_INPUT, false); }

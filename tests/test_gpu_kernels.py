@@ -847,6 +847,38 @@ def test_batchnorm_matches_oracle(rows, C):
         check_close(gx.cpu().numpy(), 2 * dxo.reshape(rows, C), GRAD_TOL)
 
 
+# edges of the ranges small tensors are cut into: one sweep of 256 16-byte elements per workgroup (64 rows of 16 channels), 512
+# workgroups, slabs of two sweeps, the 256th slab; channel groups that are no power of two, and more than 512 of them
+@pytest.mark.parametrize("rows,C", [(3, 4), (63, 16), (64, 16), (65, 16), (127, 16), (129, 16), (32767, 16), (32769, 16), (300, 24), (9, 2052)])
+@pytest.mark.parametrize("slabs", [1, 3, 1024])
+def test_batchnorm_backward_on_small_tensors(rows, C, slabs):
+    torch = torch_mod()
+    rng = np.random.default_rng(rows * 131 + C)
+    x = rng.standard_normal((rows, C), dtype=np.float32)
+    gamma = rng.uniform(0.5, 1.5, C).astype(np.float32)
+    beta = (0.1 * rng.standard_normal(C)).astype(np.float32)
+    dy = rng.standard_normal((rows, C), dtype=np.float32)
+    xo, dyo = x.astype(np.float64).reshape(rows, C, 1, 1), dy.astype(np.float64).reshape(rows, C, 1, 1)
+    yo, mean, invstd = nm.bn_fwd(xo, gamma.astype(np.float64), beta.astype(np.float64), 1e-5)
+    dxo, dgo, dbo = nm.bn_bwd_from_input(dyo, xo, gamma.astype(np.float64), mean, invstd)
+    dx_, dg_, db_, dd = dev(x), dev(gamma), dev(beta), dev(dy)
+    stats = dev(np.concatenate([mean.ravel(), invstd.ravel()]).astype(np.float32))
+    y = torch.full((rows, C), float("nan"), dtype=torch.float32, device="cuda")
+    monet.call("monet_bn_apply", None, dx_.data_ptr(), y.data_ptr(), dg_.data_ptr(), db_.data_ptr(), stats.data_ptr(), rows, C)
+    check_close(y.cpu().numpy(), yo.reshape(rows, C), ACT_TOL)
+    # scratch for `slabs` partial results and the two coefficient vectors, with a guard behind it
+    floats = (slabs + 1) * 2 * C
+    scratch = torch.full((floats + 64,), -7.0, dtype=torch.float32, device="cuda")
+    gx = torch.full((rows, C), float("nan"), dtype=torch.float32, device="cuda")
+    gg, gb = torch.empty(C, device="cuda"), torch.empty(C, device="cuda")
+    monet.call("monet_bn_bwd", None, dd.data_ptr(), dx_.data_ptr(), 0, dg_.data_ptr(), db_.data_ptr(), stats.data_ptr(),
+               gx.data_ptr(), gg.data_ptr(), gb.data_ptr(), rows, C, 0, scratch.data_ptr(), floats * 4)
+    check_close(gx.cpu().numpy(), dxo.reshape(rows, C), GRAD_TOL)
+    check_close(gg.cpu().numpy(), dgo, GRAD_TOL)
+    check_close(gb.cpu().numpy(), dbo, GRAD_TOL)
+    assert (scratch[floats:] == -7.0).all()
+
+
 def test_batchnorm_statistics_with_large_offset():
     """Mean far from zero: a sum-of-squares formulation would lose the variance here."""
     torch = torch_mod()
