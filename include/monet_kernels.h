@@ -29,8 +29,9 @@ extern "C" {
  *   splits > 1: ws >= splits * |result| floats; a second kernel adds the partial results.  A launch uses fewer ranges than
  *     it is given where more would only cost partial results.
  *   splits == 1: the reduction is not cut; a workspace is accepted and left alone.
- * Products are exact fp32 products to about 2^-25 (three bf16 pieces per operand on the matrix cores), sums are fp32; infinities and
- * NaNs come out as the fp32 product's.
+ * A product is worked in six terms of three bf16 pieces per operand on the matrix cores, to 2^-24 of itself at worst; sums are
+ * fp32.  A tile of the result (up to 128x128) that ends with an infinity or a NaN in it is worked once more with the fp32
+ * matrix instruction: infinities, NaNs and overflows come out as fp32 arithmetic's.
  * Appendix D's workspace / speed trade-off of convolution algorithms is this choice.
  *
  * y[N,P,Q,K] = cross-correlation of x[N,H,W,C] with w[K,R,S,C], zero padding, no bias. */

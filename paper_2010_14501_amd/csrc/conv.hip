@@ -118,7 +118,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     constexpr int SA = BM * 4, SB = BN * 4, LA = SA >= NT ? SA / NT : 1, LB = SB >= NT ? SB / NT : 1;
     __shared__ __attribute__((aligned(16))) unsigned As[2][A_SZ];
     __shared__ __attribute__((aligned(16))) unsigned Bs[2][B_SZ];
-    __shared__ int redo;     // a first pass left an infinity or a NaN: once more with the special split
+    __shared__ int redo;     // a first pass left an infinity or a NaN: once more with the fp32 matrix instruction
     // First layers (3 input channels): the element-wise forward loader looks the (r, s, c) of a reduction index up
     // instead of dividing (measured 925 -> 815 us on the ResNet-50 stem).  Only the 64 columns wide tiles have
     // the LDS to spare (2 KiB), and those are the ones results up to 64 channels wide, i.e. every first layer, use.
@@ -646,13 +646,10 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
 
     // One operand's slot (two slots where they share words), split into pieces and written as words of two neighbouring
     // reduction indices.
-    auto put_unit = [&](auto odd, auto kc, auto count, auto width, auto unit, int t, unsigned *dst, const auto &reg) {
+    auto put_unit = [&](auto kc, auto count, auto width, auto unit, int t, unsigned *dst, const auto &reg) {
         constexpr bool KC = decltype(kc)::value;
         constexpr int L = decltype(count)::value, n = decltype(width)::value, PL = plane_words(KC, n), u = decltype(unit)::value;
-        auto pieces = [&](float x, float y) {
-            if constexpr (decltype(odd)::value) return split_pair_special(x, y);
-            else return split_pair(x, y);
-        };
+        auto pieces = [&](float x, float y) { return split_pair(x, y); };
         if constexpr (KC) {
             const int idx = t + u * NT;
             const float4 v = reg[u];
@@ -688,18 +685,18 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     };
     constexpr int UA = A_KC || LA == 1 ? LA : LA / 2, UB = B_KC || LB == 1 ? LB : LB / 2, UNITS = UA + UB;
     // unit i of the step held in register stage `set` goes to LDS buffer `buf`; `again`: and its registers take the next loads
-    auto unit = [&](auto odd, auto i, int buf, auto set, auto again) {
+    auto unit = [&](auto i, int buf, auto set, auto again) {
         constexpr int u = decltype(i)::value;
         float4 (&a_reg)[LA] = a_regs[decltype(set)::value];
         float4 (&b_reg)[LB] = b_regs[decltype(set)::value];
         if constexpr (u < UA) {
-            put_unit(odd, std::bool_constant<A_KC>{}, std::integral_constant<int, LA>{}, std::integral_constant<int, BM>{}, std::integral_constant<int, u>{}, tid_a, As[buf], a_reg);
+            put_unit(std::bool_constant<A_KC>{}, std::integral_constant<int, LA>{}, std::integral_constant<int, BM>{}, std::integral_constant<int, u>{}, tid_a, As[buf], a_reg);
             if constexpr (decltype(again)::value) {
                 if constexpr (A_KC || LA == 1) load_a(a_reg, u);
                 else { load_a(a_reg, 2 * u); load_a(a_reg, 2 * u + 1); }
             }
         } else {
-            put_unit(odd, std::bool_constant<B_KC>{}, std::integral_constant<int, LB>{}, std::integral_constant<int, BN>{}, std::integral_constant<int, u - UA>{}, tid_b, Bs[buf], b_reg);
+            put_unit(std::bool_constant<B_KC>{}, std::integral_constant<int, LB>{}, std::integral_constant<int, BN>{}, std::integral_constant<int, u - UA>{}, tid_b, Bs[buf], b_reg);
             if constexpr (decltype(again)::value) {
                 if constexpr (B_KC || LB == 1) load_b(b_reg, u - UA);
                 else { load_b(b_reg, 2 * (u - UA)); load_b(b_reg, 2 * (u - UA) + 1); }
@@ -709,8 +706,8 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     auto each_unit = [&](auto f) {
         for_each_int(f, std::make_integer_sequence<int, UNITS>{});
     };
-    auto store_tiles = [&](auto odd, int buf, auto set) {
-        each_unit([&](auto i) { unit(odd, i, buf, set, std::false_type{}); });
+    auto store_tiles = [&](int buf, auto set) {
+        each_unit([&](auto i) { unit(i, buf, set, std::false_type{}); });
     };
 
     // Two sums per result: the h * h terms and the five smaller ones.  A matrix instruction rounds its sum to fp32; the smaller terms'
@@ -762,7 +759,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             else if constexpr (J == 1) { term(low, am, bh); term(low, am, bm); al = frag_a(buf, 2); bl = frag_b(buf, 2); }
             else { term(low, ah, bl); term(low, al, bh); }
             each_unit([&](auto i) {
-                if constexpr (decltype(i)::value * 3 / UNITS == J) unit(std::false_type{}, i, buf ^ 1, set, std::true_type{});
+                if constexpr (decltype(i)::value * 3 / UNITS == J) unit(i, buf ^ 1, set, std::true_type{});
             });
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -784,7 +781,6 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     };
     clear();
     if (tid == 0) redo = 0;      // read behind the barriers below
-    const std::false_type ordinary{};
     if (kt0 < kt1) {
         const int steps = kt1 - kt0;
         if (ROWTAB) {
@@ -804,7 +800,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             if constexpr (STAGES == 2) {
                 if (steps > 1) load_tiles(s1);
             }
-            store_tiles(ordinary, 0, s0);
+            store_tiles(0, s0);
             if (steps > STAGES) load_tiles(s0);
             __syncthreads();
             int t = 0;
@@ -826,14 +822,14 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
                 }
             }
         } else {
-            store_tiles(ordinary, 0, s0);
+            store_tiles(0, s0);
             __syncthreads();
             for (int t = 0; t + 1 < steps; ++t) {
                 load_tiles(s0);
                 __builtin_amdgcn_sched_barrier(0);
                 compute(t & 1);
                 __builtin_amdgcn_sched_barrier(0);
-                store_tiles(ordinary, (t + 1) & 1, s0);
+                store_tiles((t + 1) & 1, s0);
                 __syncthreads();
             }
         }
@@ -844,8 +840,9 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         for (int i = 0; i < 2; ++i) acc[i] += low[i];
     };
     join();
-    // An infinity or a NaN in the result says that an operand held one, or that a product overflowed (perhaps only with pieces
-    // rounded up): this tile once more with the split that treats those as the fp32 product would.  Finite data: one barrier and 32 additions per tile.
+    // An infinity or a NaN in the result says that an operand held one, that a value near the type's largest rounded to infinity in
+    // bf16, or that a product or a sum overflowed: pieces of such numbers do not add up to what fp32 arithmetic gives, so this tile is
+    // worked once more with the fp32 matrix instruction.  Finite data: one barrier and 32 additions per tile.
     {
         float probe[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -869,14 +866,44 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             fill_rows(kt0, 0);
             __syncthreads();
         }
+        // One step at a time, nothing overlapped: these tiles are rare.  The operands lie in the first buffer's place as floats,
+        // [row][17] where the reduction is contiguous, else [reduction index][column + 4].
+        auto whole = [](auto kc, auto width, int red, int r) {
+            if constexpr (decltype(kc)::value) return r * (BK + 1) + red;
+            else return red * (decltype(width)::value + 4) + r;
+        };
+        auto put_whole = [&](auto kc, auto count, auto width, int t, float *dst, const auto &reg) {
+            constexpr bool KC = decltype(kc)::value;
+            constexpr int L = decltype(count)::value, n = decltype(width)::value;
+            static_assert((KC ? n * (BK + 1) : BK * (n + 4)) <= 2 * 3 * plane_words(KC, n), "a step's floats fit the two buffers");
+#pragma unroll
+            for (int s = 0; s < L; ++s) {
+                const float e[4] = {reg[s].x, reg[s].y, reg[s].z, reg[s].w};
+                const int idx = t + s * NT;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    dst[KC ? whole(kc, width, (idx % 4) * 4 + u, idx / 4) : whole(kc, width, rc_red(t, s, L, n), rc_col4(t, s, L, n) * 4 + u)] = e[u];
+            }
+        };
+        const std::bool_constant<A_KC> kc_a{};
+        const std::bool_constant<B_KC> kc_b{};
+        const std::integral_constant<int, BM> rows{};
+        const std::integral_constant<int, BN> cols{};
+        float *fa = (float *)&As[0][0], *fb = (float *)&Bs[0][0];
         for (int t = kt0; t < kt1; ++t) {
             load_tiles(std::integral_constant<int, 0>{});
-            store_tiles(std::true_type{}, 0, std::integral_constant<int, 0>{});
+            put_whole(kc_a, std::integral_constant<int, LA>{}, rows, tid_a, fa, a_regs[0]);
+            put_whole(kc_b, std::integral_constant<int, LB>{}, cols, tid_b, fb, b_regs[0]);
             __syncthreads();
-            compute(0);
+#pragma unroll
+            for (int k = 0; k < BK; k += 2) {
+                const float y = fb[whole(kc_b, cols, k + g, wn * 32 + l32)];
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+                    acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[whole(kc_a, rows, k + g, wm * 64 + mi * 32 + l32)], y, acc[mi], 0, 0, 0);
+            }
             __syncthreads();
         }
-        join();
     }
 
     // ---------------- epilogue: lane holds column l32 of rows 8*(v/4) + 4*g + v%4 of each 32x32 block

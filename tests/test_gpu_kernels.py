@@ -143,10 +143,11 @@ SPECIAL_CASES = [
 
 
 @pytest.mark.parametrize("case", SPECIAL_CASES)
-@pytest.mark.parametrize("kind", ["inf", "nan", "inf_times_zero", "both_inf", "near_max", "overflow", "tiny"])
+@pytest.mark.parametrize("kind", ["inf", "nan", "inf_times_zero", "inf_times_subnormal", "both_inf", "near_max", "overflow", "tiny"])
 def test_conv_of_infinities_nans_and_extreme_values(case, kind):
-    """Every float is worked as three bf16 pieces: infinities, NaNs, values that round to infinity in bf16 and products that
-    overflow have to come out as the fp32 product's.  Reference: the same sums in fp64, rounded to fp32."""
+    """The matrix products are worked in three bf16 pieces per float: infinities, NaNs, values that round to infinity in bf16 and
+    products that overflow have to come out as the fp32 product's, with the finite results beside them as close as ever.
+    Reference: the same sums in fp64, rounded to fp32."""
     torch = torch_mod()
     N, H, W, C, K = case
     rng = np.random.default_rng(5)
@@ -160,6 +161,8 @@ def test_conv_of_infinities_nans_and_extreme_values(case, kind):
         x[0, 1, 2, 3], dy[0, 2, 2, 5] = np.nan, np.nan
     elif kind == "inf_times_zero":
         x[0, 1, 2, 3], w[2, 0, 0, 3], w[3, 0, 0, 3], dy[0, 1, 2, 9] = inf, 0.0, -0.0, 0.0
+    elif kind == "inf_times_subnormal":      # 1e-41 is below bf16's smallest number
+        x[0, 1, 2, 3], w[2, 0, 0, 3], w[3, 0, 0, 3], dy[0, 1, 2, 9] = inf, 1e-41, -1e-41, 1e-41
     elif kind == "both_inf":
         x[0, 1, 2, 3], w[2, 0, 0, 3], w[3, 0, 0, 3], dy[0, 1, 2, 9] = inf, inf, -inf, -inf
     elif kind == "near_max":      # 3.4e38 rounds to infinity in bf16
@@ -171,25 +174,108 @@ def test_conv_of_infinities_nans_and_extreme_values(case, kind):
     with np.errstate(all="ignore"):
         x2, w2, g2 = x.reshape(-1, C).astype(np.float64), w.reshape(K, C).astype(np.float64), dy.reshape(-1, K).astype(np.float64)
 
-        def product(a, b):      # a[m, r] b[r, n] in fp32 semantics: every product and the sum rounded to fp32's range
+        def product(a, b):      # a[m, r] b[r, n] in fp32 semantics (every product and the sum rounded to fp32's range) and sum |a b|
             p = (a[:, :, None] * b[None, :, :]).astype(np.float32).astype(np.float64)
-            return p.sum(1).astype(np.float32)
-        want = dict(y=product(x2, w2.T), dx=product(g2, w2), dw=np.concatenate([product(g2.T[i:i + 8], x2) for i in range(0, K, 8)]))
+            return p.sum(1).astype(np.float32), np.abs(p).sum(1)
+
+        def rows(a, b):
+            parts = [product(a[i:i + 8], b) for i in range(0, len(a), 8)]
+            return tuple(np.concatenate([q[j] for q in parts]) for j in (0, 1))
+        want = dict(y=rows(x2, w2.T), dx=rows(g2, w2), dw=rows(g2.T, x2))
     gx, gw, gd = dev(x), dev(w), dev(dy)
     got = dict(y=torch.empty(N * H * W, K, device="cuda"), dx=torch.empty(N * H * W, C, device="cuda"), dw=torch.empty(K, C, device="cuda"))
     dims = (N, H, W, C, K, 1, 1, 1, 0)
-    ws = torch.empty(3 * K * C, device="cuda")
+    ws = torch.empty(3 * max(t.numel() for t in got.values()), device="cuda")
     for splits in (1, 3):
-        monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), got["y"].data_ptr(), *dims, 1, None, 0)
-        monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), got["dx"].data_ptr(), *dims, 0, 1, None, 0)
-        monet.call("monet_conv_wgrad", None, gx.data_ptr(), gd.data_ptr(), got["dw"].data_ptr(), *dims, splits, ws.data_ptr(), ws.numel() * 4)
+        wsp = (ws.data_ptr(), ws.numel() * 4)
+        monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), got["y"].data_ptr(), *dims, splits, *wsp)
+        monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), got["dx"].data_ptr(), *dims, 0, splits, *wsp)
+        monet.call("monet_conv_wgrad", None, gx.data_ptr(), gd.data_ptr(), got["dw"].data_ptr(), *dims, splits, *wsp)
         for name, t in got.items():
-            a, b = t.cpu().numpy(), want[name]
+            a, (b, mag) = t.cpu().numpy(), want[name]
             assert np.array_equal(np.isnan(a), np.isnan(b)), (name, splits)
             assert np.array_equal(np.isinf(a), np.isinf(b)) and np.array_equal(a[np.isinf(b)], b[np.isinf(b)]), (name, splits)
             fine = np.isfinite(b)
-            # at most 324 products of like size: their fp32 sums differ from fp64's by less than 324 * 2^-24
-            assert np.all(np.abs(a[fine] - b[fine]) <= 324 * 2.0 ** -24 * np.maximum(np.abs(b[fine]), 1.0) * 8), (name, splits)
+            err = np.abs(a[fine].astype(np.float64) - b[fine]) / mag[fine]
+            # sums of n products, n additions rounded to 2^-24 each and the terms the pieces leave out (2^-24): at worst
+            # (n + 1) 2^-24 of sum |a b| apiece, and over many results, whose roundings do not add up, sqrt(n) 2^-24 in the norm
+            n = dict(y=C, dx=K, dw=N * H * W)[name]
+            assert err.max() <= (n + 1) * 2.0 ** -24, (name, splits, err.max() * 2.0 ** 24)
+            assert np.sqrt((err ** 2).mean()) <= np.sqrt(n) * 2.0 ** -24, (name, splits, np.sqrt((err ** 2).mean()) * 2.0 ** 24)
+
+
+def test_conv_of_one_infinity_leaves_its_neighbours_precise():
+    """Four products per result, every operand 1 + 2^-7 - 2^-23 (the largest rest that eight bits can leave), one infinity in each
+    activation: the finite results of the same tile are as close as fp32 sums are, 4 * 2^-24."""
+    torch = torch_mod()
+    N, H, W, C, K = 1, 2, 2, 4, 4
+    v = np.float32(1 + 2.0 ** -7 - 2.0 ** -23)
+    x, w, dy = (np.full(s, v, np.float32) for s in ((4, C), (K, C), (4, K)))
+    x[0, 0], dy[0, 0] = np.inf, np.inf
+    gx, gw, gd = dev(x), dev(w), dev(dy)
+    y, dx, dw = (torch.empty(4, 4, device="cuda") for _ in range(3))
+    dims = (N, H, W, C, K, 1, 1, 1, 0)
+    monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), y.data_ptr(), *dims, 1, None, 0)
+    monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), dx.data_ptr(), *dims, 0, 1, None, 0)
+    monet.call("monet_conv_wgrad", None, gx.data_ptr(), gd.data_ptr(), dw.data_ptr(), *dims, 1, None, 0)
+    want = 4 * np.float64(v) ** 2
+    for got, rows in ((y, 1), (dx, 1)):
+        got = got.cpu().numpy()
+        assert np.all(np.isposinf(got[:rows])) and np.all(np.abs(got[rows:] - want) <= 4 * 2.0 ** -24 * want), (got[1, 1] / want - 1) * 2.0 ** 24
+    got = dw.cpu().numpy()
+    assert np.all(np.isposinf(got[0])) and np.all(np.isposinf(got[:, 0]))
+    assert np.all(np.abs(got[1:, 1:] - want) <= 4 * 2.0 ** -24 * want), (got[1, 1] / want - 1) * 2.0 ** 24
+
+
+# every way a reduction is walked: aligned, partly empty last step, straddling filter taps, strided residue classes, element-wise
+WALK_CASES = [
+    # N, H, W, C, K, R, stride, pad
+    (2, 13, 11, 64, 96, 1, 1, 0),
+    (2, 13, 11, 36, 44, 1, 1, 0),
+    (2, 13, 11, 32, 48, 3, 1, 1),
+    (2, 13, 11, 36, 28, 3, 1, 1),
+    (2, 14, 11, 20, 32, 3, 2, 1),
+    (1, 13, 11, 27, 33, 3, 1, 1),
+    (2, 12, 12, 512, 32, 1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("case", WALK_CASES)
+@pytest.mark.parametrize("splits", [1, 3])
+def test_conv_of_infinities_on_every_loader_and_in_ranges(case, splits):
+    """An infinity in the first and in the last reduction indices (whole reductions and ranges that start in the middle): the
+    results that it meets are infinite with its sign, the others are as precise as without it."""
+    torch = torch_mod()
+    N, H, W, C, K, R, stride, pad = case
+    rng = np.random.default_rng(17)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    x = rng.standard_normal((N, H, W, C), dtype=np.float32)
+    w = (np.abs(rng.standard_normal((K, R, R, C))) + 0.1).astype(np.float32)
+    dy = rng.standard_normal((N, P, Q, K), dtype=np.float32)
+    dpos = (np.abs(dy) + 0.1).astype(np.float32)
+    xi, dyi = x.copy(), dy.copy()
+    xi[0, 2, 3, 1], xi[N - 1, H - 2, W - 2, C - 2] = np.inf, -np.inf
+    dyi[0, 1, 1, 0], dyi[N - 1, P - 2, Q - 2, K - 1] = -np.inf, np.inf
+    wo = wt.weight_to_oracle(w)
+    with np.errstate(all="ignore"):
+        want_y = wt.act_from_oracle(nm.conv2d_fwd(wt.act_to_oracle(xi), wo, stride, pad))
+        want_dx = wt.act_from_oracle(nm.conv2d_dgrad(wt.act_to_oracle(dyi), wo, (N, C, H, W), stride, pad))
+        want_dw = wt.weight_from_oracle(nm.conv2d_wgrad(wt.act_to_oracle(xi), wt.act_to_oracle(dpos), R, R, stride, pad))
+    gx, gw, gd, gp = dev(xi), dev(w), dev(dyi), dev(dpos)
+    y, dx, dw = (torch.full(a.shape, float("nan"), device="cuda") for a in (want_y, want_dx, want_dw))
+    ws = torch.empty(3 * max(want_y.size, want_dx.size, want_dw.size), device="cuda")
+    dims = (N, H, W, C, K, R, R, stride, pad)
+    wsp = (ws.data_ptr(), ws.numel() * 4)
+    monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), y.data_ptr(), *dims, splits, *wsp)
+    monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), dx.data_ptr(), *dims, 0, splits, *wsp)
+    monet.call("monet_conv_wgrad", None, gx.data_ptr(), gp.data_ptr(), dw.data_ptr(), *dims, splits, *wsp)
+    for name, t, b in (("y", y, want_y), ("dx", dx, want_dx), ("dw", dw, want_dw)):
+        a = t.cpu().numpy()
+        assert np.isinf(b).any() and np.isfinite(b).any(), name
+        assert np.array_equal(np.isnan(a), np.isnan(b)), name
+        assert np.array_equal(a[np.isinf(b)], b[np.isinf(b)]) and np.array_equal(np.isinf(a), np.isinf(b)), name
+        fine = np.isfinite(b)
+        check_close(a[fine], b[fine], 1e-6, what=name)      # fp32 sums of at most 512 products: 1e-6 in the norm
 
 
 def test_conv_ragged_last_round_is_split_and_counts_reset():
