@@ -29,7 +29,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <type_traits>
 
 #include "bf16_pieces.hpp"
 #include "buffer_addr.hpp"
@@ -218,30 +217,47 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const float *__restric
 // Filter gradient: a workgroup of K / 32 waves walks tiles like the forward kernel; wave kb keeps the 32 x (R * 3 S)
 // block of dw of its output channels in registers (NBC column blocks of 32) over all its tiles and leaves it in
 // part[workgroup] at the end.
-template <int R, int S, int ST>
-__global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, StemGeom gm) {
-    extern __shared__ float lds[];
-    constexpr int RUN = 3 * S, COLS = R * RUN, NBC = (COLS + 31) / 32;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-    const int kb = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nthreads = blockDim.x;
-    // LDS offset of this lane's column (r, j) in every column block relative to a position's window; a column beyond
-    // R * 3 S reads the window's first float into a result column that is never written
-    int coloff[NBC];
+
+// LDS offset of this lane's column (r, j) in every column block relative to a position's window; a column beyond
+// R * 3 S reads the window's first float into a result column that is never written
+template <int R, int S, int NBC>
+__device__ __forceinline__ void wgrad_columns(int (&coloff)[NBC], const StemGeom &gm) {
+    constexpr int RUN = 3 * S, COLS = R * RUN;
+    const int l32 = threadIdx.x & 31;
 #pragma unroll
     for (int c = 0; c < NBC; ++c) {
         int col = 32 * c + l32;
         if (col >= COLS) col = 0;
         coloff[c] = (col / RUN) * gm.rowlen + col % RUN;
     }
-    floatx16 acc[NBC], low[NBC];      // the h * h terms and the smaller ones
-    const int total4 = gm.rows_in * (gm.rowlen / 4);
-    __shared__ int redo;              // an infinity or a NaN in the result: all tiles once more with the split that carries them
-    auto all_tiles = [&](auto special) {
+}
+// this workgroup's partial result, laid out as dw[k][r][s][c]: lane holds column l32 of rows 8 (i / 4) + 4 h + i % 4
+template <int R, int S, int NBC>
+__device__ __forceinline__ void wgrad_store(const floatx16 (&acc)[NBC], float *part, const StemGeom &gm) {
+    constexpr int COLS = R * 3 * S;
+    const int l32 = threadIdx.x & 31, h = (threadIdx.x & 63) >> 5, kb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float *mine = part + (int64_t)blockIdx.x * gm.K * COLS;
 #pragma unroll
     for (int c = 0; c < NBC; ++c)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[c][i] = low[c][i] = 0.0f;
+        for (int i = 0; i < 16; ++i) {
+            const int row = kb * 32 + 8 * (i / 4) + 4 * h + (i % 4), col = 32 * c + l32;
+            if (col < COLS) mine[row * COLS + col] = acc[c][i];
+        }
+}
+// acc = this workgroup's sums over all its tiles with the fp32 matrix instruction
+template <int R, int S, int ST, int NBC>
+__device__ __forceinline__ void wgrad_tiles_fp32(floatx16 (&acc)[NBC], const int (&coloff)[NBC], float *lds, const float *__restrict__ x,
+                                                 const float *__restrict__ dy, const StemGeom &gm) {
+    constexpr int U = NBC >= 4 ? 8 : 16;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int kb = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nthreads = blockDim.x;
+#pragma unroll
+    for (int c = 0; c < NBC; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][i] = 0.0f;
+    const int total4 = gm.rows_in * (gm.rowlen / 4);
     for (int64_t tile = blockIdx.x; tile < gm.tiles; tile += gridDim.x) {
         int n, p0, q0;
         tile_origin(gm, tile, n, p0, q0);
@@ -256,16 +272,97 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
         const int npos = gm.nrow == 1 ? cols_here : rows_here * gm.qn;      // positions of the tile that exist: m * K floats apart in dy
         const __amdgpu_buffer_rsrc_t rdy = buffer_of(dy + (((int64_t)n * gm.P + p0) * gm.Q + q0) * gm.K);
         const unsigned kbytes = (unsigned)gm.K * 4u, lbytes = (unsigned)(kb * 32 + l32) * 4u;
+        // groups of U position pairs, two register sets: the dy loads of the next group are issued before the matrix
+        // instructions of the current one
+        struct Set { float a[U]; int po[U]; };
+        auto load = [&](Set &t, int m0) {      // pairs (m0 + 2 u, m0 + 2 u + 1), this lane takes position m0 + 2 u + h
+            int m = m0 + h;
+            int pr = gm.nrow == 1 ? 0 : m / gm.qn, qq = m - pr * gm.qn;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float got = buffer_load(rdy, (m < npos ? (unsigned)m * kbytes : 0u) + lbytes, 0u);      // in bounds either way
+                t.a[u] = m < npos ? got : 0.0f;
+                const bool in = pr < gm.nrow;      // a nominal position: its window lies in the staged rows
+                t.po[u] = in ? pr * ST * gm.rowlen + qq * ST * 3 + gm.xlead : gm.xlead;
+                m += 2; qq += 2;
+                if (qq >= gm.qn) { qq -= gm.qn; ++pr; }
+            }
+        };
+        // A position beyond the tile is no term of the sum: neither operand may stand there as it is (its window in LDS is real
+        // image data, and zero times an infinity would be a NaN).  Only a tile's last group has such positions.
+        auto compute = [&](const Set &t, int m0) {
+            if (m0 + 2 * U <= npos) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int c = 0; c < NBC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.a[u], lds[t.po[u] + coloff[c]], acc[c], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int c = 0; c < NBC; ++c) {
+                        const float w = lds[t.po[u] + coloff[c]];
+                        acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.a[u], m0 + 2 * u + h < npos ? w : 0.0f, acc[c], 0, 0, 0);
+                    }
+            }
+        };
+        const int groups = (npos + 2 * U - 1) / (2 * U);
+        Set s0, s1;
+        if (groups > 0) load(s0, 0);
+        for (int g = 0; g < groups; g += 2) {
+            if (g + 1 < groups) load(s1, (g + 1) * 2 * U);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(s0, g * 2 * U);
+            __builtin_amdgcn_sched_barrier(0);
+            if (g + 2 < groups) load(s0, (g + 2) * 2 * U);
+            __builtin_amdgcn_sched_barrier(0);
+            if (g + 1 < groups) compute(s1, (g + 1) * 2 * U);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// Filter gradient of the 7x7 / stride 2 filter on bf16 pieces.
+template <int R, int S, int ST>
+__global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, StemGeom gm) {
+    extern __shared__ float lds[];
+    constexpr int NBC = (R * 3 * S + 31) / 32;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int kb = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nthreads = blockDim.x;
+    int coloff[NBC];
+    wgrad_columns<R, S>(coloff, gm);
+    floatx16 acc[NBC], low[NBC];      // the h * h terms and the smaller ones
+    const int total4 = gm.rows_in * (gm.rowlen / 4);
+    __shared__ int redo;              // an infinity or a NaN in the result: all tiles once more on the fp32 matrix instruction
+#pragma unroll
+    for (int c = 0; c < NBC; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][i] = low[c][i] = 0.0f;
+    if (tid == 0) redo = 0;           // read behind the barriers below
+    for (int64_t tile = blockIdx.x; tile < gm.tiles; tile += gridDim.x) {
+        int n, p0, q0;
+        tile_origin(gm, tile, n, p0, q0);
+        __syncthreads();      // the previous tile has been read
+        for (int k0 = 0; k0 * nthreads < total4; k0 += FILL) {
+            float4 staged[FILL];
+            stem_fill_load<ST>(staged, x, gm, n, p0, q0, tid, nthreads, k0);
+            stem_fill_write(lds, staged, gm, tid, nthreads, k0);
+        }
+        __syncthreads();
+        const int rows_here = min(gm.nrow, gm.P - p0), cols_here = min(gm.qn, gm.Q - q0);
+        const int npos = gm.nrow == 1 ? cols_here : rows_here * gm.qn;      // positions of the tile that exist: m * K floats apart in dy
+        // the descriptor ends with the tile: a position beyond it reads zero
+        const __amdgpu_buffer_rsrc_t rdy = buffer_of(dy + (((int64_t)n * gm.P + p0) * gm.Q + q0) * gm.K, (unsigned)(npos * gm.K) * 4u);
+        const unsigned kbytes = (unsigned)gm.K * 4u, lbytes = (unsigned)(kb * 32 + l32) * 4u;
         // groups of 16 positions, two register sets: the dy loads of the next group are issued before the matrix
-        // instructions of the current one.  A position beyond the tile contributes zero (its window in LDS is the image's).
+        // instructions of the current one.  A position beyond the tile contributes zero times its window
+        // in LDS; where that holds an infinity the NaN sends the workgroup to the fp32 pass.
         struct Set { float a[8]; };
         auto load = [&](Set &t, int m0) {      // this lane takes positions m0 + 8 h .. m0 + 8 h + 7
-            const int m = m0 + 8 * h;
+            const unsigned first = (unsigned)(m0 + 8 * h) * kbytes + lbytes;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float got = buffer_load(rdy, (m + i < npos ? (unsigned)(m + i) * kbytes : 0u) + lbytes, 0u);      // in bounds either way
-                t.a[i] = m + i < npos ? got : 0.0f;
-            }
+            for (int i = 0; i < 8; ++i) t.a[i] = buffer_load(rdy, first, (unsigned)i * kbytes);
         };
         auto compute = [&](const Set &t, int m0) {
             int po[8];
@@ -280,7 +377,7 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
                     if (gm.nrow > 1 && qq >= gm.qn) { qq -= gm.qn; ++pr; }
                 }
             }
-            const PieceRow a = split_row<decltype(special)::value>(t.a);
+            const PieceRow a = split_row(t.a);
             float v[8], next[8];
             auto read = [&](int c, float (&o)[8]) {
 #pragma unroll
@@ -291,7 +388,7 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
             for (int c = 0; c < NBC; ++c) {
                 if (c + 1 < NBC) read(c + 1, next);
                 __builtin_amdgcn_sched_barrier(0);
-                const PieceRow b = split_row<decltype(special)::value>(v);
+                const PieceRow b = split_row(v);
                 acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc[c], 0, 0, 0);
                 low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, low[c], 0, 0, 0);
                 low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, low[c], 0, 0, 0);
@@ -317,10 +414,7 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
     }
 #pragma unroll
     for (int c = 0; c < NBC; ++c) acc[c] += low[c];
-    };
-    if (tid == 0) redo = 0;
-    __syncthreads();
-    all_tiles(std::false_type{});
+    __syncthreads();      // redo is zero, also where there was no tile
     {
         float sum = 0.0f;
 #pragma unroll
@@ -330,103 +424,21 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
         if (!(__builtin_fabsf(sum) < __builtin_inff())) redo = 1;
     }
     __syncthreads();
-    if (redo) all_tiles(std::true_type{});
-    // this workgroup's partial result, laid out as dw[k][r][s][c]: lane holds column l32 of rows 8 (i / 4) + 4 h + i % 4
-    float *mine = part + (int64_t)blockIdx.x * gm.K * COLS;
-#pragma unroll
-    for (int c = 0; c < NBC; ++c)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = kb * 32 + 8 * (i / 4) + 4 * h + (i % 4), col = 32 * c + l32;
-            if (col < COLS) mine[row * COLS + col] = acc[c][i];
-        }
+    if (redo) wgrad_tiles_fp32<R, S, ST>(acc, coloff, lds, x, dy, gm);      // uniform over the workgroup
+    wgrad_store<R, S>(acc, part, gm);
 }
 
-// The same with the fp32 matrix instruction, for the 3x3 filters: 27 columns, bound by reading dy, which groups of 16 positions
-// in place of 32 slowed down (stride 1, 64 channels, 224x224, batch 176: 755 against 866 us).  A workgroup of K / 32 waves walks tiles; wave kb keeps the 32 x (R * 3 S)
-// block of dw of its output channels in registers (NBC column blocks of 32) over all its tiles and leaves it in
-// part[workgroup] at the end.
+// Filter gradient of the 3x3 filters, on the fp32 matrix instruction: 27 columns, bound by reading dy, which groups of 16 positions
+// in place of 32 slowed down (stride 1, 64 channels, 224x224, batch 176: 755 against 866 us).
 template <int R, int S, int ST>
 __global__ __launch_bounds__(256, 2) void stem_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, StemGeom gm) {
     extern __shared__ float lds[];
-    constexpr int RUN = 3 * S, COLS = R * RUN, NBC = (COLS + 31) / 32, U = NBC >= 4 ? 8 : 16;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-    const int kb = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nthreads = blockDim.x;
-    // LDS offset of this lane's column (r, j) in every column block relative to a position's window; a column beyond
-    // R * 3 S reads the window's first float into a result column that is never written
+    constexpr int NBC = (R * 3 * S + 31) / 32;
     int coloff[NBC];
-#pragma unroll
-    for (int c = 0; c < NBC; ++c) {
-        int col = 32 * c + l32;
-        if (col >= COLS) col = 0;
-        coloff[c] = (col / RUN) * gm.rowlen + col % RUN;
-    }
+    wgrad_columns<R, S>(coloff, gm);
     floatx16 acc[NBC];
-#pragma unroll
-    for (int c = 0; c < NBC; ++c)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[c][i] = 0.0f;
-    const int total4 = gm.rows_in * (gm.rowlen / 4);
-    for (int64_t tile = blockIdx.x; tile < gm.tiles; tile += gridDim.x) {
-        int n, p0, q0;
-        tile_origin(gm, tile, n, p0, q0);
-        __syncthreads();      // the previous tile has been read
-        for (int k0 = 0; k0 * nthreads < total4; k0 += FILL) {
-            float4 staged[FILL];
-            stem_fill_load<ST>(staged, x, gm, n, p0, q0, tid, nthreads, k0);
-            stem_fill_write(lds, staged, gm, tid, nthreads, k0);
-        }
-        __syncthreads();
-        const int rows_here = min(gm.nrow, gm.P - p0), cols_here = min(gm.qn, gm.Q - q0);
-        const int npos = gm.nrow == 1 ? cols_here : rows_here * gm.qn;      // positions of the tile that exist: m * K floats apart in dy
-        const __amdgpu_buffer_rsrc_t rdy = buffer_of(dy + (((int64_t)n * gm.P + p0) * gm.Q + q0) * gm.K);
-        const unsigned kbytes = (unsigned)gm.K * 4u, lbytes = (unsigned)(kb * 32 + l32) * 4u;
-        // groups of U position pairs, two register sets: the dy loads of the next group are issued before the matrix
-        // instructions of the current one.  A position beyond the tile contributes zero (its window in LDS is finite).
-        struct Set { float a[U]; int po[U]; };
-        auto load = [&](Set &t, int m0) {      // pairs (m0 + 2 u, m0 + 2 u + 1), this lane takes position m0 + 2 u + h
-            int m = m0 + h;
-            int pr = gm.nrow == 1 ? 0 : m / gm.qn, qq = m - pr * gm.qn;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float got = buffer_load(rdy, (m < npos ? (unsigned)m * kbytes : 0u) + lbytes, 0u);      // in bounds either way
-                t.a[u] = m < npos ? got : 0.0f;
-                const bool in = pr < gm.nrow;      // a nominal position: its window lies in the staged rows
-                t.po[u] = in ? pr * ST * gm.rowlen + qq * ST * 3 + gm.xlead : gm.xlead;
-                m += 2; qq += 2;
-                if (qq >= gm.qn) { qq -= gm.qn; ++pr; }
-            }
-        };
-        auto compute = [&](const Set &t) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int c = 0; c < NBC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.a[u], lds[t.po[u] + coloff[c]], acc[c], 0, 0, 0);
-        };
-        const int groups = (npos + 2 * U - 1) / (2 * U);
-        Set s0, s1;
-        if (groups > 0) load(s0, 0);
-        for (int g = 0; g < groups; g += 2) {
-            if (g + 1 < groups) load(s1, (g + 1) * 2 * U);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(s0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (g + 2 < groups) load(s0, (g + 2) * 2 * U);
-            __builtin_amdgcn_sched_barrier(0);
-            if (g + 1 < groups) compute(s1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    // this workgroup's partial result, laid out as dw[k][r][s][c]: lane holds column l32 of rows 8 (i / 4) + 4 h + i % 4
-    float *mine = part + (int64_t)blockIdx.x * gm.K * COLS;
-#pragma unroll
-    for (int c = 0; c < NBC; ++c)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = kb * 32 + 8 * (i / 4) + 4 * h + (i % 4), col = 32 * c + l32;
-            if (col < COLS) mine[row * COLS + col] = acc[c][i];
-        }
+    wgrad_tiles_fp32<R, S, ST>(acc, coloff, lds, x, dy, gm);
+    wgrad_store<R, S>(acc, part, gm);
 }
 
 struct StemPlan { bool ok; int R, S, ST, mbw; StemGeom gm; size_t lds_bytes; };
