@@ -30,8 +30,9 @@ extern "C" {
  *     it is given where more would only cost partial results.
  *   splits == 1: the reduction is not cut; a workspace is accepted and left alone.
  * A product is worked in six terms of three bf16 pieces per operand on the matrix cores, to 2^-24 of itself at worst; sums are
- * fp32.  A tile of the result (up to 128x128) that ends with an infinity or a NaN in it is worked once more with the fp32
- * matrix instruction: infinities, NaNs and overflows come out as fp32 arithmetic's.
+ * fp32.  A tile of the result (up to 128x128) is worked once more with the fp32 matrix instruction where that does not hold: where it
+ * ends with an infinity or a NaN in it (infinities, NaNs and overflows come out as fp32 arithmetic's), or where an operand below 2^-110 has
+ * bits that the pieces cannot hold.  Tensors with such values in every tile take 2 to 2.5 times as long.
  * Appendix D's workspace / speed trade-off of convolution algorithms is this choice.
  *
  * y[N,P,Q,K] = cross-correlation of x[N,H,W,C] with w[K,R,S,C], zero padding, no bias. */

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     constexpr int SA = BM * 4, SB = BN * 4, LA = SA >= NT ? SA / NT : 1, LB = SB >= NT ? SB / NT : 1;
     __shared__ __attribute__((aligned(16))) unsigned As[2][A_SZ];
     __shared__ __attribute__((aligned(16))) unsigned Bs[2][B_SZ];
-    __shared__ int redo;     // a first pass left an infinity or a NaN: once more with the fp32 matrix instruction
+    __shared__ int redo;     // the pieces do not hold this tile's numbers: once more with the fp32 matrix instruction
     // First layers (3 input channels): the element-wise forward loader looks the (r, s, c) of a reduction index up
     // instead of dividing (measured 925 -> 815 us on the ResNet-50 stem).  Only the 64 columns wide tiles have
     // the LDS to spare (2 KiB), and those are the ones results up to 64 channels wide, i.e. every first layer, use.
@@ -644,12 +644,14 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         advance();
     };
 
+    unsigned lost = 0;      // bits of operands too small to be three pieces
+
     // One operand's slot (two slots where they share words), split into pieces and written as words of two neighbouring
     // reduction indices.
     auto put_unit = [&](auto kc, auto count, auto width, auto unit, int t, unsigned *dst, const auto &reg) {
         constexpr bool KC = decltype(kc)::value;
         constexpr int L = decltype(count)::value, n = decltype(width)::value, PL = plane_words(KC, n), u = decltype(unit)::value;
-        auto pieces = [&](float x, float y) { return split_pair(x, y); };
+        auto pieces = [&](float x, float y) { return split_pair(x, y, lost); };
         if constexpr (KC) {
             const int idx = t + u * NT;
             const float4 v = reg[u];
@@ -841,8 +843,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     };
     join();
     // An infinity or a NaN in the result says that an operand held one, that a value near the type's largest rounded to infinity in
-    // bf16, or that a product or a sum overflowed: pieces of such numbers do not add up to what fp32 arithmetic gives, so this tile is
-    // worked once more with the fp32 matrix instruction.  Finite data: one barrier and 32 additions per tile.
+    // bf16, or that a product or a sum overflowed: pieces of such numbers do not add up to what fp32 arithmetic gives.  Bits lost in the
+    // split say that an operand lies below 2^-110.  Such a tile is worked once more with the fp32 matrix instruction.
+    // What that costs (3x3, 256 -> 256, 56x56, batch 32, every tile affected): forward 735 -> 1700 us, the fp32 kernel took 1020;
+    // 1x1, 1024 -> 256, 14x14, batch 184: 130 -> 310.  Otherwise: one barrier and 32 additions per tile, one vector instruction per pair of
+    // operands (0 - 3 % of a layer).
     {
         float probe[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -853,7 +858,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             probe[3] += acc[1][v + 8];
         }
         const float sum = (probe[0] + probe[1]) + (probe[2] + probe[3]);
-        if (!(__builtin_fabsf(sum) < __builtin_inff())) redo = 1;
+        if (!(__builtin_fabsf(sum) < __builtin_inff()) || pieces_lost(lost)) redo = 1;
     }
     __syncthreads();       // also: every wave is done with the operand tiles in LDS
     if (redo) {

@@ -334,12 +334,13 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
     wgrad_columns<R, S>(coloff, gm);
     floatx16 acc[NBC], low[NBC];      // the h * h terms and the smaller ones
     const int total4 = gm.rows_in * (gm.rowlen / 4);
-    __shared__ int redo;              // an infinity or a NaN in the result: all tiles once more on the fp32 matrix instruction
+    __shared__ int redo;              // an infinity or a NaN in the result, or an operand too small to split: all tiles once more on the fp32 instruction
 #pragma unroll
     for (int c = 0; c < NBC; ++c)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[c][i] = low[c][i] = 0.0f;
     if (tid == 0) redo = 0;           // read behind the barriers below
+    unsigned lost = 0;      // bits of operands too small to be three pieces
     for (int64_t tile = blockIdx.x; tile < gm.tiles; tile += gridDim.x) {
         int n, p0, q0;
         tile_origin(gm, tile, n, p0, q0);
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
                     if (gm.nrow > 1 && qq >= gm.qn) { qq -= gm.qn; ++pr; }
                 }
             }
-            const PieceRow a = split_row(t.a);
+            const PieceRow a = split_row(t.a, lost);
             float v[8], next[8];
             auto read = [&](int c, float (&o)[8]) {
 #pragma unroll
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
             for (int c = 0; c < NBC; ++c) {
                 if (c + 1 < NBC) read(c + 1, next);
                 __builtin_amdgcn_sched_barrier(0);
-                const PieceRow b = split_row(v);
+                const PieceRow b = split_row(v, lost);
                 acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc[c], 0, 0, 0);
                 low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, low[c], 0, 0, 0);
                 low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, low[c], 0, 0, 0);
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(256, 2) void stem7_wgrad_kernel(const float *__rest
         for (int c = 0; c < NBC; ++c)
 #pragma unroll
             for (int i = 0; i < 16; ++i) sum += acc[c][i];
-        if (!(__builtin_fabsf(sum) < __builtin_inff())) redo = 1;
+        if (!(__builtin_fabsf(sum) < __builtin_inff()) || pieces_lost(lost)) redo = 1;
     }
     __syncthreads();
     if (redo) wgrad_tiles_fp32<R, S, ST>(acc, coloff, lds, x, dy, gm);      // uniform over the workgroup

@@ -278,6 +278,41 @@ def test_conv_of_infinities_on_every_loader_and_in_ranges(case, splits):
         check_close(a[fine], b[fine], 1e-6, what=name)      # fp32 sums of at most 512 products: 1e-6 in the norm
 
 
+@pytest.mark.parametrize("case", WALK_CASES)
+@pytest.mark.parametrize("exponent,other", [(-100, 60), (-112, 60), (-118, 60), (-125, 60), (-62, -62)])
+def test_conv_of_operands_at_the_bottom_of_the_range(case, exponent, other):
+    """One operand of about 2^exponent (at -125 one element in three is subnormal), the other of 2^60: the result is an ordinary
+    number and as precise as for operands of about 1, whole and in ranges, on every loader.  Likewise where the terms of a
+    product, not the operands, reach the bottom of the range (2^-62 each)."""
+    torch = torch_mod()
+    N, H, W, C, K, R, stride, pad = case
+    rng = np.random.default_rng(23)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    small, big = np.float64(2.0 ** exponent), np.float64(2.0 ** other)
+
+    def of_size(scale, shape):      # (fp32 tensor, the same values over the scale in 64 bits)
+        t = (rng.standard_normal(shape) * scale).astype(np.float32)
+        return t, t.astype(np.float64) / scale
+    (x, xn), (dy, dyn) = of_size(small, (N, H, W, C)), of_size(small, (N, P, Q, K))
+    (w, wn), (z, zn) = of_size(big, (K, R, R, C)), of_size(big, (N, P, Q, K))
+    unit = small * big
+    want = dict(y=wt.act_from_oracle(nm.conv2d_fwd(wt.act_to_oracle(xn), wt.weight_to_oracle(wn), stride, pad)),
+                dx=wt.act_from_oracle(nm.conv2d_dgrad(wt.act_to_oracle(dyn), wt.weight_to_oracle(wn), (N, C, H, W), stride, pad)),
+                dw=wt.weight_from_oracle(nm.conv2d_wgrad(wt.act_to_oracle(xn), wt.act_to_oracle(zn), R, R, stride, pad)))
+    gx, gw, gd, gz = dev(x), dev(w), dev(dy), dev(z)
+    ws = torch.empty(3 * max(a.size for a in want.values()), device="cuda")
+    dims = (N, H, W, C, K, R, R, stride, pad)
+    wsp = (ws.data_ptr(), ws.numel() * 4)
+    for splits in (1, 3):
+        got = {k: torch.full(a.shape, float("nan"), device="cuda") for k, a in want.items()}
+        monet.call("monet_conv_fwd", None, gx.data_ptr(), gw.data_ptr(), got["y"].data_ptr(), *dims, splits, *wsp)
+        monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), got["dx"].data_ptr(), *dims, 0, splits, *wsp)
+        monet.call("monet_conv_wgrad", None, gx.data_ptr(), gz.data_ptr(), got["dw"].data_ptr(), *dims, splits, *wsp)
+        for name, b in want.items():
+            # fp32 sums of at most 512 products: 1e-6 in the norm, as for operands of any other size
+            check_close(got[name].cpu().numpy().astype(np.float64) / unit, b, 1e-6, what=(name, splits))
+
+
 def test_conv_ragged_last_round_is_split_and_counts_reset():
     """More than 256 tiles and not a multiple of it, with the workspace that lets a library cut the tiles of the last round.
     Several calls in a row, forward and input gradient with accumulation, against the oracle and against the call
@@ -762,17 +797,18 @@ def test_first_layer_forward_and_filter_gradient_from_rows_staged_in_lds(case):
 STEM7_CASES = [(2, 40, 38, 64), (1, 24, 24, 32), (1, 31, 29, 96), (1, 15, 300, 96)]      # N, H, W, K; the last: rows in segments, the last one shorter
 
 
-@pytest.mark.parametrize("kind", ["finite", "inf", "inf_at_the_edges", "nan", "near_max"])
+@pytest.mark.parametrize("kind", ["finite", "inf", "inf_at_the_edges", "nan", "near_max", "2^-112", "2^-118", "2^-125"])
 @pytest.mark.parametrize("case", STEM7_CASES)
-def test_first_layer_filter_gradient_of_infinities_and_nans(case, kind):
+def test_first_layer_filter_gradient_of_infinities_and_small_values(case, kind):
     """7x7 / stride 2 filter gradient (bf16 pieces): special values come out as the fp32 products' sums, also in the image's corners
-    and beside tile positions that do not exist, and the finite results beside them are as precise as ever."""
+    and beside tile positions that do not exist, the finite results beside them and those of small operands are as precise as ever."""
     torch = torch_mod()
     N, H, W, K = case
     rng = np.random.default_rng(3)
     P, Q = (H - 1) // 2 + 1, (W - 1) // 2 + 1
     x = (np.abs(rng.standard_normal((N, H, W, 3))) + 0.5).astype(np.float32)
     dy = (np.abs(rng.standard_normal((N, P, Q, K))) + 0.5).astype(np.float32)
+    unit = 1.0
     if kind == "inf":
         dy[0, 3, 5, 3], x[0, 8, 9, 1] = -np.inf, np.inf
     elif kind == "inf_at_the_edges":
@@ -782,6 +818,9 @@ def test_first_layer_filter_gradient_of_infinities_and_nans(case, kind):
     elif kind == "near_max":      # rounds to infinity in bf16
         dy[0, 3, 5, 3] = 3.4e38
         x[0, 3:10, 7:14] *= 1e-4
+    elif kind != "finite":
+        small = np.float64(2.0 ** int(kind[2:]))
+        dy, x, unit = (dy * small).astype(np.float32), x * np.float32(2.0 ** 60), small * 2.0 ** 60
     pad = np.zeros((N, H + 6, W + 6, 3), np.float64)
     pad[:, 3:3 + H, 3:3 + W] = x
     want = np.empty((K, 7, 7, 3))
@@ -795,7 +834,7 @@ def test_first_layer_filter_gradient_of_infinities_and_nans(case, kind):
     ws = torch.empty(splits * K * 147, device="cuda")
     gx, gd, dw = dev(x), dev(dy), torch.empty((K, 7, 7, 3), device="cuda")
     monet.call("monet_conv_stem_wgrad", None, gx.data_ptr(), gd.data_ptr(), dw.data_ptr(), N, H, W, K, 7, 7, 2, 3, splits, ws.data_ptr(), ws.numel() * 4)
-    got = dw.cpu().numpy()
+    got, want = dw.cpu().numpy().astype(np.float64) / unit, want / unit
     assert np.array_equal(np.isnan(got), np.isnan(want))
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)]) and np.array_equal(np.isinf(got), np.isinf(want))
     fine = np.isfinite(want)
