@@ -313,6 +313,21 @@ def test_conv_of_operands_at_the_bottom_of_the_range(case, exponent, other):
             check_close(got[name].cpu().numpy().astype(np.float64) / unit, b, 1e-6, what=(name, splits))
 
 
+def test_conv_of_one_product_is_the_rounded_product():
+    """1x1 layers with a single input channel (forward) and a single output channel (input gradient): nothing is summed, so the
+    result is the fp32 product itself."""
+    torch = torch_mod()
+    rng = np.random.default_rng(29)
+    a = rng.standard_normal((3, 9, 11, 1), dtype=np.float32)
+    b = rng.standard_normal((1, 20), dtype=np.float32)
+    ga, gb, y = dev(a), dev(b), torch.empty(3, 9, 11, 20, device="cuda")
+    monet.call("monet_conv_fwd", None, ga.data_ptr(), gb.data_ptr(), y.data_ptr(), 3, 9, 11, 1, 20, 1, 1, 1, 0, 1, None, 0)
+    assert np.array_equal(y.cpu().numpy(), a * b[0])
+    y.fill_(float("nan"))
+    monet.call("monet_conv_dgrad", None, ga.data_ptr(), gb.data_ptr(), y.data_ptr(), 3, 9, 11, 20, 1, 1, 1, 1, 0, 0, 1, None, 0)
+    assert np.array_equal(y.cpu().numpy(), a * b[0])
+
+
 def test_conv_ragged_last_round_is_split_and_counts_reset():
     """More than 256 tiles and not a multiple of it, with the workspace that lets a library cut the tiles of the last round.
     Several calls in a row, forward and input gradient with accumulation, against the oracle and against the call
