@@ -1162,6 +1162,10 @@ int useful_splits(int mode, int splits, int64_t tiles, int64_t slots, double flo
     return best;
 }
 
+// Tile shapes: index -> waves (rows x columns of 64x32 wave tiles)
+//   0: 128x128   1: 256x64   2: 64x256   3: 128x64   4: 64x128   5: 64x64
+int g_cfg_override = -1;   // tuning and test aid: force one tile shape, and exactly the ranges asked for, on every launch
+
 template <int MODE, int WM, int WN, int TAG = 0>
 void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, int splits, float *ws, size_t ws_bytes, int64_t steps,
                  bool accumulate, const char *who) {
@@ -1170,7 +1174,7 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
     set_row_magic(ta);
     if (splits > steps) splits = (int)std::max<int64_t>(steps, 1);
     if (splits > 1 && (!ws || ws_bytes < (size_t)splits * ta.out_elems * 4)) throw KernelError(std::string(who) + ": workspace too small for the requested splits");
-    if (splits > 1)
+    if (splits > 1 && g_cfg_override < 0)
         splits = useful_splits(MODE, splits, (ta.Mg + BM - 1) / BM * ((ta.Ng + BN - 1) / BN) * zdim, (int64_t)NUM_CU * resident_workgroups(MODE, WM, WN),
                                2.0 * ta.Mg * ta.Ng * ta.Kg * zdim, 4.0 * ta.out_elems);
     int64_t tiles_m = (ta.Mg + BM - 1) / BM;
@@ -1209,10 +1213,6 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
     hip_check(hipGetLastError(), "conv launch");
     if (slabs) launch_split_reduce(st, ws, out, ta.out_elems, splits, MODE != WGRAD && accumulate);
 }
-
-// Tile shapes: index -> waves (rows x columns of 64x64 wave tiles)
-//   0: 128x128   1: 256x64   2: 64x256   3: 128x64   4: 64x128   5: 64x64
-int g_cfg_override = -1;   // tuning aid: force one tile shape for every launch
 
 // Choice measured on the ResNet-50, VGG-16, MobileNetV2 and inception layer sets.  The square tile moves the least through LDS and
 // L2 per product (3x3, 256 -> 256, 56x56, batch 176: 3.25 ms against 3.67 with 128x64), the 128x64 tile has twice as many workgroups,

@@ -715,20 +715,21 @@ def test_convolution_through_patch_matrix_matches_oracle(case):
 
 MANY_RANGE_CASES = [
     # N, H, W, C, K, R, stride, pad, splits: reduction ranges of a few steps each, several workgroups per compute unit
-    (16, 112, 112, 16, 96, 1, 1, 0, 1792),      # MobileNetV2's first expansion (reduced batch): 7 steps per range
-    (16, 112, 112, 16, 96, 1, 1, 0, 3136),      # 4 steps per range: one turn of the pipelined loop
-    (16, 56, 56, 64, 64, 3, 1, 1, 640),         # padded 3x3: rows of a step straddle image borders
-    (64, 14, 14, 256, 256, 3, 1, 1, 96),
-    (16, 57, 57, 32, 48, 3, 2, 1, 640),         # stride 2, odd size
+    (16, 112, 112, 16, 96, 1, 1, 0, 1792),      # MobileNetV2's first expansion (reduced batch): 7 steps per range, a second table begun
+    (16, 112, 112, 16, 96, 1, 1, 0, 3136),      # 4 steps per range: one table, one turn of the pipelined loop
+    (16, 112, 112, 16, 96, 1, 1, 0, 12544),     # a single step
+    (16, 56, 56, 64, 64, 3, 1, 1, 640),         # padded 3x3: rows of a step straddle image borders; 5 steps
+    (64, 14, 14, 256, 256, 3, 1, 1, 96),        # 9 steps: the first table written again while the second is read
+    (16, 57, 57, 32, 48, 3, 2, 1, 640),         # stride 2, odd size; 2 steps, empty ranges behind the last
 ]
 
 
 @pytest.mark.parametrize("case", MANY_RANGE_CASES)
 def test_filter_gradient_with_many_short_ranges_on_every_tile_shape(case):
-    """The aligned filter-gradient loader shares a per-step table of output positions through LDS; this runs it
-    with thousands of short reduction ranges (several workgroups resident per compute unit, the loop entered and
-    left after one or two turns) on each of the six tile shapes, against the oracle, twice: the two runs must agree
-    bit for bit."""
+    """The aligned filter-gradient loader shares tables of output positions (four steps each, two of them in turn) through LDS; this
+    runs it with hundreds to thousands of reduction ranges of one to nine steps (several workgroups resident per compute unit, the
+    loop entered and left after one or two turns) on each of the six tile shapes, against the oracle, twice: the two runs must
+    agree bit for bit.  With a forced shape the launch takes the ranges as asked: every one of their partial results is written."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad, splits = case
     rng = np.random.default_rng(hash(case) % (2 ** 32))
@@ -750,6 +751,7 @@ def test_filter_gradient_with_many_short_ranges_on_every_tile_shape(case):
                            ws.data_ptr(), ws.numel() * 4)
                 torch.cuda.synchronize()
                 got.append(dw.cpu().numpy())
+                assert not torch.isnan(ws).any(), (cfg, "fewer ranges than asked")
             assert np.array_equal(got[0], got[1]), (cfg, "two runs differ")
             check_close(got[0], want, 1e-5, what=f"tile shape {cfg}")
     finally:
