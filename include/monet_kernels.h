@@ -225,7 +225,8 @@ int monet_softmaxce_rows_bwd(void *stream, const float *logits, const int32_t *l
                              int64_t rows, int classes, int accumulate);
 
 /* Tuning and test aid: force the workgroup tile of the three convolution kernels (0: 128x128, 1: 256x64,
- * 2: 64x256, 3: 128x64, 4: 64x128, 5: 64x64 as rows x columns of the implicit GEMM) and make a launch cut its reduction into
+ * 2: 64x256, 3: 128x64, 4: 64x128, 5: 64x64 as rows x columns of the implicit GEMM; a shape that a kernel does not have, 1, 2 and
+ * for forward and input gradient 4, 5, stands for the nearest one that it has) and make a launch cut its reduction into
  * exactly the ranges that it is given; -1 restores the built-in choices.  Process-wide, not thread-safe. */
 int monet_conv_force_tile(int cfg);
 

@@ -326,7 +326,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     }
     // FAST == 3: reduction index of this lane's float4 (A; FWD's B has the same) or filter row (DGRAD's B) in the step to load, as
     // (tap, channel), and the tap's offset
-    struct LaneTap { int at, c, row, col; unsigned bit, off; };
+    struct LaneTap { int c, row, col; unsigned bit, off; };
     constexpr int UB3 = LB == 1 ? 1 : LB / 2;
     LaneTap la3, lb3[UB3];
     __amdgpu_buffer_rsrc_t ra = buffer_of(ta.a - a_shift, ta.a_bytes + (unsigned)a_shift * 4u),
@@ -375,7 +375,6 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             auto place = [&](LaneTap &t, int at) {
                 const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : max(ns, 1), taps = MODE == FWD ? cs.R * cs.S : nr * ns;
                 const int tap = at / inner;
-                t.at = at;
                 t.c = at - tap * inner;
                 t.row = tap / cols;
                 t.col = tap - t.row * cols;
@@ -1162,8 +1161,8 @@ int useful_splits(int mode, int splits, int64_t tiles, int64_t slots, double flo
     return best;
 }
 
-// Tile shapes: index -> waves (rows x columns of 64x32 wave tiles)
-//   0: 128x128   1: 256x64   2: 64x256   3: 128x64   4: 64x128   5: 64x64
+// Tile shapes that the choice below takes: 0: 128x128, 3: 128x64 for every mode, 4: 64x128 and 5: 64x64 for filter gradients.  1 (256x64)
+// and 2 (64x256) stand for the nearest of these.
 int g_cfg_override = -1;   // tuning and test aid: force one tile shape, and exactly the ranges asked for, on every launch
 
 template <int MODE, int WM, int WN, int TAG = 0>
@@ -1200,7 +1199,10 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
         // forward or input-gradient channels that are no multiple of 16
         const bool part = MODE == FWD ? ta.cs.C % BK != 0 : MODE == DGRAD ? ta.cs.K % BK != 0 : false;
         if constexpr (MODE != WGRAD) {
-            if (fast && part && ta.cs.R * ta.cs.S > 1) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 3>), grid, dim3(NT), 0, st, ta); }
+            if (fast && part && ta.cs.R * ta.cs.S > 1) {
+                if constexpr (WM == 2 && WN == 2) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 3>), grid, dim3(NT), 0, st, ta); }
+                else throw KernelError("conv: straddling reduction steps need the 128x64 tile");
+            }
             else if (fast && part) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 2>), grid, dim3(NT), 0, st, ta); }
             else if (fast && WM * WN == 4 && steps <= 6) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, WM * WN == 4 ? 4 : 1>), grid, dim3(NT), 0, st, ta); }
             else if (fast) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1>), grid, dim3(NT), 0, st, ta); }
@@ -1221,27 +1223,26 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // 76 us; 1x1, 512 -> 128, 28x28: 126 against 132; at 2256 tiles, 1x1, 256 -> 1024, 14x14: 126 against 118).  A reduction cut into
 // ranges fills it anyway.  `straddle`: reduction steps that cross filter taps.
 int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool straddle) {
-    if (g_cfg_override >= 0) return g_cfg_override;
     if (mode == WGRAD) {
+        static const int nearest[6] = {0, 3, 4, 3, 4, 5};
+        if (g_cfg_override >= 0) return nearest[g_cfg_override];
         if (Ng <= 64) return Mg <= 64 ? 5 : 3;
         if (Mg <= 64) return (Ng + 127) / 128 * 128 <= (Ng + 63) / 64 * 64 * 9 / 8 ? 4 : 5;
         return 0;
     }
-    if (Ng <= 64 || straddle) return 3;      // straddling lanes carry their tap: registers the larger tiles do not have
+    if (straddle) return 3;      // straddling lanes carry their tap: registers the larger tile does not have
+    if (g_cfg_override >= 0) return g_cfg_override == 0 ? 0 : 3;
+    if (Ng <= 64) return 3;
     if (splits > 1) return 0;
     return steps > 6 && (Mg + 127) / 128 * ((Ng + 127) / 128) * classes >= 6 * NUM_CU ? 0 : 3;
 }
 
 template <int MODE, class... Rest>
 void launch_cfg(int cfg, Rest... rest) {
-    switch (cfg) {
-        case 0: launch_tile<MODE, 2, 4>(rest...); break;
-        case 1: launch_tile<MODE, 4, 2>(rest...); break;
-        case 2: launch_tile<MODE, 1, 8>(rest...); break;
-        case 3: launch_tile<MODE, 2, 2>(rest...); break;
-        case 4: launch_tile<MODE, 1, 4>(rest...); break;
-        default: launch_tile<MODE, 1, 2>(rest...); break;
-    }
+    if (cfg == 0) launch_tile<MODE, 2, 4>(rest...);
+    else if (MODE == WGRAD && cfg == 4) launch_tile<WGRAD, 1, 4>(rest...);
+    else if (MODE == WGRAD && cfg == 5) launch_tile<WGRAD, 1, 2>(rest...);
+    else launch_tile<MODE, 2, 2>(rest...);
 }
 
 // the batched GEMMs only ever see the two tile shapes the forward heuristic picks
@@ -1292,9 +1293,6 @@ size_t conv_workspace_bytes(int which, const ConvShape &cs, int splits) {
     const int64_t s = std::min<int64_t>({NUM_CU / tail, sg.steps / 4, 16});
     return s >= 2 ? (size_t)(s * tail * bm * bn * 4) : 0;
 }
-
-namespace {
-}  // namespace
 
 void gemm_batched(hipStream_t st, const float *a, const float *b, float *out, int batch, int64_t rows, int cols, int red, bool adjoint_use) {
     if (batch < 1 || rows < 1 || cols < 1 || red < 1 || red % BK || cols % 4) throw KernelError("gemm_batched: bad shape");

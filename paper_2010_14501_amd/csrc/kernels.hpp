@@ -122,7 +122,7 @@ void split_reduce(hipStream_t st, const float *ws, float *out, int64_t n, int sp
 bool pointwise_wgrad_applies(const ConvShape &cs, int splits, size_t ws_bytes);
 void pointwise_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, const ConvShape &cs, int splits, float *ws, size_t ws_bytes);
 
-// tuning and test aid: cfg 0..5 forces tile shape (128x128, 256x64, 64x256, 128x64, 64x128, 64x64) and exactly the reduction ranges
+// tuning and test aid: cfg 0..5 forces tile shape (128x128, 256x64, 64x256, 128x64, 64x128, 64x64, or the nearest one there is) and exactly the reduction ranges
 // that a call asks for; -1 restores the heuristics
 void conv_force_tile(int cfg);
 // workspace bytes of conv_fwd (which = 0) / conv_dgrad (which = 1) for `splits` ranges; for splits = 1 a size

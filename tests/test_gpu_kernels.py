@@ -100,7 +100,7 @@ def test_conv_trio_matches_oracle(case):
 @pytest.mark.parametrize("tile", range(6))
 @pytest.mark.parametrize("case", [(3, 15, 14, 48, 112, 3, 1, 1), (2, 11, 13, 20, 76, 3, 2, 1), (2, 9, 8, 30, 70, 3, 1, 1), (2, 20, 18, 132, 72, 1, 1, 0)])
 def test_conv_trio_on_every_tile_shape(case, tile):
-    """Each of the six tile shapes, with rows and columns beyond a tile's edge, aligned, straddling and element-wise loaders,
+    """Each of the shape numbers (every tile shape there is, and those that stand for another), with rows and columns beyond a tile's edge, aligned, straddling and element-wise loaders,
     whole and in ranges, forward and both gradients, plain and accumulating."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad = case
@@ -728,7 +728,7 @@ MANY_RANGE_CASES = [
 def test_filter_gradient_with_many_short_ranges_on_every_tile_shape(case):
     """The aligned filter-gradient loader shares tables of output positions (four steps each, two of them in turn) through LDS; this
     runs it with hundreds to thousands of reduction ranges of one to nine steps (several workgroups resident per compute unit, the
-    loop entered and left after one or two turns) on each of the six tile shapes, against the oracle, twice: the two runs must
+    loop entered and left after one or two turns) on every tile shape, against the oracle, twice: the two runs must
     agree bit for bit.  With a forced shape the launch takes the ranges as asked: every one of their partial results is written."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad, splits = case
