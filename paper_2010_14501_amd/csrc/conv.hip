@@ -918,18 +918,20 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     float *out = ta.out;
     out += (int64_t)split * ta.out_elems;
     const bool do_acc = MODE != WGRAD && ta.accumulate && nsplit == 1;
-    if (FAST && (ta.Ng & 3) == 0) {
+    // (Element-wise loaders too, except for the filter gradient: results of few terms are bound by their stores.  1x1, 2 -> 64 input gradient,
+    // 416x608, batch 11: 224 us with 4-byte stores, 143 so; accumulating 686 and 346.)
+    if ((FAST || MODE != WGRAD) && (ta.Ng & 3) == 0) {
         // Vector path: each wave transposes its 64x32 result through a private 16x32 LDS patch, four
         // passes of 16 rows, and writes whole 16-byte pieces, 128 contiguous bytes per row.
         constexpr int NW = WM * WN;
         __syncthreads();   // every wave has finished reading the operand tiles
         static_assert(2 * A_SZ >= NW * 512 || 2 * B_SZ >= NW * 512, "the epilogue's patches fit one operand's tiles");
         float *stage = (float *)(2 * A_SZ >= NW * 512 ? &As[0][0] : &Bs[0][0]) + wave * 512;
-        const bool want_stats = MODE == FWD && ta.stats_part != nullptr;
+        const bool want_stats = FAST && MODE == FWD && ta.stats_part != nullptr;
         LaneStats ls;
         ls.init();
         // a lane writes the same four columns in every pass: one pair of BatchNorm coefficients each
-        const bool want_affine = MODE == FWD && ta.affine.gamma != nullptr;
+        const bool want_affine = FAST && MODE == FWD && ta.affine.gamma != nullptr;
         float bn_a[4] = {1, 1, 1, 1}, bn_b[4] = {0, 0, 0, 0};
         if (MODE == FWD && want_affine) {
             const int c0 = col0 + wn * 32 + 4 * (lane & 7);
@@ -1041,24 +1043,34 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         }
         return;
     }
+    const int col = col0 + wn * 32 + l32;
+    if (col >= ta.Ng) return;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            int64_t row = row0 + wm * 64 + mi * 32 + 8 * (v / 4) + 4 * g + (v % 4);
-            if (row >= Mg) continue;
-            int64_t orow = row;
+        for (int v4 = 0; v4 < 4; ++v4) {
+            // four consecutive rows: with strided residue classes, the first one's place is decoded and the others' follow from it
+            const int64_t first = row0 + wm * 64 + mi * 32 + 8 * v4 + 4 * g;
+            int wc = 0, hc = 0, n = 0;
             if (MODE == DGRAD && cs.stride > 1) {   // class row (n,hc,wc) -> position (n, hc*st+ph, wc*st+pw)
-                const unsigned r32 = (unsigned)row, t = r32 / (unsigned)Wc, n = t / (unsigned)Hc;      // rows are bounded below 2^31 by the host
-                const int wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - n * (unsigned)Hc);
-                orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
+                const unsigned r32 = (unsigned)first, t = r32 / (unsigned)Wc;      // rows are bounded below 2^31 by the host
+                n = (int)(t / (unsigned)Hc);
+                wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - (unsigned)n * (unsigned)Hc);
             }
-            const int col = col0 + wn * 32 + l32;
-            if (col < ta.Ng) {
-                float *dst = out + orow * ta.Ng + col;
-                float r = acc[mi][v];
-                if (do_acc) r += *dst;
-                *dst = r;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (first + j < Mg) {
+                    int64_t orow = first + j;
+                    if (MODE == DGRAD && cs.stride > 1) orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
+                    float *dst = out + orow * ta.Ng + col;
+                    float r = acc[mi][4 * v4 + j];
+                    if (do_acc) r += *dst;
+                    *dst = r;
+                }
+                if (MODE == DGRAD && cs.stride > 1 && ++wc == Wc) {
+                    wc = 0;
+                    if (++hc == Hc) { hc = 0; ++n; }
+                }
             }
         }
 }

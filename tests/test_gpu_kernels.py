@@ -97,6 +97,33 @@ def test_conv_trio_matches_oracle(case):
         check_close(gw.cpu().numpy(), want, GRAD_TOL, what=splits)
 
 
+@pytest.mark.parametrize("case", [
+    # N, H, W, C, K, R, stride, pad: element-wise loaders; results stored element by element (C no multiple of 4: four rows of a residue class
+    # in one go, across ends of rows and images) or in 16-byte pieces (C a multiple of 4)
+    (5, 3, 2, 7, 5, 3, 2, 1), (9, 5, 1, 6, 9, 1, 2, 0), (7, 2, 3, 11, 3, 2, 3, 1), (40, 4, 5, 3, 2, 1, 4, 0), (3, 9, 7, 130, 6, 3, 2, 1),
+    (5, 3, 2, 8, 5, 3, 2, 1), (3, 13, 9, 64, 2, 1, 1, 0), (2, 13, 9, 132, 3, 3, 2, 1), (2, 11, 9, 416, 1, 3, 1, 0), (2, 9, 9, 145, 17, 2, 3, 0),
+])
+def test_input_gradient_on_element_wise_loaders(case):
+    torch = torch_mod()
+    N, H, W, C, K, R, stride, pad = case
+    rng = np.random.default_rng(31)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    w = rng.standard_normal((K, R, R, C), dtype=np.float32)
+    dy = rng.standard_normal((N, P, Q, K), dtype=np.float32)
+    x = rng.standard_normal((N, H, W, C), dtype=np.float32)
+    want = wt.act_from_oracle(nm.conv2d_dgrad(wt.act_to_oracle(dy), wt.weight_to_oracle(w), (N, C, H, W), stride, pad))
+    gd, gw = dev(dy), dev(w)
+    guard = 64
+    for acc in (0, 1):
+        flat = torch.full((N * H * W * C + 2 * guard,), -7.0, device="cuda")
+        dx = flat[guard:guard + N * H * W * C].view(N, H, W, C)
+        dx.copy_(dev(x))
+        monet.call("monet_conv_dgrad", None, gd.data_ptr(), gw.data_ptr(), dx.data_ptr(), N, H, W, C, K, R, R, stride, pad, acc, 1, None, 0)
+        # fp32 sums of at most 54 products and the accumulated value: 1e-6 in the norm
+        check_close(dx.cpu().numpy(), want + x.astype(np.float64) * acc, 1e-6, what=acc)
+        assert (flat[:guard] == -7.0).all() and (flat[guard + N * H * W * C:] == -7.0).all()
+
+
 @pytest.mark.parametrize("tile", range(6))
 @pytest.mark.parametrize("case", [(3, 15, 14, 48, 112, 3, 1, 1), (2, 11, 13, 20, 76, 3, 2, 1), (2, 9, 8, 30, 70, 3, 1, 1), (2, 20, 18, 132, 72, 1, 1, 0)])
 def test_conv_trio_on_every_tile_shape(case, tile):
