@@ -1234,7 +1234,11 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // batch 184: 214 against 250 us) and where square tiles are too few to fill the GPU evenly (1x1, 160 -> 960, 7x7, batch 272: 47 against
 // 76 us; 1x1, 512 -> 128, 28x28: 126 against 132; at 2256 tiles, 1x1, 256 -> 1024, 14x14: 126 against 118).  A reduction cut into
 // ranges fills it anyway.  `straddle`: reduction steps that cross filter taps.
-int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool straddle) {
+// Element-wise loaders (`fast` false) are bound by loading: a wider tile reads each activation for fewer column tiles.  Forward, 128x64
+// against 128x128: 5x5, 141 -> 464, 106x106, batch 2: 1459 and 897 us; 3x3, 258 -> 514, 14x14, batch 64: 709 and 389; 1x1, 18 -> 239,
+// 90x90, batch 23: 67 and 56.  Input gradient of the first: 2643 and 2001; of a 3x3 layer, 416 -> 1, in one step: 60 and 52; of a 2x2 stride-3 layer,
+// 145 -> 17, in two steps: 55 and 65, where square tiles cover a third more columns: short reductions take them up to a fifth.
+int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool fast, bool straddle) {
     if (mode == WGRAD) {
         static const int nearest[6] = {0, 3, 4, 3, 4, 5};
         if (g_cfg_override >= 0) return nearest[g_cfg_override];
@@ -1246,6 +1250,7 @@ int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, i
     if (g_cfg_override >= 0) return g_cfg_override == 0 ? 0 : 3;
     if (Ng <= 64) return 3;
     if (splits > 1) return 0;
+    if (!fast) return mode == FWD || steps > 6 || (Ng + 127) / 128 * 128 * 5 <= (Ng + 63) / 64 * 64 * 6 ? 0 : 3;
     return steps > 6 && (Mg + 127) / 128 * ((Ng + 127) / 128) * classes >= 6 * NUM_CU ? 0 : 3;
 }
 
@@ -1367,7 +1372,7 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
     if (affine && affine->mask && (!affine->relu || cs.K % 64)) throw KernelError("conv_fwd: a sign code in the epilogue needs the ReLU and K % 64 == 0");
     ta.stats_part = stats_part;
     if (affine) ta.affine = *affine;
-    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, (ta.Kg + BK - 1) / BK, 1, splits, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, accumulate, "conv_fwd");
+    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, (ta.Kg + BK - 1) / BK, 1, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, accumulate, "conv_fwd");
 }
 
 void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, const ConvShape &cs, bool accumulate, int splits, float *ws,
@@ -1384,7 +1389,7 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     const int64_t span32 = ((int64_t)1 << 32) - (1 << 20);
     const int64_t reach = ((int64_t)cs.R * cs.Q + cs.S) * cs.K * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
-    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, splits, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
+    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, splits, fast, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
 }
 
 void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, const ConvShape &cs, int splits, float *ws, size_t ws_bytes) {
@@ -1409,7 +1414,7 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
     const int64_t lead = ((int64_t)cs.pad * cs.W + cs.pad) * cs.C * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 < span32 &&
                 (int64_t)cs.N * cs.H * cs.W * cs.C * 4 + lead < span32;
-    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, splits, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, false, "conv_wgrad");
+    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, false, "conv_wgrad");
 }
 
 }  // namespace monet
