@@ -28,7 +28,9 @@ extern "C" {
  * the workspace size only.
  *   splits > 1: ws >= splits * |result| floats; a second kernel adds the partial results.  A launch uses fewer ranges than
  *     it is given where more would only cost partial results.
- *   splits == 1: the reduction is not cut; a workspace is accepted and left alone.
+ *   fwd, dgrad with splits == 1 and a workspace: a launch that leaves at least half of the 256 CUs without a tile cuts its
+ *     reduction into as many ranges as the workspace holds results (monet_conv_workspace_bytes gives a useful size); otherwise, and
+ *     with ws == NULL, nothing is cut.
  * A product is worked in six terms of three bf16 pieces per operand on the matrix cores, to 2^-24 of itself at worst; sums are
  * fp32.  A tile of the result (up to 128x128) is worked once more with the fp32 matrix instruction where that does not hold: where it
  * ends with an infinity or a NaN in it (infinities, NaNs and overflows come out as fp32 arithmetic's), or where an operand below 2^-110 has
@@ -146,7 +148,8 @@ int monet_conv_winograd_wgrad(void *stream, const float *x, const float *dy, flo
                               int m, float *ws, size_t ws_bytes);
 int64_t monet_conv_winograd_wgrad_workspace_bytes(int N, int H, int W, int C, int K, int m);
 /* Workspace bytes for monet_conv_fwd (which = 0) / monet_conv_dgrad (which = 1) of this shape with `splits` ranges;
- * for splits == 1 the size that earlier versions used for the ragged last round of tiles (0: none; it is no longer needed).
+ * for splits == 1 room for the tiles beyond a multiple of the 256 CUs in up to 16 ranges (0: nothing to gain): used where these are the whole
+ * launch, left alone where there are more.
  * Negative: error code. */
 int64_t monet_conv_workspace_bytes(int which, int N, int H, int W, int C, int K, int R, int S, int stride, int pad, int splits);
 /* dx[N,H,W,C] (+)= gradient of the above wrt x, from dy[N,P,Q,K]. */

@@ -262,16 +262,18 @@ bool bn_stats_in_row_groups(int64_t rows, int C, size_t scratch_bytes) {
     return (size_t)(groups + folded) * C * 2 * sizeof(float) <= scratch_bytes;
 }
 
+void bn_stats_row_groups(hipStream_t st, const float *x, float *part, int64_t rows, int C) {
+    const int chunks = (C + 63) / 64;
+    const int64_t units = (rows + STAT_ROWS - 1) / STAT_ROWS * chunks;
+    hipLaunchKernelGGL(bn_stats_rows64, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, st, x, part, rows, C, chunks, units);
+    hip_check(hipGetLastError(), "bn_stats launch");
+}
 void bn_stats(hipStream_t st, const float *x, float *stats, int64_t rows, int C, float eps, float *scratch, size_t scratch_bytes,
               bool partials_ready) {
     if (rows <= 0) throw KernelError("BatchNorm: no rows");
     if (bn_stats_in_row_groups(rows, C, scratch_bytes)) {
         const int64_t groups = (rows + STAT_ROWS - 1) / STAT_ROWS;
-        if (!partials_ready) {
-            const int chunks = (C + 63) / 64;
-            const int64_t units = groups * chunks;
-            hipLaunchKernelGGL(bn_stats_rows64, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, st, x, scratch, rows, C, chunks, units);
-        }
+        if (!partials_ready) bn_stats_row_groups(st, x, scratch, rows, C);
         if (groups > FOLD_ABOVE) {
             const int64_t folded = (groups + FOLD - 1) / FOLD;
             float *second = scratch + groups * C * 2;

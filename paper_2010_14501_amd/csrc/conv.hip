@@ -1296,6 +1296,15 @@ SplitGemm split_gemm_of(int which, const ConvShape &cs) {
 }
 }  // namespace
 
+// Ranges for a launch that was given a workspace but not told to cut its reduction (splits == 1): with at most half as many square tiles as
+// CUs, as many ranges as fill the GPU once and the workspace holds, of at least eight steps each.  3x3, 512 -> 512, 7x7, batch 1: 141 us
+// uncut, 18 so; 1x1, 2048 -> 512, 7x7, batch 2: 66 and 14.
+static int ranges_by_workspace(const SplitGemm &sg, int64_t out_elems, const float *ws, size_t ws_bytes) {
+    if (!ws || sg.classes != 1 || g_cfg_override >= 0) return 1;
+    const int64_t tiles = (sg.rows + 127) / 128 * (sg.cols <= 64 ? 1 : (sg.cols + 127) / 128);
+    return (int)std::max<int64_t>(1, std::min<int64_t>({NUM_CU / tiles, sg.steps / 8, 16, (int64_t)(ws_bytes / 4) / out_elems}));
+}
+
 size_t conv_workspace_bytes(int which, const ConvShape &cs, int splits) {
     check_shape(cs);
     const SplitGemm sg = split_gemm_of(which, cs);
@@ -1370,6 +1379,18 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
     if (stats_part && affine) throw KernelError("conv_fwd: either the statistics of the output or its BatchNorm apply step, not both");
     if (affine && (!affine->gamma || !affine->beta || !affine->stats)) throw KernelError("conv_fwd: incomplete BatchNorm coefficients");
     if (affine && affine->mask && (!affine->relu || cs.K % 64)) throw KernelError("conv_fwd: a sign code in the epilogue needs the ReLU and K % 64 == 0");
+    if (splits == 1) {
+        splits = ranges_by_workspace(split_gemm_of(0, cs), ta.out_elems, ws, ws_bytes);
+        if (splits > 1 && (stats_part || affine)) {      // the sums are complete only behind the second kernel: what rode in the epilogue follows it
+            conv_fwd(st, x, w, y, cs, splits, ws, ws_bytes);
+            if (stats_part) bn_stats_row_groups(st, y, stats_part, cs.M(), cs.K);
+            else if (affine->relu)
+                fwd_chain(st, y, nullptr, affine->gamma, affine->beta, affine->stats, cs.K, affine->relu_out ? y : nullptr, nullptr,
+                          affine->relu_out ? affine->relu_out : y, (uint64_t *)affine->mask, ta.out_elems, affine->relu == 2);
+            else bn_apply(st, y, y, affine->gamma, affine->beta, affine->stats, cs.M(), cs.K);
+            return;
+        }
+    }
     ta.stats_part = stats_part;
     if (affine) ta.affine = *affine;
     launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, (ta.Kg + BK - 1) / BK, 1, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, accumulate, "conv_fwd");
@@ -1386,6 +1407,7 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     ta.Ng = cs.C;
     ta.Kg = 0;   // per class, computed in the kernel
     ta.out_elems = (int64_t)cs.N * cs.H * cs.W * cs.C;
+    if (splits == 1) splits = ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes);
     const int64_t span32 = ((int64_t)1 << 32) - (1 << 20);
     const int64_t reach = ((int64_t)cs.R * cs.Q + cs.S) * cs.K * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;

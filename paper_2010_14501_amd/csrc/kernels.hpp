@@ -47,7 +47,8 @@ bool conv_epilogue_writes_mask(const ConvShape &cs, bool winograd_fused);
 
 // ---- convolution (implicit GEMM; fp32 products as sums of bf16 matrix instructions)
 // Every variant can cut its reduction into `splits` ranges: partial results go to ws (splits * |output|
-// floats) and are added in range order.  splits == 1 needs no workspace.
+// floats) and are added in range order.  splits == 1 needs no workspace; given one, forward pass and input gradient cut a launch of
+// few tiles into as many ranges as it holds.
 // y (+)= conv(x, w)
 // stats_part: if given, the epilogue also leaves BatchNorm's partial statistics of y (groups of 64 rows, the
 // layout bn_stats() reads with partials_ready) there; needs conv_fwd_aligned(cs), K % 4 == 0, splits == 1, no accumulation.
@@ -125,8 +126,8 @@ void pointwise_wgrad(hipStream_t st, const float *x, const float *dy, float *dw,
 // tuning and test aid: cfg 0..5 forces tile shape (128x128, 256x64, 64x256, 128x64, 64x128, 64x64, or the nearest one there is) and exactly the reduction ranges
 // that a call asks for; -1 restores the heuristics
 void conv_force_tile(int cfg);
-// workspace bytes of conv_fwd (which = 0) / conv_dgrad (which = 1) for `splits` ranges; for splits = 1 a size
-// that callers' saved plans declare and the kernels leave alone (0 where none was ever declared)
+// workspace bytes of conv_fwd (which = 0) / conv_dgrad (which = 1) for `splits` ranges; for splits = 1 what lets the tiles
+// beyond a multiple of the CU count be cut (used where they are the whole launch; 0: none)
 size_t conv_workspace_bytes(int which, const ConvShape &cs, int splits);
 
 // Workgroups of a pass that streams `total4` 16-byte elements: one per 2048 (32 KiB; many short contiguous streams measured
@@ -146,6 +147,8 @@ constexpr int64_t kBnScratchFloats = 1 << 20;
 // partial results in `scratch`; only the final merge runs.  Allowed only where bn_stats_in_row_groups() holds.
 void bn_stats(hipStream_t st, const float *x, float *stats, int64_t rows, int C, float eps, float *scratch,
               size_t scratch_bytes, bool partials_ready = false);
+// its first level alone: the partial results of groups of 64 rows, as a convolution's epilogue leaves them
+void bn_stats_row_groups(hipStream_t st, const float *x, float *part, int64_t rows, int C);
 // The same with the partial results in a 4 MiB array inside the library (no scratch argument, no allocation); result
 // bit-identical to bn_stats() with a 4 MiB scratch.  Calls that overlap in time on one GPU share the array and race.
 constexpr int kBnStaticMaxC = 8192;

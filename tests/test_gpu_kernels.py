@@ -355,8 +355,36 @@ def test_conv_of_one_product_is_the_rounded_product():
     assert np.array_equal(y.cpu().numpy(), a * b[0])
 
 
-def test_conv_ragged_last_round_is_split_and_counts_reset():
-    """More than 256 tiles and not a multiple of it, with the workspace that lets a library cut the tiles of the last round.
+def test_conv_of_few_tiles_uses_the_workspace_it_is_given():
+    """splits == 1 and a workspace: a launch of few tiles cuts its reduction by itself, as many ranges as the workspace holds and
+    at least eight steps each, with the bits of the call that asks for as many; one that holds a single result changes nothing."""
+    torch = torch_mod()
+    for N, H, W, C, K, R, ranges in ((1, 7, 7, 512, 512, 3, 16), (2, 9, 9, 48, 64, 3, 3), (6, 28, 28, 256, 130, 1, 2)):
+        rng = np.random.default_rng(37)
+        x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, H, W, K), dtype=np.float32)
+        w = rng.standard_normal((K, R, R, C), dtype=np.float32)
+        gx, gw, gd = dev(x), dev(w), dev(dy)
+        for name, src, out, adj in (("monet_conv_fwd", gx, K, ()), ("monet_conv_dgrad", gd, C, (1,))):
+            n = N * H * W * out
+            dims = (N, H, W, C, K, R, R, 1, R // 2) + adj
+            red = R * R * (C if out == K else K)
+            most = max(1, min(ranges, -(-red // 16) // 8, 256 // (-(-N * H * W // 128) * -(-out // 128))))
+            ws = torch.empty(ranges * n, device="cuda")
+
+            def go(splits, floats):
+                ws.fill_(float("nan"))
+                y = torch.full((N, H, W, out), 1.0, device="cuda")
+                monet.call(name, None, src.data_ptr(), gw.data_ptr(), y.data_ptr(), *dims, splits, ws.data_ptr() if floats else None, floats * 4)
+                return y, int((~torch.isnan(ws)).sum()) // n
+            y, used = go(1, ranges * n)
+            assert used == (most if most > 1 else 0), (name, used, most)
+            assert torch.equal(y, go(most, ranges * n)[0]), (name, "as many ranges, asked for")
+            y, used = go(1, 2 * n - 1)
+            assert used == 0 and torch.equal(y, go(1, 0)[0]), (name, "room for one result")
+
+
+def test_conv_of_a_ragged_last_round_leaves_its_workspace_alone():
+    """More than 256 tiles and not a multiple of it, with the workspace that earlier kernels cut the tiles of the last round with.
     Several calls in a row, forward and input gradient with accumulation, against the oracle and against the call
     without a workspace."""
     torch = torch_mod()
@@ -368,14 +396,14 @@ def test_conv_ragged_last_round_is_split_and_counts_reset():
     xo, wo, dyo = wt.act_to_oracle(x), wt.weight_to_oracle(w), wt.act_to_oracle(dy)
     dx, dwt, ddy = dev(x), dev(w), dev(dy)
     need = [monet.call("monet_conv_workspace_bytes", which, N, H, W, C, K, R, R, stride, pad, 1) for which in (0, 1)]
-    assert need[0] == need[1] == 2 * 38 * 128 * 128 * 4                      # 38 tiles beyond 256, two ranges of four steps
+    assert need[0] == need[1] == 2 * 38 * 128 * 128 * 4                      # 38 tiles beyond 256, in two ranges
     ws = torch.full((need[0] // 4,), float("nan"), dtype=torch.float32, device="cuda")
     want_y = wt.act_from_oracle(nm.conv2d_fwd(xo, wo, stride, pad))
     want_dx = wt.act_from_oracle(nm.conv2d_dgrad(dyo, wo, xo.shape, stride, pad))
     y0 = torch.empty((N, H, W, K), dtype=torch.float32, device="cuda")
     monet.call("monet_conv_fwd", None, dx.data_ptr(), dwt.data_ptr(), y0.data_ptr(), N, H, W, C, K, R, R, stride, pad, 1, None, 0)
-    # a refused call (workspace announced smaller than two partial results) enqueues nothing and leaves the table alone;
-    # an explicit reset of the table between good calls changes nothing either
+    # a refused call (workspace announced smaller than two partial results) enqueues nothing; monet_conv_reset_arrivals, kept
+    # for earlier callers, changes nothing
     with pytest.raises(monet.MonetError):
         monet.call("monet_conv_fwd", None, dx.data_ptr(), dwt.data_ptr(), y0.data_ptr(), N, H, W, C, K, R, R, stride, pad, 2, ws.data_ptr(), 1024)
     for rep in range(3):
@@ -384,8 +412,7 @@ def test_conv_ragged_last_round_is_split_and_counts_reset():
         y = torch.full((N, H, W, K), float("nan"), dtype=torch.float32, device="cuda")
         monet.call("monet_conv_fwd", None, dx.data_ptr(), dwt.data_ptr(), y.data_ptr(), N, H, W, C, K, R, R, stride, pad, 1, ws.data_ptr(), need[0])
         check_close(y.cpu().numpy(), want_y, ACT_TOL, what=rep)
-        assert torch.equal(y[:32], y0[:32])                                   # whole tiles: same kernel path, same bits
-        assert rel(y.cpu().numpy(), y0.cpu().numpy()) < 1e-6
+        assert torch.equal(y, y0) and torch.isnan(ws).all()
         gx = torch.full((N, H, W, C), float("nan"), dtype=torch.float32, device="cuda")
         monet.call("monet_conv_dgrad", None, ddy.data_ptr(), dwt.data_ptr(), gx.data_ptr(), N, H, W, C, K, R, R, stride, pad, 0, 1, ws.data_ptr(), need[1])
         check_close(gx.cpu().numpy(), want_dx, GRAD_TOL, what=rep)
@@ -397,14 +424,15 @@ def test_conv_ragged_last_round_is_split_and_counts_reset():
     (3, 14, 14, 64, 128, 3, 1, 1),      # ragged last row group (588 rows)
     (2, 28, 28, 64, 256, 1, 1, 0),      # two column tiles
     (2, 15, 13, 32, 80, 3, 2, 1),       # stride 2, a column tile that is only partly used (80 of 128)
-    (2, 28, 28, 128, 64, 1, 2, 0),      # the 256x64 tile: four row groups per workgroup
-    (48, 28, 28, 128, 128, 1, 1, 0),    # ragged last round cut and met inside the kernel
+    (2, 28, 28, 128, 64, 1, 2, 0),      # 64 columns
+    (48, 28, 28, 128, 128, 1, 1, 0),    # more tiles than CUs, and no multiple of them
     (2, 28, 28, 24, 144, 1, 1, 0),      # 1x1 with 24 input channels (last reduction step half empty)
     (3, 15, 13, 40, 36, 1, 2, 0),
 ])
-def test_statistics_from_the_conv_epilogue_are_the_stand_alone_bits(case):
+@pytest.mark.parametrize("room", [True, False])
+def test_statistics_from_the_conv_epilogue_are_the_stand_alone_bits(case, room):
     """BatchNorm's forward statistics come out of the convolution's epilogue with the same bits as from a pass
-    over the convolution's output, and match the oracle."""
+    over the convolution's output, and match the oracle; likewise behind a reduction cut into ranges (few tiles and a workspace)."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad = case
     rng = np.random.default_rng(hash(case) % (2 ** 32))
@@ -418,7 +446,7 @@ def test_statistics_from_the_conv_epilogue_are_the_stand_alone_bits(case):
     groups = (rows + 63) // 64
     sb = 8 * (groups + (groups + 63) // 64) * K                      # first and second level of the statistics
     scratch = torch.full((sb // 4,), float("nan"), dtype=torch.float32, device="cuda")
-    need = monet.call("monet_conv_workspace_bytes", 0, N, H, W, C, K, R, R, stride, pad, 1)
+    need = monet.call("monet_conv_workspace_bytes", 0, N, H, W, C, K, R, R, stride, pad, 1) if room else 0
     ws = torch.empty(max(need // 4, 1), dtype=torch.float32, device="cuda")
     y = torch.full((N, P, Q, K), float("nan"), dtype=torch.float32, device="cuda")
     fused = torch.full((2 * K,), float("nan"), dtype=torch.float32, device="cuda")
@@ -442,16 +470,18 @@ def test_statistics_from_the_conv_epilogue_are_the_stand_alone_bits(case):
     (3, 14, 14, 64, 128, 3, 1, 1, 0),      # implicit GEMM, ragged rows
     (2, 28, 28, 64, 256, 1, 1, 0, 0),      # two column tiles
     (2, 15, 13, 32, 80, 3, 2, 1, 0),       # stride 2, a column tile that is only partly used
-    (2, 28, 28, 128, 64, 1, 2, 0, 0),      # the 256x64 tile
-    (48, 28, 28, 128, 128, 1, 1, 0, 0),    # ragged last round cut and met inside the kernel
+    (2, 28, 28, 128, 64, 1, 2, 0, 0),      # 64 columns
+    (48, 28, 28, 128, 128, 1, 1, 0, 0),    # more tiles than CUs, and no multiple of them
     (2, 28, 28, 24, 128, 1, 1, 0, 0),      # 1x1 with 24 input channels (last reduction step half empty)
     (3, 14, 14, 64, 128, 3, 1, 1, 2),      # Winograd, 2x2 output tiles
     (3, 14, 14, 64, 128, 3, 1, 1, 4),      # Winograd, 4x4 output tiles (last tile row / column partly outside)
     (2, 9, 7, 32, 48, 3, 1, 1, 4),
 ])
-def test_batchnorm_apply_in_the_conv_epilogue_is_the_stand_alone_bits(case):
+@pytest.mark.parametrize("room", [True, False])
+def test_batchnorm_apply_in_the_conv_epilogue_is_the_stand_alone_bits(case, room):
     """A recomputed convolution that applies the BatchNorm behind it in its epilogue writes exactly what the
-    convolution followed by the in-place apply kernel writes (implicit GEMM and both Winograd forms)."""
+    convolution followed by the in-place apply kernel writes (implicit GEMM, whole and cut into ranges where there is room for
+    them, and both Winograd forms)."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad, m = case
     rng = np.random.default_rng(hash(case) % (2 ** 32))
@@ -466,7 +496,7 @@ def test_batchnorm_apply_in_the_conv_epilogue_is_the_stand_alone_bits(case):
     if m:
         need = monet.call("monet_conv_winograd_workspace_bytes", N, H, W, C, K, m)
     else:
-        need = monet.call("monet_conv_workspace_bytes", 0, N, H, W, C, K, R, R, stride, pad, 1)
+        need = monet.call("monet_conv_workspace_bytes", 0, N, H, W, C, K, R, R, stride, pad, 1) if room else 0
     ws = torch.empty(max(need // 4, 1), dtype=torch.float32, device="cuda")
     wsp = ws.data_ptr() if need else None
     fused = torch.full((N, P, Q, K), float("nan"), dtype=torch.float32, device="cuda")
