@@ -905,6 +905,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < BK; k += 2) {
+                if (k >= (int)Kg - t * BK) break;      // beyond the reduction
                 const float y = fb[whole(kc_b, cols, k + g, wn * 32 + l32)];
 #pragma unroll
                 for (int mi = 0; mi < 2; ++mi)
@@ -1057,21 +1058,30 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
                 n = (int)(t / (unsigned)Hc);
                 wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - (unsigned)n * (unsigned)Hc);
             }
+            float *dst[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (first + j < Mg) {
-                    int64_t orow = first + j;
-                    if (MODE == DGRAD && cs.stride > 1) orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
-                    float *dst = out + orow * ta.Ng + col;
-                    float r = acc[mi][4 * v4 + j];
-                    if (do_acc) r += *dst;
-                    *dst = r;
+                int64_t orow = first + j;
+                if (MODE == DGRAD && cs.stride > 1) {
+                    orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
+                    if (++wc == Wc) {
+                        wc = 0;
+                        if (++hc == Hc) { hc = 0; ++n; }
+                    }
                 }
-                if (MODE == DGRAD && cs.stride > 1 && ++wc == Wc) {
-                    wc = 0;
-                    if (++hc == Hc) { hc = 0; ++n; }
-                }
+                dst[j] = out + orow * ta.Ng + col;
             }
+            float r[4] = {acc[mi][4 * v4], acc[mi][4 * v4 + 1], acc[mi][4 * v4 + 2], acc[mi][4 * v4 + 3]};
+            if (do_acc) {      // the four loads together
+                float o[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = first + j < Mg ? *dst[j] : 0.0f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) r[j] += o[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (first + j < Mg) *dst[j] = r[j];
         }
 }
 
