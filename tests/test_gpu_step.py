@@ -232,6 +232,42 @@ def test_fused_neighbours_give_identical_bits():
     assert recomputed_bn > 0 and apply_launches < recomputed_bn
 
 
+def test_steps_of_two_plans_overlap_on_two_streams():
+    """Nothing is shared between plans: two of them, each stepped again and again by a thread of its own on a stream of its own, give
+    the bits of their steps taken alone.  The convolutions of both run split reductions and Winograd layers at the same time."""
+    import threading
+    import torch
+    cases = [(graphs.resnet50(batch=16, hw=64, classes=10, widths=(64, 128), depths=(2, 2), stem=64), schedules.block_output_schedule),
+             (graphs.resnet50(batch=12, hw=64, classes=10, widths=(64, 96), depths=(2, 1), stem=32), schedules.store_everything_schedule)]
+    runs, alone = [], []
+    for seed, (g, sched) in enumerate(cases):
+        exts, params = tensors.make_inputs(g, seed=seed, gamma_beta="random")
+        run = StepRunner(g.text(), sched(g).text(), exts, params)
+        peak = run.step()
+        runs.append(run)
+        alone.append((peak, run.grads_numpy(), run.loss_value()))
+        for t in run.grads:
+            t.fill_(float("nan"))
+    torch.cuda.synchronize()
+    peaks = [set(), set()]
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        for _ in range(20):
+            peaks[i].add(runs[i].step(stream))
+        stream.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for run, (peak, grads, loss), seen in zip(runs, alone, peaks):
+        assert seen == {peak}
+        got = run.grads_numpy()
+        assert run.loss_value() == loss
+        assert all(np.array_equal(got[p], grads[p]) for p in grads)
+
+
 def test_recomputed_relu_rides_in_the_convolution_epilogue_when_its_mask_is_kept():
     """A schedule that keeps block outputs and every ReLU's 1-bit sign mask: the recomputed convolution -> BatchNorm -> ReLU
     chains then write no mask, and the executor runs each as one launch (BatchNorm apply and ReLU in the convolution's
