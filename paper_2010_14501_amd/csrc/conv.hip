@@ -51,6 +51,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 namespace {
 
 constexpr int BK = 16;        // reduction step
+constexpr int KTAB = 256;     // reduction indices in the element-wise forward loader's table
 constexpr int NUM_XCD = 8;
 
 // LDS tile of one operand: three planes (h, m, l) of 32-bit words that hold two neighbouring reduction indices.
@@ -123,7 +124,6 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     // instead of dividing (measured 925 -> 815 us on the ResNet-50 stem).  Only the 64 columns wide tiles have
     // the LDS to spare (2 KiB), and those are the ones results up to 64 channels wide, i.e. every first layer, use.
     constexpr bool HAS_KTAB = !FAST && MODE == FWD && BN == 64;
-    constexpr int KTAB = 256;
     __shared__ int2 ktab[HAS_KTAB ? KTAB : 1];   // x = ((r*W + s)*C + c), y = r | s << 8, or y < 0 beyond the reduction
     // Aligned filter gradient: the output positions of four reduction steps, decoded once for the whole workgroup by the 64 lanes of one
     // wave: x = byte offset of the position's window in the (shifted) input tensor, y = bit per filter tap that falls inside the
@@ -1248,6 +1248,8 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // against 128x128: 5x5, 141 -> 464, 106x106, batch 2: 1459 and 897 us; 3x3, 258 -> 514, 14x14, batch 64: 709 and 389; 1x1, 18 -> 239,
 // 90x90, batch 23: 67 and 56.  Input gradient of the first: 2643 and 2001; of a 3x3 layer, 416 -> 1, in one step: 60 and 52; of a 2x2 stride-3 layer,
 // 145 -> 17, in two steps: 55 and 65, where square tiles cover a third more columns: short reductions take them up to a fifth.
+// Forward the narrow tile has a table of reduction indices for up to 256 of them: 5x5, 10 -> 192, 28x28, batch 64: 68 and 88 (a third more
+// columns); 5x5, 3 -> 96, 112x112, batch 32: 124 and 117 (as many).
 int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool fast, bool straddle) {
     if (mode == WGRAD) {
         static const int nearest[6] = {0, 3, 4, 3, 4, 5};
@@ -1260,7 +1262,7 @@ int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, i
     if (g_cfg_override >= 0) return g_cfg_override == 0 ? 0 : 3;
     if (Ng <= 64) return 3;
     if (splits > 1) return 0;
-    if (!fast) return mode == FWD || steps > 6 || (Ng + 127) / 128 * 128 * 5 <= (Ng + 63) / 64 * 64 * 6 ? 0 : 3;
+    if (!fast) return steps > (mode == FWD ? KTAB / BK : 6) || (Ng + 127) / 128 * 128 * 5 <= (Ng + 63) / 64 * 64 * 6 ? 0 : 3;
     return steps > 6 && (Mg + 127) / 128 * ((Ng + 127) / 128) * classes >= 6 * NUM_CU ? 0 : 3;
 }
 
