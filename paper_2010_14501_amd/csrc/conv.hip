@@ -102,8 +102,10 @@ __device__ __forceinline__ void for_each_int(F &f, std::integer_sequence<int, I.
 // FAST: 0 element-wise loaders, 1 aligned loaders, 2 aligned loaders of a 1x1 layer whose last reduction step is partly
 // empty (a kernel of its own: the two tests per step would cost the other layers 2 %, measured on ResNet-50), 3 aligned
 // loaders of a larger filter over channels that are a multiple of 4 but not of 16: a step straddles filter taps, every
-// lane carries the tap and channel of its four reduction indices, 4 as 1 for reductions of at most six steps (5x5 filter, 24 -> 64 channels, 14x14 maps, batch 320:
-// 160 -> 38 us forward, 134 -> 82 us input gradient against the element-wise loaders)
+// lane carries the tap and channel of its four reduction indices (5x5 filter, 24 -> 64 channels, 14x14 maps, batch 320:
+// 160 -> 38 us forward, 134 -> 82 us input gradient against the element-wise loaders), 4 as 1 with a single register stage, for reductions of at
+// most six steps (1x1, C -> 256, 56x56, batch 184, one stage against two: C = 32: 123 and 138 us, 64: 173 and 197, 96: 225 and 242; beyond the
+// line the gain shrinks: 112: 256 and 268, 128: 316 and 328, 192: 421 and 430, 256 level; level at every C on 14x14)
 template <int MODE, int WM, int WN, int FAST, int TAG = 0>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST != 2 && FAST != 4) ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
     // Register stages of the aligned variants: loads run this many steps ahead of the split.  The tiles of at most four waves take
@@ -277,12 +279,12 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     }
 
     // ---------------- aligned forward / input-gradient loaders: buffer addressing
-    // Every vector instruction takes its cycles from the matrix pipe of the same SIMD, so an address is split into what
+    // A matrix instruction leaves room for about six vector instructions, which the splits use up, so an address is split into what
     // differs between lanes and never changes (a 32-bit byte offset per slot, computed once) and what changes from step
     // to step and is the same for every lane (the filter tap and the channel block: a scalar offset).  The descriptor of
-    // the activation operand starts `a_shift` floats before the tensor, enough for the most negative tap offset and for
-    // the offset that sends an absent element (padding, rows beyond the tensor) to the tensor's first floats instead;
-    // bit t of a_taps says whether tap t of the slot exists.  The host takes this path only for tensors the 32-bit
+    // the activation operand starts `a_shift` floats before the tensor, enough for the most negative tap offset, and ends with the
+    // tensor: an absent element (padding, rows beyond the tensor) is a load at BUFFER_ABSENT, which reads zero.
+    // Bit t of a_taps says whether tap t of the slot exists.  The host takes this path only for tensors the 32-bit
     // offsets can span and for filters of at most 32 taps.
     unsigned a_voff[LA], a_taps[LA], b_voff[LB];
     int64_t a_shift = 0;
@@ -1169,6 +1171,9 @@ constexpr int resident_workgroups(int mode, int wm, int wn) {
 // results.  `slots`: workgroups of the tile shape that are on the GPU together.
 //   Filter gradients (few tiles, many ranges): the fullest of one to four rounds of workgroups, by an estimate of the matrix
 //   instructions (180 TFLOP/s, 7 % lost to the uneven end of a single round) and of writing and reading the slabs (4 TB/s).
+//   Over 13 layers of the networks at half a round to six rounds (forced): what it takes is within 5 % of the best of them and 4 - 10 % ahead
+//   of what was asked for on small results (1x1, 64 -> 64, 56x56: 768 ranges 80 us, 1536 78, 4096 100; 1x1, 1024 -> 256, 14x14: 16 ranges
+//   152, 32 128, 64 135; 3x3 stride 2, 128 -> 128, 56x56: 28 ranges 326, 56 271, 85 - taken - 286, 113 287).
 //   Forward / input gradient: at most five workgroups per CU; beyond that the slabs cost more than the better balance gives.
 int useful_splits(int mode, int splits, int64_t tiles, int64_t slots, double flops, double slab_bytes) {
     if (mode != WGRAD) return (int)std::max<int64_t>(1, std::min<int64_t>(splits, (5 * NUM_CU + tiles - 1) / tiles));
@@ -1242,7 +1247,9 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // L2 per product (3x3, 256 -> 256, 56x56, batch 176: 3.25 ms against 3.67 with 128x64), the 128x64 tile has twice as many workgroups,
 // four of them on a CU: it is the faster one where a reduction is short and the time goes into loads and stores (1x1, 64 -> 256, 56x56,
 // batch 184: 214 against 250 us) and where square tiles are too few to fill the GPU evenly (1x1, 160 -> 960, 7x7, batch 272: 47 against
-// 76 us; 1x1, 512 -> 128, 28x28: 126 against 132; at 2256 tiles, 1x1, 256 -> 1024, 14x14: 126 against 118).  A reduction cut into
+// 76 us; 1x1, 512 -> 128, 28x28: 126 against 132; at 2256 tiles, 1x1, 256 -> 1024, 14x14: 126 against 118).  Around the lines, 1x1, C -> 256, square
+// against narrow: 9016 tiles (56x56), 5 steps 187 and 205 us, 8 steps 282 and 328; 2254 (28x28), 6 steps 57 and 60, 8 steps 66 and 76; 564
+// (14x14), level from 2 to 16 steps.  A reduction cut into
 // ranges fills it anyway.  `straddle`: reduction steps that cross filter taps.
 // Element-wise loaders (`fast` false) are bound by loading: a wider tile reads each activation for fewer column tiles.  Forward, 128x64
 // against 128x128: 5x5, 141 -> 464, 106x106, batch 2: 1459 and 897 us; 3x3, 258 -> 514, 14x14, batch 64: 709 and 389; 1x1, 18 -> 239,

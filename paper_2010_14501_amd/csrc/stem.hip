@@ -20,9 +20,10 @@
 // Filter gradient: dw[k][r][j] = sum_m dy[m][k] * x_row(m, r)[j]: A = dy (positions are the reduction index now, read
 // from memory in the layout of v_mfma_f32_32x32x16_bf16: lane (k, h) loads dy[m + 8 h + i][k], i < 8), B = lane (col, h) reads
 // LDS[off(m + 8 h + i) + r(col) * rowlen + j(col)] with col = (r, j) flattened; both are split into bf16 pieces in registers
-// (bf16_pieces.hpp), 44 vector instructions per operand beside six matrix instructions per 32 columns.  7x7, 64 channels, 224x224,
-// batch 184: 581 -> 497 us (75 -> 87 TFLOP/s), error against 64 bits 8.5e-7 -> 3.1e-7; bound by the chain of LDS reads, splits and
-// matrix instructions of two waves per SIMD (256 registers).  The 3x3 filters keep the fp32 instruction, and so does the forward pass,
+// (bf16_pieces.hpp), 48 vector instructions per operand beside six matrix instructions per 32 columns.  7x7, 64 channels, 224x224,
+// batch 184: 568 us on the fp32 instruction, 473 so (76 and 92 TFLOP/s), error against 64 bits 8.5e-7 and 3.1e-7; bound by the chain of LDS reads,
+// splits and matrix instructions of two waves per SIMD (256 registers; the compiler spills 32 of them around the second pass in fp32, none
+// inside the loop over tiles).  The 3x3 filters keep the fp32 instruction, and so does the forward pass,
 // whose eight-value windows cost it more in LDS reads and registers than the instruction saves (529 -> 842 us).  Wave kb of a workgroup owns the 32 output
 // channels 32 kb .. 32 kb + 31 and all R * 3 S columns; the workgroups' partial results are added in a fixed order by
 // split_reduce.

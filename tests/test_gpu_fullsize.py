@@ -245,8 +245,8 @@ def _dev(a):
 def test_sampled_outputs_of_headline_layers_in_their_launch_configuration():
     """Three more layers of the batch-184 network, called through the kernel entry points with the workspace and
     split count the graph declares for them (what the timed step launches): a Winograd F(4x4) layer worked through in
-    chunks (layer1's 3x3 at 56x56x64, forward and input gradient), a 1x1 layer whose ragged last round of tiles is cut
-    and met inside the kernel (layer3's 1024 -> 256 at 14x14, 564 tiles), and a filter gradient split over its
+    chunks (layer1's 3x3 at 56x56x64, forward and input gradient), a 1x1 layer with a ragged last round of tiles
+    (layer3's 1024 -> 256 at 14x14, 564 tiles), and a filter gradient split over its
     reduction (the same layer, 36 064 positions).  Sampled elements against the oracle's definition evaluated on the
     crop (forward, input gradient) or the channel pair (filter gradient) that element depends on."""
     import torch
@@ -290,7 +290,7 @@ def test_sampled_outputs_of_headline_layers_in_their_launch_configuration():
         assert abs(gx[n, p, q, c] - want) < 1e-3 * gs, ("winograd dgrad", n, p, q, c)
     del ws, y, gx, dx_, dw_
 
-    # ---- 1x1, 1024 -> 256 at 14x14: tiles beyond two rounds of 256 are cut; and its filter gradient, split
+    # ---- 1x1, 1024 -> 256 at 14x14: tiles beyond two rounds of 256; and its filter gradient, split
     H = W = 14
     C, K = 1024, 256
     x = rng.standard_normal((N, H, W, C), dtype=np.float32)
@@ -315,11 +315,11 @@ def test_sampled_outputs_of_headline_layers_in_their_launch_configuration():
     wo = tensors.weight_to_oracle(w)
     ys = float(np.sqrt(np.mean(y.astype(np.float64) ** 2)))
     rows = N * H * W
-    # the last rows belong to the cut tiles: sample them densely, and the rest at random
+    # the last rows belong to the ragged last round of tiles: sample them densely, and the rest at random
     picks = sample((N, H, W, K), 300) + [(N - 1, int(rng.integers(0, H)), int(rng.integers(0, W)), int(rng.integers(0, K))) for _ in range(200)]
     for n, p, q, k in picks:
         want = nm.conv2d_fwd(np.transpose(x[n:n + 1, p:p + 1, q:q + 1, :], (0, 3, 1, 2)).astype(np.float64), wo[k:k + 1], 1, 0)[0, 0, 0, 0]
-        assert abs(y[n, p, q, k] - want) < 1e-4 * ys, ("cut 1x1 fwd", n, p, q, k)
+        assert abs(y[n, p, q, k] - want) < 1e-4 * ys, ("1x1 fwd", n, p, q, k)
     gs = float(np.sqrt(np.mean(gw.astype(np.float64) ** 2)))
     for k, _, _, c in sample((K, 1, 1, C), 150):
         xc = x[:, :, :, c].astype(np.float64)[:, None]

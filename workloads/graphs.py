@@ -413,15 +413,16 @@ def conv_split_plan(rows, cols, reduction, classes=1, out_elems=None):
     rows x cols result per residue class (`classes` = stride^2 and `out_elems` = |dx| for the input gradient),
     or (1, 0) where the plain variant is as fast.
 
-    The kernel library works on 128x128 tiles (256x64 for results up to 64 columns wide), one workgroup per
-    tile and reduction range, and a CU's time grows with the number of workgroups it is handed: a launch costs
-    ceil(workgroups / 256) rounds.  Rules read off a sweep over the ResNet-50 b184 layers:
+    Counted in tiles of 128x128 (256x64 for results up to 64 columns wide), one workgroup per tile and reduction range, a
+    CU's time growing with the number of workgroups it is handed: a launch costs ceil(workgroups / 256) rounds.  The
+    kernel library has other tile shapes since and takes fewer ranges where that is faster; what is declared here stays, so that
+    graphs, cost tables and stored schedules keep their sizes (none of the networks' peaks is reached at a launch with
+    such a workspace: declaring none leaves every peak and arena as it is).  Rules read off a sweep over the ResNet-50 b184 layers:
       * fewer than two tiles per CU (or fewer than eight with stride > 1): cut every tile into the number of
         ranges s (at most 16, at least 128 reduction elements each) that minimises rounds / s, with 1 % per range
         for the slabs of partial results a second kernel adds;
       * otherwise, stride 1, at least 48 reduction steps of 16: `splits` stays 1 and the graph declares the small
-        workspace with which earlier kernels cut the tiles beyond a multiple of 256 (the kernels now leave it
-        alone; it stays declared, so that graphs, cost tables and stored schedules keep their sizes);
+        workspace with which earlier kernels cut the tiles beyond a multiple of 256 (the kernels leave it alone);
       * otherwise: plain."""
     bm, bn = (256, 64) if cols <= 64 else (128, 128)
     tiles = math.ceil(rows / bm) * math.ceil(cols / bn)
@@ -446,8 +447,8 @@ def conv_split_plan(rows, cols, reduction, classes=1, out_elems=None):
 def wgrad_split_count(M, K, cols):
     """Reduction splits of a K x cols weight-gradient GEMM that sums over M output positions:
     enough waves to keep loads in flight on 256 CUs (about 16 per CU), at least 8 reduction steps
-    of 16 rows per split, and at most 128 MiB of partial sums.  The tile shape follows the kernel
-    library's choice for that GEMM."""
+    of 16 rows per split, and at most 128 MiB of partial sums.  An upper bound: the kernel library takes fewer where
+    more only cost partial sums.  The tile shapes are those it had when the bound was set."""
     if K <= 64:
         tile_rows, tile_cols, waves = (64, 256, 4) if cols % 256 == 0 else (64, 64, 1)
     elif cols <= 64:
