@@ -139,9 +139,10 @@ def cmd_counters(a):
                 lines.append(f"    {'CU busy / (cycles x 256 CUs)':<32} {v['SQ_BUSY_CU_CYCLES'] / (chip * 256):.3f}")
             if "SQ_VALU_MFMA_BUSY_CYCLES" in v:
                 lines.append(f"    {'MFMA busy / (cycles x 1024 SIMDs)':<32} {v['SQ_VALU_MFMA_BUSY_CYCLES'] / (chip * 1024):.3f}")
-        if "SQ_INSTS_VALU" in v and "SQ_INSTS_VALU_MFMA_MOPS_F32" in v and v["SQ_INSTS_VALU_MFMA_MOPS_F32"] > 0:
-            # one 32x32x2 fp32 instruction = 4096 flop = 8 counted units of 512 flop; SQ_INSTS_VALU counts matrix instructions too
-            mfma = v["SQ_INSTS_VALU_MFMA_MOPS_F32"] / 8.0
+        # SQ_INSTS_VALU counts matrix instructions too.  Where SQ_INSTS_MFMA was not taken: one 32x32x2 fp32 instruction = 4096 flop = 8
+        # counted units of 512 flop
+        mfma = v.get("SQ_INSTS_MFMA", v.get("SQ_INSTS_VALU_MFMA_MOPS_F32", 0) / 8.0)
+        if "SQ_INSTS_VALU" in v and mfma > 0:
             lines.append(f"    {'other vector instr. / MFMA instr.':<32} {(v['SQ_INSTS_VALU'] - mfma) / mfma:.2f}")
         if "SQ_WAVE_CYCLES" in v and "SQ_WAIT_INST_ANY" in v and v["SQ_WAVE_CYCLES"] > 0:
             lines.append(f"    {'any wait / wave cycles':<32} {v['SQ_WAIT_INST_ANY'] / v['SQ_WAVE_CYCLES']:.3f}")
