@@ -232,6 +232,33 @@ def test_fused_neighbours_give_identical_bits():
     assert recomputed_bn > 0 and apply_launches < recomputed_bn
 
 
+def test_layers_with_a_workspace_and_one_range_cut_their_reduction_in_a_plan(monkeypatch):
+    """Convolutions that declare a workspace with splits = 1 cut a reduction of few tiles by themselves.  Statistics, BatchNorm and ReLU that ride
+    in the epilogue otherwise then follow it: the same bits with fused launches as one by one, and the loss and
+    gradients of the plan without such workspaces to rounding (block by block the tolerance of all gradients)."""
+    sched = lambda g: schedules.block_output_schedule(g, schedules.IGEMM_VARIANTS)
+    make = lambda: graphs.resnet50(batch=2, hw=32, classes=10, widths=(64, 128), depths=(2, 1), stem=16)
+    results = []
+    for plan in (lambda rows, cols, red, classes=1, out=None: (1, 0),
+                 lambda rows, cols, red, classes=1, out=None: (1, 16 * 4 * (rows * cols * classes if out is None else out))):
+        monkeypatch.setattr(graphs, "conv_split_plan", plan)
+        g = make()
+        exts, params = tensors.make_inputs(g, seed=4, gamma_beta="random")
+        run = StepRunner(g.text(), sched(g).text(), exts, params)
+        run.step()
+        fused, loss = run.grads_numpy(), run.loss_value()
+        run.plan.set_fusion(False)
+        run.step()
+        plain = run.grads_numpy()
+        assert run.loss_value() == loss and all(np.array_equal(fused[p], plain[p]) for p in fused)
+        results.append((loss, fused))
+    (loss0, grads0), (loss1, grads1) = results
+    assert any(not np.array_equal(grads0[p], grads1[p]) for p in grads0), "no reduction was cut"
+    assert abs(loss0 - loss1) < ACT_TOL * abs(loss0)
+    for p in grads0:
+        check_close(grads1[p], grads0[p], GRAD_TOL, what=p, floor=1e-2 * np.linalg.norm(grads0[max(p - 1, 0)]))
+
+
 def test_steps_of_two_plans_overlap_on_two_streams():
     """Nothing is shared between plans: two of them, each stepped again and again by a thread of its own on a stream of its own, give
     the bits of their steps taken alone.  The convolutions of both run split reductions and Winograd layers at the same time."""
