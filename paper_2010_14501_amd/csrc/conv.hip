@@ -106,8 +106,8 @@ __device__ __forceinline__ void for_each_int(F &f, std::integer_sequence<int, I.
 // 160 -> 38 us forward, 134 -> 82 us input gradient against the element-wise loaders), 4 as 1 with a single register stage, for reductions of at
 // most six steps (1x1, C -> 256, 56x56, batch 184, one stage against two: C = 32: 123 and 138 us, 64: 173 and 197, 96: 225 and 242; beyond the
 // line the gain shrinks: 112: 256 and 268, 128: 316 and 328, 192: 421 and 430, 256 level; level at every C on 14x14)
-// Registers: 128 in the eight-wave tiles (four waves per SIMD), of which the partly empty last step spills 1 - 5 and the element-wise filter
-// gradient 9; 150 - 168 in the others, where the 64x64 filter gradient spills 1.  The other kernels spill none.
+// Registers: 128 in the eight-wave tiles and for FAST 2 and 4 (four waves per SIMD), where the narrow tile's FAST 2 spills 2 forward and 5 in the
+// input gradient and the element-wise filter gradient 9; up to 168 in the others, where the 64x64 filter gradient spills 1.
 template <int MODE, int WM, int WN, int FAST, int TAG = 0>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST != 2 && FAST != 4) ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
     // Register stages of the aligned variants: loads run this many steps ahead of the split.  The tiles of at most four waves take
