@@ -107,7 +107,7 @@ __device__ __forceinline__ void for_each_int(F &f, std::integer_sequence<int, I.
 // most six steps (1x1, C -> 256, 56x56, batch 184, one stage against two: C = 32: 123 and 138 us, 64: 173 and 197, 96: 225 and 242; beyond the
 // line the gain shrinks: 112: 256 and 268, 128: 316 and 328, 192: 421 and 430, 256 level; level at every C on 14x14)
 // Registers: 128 in the eight-wave tiles and for FAST 2 and 4 (four waves per SIMD), where the narrow tile's FAST 2 spills 2 forward and 5 in the
-// input gradient and the element-wise filter gradient 9; up to 168 in the others, where the 64x64 filter gradient spills 1.
+// input gradient; up to 168 in the others, where the 64x64 filter gradient spills 1.
 template <int MODE, int WM, int WN, int FAST, int TAG = 0>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST != 2 && FAST != 4) ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
     // Register stages of the aligned variants: loads run this many steps ahead of the split.  The tiles of at most four waves take
@@ -1238,7 +1238,8 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
             else { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 0>), grid, dim3(NT), 0, st, ta); }
         } else {
             if (fast) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1>), grid, dim3(NT), 0, st, ta); }
-            else { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 0>), grid, dim3(NT), 0, st, ta); }
+            else if constexpr (WM * WN <= 4) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 0>), grid, dim3(NT), 0, st, ta); }
+            else throw KernelError("conv: element-wise filter gradients have no 128x128 tile");
         }
     }
     hip_check(hipGetLastError(), "conv launch");
@@ -1259,13 +1260,16 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // 145 -> 17, in two steps: 55 and 65, where square tiles cover a third more columns: short reductions take them up to a fifth.
 // Forward the narrow tile has a table of reduction indices for up to 256 of them: 5x5, 10 -> 192, 28x28, batch 64: 68 and 88 (a third more
 // columns); 5x5, 3 -> 96, 112x112, batch 32: 124 and 117 (as many).
+// Element-wise filter gradients take 128x64 in place of 128x128, whose 128 registers they exceed: 5x5 stride 3, 438 -> 392, 32x32, batch 38: 501
+// and 756 us; 3x3, 258 -> 514, 14x14, batch 64, ten ranges: 434 and 501; 1x1, 438 -> 391, 32x32, batch 38, 64 ranges: 251 and 287.
+// (It loses where its twice as many tiles just begin a second round: 7x7, 402 -> 304, 16x16, batch 10: 221 and 196.)
 int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool fast, bool straddle) {
     if (mode == WGRAD) {
         static const int nearest[6] = {0, 3, 4, 3, 4, 5};
-        if (g_cfg_override >= 0) return nearest[g_cfg_override];
+        if (g_cfg_override >= 0) return nearest[g_cfg_override] == 0 && !fast ? 3 : nearest[g_cfg_override];
         if (Ng <= 64) return Mg <= 64 ? 5 : 3;
         if (Mg <= 64) return (Ng + 127) / 128 * 128 <= (Ng + 63) / 64 * 64 * 9 / 8 ? 4 : 5;
-        return 0;
+        return fast ? 0 : 3;
     }
     if (straddle) return 3;      // straddling lanes carry their tap: registers the larger tile does not have
     if (g_cfg_override >= 0) return g_cfg_override == 0 ? 0 : 3;
