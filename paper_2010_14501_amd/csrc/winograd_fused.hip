@@ -22,9 +22,10 @@
 // the transformed filters from L2.  With many channels the input passes and the filter stream (36 x 64 floats per input
 // channel and workgroup) cost more than the workspace form's large GEMM tiles save; the graph offers this form where it
 // was measured to be faster.
-#include "bn_affine.hpp"
-#include "buffer_addr.hpp"
-#include "kernels.hpp"
+//
+// Reductions of at least 64 channels, in multiples of 16, run on fp16 pieces instead (winograd_pieces.hip, 1.4 - 1.9 times as fast); this kernel is
+// for the shorter and the ragged ones, where the pieces' 2^-23 would show or a chunk would not be whole.
+#include "winograd_f4.hpp"
 
 namespace monet {
 
@@ -33,45 +34,15 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int FT = 32;            // tiles per workgroup
-constexpr int FK = 64;            // output channels per workgroup
+constexpr int FT = FUSED_TILES, FK = FUSED_OUT;
 constexpr int FC = 8;             // reduction channels per chunk
-constexpr int FUSED_CUS = 256;    // one workgroup per CU (LDS)
 constexpr int VROW = FC + 1;      // row of V[z][tile][.] in LDS, padded: 32 tiles x 9 words hit 32 different banks
 constexpr int MROW = 33;          // row of M[z][tile][.] in LDS
 constexpr int LDS_FLOATS = 36 * FT * MROW;               // 152 064 bytes; the two V buffers take the first 82 944
 static_assert(2 * 36 * FT * VROW <= LDS_FLOATS, "V buffers must fit");
 
-// The one-dimensional maps of F(4, 3).  On this chip fp32 matrix instructions and ordinary vector arithmetic exclude each
-// other on a SIMD (measured: every vector instruction costs the matrix pipe about 4.7 cycles, whichever wave issues it),
-// so the transforms are written for the fewest instructions: B^T in twelve multiply-adds
-//   B^T = [4 0 -5 0 1 0; 0 -4 -4 1 1 0; 0 4 -4 -1 1 0; 0 -2 -1 2 1 0; 0 2 -1 -2 1 0; 0 4 0 -5 0 1]
-__device__ inline void f4_bt(float v0, float v1, float v2, float v3, float v4, float v5, float (&o)[6]) {
-    const float p = __builtin_fmaf(-4.0f, v2, v4), q = __builtin_fmaf(-4.0f, v1, v3);
-    const float r = v4 - v2, t = v3 - v1;
-    o[0] = __builtin_fmaf(4.0f, v0, __builtin_fmaf(-5.0f, v2, v4));
-    o[1] = p + q;
-    o[2] = p - q;
-    o[3] = __builtin_fmaf(2.0f, t, r);
-    o[4] = __builtin_fmaf(-2.0f, t, r);
-    o[5] = __builtin_fmaf(4.0f, v1, __builtin_fmaf(-5.0f, v3, v5));
-}
-__device__ inline void f4_g(float g0, float g1, float g2, float (&o)[6]) {
-    o[0] = 0.25f * g0;
-    o[1] = (-1.0f / 6.0f) * (g0 + g1 + g2);
-    o[2] = (-1.0f / 6.0f) * (g0 - g1 + g2);
-    o[3] = (1.0f / 24.0f) * g0 + (1.0f / 12.0f) * g1 + (1.0f / 6.0f) * g2;
-    o[4] = (1.0f / 24.0f) * g0 - (1.0f / 12.0f) * g1 + (1.0f / 6.0f) * g2;
-    o[5] = g2;
-}
-//   A^T = [1 1 1 1 1 0; 0 1 -1 2 -2 0; 0 1 1 4 4 0; 0 1 -1 8 -8 1]
-__device__ inline void f4_at(float m0, float m1, float m2, float m3, float m4, float m5, float (&o)[4]) {
-    const float p = m1 + m2, q = m1 - m2, r = m3 + m4, t = m3 - m4;
-    o[0] = m0 + p + r;
-    o[1] = __builtin_fmaf(2.0f, t, q);
-    o[2] = __builtin_fmaf(4.0f, r, p);
-    o[3] = __builtin_fmaf(8.0f, t, q) + m5;
-}
+// On this chip fp32 matrix instructions and ordinary vector arithmetic exclude each other on a SIMD (measured: every vector
+// instruction costs the matrix pipe about 4.7 cycles, whichever wave issues it), so the transforms are written for the fewest instructions.
 
 // Transformed filters in the order the matrix-core lanes read them:
 //   Up[z][out / 32][red / 8][lane][j],  lane = 32 * (red % 2) + out % 32,  j = (red % 8) / 2
@@ -106,19 +77,6 @@ __global__ __launch_bounds__(256) void wino4_filter_fused_kernel(const float *__
     }
 }
 
-
-struct FusedGeom {
-    int N, H, W, th, tw;
-    int64_t T;          // tiles
-    int red, outc;      // reduction / output channels
-    int nch;            // red / 8
-    int kblocks;        // ceil(outc / 64)
-    int64_t items;      // ceil(T / 32) * kblocks
-    // Items [main_items, items) are worked as two half items of 32 output channels each (the ragged last round of a launch
-    // with few items: a half item takes about 0.6 of a whole one, and twice as many CUs take part).  main_items is a
-    // multiple of 8; main_items == items: no item is halved.
-    int64_t main_items;
-};
 
 // What a patch lane knows about its (tile, channel): byte offsets of the six patch columns / rows (clamped into the map) and
 // which of them exist.  Patch element (a, b) of chunk ch sits at byte x + coff[b] + roff[a] + 32 * ch; the host checks that
@@ -337,32 +295,10 @@ __global__ __launch_bounds__(512) void wino4_fused_kernel(const float *__restric
     __shared__ unsigned tinfo[FT][2];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // the same for the whole wave: kept in a scalar register
-    // Work item: hardware deals workgroups to the 8 XCDs in turn; item = (id mod 8) * (grid / 8) + id / 8 gives each XCD a
-    // contiguous share, so that neighbouring tile rows (shared halo) and the channel blocks of one tile range (same input)
-    // meet in one L2.  The grid is a multiple of 8; items beyond the last one do nothing.
-    // Every XCD takes its share of the whole items first, then its share of the half items, so that the short ones come
-    // last everywhere.
-    const int64_t id = blockIdx.x, xcd = id & 7, idx = id >> 3;
-    const int64_t pm = gm.main_items >> 3;
-    int64_t item;
-    int nh = 2, hsel = 0;          // blocks of 32 output channels this workgroup computes; the first of them within the item
-    if (gm.main_items == gm.items) {      // no item is halved: a contiguous share of the items per XCD
-        item = xcd * ((int64_t)gridDim.x >> 3) + idx;
-        if (item >= gm.items) return;
-    } else if (idx < pm) {
-        item = xcd * pm + idx;
-    } else {
-        const int64_t nhalf = (gm.items - gm.main_items) * 2, pt = (nhalf + 7) >> 3;
-        const int64_t j = xcd * pt + (idx - pm);
-        if (idx - pm >= pt || j >= nhalf) return;
-        item = gm.main_items + (j >> 1);
-        nh = 1;
-        hsel = (int)(j & 1);
-    }
-    const int kb = (int)(item % gm.kblocks);
-    const int64_t tb = item / gm.kblocks;
-    const int ob = 2 * kb + hsel;
-    if (ob * 32 >= gm.outc) return;      // the second half of a last, half-empty channel block (uniform over the workgroup)
+    FusedItem it;
+    if (!fused_item(gm, it)) return;
+    const int64_t tb = it.tb;
+    const int ob = it.ob, nh = it.nh;
 
     floatx16 acc[5][2];
 #pragma unroll
@@ -449,26 +385,16 @@ void conv_winograd_fused(hipStream_t st, const float *in, const float *w, float 
         throw KernelError("conv_winograd_fused: needs a 3x3 / stride 1 / pad 1 layer whose reduction channels are a multiple of 8");
     if (!ws || ws_bytes < winograd_fused_workspace_bytes(cs, adjoint))
         throw KernelError("conv_winograd_fused: workspace too small for the transformed filters");
+    const BnAffine bn = affine ? *affine : BnAffine{};
+    if (winograd_pieces_applies(cs, adjoint)) {
+        conv_winograd_pieces(st, in, w, out, cs, adjoint, accumulate, ws, bn);
+        return;
+    }
     FusedGeom gm;
-    gm.N = cs.N; gm.H = cs.H; gm.W = cs.W;
-    gm.th = (cs.H + 3) / 4; gm.tw = (cs.W + 3) / 4;
-    gm.T = (int64_t)cs.N * gm.th * gm.tw;
-    gm.red = adjoint ? cs.K : cs.C;
-    gm.outc = adjoint ? cs.C : cs.K;
-    gm.nch = gm.red / FC;
-    gm.kblocks = (gm.outc + FK - 1) / FK;
-    gm.items = (gm.T + FT - 1) / FT * gm.kblocks;
-    // the ragged last round: at most half a round of whole items beyond a multiple of the CU count becomes at most one
-    // round of half items
-    gm.main_items = gm.items;
-    if (gm.items % FUSED_CUS && gm.items % FUSED_CUS <= FUSED_CUS / 2) gm.main_items = gm.items - gm.items % FUSED_CUS;      // also a launch of at most half a round
-    const int64_t grid = gm.main_items == gm.items ? (gm.items + 7) / 8 * 8 : gm.main_items + ((gm.items - gm.main_items) * 2 + 7) / 8 * 8;
-    if (gm.T < 1 || gm.T >= 0x7fffffffll || grid >= 0x7fffffffll || (int64_t)(cs.N * (int64_t)cs.H + 8) * cs.W * std::max(gm.red, gm.outc) * 4 >= ((int64_t)1 << 32) - 65536)
-        throw KernelError("conv_winograd_fused: shape out of range (input and output must have fewer than 2^32 bytes each)");
+    const int64_t grid = fused_geometry(gm, cs, adjoint, FC);
     const int out_pad = gm.kblocks * FK;
     const int64_t fe = (int64_t)out_pad * gm.red;
     const dim3 fg((unsigned)((fe + 255) / 256)), blk(256), wg(512);
-    const BnAffine bn = affine ? *affine : BnAffine{};
     const dim3 gd((unsigned)grid);
     if (adjoint) {
         hipLaunchKernelGGL(wino4_filter_fused_kernel<true>, fg, blk, 0, st, w, ws, cs.K, cs.C, out_pad);

@@ -1,0 +1,557 @@
+// Winograd F(4x4, 3x3) in one kernel, its products on the fp16 matrix cores at fp32 precision (winograd_fused.hip is the same form on
+// the fp32 instruction, for reductions that are too short or ragged for this one).
+//
+// A workgroup (sixteen waves, four per SIMD) owns 32 tiles x 64 output channels for all 36 positions z of the transformed tile.  The
+// reduction runs in chunks of 16 channels, double-buffered through LDS:
+//   * waves 12-15 load the 6x6 patch of one tile for two neighbouring channels per lane, transform it, split it into pieces and
+//     leave them in LDS in the order in which the matrix instruction's lanes read them;
+//   * waves 0-11 multiply three positions each (96 accumulators per lane);
+//   * the transformed filters come from the workspace, already in pieces and in lane order.
+//
+// Pieces.  v = h + m with h and m in fp16, each rounded to nearest: 22 bits and a sign.  Of a product the terms m*h, h*m and h*h are kept;
+// every term is exact in the matrix unit, whose sums are fp32: three roundings per 16 products instead of one per two.  Against 64
+// bits that is closer than the fp32 instruction from 64 reduction channels on (normwise, one layer of random numbers, 64 / 128 / 512 channels:
+// 1.0e-6 / 1.1e-6 / 1.7e-6, the fp32 instruction 1.1e-6 / 1.3e-6 / 2.5e-6); below, the pieces' 2^-23 shows and the fp32 form stays.
+//
+// Range.  fp16 reaches from 2^-24 to 2^16, so both operands carry powers of two: a filter one per output channel (its largest weight comes
+// to lie in [2^13, 2^14)), a tile one that its first chunk with a value other than zero sets (that patch's largest value in [2^3, 2^4): transformed
+// values are up to a hundred times as large, later chunks may be larger by some tens).  What is left of an operand below 2^-25 in that scale
+// is lost.  Two tests say whether that can show in a result: the 36 sums of a (tile, channel) are all finite (else an operand was an infinity or a
+// NaN, or grew beyond its scale), and the largest of them is at least 2^11 * sqrt(channels) (the lost parts' sum is about 2^-11 * sqrt(channels) at
+// most; random data lie near 2^19 * sqrt(channels)).  A half item that fails is worked once more on the fp32 instruction, with the filters
+// transformed from the weights on the way.
+//
+// What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512): fp32 form
+// 2187 / 206 / 174 / 1926, this one 1344 / 108 / 102 / 1089.  A chunk takes 3.2 us where its matrix instructions alone take 1.3 (measured with the
+// other parts left out, at the power limit's clock), and an item another 14 us for its first patch and its outputs.  What the chunk waits for is the vector
+// memory path: 147 KB of filters and 74 KB of patches per chunk (at 64 bytes per clock 1.7 us) and the latency of the patches, whose registers
+// are free again only when the patch before is split.  Eight waves of which four make the patches and multiply less took the same time to 2 %;
+// higher wave priority for the patches nothing.
+#include "winograd_f4.hpp"
+
+namespace monet {
+
+namespace {
+
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+
+constexpr int FT = FUSED_TILES, FK = FUSED_OUT;
+constexpr int CH = 16;                          // reduction channels per chunk
+constexpr int NZ = 3, MUL_WAVES = 12;           // positions of a wave that multiplies; four more waves make the patches
+constexpr int THREADS = 64 * (MUL_WAVES + 4);
+constexpr int V_WORDS = 36 * 2 * FT * CH / 2;   // one V buffer: [z][piece][channels 8g .. 8g+7][tile][4 words of two channels]
+constexpr int MROW = 33;                        // row of M[z][tile][.] in LDS
+constexpr int LDS_WORDS = 36 * FT * MROW;       // 152 064 bytes; the two V buffers take the first 147 456
+constexpr int WROW = CH + 1;                    // row of the fp32 form's V[z][tile][.]
+static_assert(2 * V_WORDS <= LDS_WORDS && 36 * FT * WROW <= LDS_WORDS, "V buffers must fit");
+constexpr int EMPTY = -1000;                    // scale of a tile without a value other than zero
+constexpr unsigned CHUNK_BYTES = 2048;          // one (position, 32 output channels, chunk) of the filters: two planes of 64 lanes x 16 bytes
+
+// exponent e of |v| < 2^e for the bits of a float that is not negative (subnormals count as 2^-126)
+__device__ __forceinline__ int exponent_of(float v) { return (int)(__float_as_uint(v) >> 23) - 126; }
+__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }      // -126 <= e <= 127
+__device__ __forceinline__ unsigned word_of(f16x2 v) { return __builtin_bit_cast(unsigned, v); }
+
+// (a, b) as pieces
+struct Pieces16 { f16x2 h, m; };
+__device__ __forceinline__ Pieces16 split16(float a, float b) {
+    Pieces16 p;
+    p.h = __builtin_convertvector(f2{a, b}, f16x2);
+    // the rests, exact in fp32: one instruction each that takes h as it is
+    float ra, rb;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(word_of(p.h)), "v"(a));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(word_of(p.h)), "v"(b));
+    p.m = __builtin_convertvector(f2{ra, rb}, f16x2);
+    return p;
+}
+// the larger of m, |a| and |b|
+__device__ __forceinline__ float max_abs(float m, float a, float b) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+    return m;
+}
+
+// Transformed filters in pieces:
+//   Up[z][out / 32][red / 16][piece][lane][j],  lane = 32 * (red % 16 / 8) + out % 32,  j = red % 8
+// `out` runs over the output channels padded to a multiple of 64 (zeros).  The power of two of output channel k, plus 128, lies in the lowest
+// bits of the eight m pieces of (z = 0, chunk 0, channels 0 .. 7): at most 2^-24 of a value of up to 2^14.
+// One workgroup: 32 output channels x 16 reduction channels; each finds the largest weight of its channels by itself (a few
+// microseconds; a launch of its own would cost as much, and the workspace has no room for its result).
+// ADJ: forward pass (out = K, red = C) or input gradient (out = C, red = K, filter turned by 180 degrees).
+template <bool ADJ>
+__global__ __launch_bounds__(512) void wino4_filter_pieces_kernel(const float *__restrict__ w, unsigned short *__restrict__ Up, int K, int C, int o32) {
+    __shared__ float part[16][32];
+    __shared__ int scale[32];
+    const int outc = ADJ ? C : K, red = ADJ ? K : C, nch = red / CH;
+    const int ob = blockIdx.x / nch, ch = blockIdx.x - ob * nch, tid = threadIdx.x;
+    const int len = 9 * red;      // weights of one output channel
+    {
+        // forward: a row of w; 16 lanes share it.  Input gradient: a column of w seen as [9 * red][C]; 32 lanes read neighbouring columns.
+        const int o = ob * 32 + (ADJ ? tid & 31 : tid >> 4), sub = ADJ ? tid >> 5 : tid & 15;
+        float mx = 0.0f;
+        if (o < outc) {
+            const float *p = ADJ ? w + o : w + (int64_t)o * len;
+            const int64_t step = ADJ ? C : 1;
+#pragma unroll 12
+            for (int i = sub; i < len; i += 16) mx = fmaxf(mx, fabsf(p[i * step]));
+        }
+        part[sub][ADJ ? tid & 31 : tid >> 4] = mx;
+    }
+    __syncthreads();
+    if (tid < 32) {
+        float mx = 0.0f;
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, part[i][tid]);
+        scale[tid] = mx > 0.0f ? min(14 - exponent_of(mx), 126) : 0;
+    }
+    __syncthreads();
+    const int ol = tid >> 4, o = ob * 32 + ol, c = ch * CH + (tid & 15);
+    float g[3][3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            g[r][s] = o >= outc ? 0.0f : (ADJ ? w[((int64_t)c * 9 + (2 - r) * 3 + (2 - s)) * C + o] : w[((int64_t)o * 9 + r * 3 + s) * C + c]);
+    float t[3][6];      // t[s][a] = (G g)[a][s]
+#pragma unroll
+    for (int s = 0; s < 3; ++s) f4_g(g[0][s], g[1][s], g[2][s], t[s]);
+    const float sc = power_of_two(scale[ol]);
+    const unsigned code = (unsigned)(scale[ol] + 128) >> (c & 7);
+    const int lane = 32 * ((c & 15) >> 3) + ol;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        float u[6];
+        f4_g(t[0][a], t[1][a], t[2][a], u);
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            const int z = 6 * a + b;
+            const Pieces16 p = split16(u[b] * sc, 0.0f);
+            unsigned short m = (unsigned short)word_of(p.m);
+            if (z == 0 && c < 8) m = (unsigned short)((m & ~1u) | (code & 1u));
+            unsigned short *at = Up + ((((int64_t)z * o32 + ob) * nch + ch) * 2 * 64 + lane) * 8 + (c & 7);
+            at[0] = (unsigned short)word_of(p.h);
+            at[64 * 8] = m;
+        }
+    }
+}
+
+// Byte offsets of the six patch columns and rows of one (tile, channel): element (a, b) of chunk ch sits at x + col[b] + row[a] + 64 * ch.  A
+// column or row outside the map, and every one of a tile that does not exist, is ABSENT: added without wrapping, that is
+// beyond the descriptor of any tensor, and the load reads zero.
+constexpr unsigned ABSENT = BUFFER_ABSENT;
+struct Patch { unsigned col[6], row[6]; };
+__device__ __forceinline__ unsigned patch_at(const Patch &p, int a, int b) { return __builtin_elementwise_add_sat(p.col[b], p.row[a]); }
+
+// tinfo[tile] = {byte offset of output element (image, 4 * ti, 4 * tj, channel 0), rows | columns << 8 of the 4x4 output tile
+// that lie inside the map (0 for a tile beyond the last one), scale}
+struct TileInfo { unsigned off, extent; int scale; };
+
+__device__ __forceinline__ Patch patch_of(const FusedGeom &gm, int64_t tb, int pt, int channel, TileInfo *info) {
+    Patch p;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) p.col[a] = p.row[a] = ABSENT;
+    const unsigned t = (unsigned)(tb * FT) + pt;      // the host checks that there are fewer than 2^31 tiles
+    unsigned off = 0, extent = 0;
+    if (t < (unsigned)gm.T) {
+        const unsigned tj = t % (unsigned)gm.tw, r = t / (unsigned)gm.tw;
+        const unsigned ti = r % (unsigned)gm.th, n = r / (unsigned)gm.th;
+        const int h0 = 4 * (int)ti - 1, w0 = 4 * (int)tj - 1;
+        const int64_t e = ((int64_t)n * gm.H * gm.W) * gm.red + channel;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            if ((unsigned)(h0 + a) < (unsigned)gm.H) p.row[a] = (unsigned)((int64_t)(h0 + a) * gm.W * gm.red * 4);
+            if ((unsigned)(w0 + a) < (unsigned)gm.W) p.col[a] = (unsigned)((e + (int64_t)(w0 + a) * gm.red) * 4);
+        }
+        off = (unsigned)((((int64_t)n * gm.H + 4 * ti) * gm.W + 4 * tj) * gm.outc * 4);
+        extent = (unsigned)min(4, gm.H - 4 * (int)ti) | ((unsigned)min(4, gm.W - 4 * (int)tj) << 8);
+    }
+    if (info) {
+        info->off = off;
+        info->extent = extent;
+    }
+    return p;
+}
+
+// Word of a V buffer, within a position and piece, that starts the eight channels 8 * half .. of a tile.  The tiles of the second half are exchanged in
+// fours, so that the eight lanes that write a tile's 16 channels meet in no bank.
+__device__ __forceinline__ int v_word(int tile, int half) { return half * (4 * FT) + (tile ^ (half << 2)) * 4; }
+
+struct Ops {      // what a workgroup reads
+    __amdgpu_buffer_rsrc_t x, u;
+    int nch, o32, ob;
+};
+
+// The reduction loop of a wave that makes the patches of eight tiles: a chunk's patch is transformed, split and left in LDS while the other waves
+// multiply the chunk before.  Returns the scale of the lane's tile.
+__device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, int lane, int pt, const Patch &patch) {
+    f2 d[36];
+    int scale = EMPTY;
+    float factor = 1.0f;
+    auto load_row = [&](const Patch &p, int a, int ch) {
+#pragma unroll
+        for (int b = 0; b < 6; ++b)
+            d[a * 6 + b] = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(op.x, (int)patch_at(p, a, b), ch * (CH * 4), 0));
+    };
+    // Transforms the patch of both channels in place, columns first, and leaves its pieces in V.  A row's registers take the patch of chunk `ch` as
+    // soon as its pieces are out: what a load waits for memory passes under the other rows.
+    auto transform_store = [&](unsigned *V, int ch) {
+        auto map_row = [&](int i) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                float o[6];
+                f4_bt(d[i][e], d[i + 1][e], d[i + 2][e], d[i + 3][e], d[i + 4][e], d[i + 5][e], o);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) d[i + k][e] = o[k];
+            }
+        };
+        if (__any(scale == EMPTY)) {      // uniform over the wave: the first chunk, and tiles that were zero so far
+            float mx = 0.0f;              // the two maps make it a hundred times as large at most
+            asm volatile("" : "+v"(mx));      // behind the branch: the compiler would compute the maximum for every chunk
+#pragma unroll
+            for (int i = 0; i < 36; ++i) mx = max_abs(mx, d[i].x, d[i].y);
+            mx = fmaxf(mx, __shfl_xor(mx, 1));      // the eight lanes of a tile
+            mx = fmaxf(mx, __shfl_xor(mx, 2));
+            mx = fmaxf(mx, __shfl_xor(mx, 4));
+            if (scale == EMPTY && mx > 0.0f) {
+                scale = min(4 - exponent_of(mx), 124);
+                factor = power_of_two(scale);
+            }
+        }
+        // columns, and the power of two with them: f4_bt with its coefficients times `factor` and three products more
+        const float s4 = 4.0f * factor, s5 = -5.0f * factor;
+#pragma unroll
+        for (int b = 0; b < 6; ++b)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const float v0 = d[b][e], v1 = d[6 + b][e], v2 = d[12 + b][e], v3 = d[18 + b][e];
+                const float f3 = factor * v3, f4 = factor * d[24 + b][e], f5 = factor * d[30 + b][e];
+                const float p = __builtin_fmaf(-s4, v2, f4), q = __builtin_fmaf(-s4, v1, f3), r = __builtin_fmaf(-factor, v2, f4), t = __builtin_fmaf(-factor, v1, f3);
+                d[b][e] = __builtin_fmaf(s4, v0, __builtin_fmaf(s5, v2, f4));
+                d[6 + b][e] = p + q;
+                d[12 + b][e] = p - q;
+                d[18 + b][e] = __builtin_fmaf(2.0f, t, r);
+                d[24 + b][e] = __builtin_fmaf(-2.0f, t, r);
+                d[30 + b][e] = __builtin_fmaf(s4, v1, __builtin_fmaf(s5, v3, f5));
+            }
+        unsigned *at = V + v_word(pt, (lane & 7) >> 2) + (lane & 3);
+        Patch p = patch;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) asm volatile("" : "+v"(p.row[a]));      // the 36 sums are made here: kept from chunk to chunk they would be spilled
+        map_row(0);
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            if (a < 5) map_row(6 * a + 6);
+#pragma unroll
+            for (int z = 6 * a; z < 6 * a + 6; ++z) {
+                const Pieces16 q = split16(d[z].x, d[z].y);
+                at[z * (16 * FT)] = word_of(q.h);
+                at[z * (16 * FT) + 8 * FT] = word_of(q.m);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_row(p, a, ch);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+#pragma unroll
+    for (int a = 0; a < 6; ++a) load_row(patch, a, 0);
+    transform_store(lds, op.nch > 1 ? 1 : 0);
+    __syncthreads();
+    for (int ch = 0; ch < op.nch; ++ch) {
+        // V[next] was last read before the barrier that ended chunk ch - 1
+        if (ch + 1 < op.nch) transform_store(lds + ((ch + 1) & 1) * V_WORDS, ch + 2 < op.nch ? ch + 2 : ch + 1);
+        __syncthreads();
+    }
+    return scale;
+}
+
+// The reduction loop of a wave that multiplies: NZ positions from z0 on.  HALF: only the block of 32 output channels ob (acc[.][0]), else
+// ob and ob + 1.
+template <bool HALF>
+__device__ __forceinline__ void multiply(const Ops &op, const unsigned *lds, int z0, int lane, floatx16 (&acc)[NZ][2]) {
+    const int nch = op.nch;
+#pragma unroll
+    for (int zi = 0; zi < NZ; ++zi)
+#pragma unroll
+        for (int h = 0; h < (HALF ? 1 : 2); ++h)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[zi][h][i] = 0.0f;
+    // Filters of one position and one block of 32 output channels at a time, RING of them ahead, each into the registers its predecessor has just left.
+    constexpr int BLOCKS = HALF ? 1 : 2, UNITS = NZ * BLOCKS, RING = HALF ? 3 : 2;
+    static_assert(UNITS % RING == 0, "a unit keeps its registers from chunk to chunk");
+    struct Piece { f16x8 h, m; };
+    Piece bq[RING];
+    const unsigned lane16 = (unsigned)lane * 16u;
+    const unsigned hbytes = (unsigned)nch * CHUNK_BYTES, zbytes = (unsigned)op.o32 * hbytes;      // the host checks the workspace's size
+    const unsigned ubase = (unsigned)z0 * zbytes + (unsigned)op.ob * hbytes;
+    auto load_b = [&](int u, int ch) {
+        const unsigned so = ubase + (u / BLOCKS) * zbytes + (u % BLOCKS) * hbytes + (unsigned)ch * CHUNK_BYTES;
+        bq[u % RING].h = __builtin_bit_cast(f16x8, buffer_load4(op.u, lane16, so));
+        bq[u % RING].m = __builtin_bit_cast(f16x8, buffer_load4(op.u, lane16 + 1024u, so));
+    };
+    auto load_a = [&](const unsigned *V, int zi) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const unsigned *at = V + (z0 + zi) * (16 * FT) + v_word(lane & 31, lane >> 5);
+        return Piece{__builtin_bit_cast(f16x8, *(const u4 *)at), __builtin_bit_cast(f16x8, *(const u4 *)(at + 8 * FT))};
+    };
+#pragma unroll
+    for (int u = 0; u < RING; ++u) load_b(u, 0);
+    __syncthreads();
+    for (int ch = 0; ch < nch; ++ch) {
+        const unsigned *V = lds + (ch & 1) * V_WORDS;
+        const int nx = ch + 1 < nch ? ch + 1 : ch;      // the last chunk requests filters that exist (its own) instead of branching; nothing reads them
+#pragma unroll
+        for (int zi = 0; zi < NZ; ++zi) {
+            const Piece a = load_a(V, zi);
+#pragma unroll
+            for (int h = 0; h < BLOCKS; ++h) {
+                const int u = zi * BLOCKS + h;
+                const Piece &f = bq[u % RING];
+                acc[zi][h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.m, f.h, acc[zi][h], 0, 0, 0);
+                acc[zi][h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, f.m, acc[zi][h], 0, 0, 0);
+                acc[zi][h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, f.h, acc[zi][h], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (u + RING < UNITS) load_b(u + RING, ch);
+                else load_b(u + RING - UNITS, nx);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();      // V[next] complete; every wave is done reading V[cur]
+    }
+}
+
+// Transformed filter at position (a, b) of the 6x6 tile: one value of G g G^T
+template <bool ADJ>
+__device__ __forceinline__ float filter_at(const float *w, int K, int C, int o, int c, const float (&ga)[3], const float (&gb)[3]) {
+    if (o >= (ADJ ? C : K)) return 0.0f;
+    float u = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        float t = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            t = __builtin_fmaf(ga[r], ADJ ? w[((int64_t)c * 9 + (2 - r) * 3 + (2 - s)) * C + o] : w[((int64_t)o * 9 + r * 3 + s) * C + c], t);
+        u = __builtin_fmaf(gb[s], t, u);
+    }
+    return u;
+}
+
+// ADJ: input gradient.  EPI: 0 plain store, 1 added to what is there, 2 followed by the BatchNorm multiply-add.
+template <bool ADJ, int EPI>
+__global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__restrict__ x, const float *__restrict__ Up, const float *__restrict__ w, float *y,
+                                                           FusedGeom gm, BnAffine bn) {
+    __shared__ __attribute__((aligned(16))) unsigned lds[LDS_WORDS];
+    __shared__ TileInfo tinfo[FT];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // the same for the whole wave: kept in a scalar register
+    FusedItem it;
+    if (!fused_item(gm, it)) return;
+    const unsigned in_bytes = (unsigned)((int64_t)gm.N * gm.H * gm.W * gm.red * 4), out_bytes = (unsigned)((int64_t)gm.N * gm.H * gm.W * gm.outc * 4);
+    const Ops op{buffer_of(x, in_bytes), buffer_of(Up), gm.nch, gm.kblocks * 2, it.ob};
+
+    floatx16 acc[NZ][2];
+    const bool makes = wave >= MUL_WAVES;
+    const int z0 = NZ * wave;
+    if (!makes) {
+        if (it.nh == 2) multiply<false>(op, lds, z0, lane, acc);
+        else multiply<true>(op, lds, z0, lane, acc);
+    } else {
+        // lane = 8 * (tile % 8) + channel / 2: eight neighbouring lanes read 64 bytes
+        const int pt = (wave - MUL_WAVES) * 8 + (lane >> 3);
+        const bool first = (lane & 7) == 0;
+        const Patch patch = patch_of(gm, it.tb, pt, 2 * (lane & 7), first ? &tinfo[pt] : nullptr);
+        const int scale = make_patches(op, lds, lane, pt, patch);
+        if (first) tinfo[pt].scale = scale;      // read behind the first barrier below
+    }
+
+    // ---- output transform, 32 channels at a time: thread = (channel ok_ of the half, tile tl).  Output element
+    // (a, b) of a tile sits at byte y + [(a * W + b) * outc * 4] + the thread's own 32-bit offset (tile + channel).
+    const int ok_ = tid & 31, tl = tid >> 5;
+    const unsigned obytes = (unsigned)gm.outc * 4, orow = (unsigned)gm.W * obytes;
+    const __amdgpu_buffer_rsrc_t ry = buffer_of(y, out_bytes);
+    const bool two = EPI == 2 && bn.relu && bn.relu_out != nullptr;           // ReLU output beside the BatchNorm's
+    const __amdgpu_buffer_rsrc_t ry2 = buffer_of(two ? bn.relu_out : y, out_bytes);
+    float *M = (float *)lds;
+
+    auto stage = [&](auto half) {
+#pragma unroll
+        for (int zi = 0; zi < NZ; ++zi)
+            if (!makes) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) M[((z0 + zi) * FT + 8 * (i >> 2) + 4 * g + (i & 3)) * MROW + l32] = acc[zi][decltype(half)::value][i];
+            }
+    };
+    // the 16 outputs of (tile tl, channel ok_) before their scale, and the largest of the 36 sums
+    auto outputs = [&](float (&o)[4][4]) {
+        const float *mp = M + tl * MROW + ok_;
+        float s[6][4], mx = 0.0f;      // s[b][a] = (A^T m)[a][b]
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            float m[6];
+#pragma unroll
+            for (int a = 0; a < 6; ++a) m[a] = mp[(6 * a + b) * (FT * MROW)];
+#pragma unroll
+            for (int a = 0; a < 6; a += 2) mx = max_abs(mx, m[a], m[a + 1]);
+            f4_at(m[0], m[1], m[2], m[3], m[4], m[5], s[b]);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) f4_at(s[0][a], s[1][a], s[2][a], s[3][a], s[4][a], s[5][a], o[a]);
+        return mx;
+    };
+    auto emit = [&](int kout, const float (&o)[4][4], int scale, float bn_a, float bn_b) {
+        const unsigned extent = kout < gm.outc ? tinfo[tl].extent : 0u, voff = tinfo[tl].off + (unsigned)kout * 4u;
+        const int nr = (int)(extent & 0xff), nc = (int)(extent >> 8);
+        unsigned *mask32 = EPI == 2 && bn.relu ? (unsigned *)bn.mask : nullptr;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const unsigned so = a * orow + b * obytes;
+                const bool here = a < nr && b < nc;
+                const unsigned at = here ? voff : ABSENT;      // beyond the descriptor: loads zero, stores nothing
+                float v = __builtin_ldexpf(o[a][b], -scale);
+                if (EPI == 1) v += buffer_load(ry, at, so);
+                if (EPI == 2) v = bn_affine(v, bn_a, bn_b);
+                if (EPI == 2 && mask32) {      // uniform over the wave
+                    // the sign code of the ReLU: the 32 lanes of a half wave hold 32 consecutive channels of one position, half
+                    // a word of the code; its first lane writes it
+                    const bool pass = here && (bn.relu == 2 ? (v > 0.0f && v < 6.0f) : v > 0.0f);
+                    const unsigned long long word = __ballot(pass);
+                    const unsigned half = lane < 32 ? (unsigned)word : (unsigned)(word >> 32);
+                    if ((lane & 31) == 0 && here) mask32[(voff + so) >> 7] = half;
+                }
+                if (EPI == 2 && bn.relu) {
+                    const float rv = relu_clamp(v, bn.relu);
+                    if (two) buffer_store(ry2, at, so, rv);
+                    else v = rv;
+                }
+                buffer_store(ry, at, so, v);
+            }
+        }
+    };
+    auto coefficients = [&](int kout, float &a, float &b) {
+        a = 1.0f;
+        b = 0.0f;
+        if (EPI == 2 && kout < gm.outc) bn_affine_coeffs(bn.gamma, bn.beta, bn.stats, gm.outc, kout, a, b);
+    };
+
+    const float enough = 2048.0f * sqrtf((float)gm.red);
+    unsigned again = 0;      // halves whose pieces do not hold their numbers
+    auto finish = [&](auto half) {
+        constexpr int h = decltype(half)::value;
+        if (h >= it.nh || (it.ob + h) * 32 >= gm.outc) return;      // uniform over the workgroup
+        stage(half);
+        // the power of two of this thread's filter
+        const int kout = (it.ob + h) * 32 + ok_;
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const u4 low = __builtin_bit_cast(u4, buffer_load4(op.u, (unsigned)ok_ * 16u + 1024u, (unsigned)(it.ob + h) * gm.nch * CHUNK_BYTES));
+        int fscale = -128;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fscale += (int)(((low[i] & 1u) << (2 * i)) | (((low[i] >> 16) & 1u) << (2 * i + 1)));
+        float bn_a, bn_b;
+        coefficients(kout, bn_a, bn_b);
+        __syncthreads();
+        float o[4][4], sum = 0.0f;
+        const float mx = outputs(o);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) sum += (o[a][0] + o[a][1]) + (o[a][2] + o[a][3]);
+        const int scale = tinfo[tl].scale;
+        const bool exists = kout < gm.outc && tinfo[tl].extent;
+        const bool bad = exists && (!(fabsf(sum) < __builtin_inff()) || (scale != EMPTY && mx < enough));
+        if (__syncthreads_or(bad)) again |= 1u << h;      // the barrier also: everyone has read this half
+        else emit(kout, o, (scale == EMPTY ? 0 : scale) + fscale, bn_a, bn_b);
+    };
+    finish(std::integral_constant<int, 0>{});
+    finish(std::integral_constant<int, 1>{});
+    if (!again) return;
+
+    // ---- on the fp32 instruction, one half at a time and nothing overlapped: such tiles are rare
+    static constexpr float G[6][3] = {{0.25f, 0, 0}, {-1.0f / 6, -1.0f / 6, -1.0f / 6}, {-1.0f / 6, 1.0f / 6, -1.0f / 6},
+                                      {1.0f / 24, 1.0f / 12, 1.0f / 6}, {1.0f / 24, -1.0f / 12, 1.0f / 6}, {0, 0, 1}};
+    const int wt = (tid >> 4) & (FT - 1), wc = tid & 15;      // the first half of the threads makes the patch of one (tile, channel) each
+    const Patch patch = patch_of(gm, it.tb, wt, wc, nullptr);
+    for (int h = 0; h < 2; ++h) {
+        if (!((again >> h) & 1u)) continue;
+        const int ob = it.ob + h;
+#pragma unroll
+        for (int zi = 0; zi < NZ; ++zi)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[zi][0][i] = 0.0f;
+        for (int ch = 0; ch < gm.nch; ++ch) {
+            __syncthreads();      // the products of the chunk before, or the outputs of the half before, have been read
+            if (tid < FT * CH) {
+                float d[36];
+#pragma unroll
+                for (int a = 0; a < 6; ++a)
+#pragma unroll
+                    for (int b = 0; b < 6; ++b) d[a * 6 + b] = buffer_load(op.x, patch_at(patch, a, b), ch * (CH * 4));
+                float m[6][6];      // m[b][a] = (B^T d)[a][b]
+#pragma unroll
+                for (int b = 0; b < 6; ++b) f4_bt(d[b], d[6 + b], d[12 + b], d[18 + b], d[24 + b], d[30 + b], m[b]);
+#pragma unroll
+                for (int a = 0; a < 6; ++a) {
+                    float o[6];
+                    f4_bt(m[0][a], m[1][a], m[2][a], m[3][a], m[4][a], m[5][a], o);
+#pragma unroll
+                    for (int b = 0; b < 6; ++b) M[((6 * a + b) * FT + wt) * WROW + wc] = o[b];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int zi = 0; zi < NZ; ++zi) {
+                if (makes) continue;
+                const int z = z0 + zi;
+                float ga[3], gb[3];
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    ga[r] = G[z / 6][r];
+                    gb[r] = G[z % 6][r];
+                }
+#pragma unroll 2
+                for (int j = 0; j < CH / 2; ++j) {
+                    const float u = filter_at<ADJ>(w, ADJ ? gm.red : gm.outc, ADJ ? gm.outc : gm.red, ob * 32 + l32, ch * CH + 2 * j + g, ga, gb);
+                    acc[zi][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(M[(z * FT + l32) * WROW + 2 * j + g], u, acc[zi][0], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();
+        stage(std::integral_constant<int, 0>{});
+        __syncthreads();
+        const int kout = ob * 32 + ok_;
+        float bn_a, bn_b;
+        coefficients(kout, bn_a, bn_b);
+        float o[4][4];
+        outputs(o);
+        emit(kout, o, 0, bn_a, bn_b);
+    }
+}
+
+}  // namespace
+
+bool winograd_pieces_applies(const ConvShape &cs, bool adjoint) {
+    const int red = adjoint ? cs.K : cs.C, out = adjoint ? cs.C : cs.K;
+    return red % CH == 0 && red >= 64 && (int64_t)36 * ((out + FK - 1) / FK * FK) * red * 4 < ((int64_t)1 << 32);
+}
+
+void conv_winograd_pieces(hipStream_t st, const float *in, const float *w, float *out, const ConvShape &cs, bool adjoint, bool accumulate, float *ws,
+                          const BnAffine &bn) {
+    FusedGeom gm;
+    const int64_t grid = fused_geometry(gm, cs, adjoint, CH);
+    const int o32 = gm.kblocks * 2;
+    const dim3 fg((unsigned)(o32 * gm.nch)), fwg(512), wg(THREADS), gd((unsigned)grid);
+    if (adjoint) {
+        hipLaunchKernelGGL(wino4_filter_pieces_kernel<true>, fg, fwg, 0, st, w, (unsigned short *)ws, cs.K, cs.C, o32);
+        if (accumulate) hipLaunchKernelGGL((wino4_pieces_kernel<true, 1>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
+        else hipLaunchKernelGGL((wino4_pieces_kernel<true, 0>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
+    } else {
+        hipLaunchKernelGGL(wino4_filter_pieces_kernel<false>, fg, fwg, 0, st, w, (unsigned short *)ws, cs.K, cs.C, o32);
+        if (bn.gamma) hipLaunchKernelGGL((wino4_pieces_kernel<false, 2>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
+        else if (accumulate) hipLaunchKernelGGL((wino4_pieces_kernel<false, 1>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
+        else hipLaunchKernelGGL((wino4_pieces_kernel<false, 0>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
+    }
+    hip_check(hipGetLastError(), "winograd pieces launch");
+}
+
+}  // namespace monet

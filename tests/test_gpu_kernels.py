@@ -718,6 +718,123 @@ def test_fused_winograd_convolution_matches_oracle(case):
             monet.call("monet_conv_winograd_fused", None, ddy.data_ptr(), dwt.data_ptr(), dx.data_ptr(), N, H, W, C, K, 1, 0, ws.data_ptr(), need)
 
 
+# one-kernel Winograd form on fp16 pieces: reductions of 64 channels and more, in chunks of 16
+PIECES_CASES = [
+    # N, H, W, C, K
+    (1, 4, 4, 64, 64),          # one tile, the shortest reduction, square for both directions
+    (3, 9, 10, 80, 64),         # ragged tiles, five chunks; one block of tiles and a part of a second
+    (2, 13, 17, 64, 96),        # half-empty second channel block forward; two blocks of outputs in the input gradient
+    (1, 5, 30, 112, 72),        # odd chunk count; 72 reduction channels in the input gradient keep the fp32 form
+    (11, 28, 28, 64, 64),       # 17 whole blocks of tiles
+]
+
+
+def winograd_one_kernel(torch, src, w, out, dims, adjoint, accumulate=0):
+    need = monet.call("monet_conv_winograd_fused_workspace_bytes", *dims, adjoint)
+    ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    monet.call("monet_conv_winograd_fused", None, src.data_ptr(), w.data_ptr(), out.data_ptr(), *dims, adjoint, accumulate, ws.data_ptr(), need)
+    return out
+
+
+def winograd64(x, w):
+    """3x3 / stride 1 / pad 1 in 64 bits; x: N,H,W,C, w: K,3,3,C."""
+    n, h, wd, _ = x.shape
+    xp = np.pad(x.astype(np.float64), ((0, 0), (1, 1), (1, 1), (0, 0)))
+    return sum(xp[:, r:r + h, s:s + wd, :] @ w[:, r, s, :].astype(np.float64).T for r in range(3) for s in range(3))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", PIECES_CASES)
+def test_winograd_on_pieces_matches_64_bits(case):
+    """Forward pass and input gradient (written, accumulated).  F(4x4, 3x3) in fp32 is within 4e-6 of 64 bits for up to 512 channels (measured
+    1.3e-6 .. 3.5e-6); the pieces have fewer roundings, so 4e-6 bounds both."""
+    torch = torch_mod()
+    N, H, W, C, K = case
+    rng = np.random.default_rng(5)
+    x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, H, W, K), dtype=np.float32)
+    w = rng.standard_normal((K, 3, 3, C), dtype=np.float32) * np.float32(np.sqrt(2.0 / (9 * C)))
+    turned = np.ascontiguousarray(w[:, ::-1, ::-1, :].transpose(3, 1, 2, 0))
+    for src, filt, out_c, adjoint in ((x, w, K, 0), (dy, turned, C, 1)):
+        want = winograd64(src, filt)
+        out = torch.full((N, H, W, out_c), float("nan"), dtype=torch.float32, device="cuda")
+        got = winograd_one_kernel(torch, dev(src), dev(w), out, case, adjoint).cpu().numpy()
+        assert np.linalg.norm(got - want) < 4e-6 * np.linalg.norm(want)
+        twice = winograd_one_kernel(torch, dev(src), dev(w), out, case, adjoint, 1).cpu().numpy()
+        assert np.linalg.norm(twice - 2 * want) < 8e-6 * np.linalg.norm(want)
+
+
+def pieces_operands(kind):
+    rng = np.random.default_rng(11)
+    N, H, W, C, K = 4, 9, 10, 64, 40
+    x = rng.standard_normal((N, H, W, C), dtype=np.float32)
+    w = rng.standard_normal((K, 3, 3, C), dtype=np.float32) * np.float32(0.05)
+    per_c = np.ldexp(np.float32(1), rng.integers(-24, 25, C)).astype(np.float32)
+    if kind == "tiny": x *= np.float32(1e-33)
+    if kind == "huge": x *= np.float32(1e33)
+    if kind == "tiny filters": w *= np.float32(1e-34)
+    if kind == "both small": x *= np.float32(1e-18); w *= np.float32(1e-17)
+    if kind == "images apart": x *= np.array([1e-25, 1, 1e25, 1e-3], np.float32)[:, None, None, None]
+    if kind == "filters apart": w *= np.ldexp(np.float32(1), rng.integers(-80, 60, K)).astype(np.float32)[:, None, None, None]
+    if kind == "zero chunk first": x[..., :32] = 0
+    if kind == "growing chunks": x *= np.repeat(np.array([1e-9, 1e-3, 1, 1e6], np.float32), 16)
+    if kind == "channels apart, filters against": x *= per_c; w /= per_c
+    if kind == "zero image": x[1] = 0
+    if kind == "zero filters": w[3:9] = 0
+    if kind == "sparse": x *= rng.random(x.shape) < 0.002
+    return x, w
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["plain", "tiny", "huge", "tiny filters", "both small", "images apart", "filters apart", "zero chunk first", "growing chunks",
+                                  "channels apart, filters against", "zero image", "zero filters", "sparse"])
+def test_winograd_on_pieces_keeps_the_range_of_fp32(kind):
+    """Scales that fp16 pieces cannot hold: every image and every output channel is as close to 64 bits as the fp32 form, whose error
+    is relative to the products' sizes: 4e-6 of |x| * |w| for each (image, channel), plus fp32's smallest number per output."""
+    torch = torch_mod()
+    x, w = pieces_operands(kind)
+    N, H, W, C = x.shape
+    K = w.shape[0]
+    want = winograd64(x, w)
+    size = winograd64(np.abs(x), np.abs(w))
+    out = torch.full((N, H, W, K), float("nan"), dtype=torch.float32, device="cuda")
+    got = winograd_one_kernel(torch, dev(x), dev(w), out, (N, H, W, C, K), 0).cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    err = np.linalg.norm((got - want).reshape(N, H * W, K), axis=1)
+    bound = 4e-6 * np.linalg.norm(size.reshape(N, H * W, K), axis=1) + 1e-44 * H * W
+    assert (err <= bound).all(), (err / bound).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.0e38])
+def test_winograd_on_pieces_with_values_beyond_the_pieces(value):
+    """An infinity or a NaN stays within the 4x4 tiles whose patch holds it; a value near the largest float gives finite results where the fp32
+    form's are finite.  The epilogue with BatchNorm and ReLU runs behind the second pass as behind the first."""
+    torch = torch_mod()
+    x, w = pieces_operands("plain")
+    N, H, W, C = x.shape
+    K = w.shape[0]
+    if value > 1e38 and np.isfinite(value): w = w * np.float32(1e-3)
+    x[2, 4, 5, 40] = value
+    out = torch.full((N, H, W, K), float("nan"), dtype=torch.float32, device="cuda")
+    got = winograd_one_kernel(torch, dev(x), dev(w), out, (N, H, W, C, K), 0).cpu().numpy()
+    clean = np.ones((N, H, W), bool)
+    clean[2, 4:8, 4:8] = False      # tile rows and columns 4 .. 7 hold pixel (4, 5); its patch reaches one further on each side:
+    clean[2, 0:4, 4:8] = False      # row 4 is the last row of the patches of tile rows 0 .. 3
+    x[2, 4, 5, 40] = 0
+    want = winograd64(x, w)
+    assert np.linalg.norm(got[clean] - want[clean]) < 4e-6 * np.linalg.norm(want[clean])
+    if not np.isfinite(value): assert not np.isfinite(got[2, 4, 5]).any()
+    need = monet.call("monet_conv_winograd_fused_workspace_bytes", N, H, W, C, K, 0)
+    ws = torch.empty(need // 4, dtype=torch.float32, device="cuda")
+    gamma, beta, stats = (dev(v.astype(np.float32)) for v in (np.linspace(0.5, 1.5, K), np.linspace(-0.1, 0.1, K), np.linspace(0.5, 1.0, 2 * K)))
+    x[2, 4, 5, 40] = value
+    fused, xd, wd = torch.empty((N, H, W, K), dtype=torch.float32, device="cuda"), dev(x), dev(w)
+    monet.call("monet_conv_fwd_bn_apply", None, xd.data_ptr(), wd.data_ptr(), fused.data_ptr(), N, H, W, C, K, 3, 3, 1, 1, 5, ws.data_ptr(), need,
+               gamma.data_ptr(), beta.data_ptr(), stats.data_ptr())
+    monet.call("monet_bn_apply", None, out.data_ptr(), out.data_ptr(), gamma.data_ptr(), beta.data_ptr(), stats.data_ptr(), N * H * W, K)
+    assert torch.equal(torch.nan_to_num(fused), torch.nan_to_num(out))
+
+
 IM2COL_CASES = [
     # N, H, W, C, K, R, stride, pad, chunk images (0: the recommended workspace)
     (2, 16, 16, 16, 16, 3, 1, 1, 0),
