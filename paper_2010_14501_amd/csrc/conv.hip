@@ -97,6 +97,188 @@ __device__ __forceinline__ void for_each_int(F &f, std::integer_sequence<int, I.
     (f(std::integral_constant<int, I>{}), ...);
 }
 
+// Where a wave's 64 x 32 results go: first row and column, the launch's (or residue class's) rows, the class's map and place (input gradient), the
+// whole result or a slab.
+struct TilePlace {
+    int64_t row, rows;
+    int col, Hc, Wc, ph, pw;
+    bool inside;      // the workgroup's tile lies inside the result whole
+    bool whole;       // the whole reduction: what is accumulated on is there
+    float *out;
+};
+
+// Results of a wave: the lane holds column l32 of rows 8*(v/4) + 4*g + v%4 of each 32x32 block.  `stage`: 16 x 32 floats of LDS that are the wave's own.
+// ALIGNED: the statistics or the BatchNorm step behind a forward pass may ride along, a filter gradient may take 16-byte stores.
+template <int MODE, bool ALIGNED>
+__device__ __forceinline__ void write_results(const TileArgs &ta, const floatx16 (&acc)[2], float *stage, const TilePlace &at, int lane) {
+    const ConvShape &cs = ta.cs;
+    const int l32 = lane & 31, g = lane >> 5;
+    const int64_t row0 = at.row, Mg = at.rows;
+    const int col0 = at.col, Hc = at.Hc, Wc = at.Wc, ph = at.ph, pw = at.pw;
+    float *out = at.out;
+    const bool do_acc = MODE != WGRAD && ta.accumulate && at.whole;
+    // (Element-wise loaders too, except for the filter gradient: results of few terms are bound by their stores.  1x1, 2 -> 64 input gradient,
+    // 416x608, batch 11: 224 us with 4-byte stores, 143 so; accumulating 686 and 346.)
+    if ((ALIGNED || MODE != WGRAD) && (ta.Ng & 3) == 0) {
+        // Vector path: each wave transposes its 64x32 result through a private 16x32 LDS patch, four
+        // passes of 16 rows, and writes whole 16-byte pieces, 128 contiguous bytes per row.
+        const bool want_stats = ALIGNED && MODE == FWD && ta.stats_part != nullptr;
+        LaneStats ls;
+        ls.init();
+        // a lane writes the same four columns in every pass: one pair of BatchNorm coefficients each
+        const bool want_affine = ALIGNED && MODE == FWD && ta.affine.gamma != nullptr;
+        float bn_a[4] = {1, 1, 1, 1}, bn_b[4] = {0, 0, 0, 0};
+        if (MODE == FWD && want_affine) {
+            const int c0 = col0 + 4 * (lane & 7);
+            if (c0 < ta.Ng) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, c0 + j, bn_a[j], bn_b[j]);
+            }
+        }
+        // the sign code of a ReLU applied here: per row one half word (32 columns) per wave; the values are read once more
+        // from the LDS patch with lane = column, two rows at a time, so that one ballot is two half words
+        const bool want_mask = MODE == FWD && want_affine && ta.affine.relu && ta.affine.mask != nullptr && col0 < ta.Ng;
+        float bn_ac = 1.0f, bn_bc = 0.0f;
+        if (MODE == FWD && want_mask) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, col0 + l32, bn_ac, bn_bc);
+        // A tile that lies inside the result whole (all but the last row of tiles and, for widths that are no multiple
+        // of the tile, the last column) writes through buffer addressing: the descriptor starts at the tile, a lane's
+        // byte offset inside the tile never changes and the row of a pass is a scalar offset, so a store costs no vector
+        // instruction for its address and none for a bounds test.
+        const bool inside = at.inside && ta.Ng < (1 << 24) && !(MODE == DGRAD && cs.stride > 1);
+        const unsigned row_bytes = (unsigned)ta.Ng * 4u;
+        const int64_t tile_at = (row0) * ta.Ng + col0;
+        const __amdgpu_buffer_rsrc_t r_out = buffer_of(out + tile_at);
+        const __amdgpu_buffer_rsrc_t r_relu = buffer_of(MODE == FWD && ta.affine.relu_out ? ta.affine.relu_out + tile_at : out + tile_at);
+        const unsigned t_voff = (unsigned)(lane >> 3) * row_bytes + 16u * (unsigned)(lane & 7);
+        const bool past_caches = MODE != WGRAD && ta.stream;
+        auto put4 = [&](__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, bf4 v) {
+            if (past_caches) buffer_store4_stream(r, voff, soff, v);      // uniform over the launch
+            else buffer_store4(r, voff, soff, v);
+        };
+        auto emit = [&](auto whole_tile) {
+            constexpr bool IN = decltype(whole_tile)::value;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int mi = q >> 1, vbase = 8 * (q & 1);
+#pragma unroll
+                for (int vv = 0; vv < 8; ++vv) stage[(8 * (vv >> 2) + 4 * g + (vv & 3)) * 32 + l32] = acc[mi][vbase + vv];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int idx = lane + 64 * i, rl = idx >> 3, c4 = idx & 7;
+                    float4 val = *(const float4 *)&stage[rl * 32 + 4 * c4];
+                    const int64_t row = row0 + 16 * q + rl;
+                    const int col = col0 + 4 * c4;
+                    if (IN || (row < Mg && col < ta.Ng)) {
+                        const unsigned t_soff = (unsigned)(16 * q + 8 * i) * row_bytes;
+                        int64_t orow = row;
+                        if (!IN && MODE == DGRAD && cs.stride > 1) {
+                            // rows are bounded below 2^31 by the host: 32-bit divisions
+                            const unsigned r32 = (unsigned)row, t = r32 / (unsigned)Wc, n = t / (unsigned)Hc;
+                            const int wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - n * (unsigned)Hc);
+                            orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
+                        }
+                        float4 *dst = (float4 *)(out + orow * ta.Ng + col);
+                        if (do_acc) {
+                            float4 o;
+                            if (IN) { const bf4 t = buffer_load4(r_out, t_voff, t_soff); o = make_float4(t.x, t.y, t.z, t.w); }
+                            else o = *dst;
+                            val.x += o.x; val.y += o.y; val.z += o.z; val.w += o.w;
+                        }
+                        if (MODE == FWD && want_affine)
+                            val = float4{bn_affine(val.x, bn_a[0], bn_b[0]), bn_affine(val.y, bn_a[1], bn_b[1]), bn_affine(val.z, bn_a[2], bn_b[2]),
+                                         bn_affine(val.w, bn_a[3], bn_b[3])};
+                        if (MODE == FWD && want_affine && ta.affine.relu) {
+                            const float4 rv = float4{relu_clamp(val.x, ta.affine.relu), relu_clamp(val.y, ta.affine.relu),
+                                                     relu_clamp(val.z, ta.affine.relu), relu_clamp(val.w, ta.affine.relu)};
+                            if (ta.affine.relu_out) {
+                                if (IN) put4(r_relu, t_voff, t_soff, bf4{rv.x, rv.y, rv.z, rv.w});
+                                else *(float4 *)(ta.affine.relu_out + orow * ta.Ng + col) = rv;
+                            } else val = rv;
+                        }
+                        if (IN) put4(r_out, t_voff, t_soff, bf4{val.x, val.y, val.z, val.w});
+                        else *dst = val;
+                    }
+                }
+                if (MODE == FWD && want_stats) {
+                    // the statistics' own assignment: lanes of a column group take rows (lane / 8) % 4 + 4 i of the pass, in order (the upper
+                    // 32 lanes repeat the lower ones)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int rl = ((lane >> 3) & 3) + 4 * i;
+                        const float4 val = *(const float4 *)&stage[rl * 32 + 4 * (lane & 7)];
+                        if (!IN) {
+                            if (row0 + 16 * q + rl < Mg && col0 + 4 * (lane & 7) < ta.Ng) ls.add(val.x, val.y, val.z, val.w);
+                        } else if (q == 0 && i == 0) ls.add_first(val.x, val.y, val.z, val.w);
+                        else ls.add_next(val.x, val.y, val.z, val.w);
+                    }
+                }
+                if (MODE == FWD && want_mask) {      // uniform over the wave
+                    unsigned half = 0;
+#pragma unroll
+                    for (int rr = 0; rr < 8; ++rr) {
+                        const float e = bn_affine(stage[(2 * rr + g) * 32 + l32], bn_ac, bn_bc);
+                        const bool pass = ta.affine.relu == 2 ? (e > 0.0f && e < 6.0f) : e > 0.0f;
+                        const unsigned long long word = __ballot(pass);
+                        if (lane == 2 * rr) half = (unsigned)word;
+                        if (lane == 2 * rr + 1) half = (unsigned)(word >> 32);
+                    }
+                    const int64_t mrow = row0 + 16 * q + lane;       // lanes 0 .. 15 hold the half words of the pass's rows
+                    if (lane < 16 && mrow < Mg) ((unsigned *)ta.affine.mask)[(mrow * ta.Ng + col0) >> 5] = half;
+                }
+            }
+        };
+        if (inside) emit(std::true_type{});
+        else emit(std::false_type{});
+        if (MODE == FWD && want_stats) {
+            // this wave's 64 rows are one row group of the statistics; lanes l, l^8, l^16, l^24 share their columns
+            float n, mean[4], m2[4];
+            merge_lane_stats<8>(ls, lane, n, mean, m2);
+            const int64_t first = row0;
+            if (first < Mg) store_group_stats<8>(ta.stats_part, first / STAT_ROWS, ta.Ng, col0 + 4 * (lane & 7), lane, mean, m2);
+        }
+        return;
+    }
+    const int col = col0 + l32;
+    if (col >= ta.Ng) return;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            // four consecutive rows: with strided residue classes, the first one's place is decoded and the others' follow from it
+            const int64_t first = row0 + mi * 32 + 8 * v4 + 4 * g;
+            int wc = 0, hc = 0, n = 0;
+            if (MODE == DGRAD && cs.stride > 1) {   // class row (n,hc,wc) -> position (n, hc*st+ph, wc*st+pw)
+                const unsigned r32 = (unsigned)first, t = r32 / (unsigned)Wc;      // rows are bounded below 2^31 by the host
+                n = (int)(t / (unsigned)Hc);
+                wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - (unsigned)n * (unsigned)Hc);
+            }
+            float *dst[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                int64_t orow = first + j;
+                if (MODE == DGRAD && cs.stride > 1) {
+                    orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
+                    if (++wc == Wc) {
+                        wc = 0;
+                        if (++hc == Hc) { hc = 0; ++n; }
+                    }
+                }
+                dst[j] = out + orow * ta.Ng + col;
+            }
+            float r[4] = {acc[mi][4 * v4], acc[mi][4 * v4 + 1], acc[mi][4 * v4 + 2], acc[mi][4 * v4 + 3]};
+            if (do_acc) {      // the four loads together
+                float o[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = first + j < Mg ? *dst[j] : 0.0f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) r[j] += o[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (first + j < Mg) *dst[j] = r[j];
+        }
+}
+
 // TAG only names the use in profiles: 0 a convolution, 1 / 2 / 3 the batched GEMMs of a Winograd forward / input gradient /
 // filter gradient
 // FAST: 0 element-wise loaders, 1 aligned loaders, 2 aligned loaders of a 1x1 layer whose last reduction step is partly
@@ -919,174 +1101,239 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         }
     }
 
-    // ---------------- epilogue: lane holds column l32 of rows 8*(v/4) + 4*g + v%4 of each 32x32 block
-    float *out = ta.out;
-    out += (int64_t)split * ta.out_elems;
-    const bool do_acc = MODE != WGRAD && ta.accumulate && nsplit == 1;
-    // (Element-wise loaders too, except for the filter gradient: results of few terms are bound by their stores.  1x1, 2 -> 64 input gradient,
-    // 416x608, batch 11: 224 us with 4-byte stores, 143 so; accumulating 686 and 346.)
-    if ((FAST || MODE != WGRAD) && (ta.Ng & 3) == 0) {
-        // Vector path: each wave transposes its 64x32 result through a private 16x32 LDS patch, four
-        // passes of 16 rows, and writes whole 16-byte pieces, 128 contiguous bytes per row.
-        constexpr int NW = WM * WN;
-        __syncthreads();   // every wave has finished reading the operand tiles
-        static_assert(2 * A_SZ >= NW * 512 || 2 * B_SZ >= NW * 512, "the epilogue's patches fit one operand's tiles");
-        float *stage = (float *)(2 * A_SZ >= NW * 512 ? &As[0][0] : &Bs[0][0]) + wave * 512;
-        const bool want_stats = FAST && MODE == FWD && ta.stats_part != nullptr;
-        LaneStats ls;
-        ls.init();
-        // a lane writes the same four columns in every pass: one pair of BatchNorm coefficients each
-        const bool want_affine = FAST && MODE == FWD && ta.affine.gamma != nullptr;
-        float bn_a[4] = {1, 1, 1, 1}, bn_b[4] = {0, 0, 0, 0};
-        if (MODE == FWD && want_affine) {
-            const int c0 = col0 + wn * 32 + 4 * (lane & 7);
-            if (c0 < ta.Ng) {
+    // ---------------- epilogue
+    constexpr int NW = WM * WN;
+    static_assert(2 * A_SZ >= NW * 512 || 2 * B_SZ >= NW * 512, "the epilogue's patches fit one operand's tiles");
+    __syncthreads();   // every wave has finished reading the operand tiles
+    float *stage = (float *)(2 * A_SZ >= NW * 512 ? &As[0][0] : &Bs[0][0]) + wave * 512;
+    const TilePlace at{row0 + wm * 64, Mg, col0 + wn * 32, Hc, Wc, ph, pw, row0 + BM <= Mg && col0 + BN <= ta.Ng, nsplit == 1, ta.out + (int64_t)split * ta.out_elems};
+    write_results<MODE, FAST != 0>(ta, acc, stage, at, lane);
+}
+
+// Launches of few results: a workgroup of eight waves per 64 x 32 of them, the reduction steps dealt to the waves in turn.  Each wave loads its operands straight
+// into the matrix instruction's lanes (eight reduction indices of a row or column), splits them there and adds up a 64 x 32 block of its own; the
+// eight blocks are added in wave order through LDS, and the first wave writes the result.  No operand passes through LDS, no wave waits for
+// another before the end, and all loads of a wave's first two steps are on their way at once: such launches are bound by latency.  The tile kernel
+// takes 0.7 us for each of the steps it works one after another, and needs a second kernel where its reduction is cut.
+// Measured against it (us; the tile kernel with the ranges a graph declares, cut where it says so): 3x3, 16 -> 16, 16x16, batch 2: forward 8.9 and 6.2, input gradient 9.7
+// and 6.9; 1x1, 1024 -> 256, 14x14, batch 1: input gradient (cut) 12.9 and 7.7, filter gradient 14.9 and 7.7; 3x3, 60 -> 92, 13x17, batch 3: forward (cut)
+// 12.5 and 9.3, uncut 23.2 and 9.3; 3x3, 512 -> 512, 7x7, batch 1, uncut: 140 and 44.
+// Per step of a wave 1.2 us forward and in the input gradient, 1.7 in the filter gradient (vector instructions of two waves per SIMD, loads that touch a cache
+// line per row), so that long reductions over few tiles are better spread over the GPU.
+constexpr int SHORT_WAVES = 8;
+
+template <int MODE>
+__global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs ta) {
+    __shared__ float part[SHORT_WAVES][32][64];
+    __shared__ int redo;
+    const ConvShape &cs = ta.cs;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned tile_m = blockIdx.x / (unsigned)ta.tiles_n;
+    const int64_t row0 = (int64_t)tile_m * 64;
+    const int col0 = (int)(blockIdx.x - tile_m * (unsigned)ta.tiles_n) * 32, col = col0 + l32;
+    const int RSC = (int)cs.RSC();
+    if (tid == 0) redo = 0;
+
+    // residue class of an input gradient, as in the tile kernel
+    int64_t Mg = ta.Mg, Kg = ta.Kg;
+    int ph = 0, pw = 0, r0 = 0, s0 = 0, nr = cs.R, ns = cs.S, bh = 0, bw = 0, Hc = cs.H, Wc = cs.W;
+    if (MODE == DGRAD) {
+        const int st = cs.stride, cls = blockIdx.z;
+        ph = cls / st;
+        pw = cls % st;
+        Hc = (cs.H - ph + st - 1) / st;
+        Wc = (cs.W - pw + st - 1) / st;
+        r0 = (ph + cs.pad) % st;
+        s0 = (pw + cs.pad) % st;
+        nr = r0 < cs.R ? (cs.R - r0 + st - 1) / st : 0;
+        ns = s0 < cs.S ? (cs.S - s0 + st - 1) / st : 0;
+        bh = (ph + cs.pad - r0) / st;
+        bw = (pw + cs.pad - s0) / st;
+        Mg = (int64_t)cs.N * Hc * Wc;
+        Kg = (int64_t)nr * ns * cs.K;
+        if (row0 >= Mg) return;
+        if (Kg == 0 && ta.accumulate) return;       // this class receives no contribution
+    }
+    const int steps = (int)(((unsigned)Kg + BK - 1) / BK);
+
+    // What a lane keeps of its two rows and its column: byte offsets, and one bit per filter tap that exists (see the tile kernel's loaders).
+    const int row = MODE == FWD ? cs.W : cs.Q, inner = MODE == FWD ? cs.C : cs.K, taps_n = MODE == FWD ? cs.S : ns;
+    const int64_t reach = MODE == WGRAD ? 0 : ((int64_t)(nr > 0 ? nr - 1 : 0) * row + (ns > 0 ? ns - 1 : 0)) * inner;
+    const int64_t back = ((int64_t)cs.pad * cs.W + cs.pad) * cs.C;      // how far before its image a window begins
+    const int64_t a_shift = MODE == FWD ? (back > reach ? back : reach) : reach, b_shift = MODE == WGRAD ? back : 0;
+    unsigned a_voff[2], a_taps[2], b_voff = 0, b_tapbit = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, c0 + j, bn_a[j], bn_b[j]);
-            }
+    for (int i = 0; i < 2; ++i) {
+        const int64_t m = row0 + 32 * i + l32;
+        const bool ok = m < Mg;
+        if (MODE == WGRAD) {
+            a_voff[i] = (unsigned)m * 4u;
+            a_taps[i] = ok;
+            continue;
         }
-        // the sign code of a ReLU applied here: per row one half word (32 columns) per wave; the values are read once more
-        // from the LDS patch with lane = column, two rows at a time, so that one ballot is two half words
-        const bool want_mask = MODE == FWD && want_affine && ta.affine.relu && ta.affine.mask != nullptr && col0 + wn * 32 < ta.Ng;
-        float bn_ac = 1.0f, bn_bc = 0.0f;
-        if (MODE == FWD && want_mask) bn_affine_coeffs(ta.affine.gamma, ta.affine.beta, ta.affine.stats, ta.Ng, col0 + wn * 32 + l32, bn_ac, bn_bc);
-        // A tile that lies inside the result whole (all but the last row of tiles and, for widths that are no multiple
-        // of the tile, the last column) writes through buffer addressing: the descriptor starts at the tile, a lane's
-        // byte offset inside the tile never changes and the row of a pass is a scalar offset, so a store costs no vector
-        // instruction for its address and none for a bounds test.
-        const bool inside = row0 + BM <= Mg && col0 + BN <= ta.Ng && ta.Ng < (1 << 24) && !(MODE == DGRAD && cs.stride > 1);
-        const unsigned row_bytes = (unsigned)ta.Ng * 4u;
-        const int64_t tile_at = (row0 + wm * 64) * ta.Ng + col0 + wn * 32;
-        const __amdgpu_buffer_rsrc_t r_out = buffer_of(out + tile_at);
-        const __amdgpu_buffer_rsrc_t r_relu = buffer_of(MODE == FWD && ta.affine.relu_out ? ta.affine.relu_out + tile_at : out + tile_at);
-        const unsigned t_voff = (unsigned)(lane >> 3) * row_bytes + 16u * (unsigned)(lane & 7);
-        const bool past_caches = MODE != WGRAD && ta.stream;
-        auto put4 = [&](__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, bf4 v) {
-            if (past_caches) buffer_store4_stream(r, voff, soff, v);      // uniform over the launch
-            else buffer_store4(r, voff, soff, v);
-        };
-        auto emit = [&](auto whole_tile) {
-            constexpr bool IN = decltype(whole_tile)::value;
+        const unsigned m32 = ok ? (unsigned)m : 0u, rw = (unsigned)(MODE == FWD ? cs.Q : Wc), rh = (unsigned)(MODE == FWD ? cs.P : Hc);
+        const unsigned t = m32 / rw, n = t / rh;
+        const int w = (int)(m32 - t * rw), h = (int)(t - n * rh);
+        const int h0 = MODE == FWD ? h * cs.stride - cs.pad : h + bh, w0 = MODE == FWD ? w * cs.stride - cs.pad : w + bw;
+        const int64_t image = MODE == FWD ? (int64_t)n * cs.H * cs.W * cs.C : (int64_t)n * cs.P * cs.Q * cs.K;
+        a_voff[i] = (unsigned)((image + ((int64_t)h0 * row + w0) * inner + a_shift) * 4);
+        unsigned rows = 0, cols = 0, taps = 0;
+        for (int r = 0; r < nr; ++r)
+            if (MODE == FWD ? (unsigned)(h0 + r) < (unsigned)cs.H : (unsigned)(h0 - r) < (unsigned)cs.P) rows |= 1u << r;
+        for (int c = 0; c < ns; ++c)
+            if (MODE == FWD ? (unsigned)(w0 + c) < (unsigned)cs.W : (unsigned)(w0 - c) < (unsigned)cs.Q) cols |= 1u << c;
+        for (int r = 0; r < nr; ++r)
+            if ((rows >> r) & 1) taps |= cols << (r * ns);
+        a_taps[i] = ok ? taps : 0u;
+    }
+    int b_r = 0, b_s = 0;
+    if (MODE == WGRAD) {
+        const int cc = col < RSC ? col : 0, rs = cc / cs.C;
+        b_r = rs / cs.S;
+        b_s = rs - b_r * cs.S;
+        b_voff = (unsigned)((((int64_t)b_r * cs.W + b_s) * cs.C + (cc - rs * cs.C)) * 4);
+        b_tapbit = col < RSC;
+    } else {
+        b_tapbit = col < ta.Ng;
+        b_voff = MODE == FWD ? (unsigned)((int64_t)col * RSC * 4) : (unsigned)col * 4u;
+    }
+    const __amdgpu_buffer_rsrc_t ra = buffer_of(ta.a - a_shift, ta.a_bytes + (unsigned)a_shift * 4u), rb = buffer_of(ta.b - b_shift, ta.b_bytes + (unsigned)b_shift * 4u);
+    const unsigned by_cols = taps_n > 0 ? (1024u + taps_n - 1) / taps_n : 0u;      // tap / taps_n for tap < 32
+
+    struct Step { float a[2][8], b[8]; };      // reduction indices 16 t + 8 g .. + 7
+    auto load = [&](Step &s, int t) {
+        if constexpr (MODE == WGRAD) {
+            const unsigned m0 = (unsigned)t * BK + 8u * g, q0 = m0 < (unsigned)Kg ? m0 : 0u;
+            const unsigned tt = cs.Q == 1 ? q0 : __umulhi(q0, ta.q_mul) >> ta.q_shift;
+            unsigned n = cs.P == 1 ? tt : __umulhi(tt, ta.p_mul) >> ta.p_shift, q = q0 - tt * (unsigned)cs.Q, p = tt - n * (unsigned)cs.P;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int mi = q >> 1, vbase = 8 * (q & 1);
+            for (int e = 0; e < 8; ++e) {
+                const bool in = m0 + e < (unsigned)Kg;
+                const int h0 = (int)p * cs.stride - cs.pad, w0 = (int)q * cs.stride - cs.pad;
+                const bool here = in && b_tapbit && (unsigned)(h0 + b_r) < (unsigned)cs.H && (unsigned)(w0 + b_s) < (unsigned)cs.W;
+                // windows begin up to b_shift floats before the tensor, where its descriptor starts: the sum is not negative, and below 2^32 bytes
+                const unsigned pix = (((n * (unsigned)cs.H + (unsigned)h0) * (unsigned)cs.W + (unsigned)w0) * (unsigned)cs.C + (unsigned)b_shift) * 4u;
+                s.b[e] = buffer_load(rb, here ? pix + b_voff : BUFFER_ABSENT, 0u);
 #pragma unroll
-                for (int vv = 0; vv < 8; ++vv) stage[(8 * (vv >> 2) + 4 * g + (vv & 3)) * 32 + l32] = acc[mi][vbase + vv];
+                for (int i = 0; i < 2; ++i) s.a[i][e] = buffer_load(ra, in && a_taps[i] ? (m0 + e) * (unsigned)cs.K * 4u + a_voff[i] : BUFFER_ABSENT, 0u);
+                if (++q == (unsigned)cs.Q) {
+                    q = 0;
+                    if (++p == (unsigned)cs.P) { p = 0; ++n; }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const unsigned kk = (unsigned)t * BK + 8u * g + 4u * f;      // four indices of one filter tap: inner channels are a multiple of 4
+                const bool in = kk < (unsigned)Kg;
+                const unsigned tap = in ? __umulhi(kk, ta.q_mul) >> ta.q_shift : 0u, c = kk - tap * (unsigned)inner;
+                const unsigned r = (tap * by_cols) >> 10, ss = tap - r * (unsigned)taps_n;
+                const unsigned step = MODE == FWD ? ((r * cs.W + ss) * cs.C + c) * 4u : (unsigned)((int)c - (int)((r * cs.Q + ss) * cs.K)) * 4u;
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const int idx = lane + 64 * i, rl = idx >> 3, c4 = idx & 7;
-                    float4 val = *(const float4 *)&stage[rl * 32 + 4 * c4];
-                    const int64_t row = row0 + wm * 64 + 16 * q + rl;
-                    const int col = col0 + wn * 32 + 4 * c4;
-                    if (IN || (row < Mg && col < ta.Ng)) {
-                        const unsigned t_soff = (unsigned)(16 * q + 8 * i) * row_bytes;
-                        int64_t orow = row;
-                        if (!IN && MODE == DGRAD && cs.stride > 1) {
-                            // rows are bounded below 2^31 by the host: 32-bit divisions
-                            const unsigned r32 = (unsigned)row, t = r32 / (unsigned)Wc, n = t / (unsigned)Hc;
-                            const int wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - n * (unsigned)Hc);
-                            orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
-                        }
-                        float4 *dst = (float4 *)(out + orow * ta.Ng + col);
-                        if (do_acc) {
-                            float4 o;
-                            if (IN) { const bf4 t = buffer_load4(r_out, t_voff, t_soff); o = make_float4(t.x, t.y, t.z, t.w); }
-                            else o = *dst;
-                            val.x += o.x; val.y += o.y; val.z += o.z; val.w += o.w;
-                        }
-                        if (MODE == FWD && want_affine)
-                            val = float4{bn_affine(val.x, bn_a[0], bn_b[0]), bn_affine(val.y, bn_a[1], bn_b[1]), bn_affine(val.z, bn_a[2], bn_b[2]),
-                                         bn_affine(val.w, bn_a[3], bn_b[3])};
-                        if (MODE == FWD && want_affine && ta.affine.relu) {
-                            const float4 rv = float4{relu_clamp(val.x, ta.affine.relu), relu_clamp(val.y, ta.affine.relu),
-                                                     relu_clamp(val.z, ta.affine.relu), relu_clamp(val.w, ta.affine.relu)};
-                            if (ta.affine.relu_out) {
-                                if (IN) put4(r_relu, t_voff, t_soff, bf4{rv.x, rv.y, rv.z, rv.w});
-                                else *(float4 *)(ta.affine.relu_out + orow * ta.Ng + col) = rv;
-                            } else val = rv;
-                        }
-                        if (IN) put4(r_out, t_voff, t_soff, bf4{val.x, val.y, val.z, val.w});
-                        else *dst = val;
-                    }
-                }
-                if (MODE == FWD && want_stats) {
-                    // the statistics' own assignment: lanes of a column group take rows (lane / 8) % 4 + 4 i of the pass, in order (the upper
-                    // 32 lanes repeat the lower ones)
+                    const bf4 v = buffer_load4(ra, in && ((a_taps[i] >> tap) & 1u) ? a_voff[i] + step : BUFFER_ABSENT, 0u);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int rl = ((lane >> 3) & 3) + 4 * i;
-                        const float4 val = *(const float4 *)&stage[rl * 32 + 4 * (lane & 7)];
-                        if (!IN) {
-                            if (row0 + wm * 64 + 16 * q + rl < Mg && col0 + wn * 32 + 4 * (lane & 7) < ta.Ng) ls.add(val.x, val.y, val.z, val.w);
-                        } else if (q == 0 && i == 0) ls.add_first(val.x, val.y, val.z, val.w);
-                        else ls.add_next(val.x, val.y, val.z, val.w);
-                    }
+                    for (int e = 0; e < 4; ++e) s.a[i][4 * f + e] = v[e];
                 }
-                if (MODE == FWD && want_mask) {      // uniform over the wave
-                    unsigned half = 0;
+                if constexpr (MODE == FWD) {
+                    const bf4 v = buffer_load4(rb, in && b_tapbit ? b_voff + kk * 4u : BUFFER_ABSENT, 0u);
 #pragma unroll
-                    for (int rr = 0; rr < 8; ++rr) {
-                        const float e = bn_affine(stage[(2 * rr + g) * 32 + l32], bn_ac, bn_bc);
-                        const bool pass = ta.affine.relu == 2 ? (e > 0.0f && e < 6.0f) : e > 0.0f;
-                        const unsigned long long word = __ballot(pass);
-                        if (lane == 2 * rr) half = (unsigned)word;
-                        if (lane == 2 * rr + 1) half = (unsigned)(word >> 32);
-                    }
-                    const int64_t mrow = row0 + wm * 64 + 16 * q + lane;       // lanes 0 .. 15 hold the half words of the pass's rows
-                    if (lane < 16 && mrow < Mg) ((unsigned *)ta.affine.mask)[(mrow * ta.Ng + col0 + wn * 32) >> 5] = half;
+                    for (int e = 0; e < 4; ++e) s.b[4 * f + e] = v[e];
+                } else {
+                    // W[k][r0 + st * r][s0 + st * ss][col], k = c .. c + 3
+                    const unsigned at = (c * (unsigned)RSC + (unsigned)(((r0 + cs.stride * (int)r) * cs.S + s0 + cs.stride * (int)ss) * cs.C)) * 4u + b_voff;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s.b[4 * f + e] = buffer_load(rb, in && b_tapbit ? at + (unsigned)(e * RSC) * 4u : BUFFER_ABSENT, 0u);
                 }
             }
-        };
-        if (inside) emit(std::true_type{});
-        else emit(std::false_type{});
-        if (MODE == FWD && want_stats) {
-            // this wave's 64 rows are one row group of the statistics; lanes l, l^8, l^16, l^24 share their columns
-            float n, mean[4], m2[4];
-            merge_lane_stats<8>(ls, lane, n, mean, m2);
-            const int64_t first = row0 + wm * 64;
-            if (first < Mg) store_group_stats<8>(ta.stats_part, first / STAT_ROWS, ta.Ng, col0 + wn * 32 + 4 * (lane & 7), lane, mean, m2);
         }
-        return;
+    };
+
+    floatx16 acc[2], low[2];      // the h * h terms and the rest, as in the tile kernel
+    unsigned lost = 0;
+    auto multiply = [&](const Step &s, auto pieces) {
+        if constexpr (decltype(pieces)::value) {
+            const PieceRow b = split_row(s.b, lost);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const PieceRow a = split_row(s.a[i], lost);
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, low[i], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[i][e], s.b[e], acc[i], 0, 0, 0);
+        }
+    };
+    auto clear = [&] {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = low[i][v] = 0.0f;
+    };
+    clear();
+    {
+        Step s0, s1;
+        int t = wave;
+        if (t < steps) load(s0, t);
+        if (t + SHORT_WAVES < steps) load(s1, t + SHORT_WAVES);
+        for (; t < steps; t += 2 * SHORT_WAVES) {
+            multiply(s0, std::true_type{});
+            if (t + 2 * SHORT_WAVES < steps) load(s0, t + 2 * SHORT_WAVES);
+            if (t + SHORT_WAVES < steps) {
+                multiply(s1, std::true_type{});
+                if (t + 3 * SHORT_WAVES < steps) load(s1, t + 3 * SHORT_WAVES);
+            }
+        }
     }
-    const int col = col0 + wn * 32 + l32;
-    if (col >= ta.Ng) return;
+    // once more on the fp32 instruction where the pieces do not hold an operand, as in the tile kernel
+    float probe = 0.0f;
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            // four consecutive rows: with strided residue classes, the first one's place is decoded and the others' follow from it
-            const int64_t first = row0 + wm * 64 + mi * 32 + 8 * v4 + 4 * g;
-            int wc = 0, hc = 0, n = 0;
-            if (MODE == DGRAD && cs.stride > 1) {   // class row (n,hc,wc) -> position (n, hc*st+ph, wc*st+pw)
-                const unsigned r32 = (unsigned)first, t = r32 / (unsigned)Wc;      // rows are bounded below 2^31 by the host
-                n = (int)(t / (unsigned)Hc);
-                wc = (int)(r32 - t * (unsigned)Wc), hc = (int)(t - (unsigned)n * (unsigned)Hc);
-            }
-            float *dst[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                int64_t orow = first + j;
-                if (MODE == DGRAD && cs.stride > 1) {
-                    orow = ((int64_t)n * cs.H + (hc * cs.stride + ph)) * cs.W + (wc * cs.stride + pw);
-                    if (++wc == Wc) {
-                        wc = 0;
-                        if (++hc == Hc) { hc = 0; ++n; }
-                    }
-                }
-                dst[j] = out + orow * ta.Ng + col;
-            }
-            float r[4] = {acc[mi][4 * v4], acc[mi][4 * v4 + 1], acc[mi][4 * v4 + 2], acc[mi][4 * v4 + 3]};
-            if (do_acc) {      // the four loads together
-                float o[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = first + j < Mg ? *dst[j] : 0.0f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) r[j] += o[j];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (first + j < Mg) *dst[j] = r[j];
+        for (int v = 0; v < 16; ++v) {
+            acc[i][v] += low[i][v];
+            probe += acc[i][v];
         }
+    __syncthreads();
+    if (!(__builtin_fabsf(probe) < __builtin_inff()) || pieces_lost(lost)) redo = 1;
+    __syncthreads();
+    if (redo) {
+        clear();
+        for (int t = wave; t < steps; t += SHORT_WAVES) {
+            Step s;
+            load(s, t);
+            multiply(s, std::false_type{});
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[wave][16 * i + v][lane] = acc[i][v];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 32 / SHORT_WAVES; ++k) {
+        const int v = wave * (32 / SHORT_WAVES) + k;
+        double sum = 0;      // rounded once: fp32 sums in turn would be further from 64 bits than the tile kernel's one chain
+#pragma unroll
+        for (int w = 0; w < SHORT_WAVES; ++w) sum += (double)part[w][v][lane];
+        part[0][v][lane] = (float)sum;
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = part[0][16 * i + v][lane];
+    const TilePlace at{row0, Mg, col0, Hc, Wc, ph, pw, row0 + 64 <= Mg && col0 + 32 <= ta.Ng, true, ta.out};
+    write_results<MODE, true>(ta, acc, &part[1][0][0], at, lane);
 }
 
 // Sums `splits` partial results in a fixed order.  Block = SL waves; wave sl adds splits sl, sl+SL, ...
@@ -1194,14 +1441,20 @@ int useful_splits(int mode, int splits, int64_t tiles, int64_t slots, double flo
 // and 2 (64x256) stand for the nearest of these.
 int g_cfg_override = -1;   // tuning and test aid: force one tile shape, and exactly the ranges asked for, on every launch
 
+// the ranges a caller asked for, no more than there are steps; its workspace has to hold them whatever kernel runs
+int check_splits(int splits, int64_t steps, int64_t out_elems, const float *ws, size_t ws_bytes, const char *who) {
+    if (splits < 1) throw KernelError(std::string(who) + ": splits must be >= 1");
+    if (splits > steps) splits = (int)std::max<int64_t>(steps, 1);
+    if (splits > 1 && (!ws || ws_bytes < (size_t)splits * out_elems * 4)) throw KernelError(std::string(who) + ": workspace too small for the requested splits");
+    return splits;
+}
+
 template <int MODE, int WM, int WN, int TAG = 0>
 void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, int splits, float *ws, size_t ws_bytes, int64_t steps,
                  bool accumulate, const char *who) {
     constexpr int BM = 64 * WM, BN = 32 * WN, NT = 64 * WM * WN;
-    if (splits < 1) throw KernelError(std::string(who) + ": splits must be >= 1");
     set_row_magic(ta);
-    if (splits > steps) splits = (int)std::max<int64_t>(steps, 1);
-    if (splits > 1 && (!ws || ws_bytes < (size_t)splits * ta.out_elems * 4)) throw KernelError(std::string(who) + ": workspace too small for the requested splits");
+    splits = check_splits(splits, steps, ta.out_elems, ws, ws_bytes, who);
     if (splits > 1 && g_cfg_override < 0)
         splits = useful_splits(MODE, splits, (ta.Mg + BM - 1) / BM * ((ta.Ng + BN - 1) / BN) * zdim, (int64_t)NUM_CU * resident_workgroups(MODE, WM, WN),
                                2.0 * ta.Mg * ta.Ng * ta.Kg * zdim, 4.0 * ta.out_elems);
@@ -1285,6 +1538,30 @@ void launch_cfg(int cfg, Rest... rest) {
     else if (MODE == WGRAD && cfg == 4) launch_tile<WGRAD, 1, 4>(rest...);
     else if (MODE == WGRAD && cfg == 5) launch_tile<WGRAD, 1, 2>(rest...);
     else launch_tile<MODE, 2, 2>(rest...);
+}
+
+// Launches of few results (see conv_short_kernel): at most one workgroup per CU, and from four steps on: up to three, the tile kernel's chain has fewer roundings.
+// A launch that the tile kernel would work uncut takes it up to 512 steps (0.45 us each there; 288 steps: 140 us against 44).  One that it would cut
+// into ranges costs 12 - 14 us there with the second kernel, however long: forward, 34 steps 12.5 and 9.3 us, 64 steps 12.2 and 16.2; input
+// gradient, 51 steps 13.4 and 12.6, 72 steps 14.2 and 16.2; filter gradient, 20 steps 12.6 and 9.3, 32 level, 56 steps 12.6 and 16.9.
+// Cut launches of less than eight workgroups stay there too: ranges bring more CUs to work (1x1, 512 -> 32, 9x9, batch 4, six of them: 10.3 and 10.4; eight, 5x5,
+// 24 -> 64, 10x10, batch 2: 13.1 and 9.8).
+bool short_applies(int mode, const TileArgs &ta, int64_t steps, int64_t classes, bool fast, bool cut) {
+    const int64_t longest = !cut ? 512 : mode == WGRAD ? 32 : 40, tiles = (ta.Mg + 63) / 64 * ((ta.Ng + 31) / 32) * classes;
+    return fast && g_cfg_override < 0 && steps >= 4 && steps <= longest && tiles >= (cut ? 8 : 1) && tiles <= NUM_CU;
+}
+template <int MODE>
+void launch_short(hipStream_t st, TileArgs ta, int classes, float *out, bool accumulate) {
+    set_row_magic(ta);
+    if (MODE != WGRAD) magic_of((unsigned)(MODE == FWD ? ta.cs.C : ta.cs.K), ta.q_mul, ta.q_shift);      // a reduction index' filter tap
+    ta.tiles_n = (ta.Ng + 31) / 32;
+    ta.out = out;
+    ta.splits = 1;
+    ta.accumulate = accumulate ? 1 : 0;
+    ta.stream = 0;
+    const dim3 grid((unsigned)((ta.Mg + 63) / 64 * ta.tiles_n), 1, (unsigned)classes);
+    hipLaunchKernelGGL((conv_short_kernel<MODE>), grid, dim3(64 * SHORT_WAVES), 0, st, ta);
+    hip_check(hipGetLastError(), "conv launch");
 }
 
 // the batched GEMMs only ever see the two tile shapes the forward heuristic picks
@@ -1404,6 +1681,14 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
     if (stats_part && affine) throw KernelError("conv_fwd: either the statistics of the output or its BatchNorm apply step, not both");
     if (affine && (!affine->gamma || !affine->beta || !affine->stats)) throw KernelError("conv_fwd: incomplete BatchNorm coefficients");
     if (affine && affine->mask && (!affine->relu || cs.K % 64)) throw KernelError("conv_fwd: a sign code in the epilogue needs the ReLU and K % 64 == 0");
+    const int64_t steps = (ta.Kg + BK - 1) / BK;
+    ta.stats_part = stats_part;
+    if (affine) ta.affine = *affine;
+    if (short_applies(FWD, ta, steps, 1, fast, splits > 1 || ranges_by_workspace(split_gemm_of(0, cs), ta.out_elems, ws, ws_bytes) > 1)) {
+        check_splits(splits, steps, ta.out_elems, ws, ws_bytes, "conv_fwd");
+        launch_short<FWD>(st, ta, 1, y, accumulate);
+        return;
+    }
     if (splits == 1) {
         splits = ranges_by_workspace(split_gemm_of(0, cs), ta.out_elems, ws, ws_bytes);
         if (splits > 1 && (stats_part || affine)) {      // the sums are complete only behind the second kernel: what rode in the epilogue follows it
@@ -1416,9 +1701,7 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
             return;
         }
     }
-    ta.stats_part = stats_part;
-    if (affine) ta.affine = *affine;
-    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, (ta.Kg + BK - 1) / BK, 1, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, accumulate, "conv_fwd");
+    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, steps, 1, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, steps, accumulate, "conv_fwd");
 }
 
 void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, const ConvShape &cs, bool accumulate, int splits, float *ws,
@@ -1432,10 +1715,15 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     ta.Ng = cs.C;
     ta.Kg = 0;   // per class, computed in the kernel
     ta.out_elems = (int64_t)cs.N * cs.H * cs.W * cs.C;
-    if (splits == 1) splits = ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes);
     const int64_t span32 = ((int64_t)1 << 32) - (1 << 20);
     const int64_t reach = ((int64_t)cs.R * cs.Q + cs.S) * cs.K * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
+    if (short_applies(DGRAD, ta, sg.steps, sg.classes, fast, splits > 1 || ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes) > 1)) {
+        check_splits(splits, sg.steps, ta.out_elems, ws, ws_bytes, "conv_dgrad");
+        launch_short<DGRAD>(st, ta, sg.classes, dx, accumulate);
+        return;
+    }
+    if (splits == 1) splits = ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes);
     launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, splits, fast, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
 }
 
@@ -1461,7 +1749,13 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
     const int64_t lead = ((int64_t)cs.pad * cs.W + cs.pad) * cs.C * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 < span32 &&
                 (int64_t)cs.N * cs.H * cs.W * cs.C * 4 + lead < span32;
-    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, (ta.Kg + BK - 1) / BK, false, "conv_wgrad");
+    const int64_t steps = (ta.Kg + BK - 1) / BK;
+    if (short_applies(WGRAD, ta, steps, 1, fast, splits > 1)) {
+        check_splits(splits, steps, ta.out_elems, ws, ws_bytes, "conv_wgrad");
+        launch_short<WGRAD>(st, ta, 1, dw, false);
+        return;
+    }
+    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, steps, false, "conv_wgrad");
 }
 
 }  // namespace monet

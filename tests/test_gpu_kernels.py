@@ -718,6 +718,80 @@ def test_fused_winograd_convolution_matches_oracle(case):
             monet.call("monet_conv_winograd_fused", None, ddy.data_ptr(), dwt.data_ptr(), dx.data_ptr(), N, H, W, C, K, 1, 0, ws.data_ptr(), need)
 
 
+# launches of few results: a 64 x 32 block per workgroup, reduction steps dealt to eight waves
+SHORT_CASES = [
+    # N, H, W, C, K, R, stride, pad
+    (1, 8, 8, 64, 32, 1, 1, 0),        # one block exactly, four steps forward, fewer waves at work than there are
+    (1, 5, 13, 132, 36, 1, 1, 0),      # a row and a column block more; a last step of four indices
+    (2, 9, 7, 20, 44, 3, 1, 1),        # steps that straddle taps
+    (1, 11, 10, 32, 64, 3, 2, 1),      # residue classes of 4, 2, 2 and 1 taps
+    (3, 7, 7, 16, 24, 1, 3, 0),        # classes without a tap
+    (1, 6, 6, 1024, 40, 3, 1, 1),      # 576 steps forward: the tile kernel; 23 in the input gradient
+    (1, 4, 5, 4, 256, 5, 1, 2),        # window as large as the map
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", SHORT_CASES)
+@pytest.mark.parametrize("kind", ["plain", "tiny", "infinite"])
+def test_convolutions_of_few_results_match_64_bits(case, kind):
+    """Forward pass, input gradient (written and accumulated) and filter gradient without workspace.  A sum of n products of fp32 operands, rounded once per step
+    of 16 at most: 2e-7 of the sum of the products' sizes bounds it.  Operands near 2^-120 and an infinity go through the fp32 instruction, which rounds after
+    every product: n * 2^-24 of it."""
+    torch = torch_mod()
+    N, H, W, C, K, R, st, pad = case
+    P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
+    rng = np.random.default_rng(21)
+    x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, P, Q, K), dtype=np.float32)
+    w = rng.standard_normal((K, R, R, C), dtype=np.float32)
+    if kind == "tiny":
+        x, dy = x * np.float32(2.0 ** -118), dy * np.float32(2.0 ** -121)
+    dims = (N, H, W, C, K, R, R, st, pad)
+    xs, ws, ds = dev(x), dev(w), dev(dy)
+    if kind == "infinite":
+        xs[0, 0, 0, 0] = ds[0, 0, 0, 0] = float("inf")
+
+    def taps(a):      # what lies under every filter tap, N,P,Q,C
+        ap = np.pad(a, ((0, 0), (pad, pad), (pad, pad), (0, 0)))
+        return {(r, s): ap[:, r:r + (P - 1) * st + 1:st, s:s + (Q - 1) * st + 1:st, :] for r in range(R) for s in range(R)}
+
+    def reference(a, b, d):
+        a, b, d = (v.astype(np.float64) for v in (a, b, d))
+        under = taps(a)
+        y = sum(under[r, s] @ b[:, r, s, :].T for r, s in under)
+        dx = np.zeros((N, H + 2 * pad, W + 2 * pad, C))
+        dw = np.zeros((K, R, R, C))
+        for r, s in under:
+            dx[:, r:r + (P - 1) * st + 1:st, s:s + (Q - 1) * st + 1:st, :] += d @ b[:, r, s, :]
+            dw[:, r, s, :] = np.tensordot(d, under[r, s], ((0, 1, 2), (0, 1, 2)))
+        return y, dx[:, pad:pad + H, pad:pad + W, :], dw
+
+    want, size = reference(x, w, dy), reference(np.abs(x), np.abs(w), np.abs(dy))
+    y = torch.full((N, P, Q, K), float("nan"), device="cuda")
+    dx, dw = torch.full((N, H, W, C), float("nan"), device="cuda"), torch.full((K, R, R, C), float("nan"), device="cuda")
+    monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, 1, None, 0)
+    monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), dx.data_ptr(), *dims, 0, 1, None, 0)
+    twice = dx.clone()
+    monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), twice.data_ptr(), *dims, 1, 1, None, 0)
+    monet.call("monet_conv_wgrad", None, xs.data_ptr(), ds.data_ptr(), dw.data_ptr(), *dims, 1, None, 0)
+    outs = [t.cpu().numpy() for t in (y, dx, dw)]
+    for got, ref, sz, n in zip(outs, want, size, (C * R * R, K * R * R, N * P * Q)):
+        if kind == "infinite":
+            sure = np.isfinite(got)      # untouched by the infinities: as many as the definition says, checked below
+            got, ref, sz = got[sure], ref[sure], sz[sure]
+        assert (np.abs(got - ref) <= (2e-7 if kind == "plain" else max(2e-7, n * 2.0 ** -24)) * sz + 2.0 ** -148).all()
+    if kind == "infinite":
+        xi, di = x.copy(), dy.copy()
+        xi[0, 0, 0, 0] = di[0, 0, 0, 0] = np.inf
+        with np.errstate(invalid="ignore"):
+            under = taps(xi)
+            hit = sum((~np.isfinite(under[k])).any(-1) for k in under) > 0
+        assert (np.isfinite(outs[0]).all(-1) == ~hit).all()
+        assert not np.isfinite(outs[1]).all() and not np.isfinite(outs[2]).all()
+    else:
+        assert (torch.abs(twice - 2 * dx) <= 1e-6 * torch.abs(dx) + 2.0 ** -148).all()
+
+
 # one-kernel Winograd form on fp16 pieces: reductions of 64 channels and more, in chunks of 16
 PIECES_CASES = [
     # N, H, W, C, K
