@@ -290,12 +290,14 @@ __device__ __forceinline__ void write_results(const TileArgs &ta, const floatx16
 // line the gain shrinks: 112: 256 and 268, 128: 316 and 328, 192: 421 and 430, 256 level; level at every C on 14x14)
 // Registers: 128 in the eight-wave tiles and for FAST 2 and 4 (four waves per SIMD), where the narrow tile's FAST 2 spills 2 forward and 5 in the
 // input gradient; up to 168 in the others, where the 64x64 filter gradient spills 1.
-template <int MODE, int WM, int WN, int FAST, int TAG = 0>
-__global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST != 2 && FAST != 4) ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
+// KS: groups of waves that share a tile and take the reduction's steps in turn, each with operand tiles of its own in LDS; their sums are added at the end.
+template <int MODE, int WM, int WN, int FAST, int TAG = 0, int KS = 1>
+__global__ __launch_bounds__(64 * WM * WN * KS, KS == 1 && (WM * WN < 4 || (WM * WN == 4 && FAST != 2 && FAST != 4)) ? 3 : 4) void conv_tile_kernel(TileArgs ta) {
+    static_assert(KS == 1 || (MODE != WGRAD && FAST == 1), "aligned forward passes and input gradients only");
     // Register stages of the aligned variants: loads run this many steps ahead of the split.  The tiles of at most four waves take
     // two at three waves per SIMD (1x1, 1024 -> 256, 14x14, batch 184: 123 against 142 us with one), the larger ones, and short
     // reductions, which live from many workgroups at once (64 -> 256, 56x56: 214 against 245 us), one at four (128 registers).
-    constexpr int STAGES = (FAST == 1 || FAST == 3) && WM * WN <= 4 ? 2 : 1;
+    constexpr int STAGES = (FAST == 1 || FAST == 3) && WM * WN <= 4 && KS == 1 && !(FAST == 3 && WN == 1) ? 2 : 1;
     constexpr int BM = 64 * WM, BN = 32 * WN, NT = 64 * WM * WN;
     constexpr bool A_KC = (MODE != WGRAD);          // A operand reduction-contiguous?
     constexpr bool B_KC = (MODE == FWD);
@@ -303,8 +305,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     constexpr int A_SZ = 3 * A_PL, B_SZ = 3 * B_PL;
     // float4 slots of an operand's tile per thread; a tile with fewer slots than threads is loaded twice (same value, same place)
     constexpr int SA = BM * 4, SB = BN * 4, LA = SA >= NT ? SA / NT : 1, LB = SB >= NT ? SB / NT : 1;
-    __shared__ __attribute__((aligned(16))) unsigned As[2][A_SZ];
-    __shared__ __attribute__((aligned(16))) unsigned Bs[2][B_SZ];
+    __shared__ __attribute__((aligned(16))) unsigned As_all[KS][2][A_SZ];
+    __shared__ __attribute__((aligned(16))) unsigned Bs_all[KS][2][B_SZ];
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+    unsigned (&As)[2][A_SZ] = As_all[group];
+    unsigned (&Bs)[2][B_SZ] = Bs_all[group];
     __shared__ int redo;     // the pieces do not hold this tile's numbers: once more with the fp32 matrix instruction
     // First layers (3 input channels): the element-wise forward loader looks the (r, s, c) of a reduction index up
     // instead of dividing (measured 925 -> 815 us on the ResNet-50 stem).  Only the 64 columns wide tiles have
@@ -324,7 +329,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         ta.out += (int64_t)blockIdx.z * ta.batch_out;
     }
     const ConvShape &cs = ta.cs;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x - group * NT, lane = tid & 63, wave = tid >> 6;      // within the group
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, g = lane >> 5;
     const int tid_a = SA < NT ? tid % SA : tid, tid_b = SB < NT ? tid % SB : tid;
@@ -548,9 +553,9 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     int kk0;
     int u_r, u_s, u_c;   // FWD: (r, s, c0); DGRAD: (tap row, tap column, k0)
     auto to_start = [&] {
-        kk0 = kt0 * BK;
+        kk0 = (kt0 + group) * BK;
         u_r = u_s = u_c = 0;
-        if (MODE != WGRAD && kt0 > 0) {  // a later reduction split starts in the middle: locate it once
+        if (MODE != WGRAD && kt0 + group > 0) {  // a later reduction split (or group) starts in the middle: locate it once
             const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns;
             const int tap = (int)((unsigned)kk0 / (unsigned)inner);
             u_c = kk0 - tap * inner;
@@ -781,7 +786,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
             b_reg[s] = v;
     };
     auto advance = [&] {     // to the next step
-        kk0 += BK;
+        kk0 += BK * KS;
         if constexpr (FAST == 3) {
             auto next = [&](LaneTap &t) {
                 const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns, rows = MODE == FWD ? cs.R : nr;
@@ -797,6 +802,10 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
 #pragma unroll
                 for (int u = 0; u < UB3; ++u) next(lb3[u]);
             }
+        } else if (MODE != WGRAD && KS > 1) {
+            u_c += BK * KS;
+            const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns;
+            while (u_c >= inner) { u_c -= inner; if (++u_s == cols) { u_s = 0; ++u_r; } }
         } else if (MODE == FWD) {
             u_c += BK;
             if (u_c >= cs.C) { u_c = 0; if (++u_s == cs.S) { u_s = 0; ++u_r; } }
@@ -855,16 +864,27 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         } else {
             // n / 4 lanes hold one reduction index, the next n / 4 its neighbour: after exchanging the second half of the one with
             // the first half of the other a lane holds both indices of two columns
-            static_assert(n == 64 || n == 128, "one slot per thread: 16 or 32 lanes per reduction index");
+            static_assert(n == 32 || n == 64 || n == 128, "one slot per thread: 8, 16 or 32 lanes per reduction index");
             const float4 v = reg[0];
+            const int red = rc_red(t, 0, L, n);
+            unsigned *at = dst + (red >> 1) * rc_row(n) + rc_col4(t, 0, L, n) * 4 + (red & 1) * 2;
+            if constexpr (n == 32) {
+                // 8 lanes apart: the halves of a row of 16 lanes change places
+                auto other = [](float f) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f), 0x128, 0xf, 0xf, false)); };      // row_ror:8
+                const bool odd = red & 1;
+                const float g0 = other(odd ? v.x : v.z), g1 = other(odd ? v.y : v.w);
+                const Pieces p = pieces(odd ? g0 : v.x, odd ? v.z : g0), q = pieces(odd ? g1 : v.y, odd ? v.w : g1);
+                *(uint2 *)at = make_uint2(p.h, q.h);
+                *(uint2 *)(at + PL) = make_uint2(p.m, q.m);
+                *(uint2 *)(at + 2 * PL) = make_uint2(p.l, q.l);
+                return;
+            }
             auto swap = [&](float a, float b) {
-                if constexpr (n == 64) return __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+                if constexpr (n <= 64) return __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
                 else return __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
             };
             const auto e0 = swap(v.x, v.z), e1 = swap(v.y, v.w);
             const Pieces p = pieces(__uint_as_float(e0[0]), __uint_as_float(e0[1])), q = pieces(__uint_as_float(e1[0]), __uint_as_float(e1[1]));
-            const int red = rc_red(t, 0, L, n);
-            unsigned *at = dst + (red >> 1) * rc_row(n) + rc_col4(t, 0, L, n) * 4 + (red & 1) * 2;
             *(uint2 *)at = make_uint2(p.h, q.h);
             *(uint2 *)(at + PL) = make_uint2(p.m, q.m);
             *(uint2 *)(at + 2 * PL) = make_uint2(p.l, q.l);
@@ -973,7 +993,8 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     const bool single = !FAST && Kg == 1;
     if (tid == 0) redo = single;      // read behind the barriers below
     if (kt0 < kt1 && !single) {
-        const int steps = kt1 - kt0;
+        // a group's turns, as many for each: turns beyond the range multiply zeros
+        const int steps = (kt1 - kt0 + KS - 1) / KS;
         if (ROWTAB) {
             fill_rows(kt0, 0);
             __syncthreads();
@@ -981,17 +1002,19 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         const std::integral_constant<int, 0> s0{};
         const std::integral_constant<int, STAGES - 1> s1{};
         auto loading = [&](int t) {      // step t is about to be loaded: beyond the range the loads touch no memory
-            if (t >= steps) {
+            if (KS == 1 ? t >= steps : kt0 + group + t * KS >= kt1) {
                 ra = buffer_of(ta.a, 0);
                 rb = buffer_of(ta.b, 0);
             }
         };
+        if (KS > 1) loading(0);
         load_tiles(s0);
         if constexpr (FAST) {
             if constexpr (STAGES == 2) {
                 if (steps > 1) load_tiles(s1);
             }
             store_tiles(0, s0);
+            if (KS > 1) loading(STAGES);
             if (steps > STAGES) load_tiles(s0);
             __syncthreads();
             int t = 0;
@@ -1084,7 +1107,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
         const std::integral_constant<int, BM> rows{};
         const std::integral_constant<int, BN> cols{};
         float *fa = (float *)&As[0][0], *fb = (float *)&Bs[0][0];
-        for (int t = kt0; t < kt1; ++t) {
+        for (int t = kt0 + group; t < kt1 + group; t += KS) {      // as many turns for every group
+            if (KS > 1 && t >= kt1) {
+                ra = buffer_of(ta.a, 0);
+                rb = buffer_of(ta.b, 0);
+            }
             load_tiles(std::integral_constant<int, 0>{});
             put_whole(kc_a, std::integral_constant<int, LA>{}, rows, tid_a, fa, a_regs[0]);
             put_whole(kc_b, std::integral_constant<int, LB>{}, cols, tid_b, fb, b_regs[0]);
@@ -1105,6 +1132,28 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN < 4 || (WM * WN == 4 && FAST 
     constexpr int NW = WM * WN;
     static_assert(2 * A_SZ >= NW * 512 || 2 * B_SZ >= NW * 512, "the epilogue's patches fit one operand's tiles");
     __syncthreads();   // every wave has finished reading the operand tiles
+    if constexpr (KS > 1) {
+        // the other groups' sums come through LDS, one of the two blocks at a time
+        float *pass = (float *)&As_all[0][0][0];
+        static_assert(sizeof(As_all) >= (KS - 1) * NW * 1024 * 4, "a block of every other group's waves fits the operand tiles");
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (i) __syncthreads();
+            if (group > 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) pass[(((group - 1) * NW + wave) * 16 + v) * 64 + lane] = acc[i][v];
+            }
+            __syncthreads();
+            if (group == 0) {
+#pragma unroll
+                for (int o = 0; o < KS - 1; ++o)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][v] += pass[((o * NW + wave) * 16 + v) * 64 + lane];
+            }
+        }
+        __syncthreads();
+        if (group > 0) return;
+    }
     float *stage = (float *)(2 * A_SZ >= NW * 512 ? &As[0][0] : &Bs[0][0]) + wave * 512;
     const TilePlace at{row0 + wm * 64, Mg, col0 + wn * 32, Hc, Wc, ph, pw, row0 + BM <= Mg && col0 + BN <= ta.Ng, nsplit == 1, ta.out + (int64_t)split * ta.out_elems};
     write_results<MODE, FAST != 0>(ta, acc, stage, at, lane);
@@ -1437,7 +1486,7 @@ int useful_splits(int mode, int splits, int64_t tiles, int64_t slots, double flo
     return best;
 }
 
-// Tile shapes that the choice below takes: 0: 128x128, 3: 128x64 for every mode, 4: 64x128 and 5: 64x64 for filter gradients.  1 (256x64)
+// Tile shapes that the choice below takes: 0: 128x128, 3: 128x64 for every mode, 6: 128x32 and 7: 64x128 forward and for input gradients, 4: 64x128 and 5: 64x64 for filter gradients.  1 (256x64)
 // and 2 (64x256) stand for the nearest of these.
 int g_cfg_override = -1;   // tuning and test aid: force one tile shape, and exactly the ranges asked for, on every launch
 
@@ -1447,6 +1496,17 @@ int check_splits(int splits, int64_t steps, int64_t out_elems, const float *ws, 
     if (splits > steps) splits = (int)std::max<int64_t>(steps, 1);
     if (splits > 1 && (!ws || ws_bytes < (size_t)splits * out_elems * 4)) throw KernelError(std::string(who) + ": workspace too small for the requested splits");
     return splits;
+}
+
+// Two groups of waves per workgroup (KS of the tile kernel): launches that leave a CU at most eight waves, two per SIMD.  One wave's vector instructions follow each other
+// at 5 - 7 cycles, two waves' at 2.7 each, and loads, splits and barriers of one group pass under the other's matrix instructions.  Uncut: 3x3, 256 -> 256, 14x14,
+// batch 16: 73 and 53 us; 3x3, 512 -> 512, 7x7, batch 64: 142 and 105; 1x1, 512 -> 128, 28x28, batch 20: 20.7 and 18.2; cut: 1x1, 25088 -> 4096, batch 176: 293 and
+// 259.  With twice the workgroups the groups only get in each other's way: 3x3, 128 -> 128, 28x28, batch 16, in five ranges 36 and 44 us; 1x1, 128 -> 512,
+// 28x28, batch 20: 19 and 25.  Adding the groups' sums takes a microsecond: with few steps a launch is level or loses (3x3, 32 -> 64, 100x100, batch 6, 18 steps: 19.8
+// and 20.6; 1x1, 2048 -> 1000, batch 184, 16 ranges of eight: 18.6 and 19.3; 3x3, 256 -> 256, 14x14, batch 16, ranges of 29: 31.9 and 32.1).
+template <int WM, int WN>
+bool two_wave_groups(int64_t workgroups, int64_t steps) {
+    return steps >= 32 && workgroups <= (WM * WN == 8 ? 1 : 2) * NUM_CU;
 }
 
 template <int MODE, int WM, int WN, int TAG = 0>
@@ -1480,13 +1540,25 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
     } else {
         // forward or input-gradient channels that are no multiple of 16
         const bool part = MODE == FWD ? ta.cs.C % BK != 0 : MODE == DGRAD ? ta.cs.K % BK != 0 : false;
-        if constexpr (MODE != WGRAD) {
+        if constexpr (MODE != WGRAD && WM == 1) {      // 1x1 layers of few rows
+            if (!fast || ta.cs.R * ta.cs.S > 1) throw KernelError("conv: this tile shape is for aligned 1x1 layers");
+            if (part) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 2>), grid, dim3(NT), 0, st, ta); }
+            else { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1>), grid, dim3(NT), 0, st, ta); }
+        } else if constexpr (MODE != WGRAD) {
+            if constexpr (WM == 2 && WN >= 2) {
+                if (fast && !part && g_cfg_override < 0 && two_wave_groups<WM, WN>(blocks * zdim, steps / ta.splits)) {
+                    hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1, 0, 2>), grid, dim3(2 * NT), 0, st, ta);
+                    hip_check(hipGetLastError(), "conv launch");
+                    if (slabs) launch_split_reduce(st, ws, out, ta.out_elems, splits, accumulate);
+                    return;
+                }
+            }
             if (fast && part && ta.cs.R * ta.cs.S > 1) {
-                if constexpr (WM == 2 && WN == 2) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 3>), grid, dim3(NT), 0, st, ta); }
+                if constexpr (WM == 2 && WN <= 2) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 3>), grid, dim3(NT), 0, st, ta); }
                 else throw KernelError("conv: straddling reduction steps need the 128x64 tile");
             }
             else if (fast && part) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 2>), grid, dim3(NT), 0, st, ta); }
-            else if (fast && WM * WN == 4 && steps <= 6) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, WM * WN == 4 ? 4 : 1>), grid, dim3(NT), 0, st, ta); }
+            else if (fast && WM * WN <= 4 && steps <= 6) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, WM * WN <= 4 ? 4 : 1>), grid, dim3(NT), 0, st, ta); }
             else if (fast) { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 1>), grid, dim3(NT), 0, st, ta); }
             else { hipLaunchKernelGGL((conv_tile_kernel<MODE, WM, WN, 0>), grid, dim3(NT), 0, st, ta); }
         } else {
@@ -1507,6 +1579,13 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // against narrow: 9016 tiles (56x56), 5 steps 187 and 205 us, 8 steps 282 and 328; 2254 (28x28), 6 steps 57 and 60, 8 steps 66 and 76; 564
 // (14x14), level from 2 to 16 steps.  A reduction cut into
 // ranges fills it anyway.  `straddle`: reduction steps that cross filter taps.
+// Results of up to 32 columns leave half of the 128x64 tile's matrix instructions to columns that do not exist.  6: 128x32, two waves per workgroup, where
+// workgroups are many and the reduction is more than memory: 3x3, 64 -> 32, 90x90, batch 16 (1013 workgroups, 36 steps): 61 and 48 us; its mirror's input gradient 69
+// and 50; 5x5, 32 -> 96, 28x28, batch 320, input gradient 416 and 365; 3x3, 8 -> 32, 112x112, batch 8: 18 and 14.  Half as many waves per workgroup lose where
+// there are few (5x5, 24 -> 64, 14x14, batch 320, input gradient, 490 of them: 91 and 95; 3x3 stride 2, 32 -> 32, 56x56, batch 64, 392: 19 and 22), and 1x1 layers of
+// up to 12 steps, which move memory, are level or lose (192 -> 32, 28x28, batch 272: 39 and 41).
+// 7: 64x128 for cut 1x1 layers of at most 64 rows (a small batch's fully connected layer: half of 128 rows would not exist): 25088 -> 4096, batch 64: forward 153 and
+// 115 us, input gradient 149 and 107; 2048 -> 1000, batch 64: 14.2 and 12.7.  Uncut it has no more workgroups than the 128x128 tile's groups (700 and 734).
 // Element-wise loaders (`fast` false) are bound by loading: a wider tile reads each activation for fewer column tiles.  Forward, 128x64
 // against 128x128: 5x5, 141 -> 464, 106x106, batch 2: 1459 and 897 us; 3x3, 258 -> 514, 14x14, batch 64: 709 and 389; 1x1, 18 -> 239,
 // 90x90, batch 23: 67 and 56.  Input gradient of the first: 2643 and 2001; of a 3x3 layer, 416 -> 1, in one step: 60 and 52; of a 2x2 stride-3 layer,
@@ -1516,7 +1595,7 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // Element-wise filter gradients take 128x64 in place of 128x128, whose 128 registers they exceed: 5x5 stride 3, 438 -> 392, 32x32, batch 38: 501
 // and 756 us; 3x3, 258 -> 514, 14x14, batch 64, ten ranges: 434 and 501; 1x1, 438 -> 391, 32x32, batch 38, 64 ranges: 251 and 287.
 // (It loses where its twice as many tiles just begin a second round: 7x7, 402 -> 304, 16x16, batch 10: 221 and 196.)
-int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int splits, bool fast, bool straddle) {
+int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int taps, int splits, bool fast, bool straddle) {
     if (mode == WGRAD) {
         static const int nearest[6] = {0, 3, 4, 3, 4, 5};
         if (g_cfg_override >= 0) return nearest[g_cfg_override] == 0 && !fast ? 3 : nearest[g_cfg_override];
@@ -1524,6 +1603,8 @@ int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, i
         if (Mg <= 64) return (Ng + 127) / 128 * 128 <= (Ng + 63) / 64 * 64 * 9 / 8 ? 4 : 5;
         return fast ? 0 : 3;
     }
+    if (g_cfg_override < 0 && fast && Ng <= 32 && (steps >= 16 || taps > 1) && (Mg + 127) / 128 * classes >= 640) return 6;
+    if (g_cfg_override < 0 && fast && taps == 1 && splits > 1 && Mg <= 64 && Ng > 64) return 7;      // at most 64 rows
     if (straddle) return 3;      // straddling lanes carry their tap: registers the larger tile does not have
     if (g_cfg_override >= 0) return g_cfg_override == 0 ? 0 : 3;
     if (Ng <= 64) return 3;
@@ -1537,6 +1618,8 @@ void launch_cfg(int cfg, Rest... rest) {
     if (cfg == 0) launch_tile<MODE, 2, 4>(rest...);
     else if (MODE == WGRAD && cfg == 4) launch_tile<WGRAD, 1, 4>(rest...);
     else if (MODE == WGRAD && cfg == 5) launch_tile<WGRAD, 1, 2>(rest...);
+    else if (MODE != WGRAD && cfg == 7) launch_tile<MODE == WGRAD ? FWD : MODE, 1, 4>(rest...);
+    else if (MODE != WGRAD && cfg == 6) launch_tile<MODE == WGRAD ? FWD : MODE, 2, 1>(rest...);
     else launch_tile<MODE, 2, 2>(rest...);
 }
 
@@ -1701,7 +1784,7 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
             return;
         }
     }
-    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, steps, 1, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, steps, accumulate, "conv_fwd");
+    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, steps, 1, cs.R * cs.S, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, steps, accumulate, "conv_fwd");
 }
 
 void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, const ConvShape &cs, bool accumulate, int splits, float *ws,
@@ -1724,7 +1807,7 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
         return;
     }
     if (splits == 1) splits = ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes);
-    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, splits, fast, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
+    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, cs.R * cs.S, splits, fast, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
 }
 
 void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, const ConvShape &cs, int splits, float *ws, size_t ws_bytes) {
@@ -1755,7 +1838,7 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
         launch_short<WGRAD>(st, ta, 1, dw, false);
         return;
     }
-    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, steps, false, "conv_wgrad");
+    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, cs.R * cs.S, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, steps, false, "conv_wgrad");
 }
 
 }  // namespace monet

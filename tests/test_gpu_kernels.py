@@ -731,6 +731,26 @@ SHORT_CASES = [
 ]
 
 
+def conv_taps(a, R, st, pad, P, Q):
+    """What lies under every filter tap, N,P,Q,C."""
+    ap = np.pad(a, ((0, 0), (pad, pad), (pad, pad), (0, 0)))
+    return {(r, s): ap[:, r:r + (P - 1) * st + 1:st, s:s + (Q - 1) * st + 1:st, :] for r in range(R) for s in range(R)}
+
+
+def conv64(x, w, dy, st, pad):
+    """(y, dx, dw) in 64 bits."""
+    x, w, dy = (v.astype(np.float64) for v in (x, w, dy))
+    (N, H, W, C), (K, R), (P, Q) = x.shape, w.shape[:2], dy.shape[1:3]
+    under = conv_taps(x, R, st, pad, P, Q)
+    y = sum(under[r, s] @ w[:, r, s, :].T for r, s in under)
+    dx = np.zeros((N, H + 2 * pad, W + 2 * pad, C))
+    dw = np.zeros((K, R, R, C))
+    for r, s in under:
+        dx[:, r:r + (P - 1) * st + 1:st, s:s + (Q - 1) * st + 1:st, :] += dy @ w[:, r, s, :]
+        dw[:, r, s, :] = np.tensordot(dy, under[r, s], ((0, 1, 2), (0, 1, 2)))
+    return y, dx[:, pad:pad + H, pad:pad + W, :], dw
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", SHORT_CASES)
 @pytest.mark.parametrize("kind", ["plain", "tiny", "infinite"])
@@ -751,22 +771,7 @@ def test_convolutions_of_few_results_match_64_bits(case, kind):
     if kind == "infinite":
         xs[0, 0, 0, 0] = ds[0, 0, 0, 0] = float("inf")
 
-    def taps(a):      # what lies under every filter tap, N,P,Q,C
-        ap = np.pad(a, ((0, 0), (pad, pad), (pad, pad), (0, 0)))
-        return {(r, s): ap[:, r:r + (P - 1) * st + 1:st, s:s + (Q - 1) * st + 1:st, :] for r in range(R) for s in range(R)}
-
-    def reference(a, b, d):
-        a, b, d = (v.astype(np.float64) for v in (a, b, d))
-        under = taps(a)
-        y = sum(under[r, s] @ b[:, r, s, :].T for r, s in under)
-        dx = np.zeros((N, H + 2 * pad, W + 2 * pad, C))
-        dw = np.zeros((K, R, R, C))
-        for r, s in under:
-            dx[:, r:r + (P - 1) * st + 1:st, s:s + (Q - 1) * st + 1:st, :] += d @ b[:, r, s, :]
-            dw[:, r, s, :] = np.tensordot(d, under[r, s], ((0, 1, 2), (0, 1, 2)))
-        return y, dx[:, pad:pad + H, pad:pad + W, :], dw
-
-    want, size = reference(x, w, dy), reference(np.abs(x), np.abs(w), np.abs(dy))
+    want, size = conv64(x, w, dy, st, pad), conv64(np.abs(x), np.abs(w), np.abs(dy), st, pad)
     y = torch.full((N, P, Q, K), float("nan"), device="cuda")
     dx, dw = torch.full((N, H, W, C), float("nan"), device="cuda"), torch.full((K, R, R, C), float("nan"), device="cuda")
     monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, 1, None, 0)
@@ -784,12 +789,54 @@ def test_convolutions_of_few_results_match_64_bits(case, kind):
         xi, di = x.copy(), dy.copy()
         xi[0, 0, 0, 0] = di[0, 0, 0, 0] = np.inf
         with np.errstate(invalid="ignore"):
-            under = taps(xi)
+            under = conv_taps(xi, R, st, pad, P, Q)
             hit = sum((~np.isfinite(under[k])).any(-1) for k in under) > 0
         assert (np.isfinite(outs[0]).all(-1) == ~hit).all()
         assert not np.isfinite(outs[1]).all() and not np.isfinite(outs[2]).all()
     else:
         assert (torch.abs(twice - 2 * dx) <= 1e-6 * torch.abs(dx) + 2.0 ** -148).all()
+
+
+# tile shapes and wave groups of the forward pass and the input gradient
+GROUP_CASES = [
+    # N, H, W, C, K, R, stride, pad, splits
+    (5, 28, 28, 80, 160, 3, 1, 1, 1),       # two groups on 128x64 tiles, 45 steps forward: one turn more for the first
+    (5, 27, 28, 64, 176, 3, 1, 1, 1),       # 36 and 99 steps, ragged tiles
+    (3, 28, 28, 64, 320, 3, 2, 1, 1),       # residue classes of unequal length
+    (5, 28, 28, 192, 160, 3, 1, 1, 3),      # two groups on 128x128 tiles, cut into three ranges of 36 and 30 steps
+    (2, 208, 200, 16, 24, 3, 1, 1, 1),      # 128x32 tiles: 24 columns forward, 16 in the input gradient
+    (2, 208, 200, 20, 32, 3, 1, 1, 1),      # and steps that straddle taps
+    (1, 5, 11, 512, 132, 1, 1, 0, 4),       # 64x128 tiles: at most 64 rows of a cut 1x1 layer
+    (64, 1, 1, 1284, 516, 1, 1, 0, 8),      # and a last step of four indices
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", GROUP_CASES)
+@pytest.mark.parametrize("infinite", [False, True])
+def test_convolution_tiles_and_wave_groups_match_64_bits(case, infinite):
+    """Bounds as above; `infinite`: a tile is worked again on the fp32 instruction, by both groups."""
+    torch = torch_mod()
+    N, H, W, C, K, R, st, pad, splits = case
+    P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
+    rng = np.random.default_rng(22)
+    x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, P, Q, K), dtype=np.float32)
+    w = rng.standard_normal((K, R, R, C), dtype=np.float32)
+    want, size = conv64(x, w, dy, st, pad), conv64(np.abs(x), np.abs(w), np.abs(dy), st, pad)
+    xs, ws, ds = dev(x), dev(w), dev(dy)
+    if infinite:
+        xs[0, 0, 0, 0] = ds[0, 0, 0, 0] = float("inf")
+    y, dx = torch.full((N, P, Q, K), float("nan"), device="cuda"), torch.full((N, H, W, C), float("nan"), device="cuda")
+    room = torch.empty(splits * max(y.numel(), dx.numel()), device="cuda")
+    dims = (N, H, W, C, K, R, R, st, pad)
+    monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, splits, room.data_ptr() if splits > 1 else None, room.numel() * 4 if splits > 1 else 0)
+    monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), dx.data_ptr(), *dims, 0, splits, room.data_ptr() if splits > 1 else None,
+               room.numel() * 4 if splits > 1 else 0)
+    for got, ref, sz, n in zip((y.cpu().numpy(), dx.cpu().numpy()), want, size, (C * R * R, K * R * R)):
+        sure = np.isfinite(got)
+        assert sure.all() != infinite and sure.mean() > (0.9 if N * P * Q > 100 else 0.5)
+        bound = max(2e-7, n * 2.0 ** -24) if infinite else 2e-7
+        assert (np.abs(got - ref)[sure] <= bound * sz[sure]).all()
 
 
 # one-kernel Winograd form on fp16 pieces: reductions of 64 channels and more, in chunks of 16
