@@ -839,6 +839,33 @@ def test_convolution_tiles_and_wave_groups_match_64_bits(case, infinite):
         assert (np.abs(got - ref)[sure] <= bound * sz[sure]).all()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows, C", [(1, 4), (33, 16), (512, 16), (2047, 16), (4099, 16), (70, 60), (300, 256), (300, 260), (40, 1024)])
+def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
+    """Partial sums that every apply workgroup adds for itself (up to 16 slabs and 256 channels) and beyond.  Sums of `rows` terms in fp32, in slabs: 1e-5 of the terms' sizes."""
+    torch = torch_mod()
+    rng = np.random.default_rng(9)
+    dy, x = rng.standard_normal((rows, C), dtype=np.float32), rng.standard_normal((rows, C), dtype=np.float32) + np.float32(0.5)
+    gamma, beta = rng.uniform(0.5, 1.5, C).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+    mean, inv = x.astype(np.float64).mean(0), 1 / np.sqrt(x.astype(np.float64).var(0) + 1e-5)
+    stats = np.concatenate([mean, inv]).astype(np.float32)
+    g, xhat = dy.astype(np.float64), (x - stats[:C].astype(np.float64)) * stats[C:].astype(np.float64)
+    want_b, want_g = g.sum(0), (g * xhat).sum(0)
+    scale = gamma.astype(np.float64) * stats[C:]
+    want_dx = scale * (g - want_b / rows - xhat * (want_g / rows))
+    dx = torch.full((rows, C), float("nan"), device="cuda")
+    dgamma, dbeta = torch.full((C,), float("nan"), device="cuda"), torch.full((C,), float("nan"), device="cuda")
+    scratch = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    dyd, xd, gd, bd, sd = dev(dy), dev(x), dev(gamma), dev(beta), dev(stats)
+    monet.call("monet_bn_bwd", None, dyd.data_ptr(), xd.data_ptr(), 0, gd.data_ptr(), bd.data_ptr(), sd.data_ptr(), dx.data_ptr(), dgamma.data_ptr(), dbeta.data_ptr(),
+               rows, C, 0, scratch.data_ptr(), scratch.numel())
+    size_b, size_g = np.abs(g).sum(0), (np.abs(g) * (np.abs(xhat) + np.abs(stats[:C]) * stats[C:])).sum(0)
+    assert (np.abs(dbeta.cpu().numpy() - want_b) <= 1e-5 * size_b).all()
+    assert (np.abs(dgamma.cpu().numpy() - want_g) <= 1e-5 * size_g).all()
+    bound = 1e-5 * scale * (np.abs(g) + size_b / rows + (np.abs(xhat) + np.abs(stats[:C]) * stats[C:]) * (1 + size_g / rows))
+    assert (np.abs(dx.cpu().numpy() - want_dx) <= bound).all()
+
+
 # one-kernel Winograd form on fp16 pieces: reductions of 64 channels and more, in chunks of 16
 PIECES_CASES = [
     # N, H, W, C, K
