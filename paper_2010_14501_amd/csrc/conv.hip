@@ -1526,7 +1526,7 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
     ta.accumulate = accumulate ? 1 : 0;
     ta.stream = MODE != WGRAD && TAG == 0 && splits == 1 && ta.out_elems * 4 >= (256ll << 20);
     bool slabs = false;
-    if (splits > 1) {
+    if (splits > 1 || (MODE == WGRAD && accumulate)) {      // a filter gradient is accumulated by the kernel that adds its ranges
         slabs = true;
         ta.out = ws;
         ta.splits = splits;
@@ -1568,7 +1568,7 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
         }
     }
     hip_check(hipGetLastError(), "conv launch");
-    if (slabs) launch_split_reduce(st, ws, out, ta.out_elems, splits, MODE != WGRAD && accumulate);
+    if (slabs) launch_split_reduce(st, ws, out, ta.out_elems, splits, accumulate);
 }
 
 // Choice measured on the ResNet-50, VGG-16, MobileNetV2 and inception layer sets.  The square tile moves the least through LDS and
@@ -1626,11 +1626,15 @@ void launch_cfg(int cfg, Rest... rest) {
 // Launches of few results (see conv_short_kernel): at most one workgroup per CU, and from four steps on: up to three, the tile kernel's chain has fewer roundings.
 // A launch that the tile kernel would work uncut takes it up to 512 steps (0.45 us each there; 288 steps: 140 us against 44).  One that it would cut
 // into ranges costs 12 - 14 us there with the second kernel, however long: forward, 34 steps 12.5 and 9.3 us, 64 steps 12.2 and 16.2; input
-// gradient, 51 steps 13.4 and 12.6, 72 steps 14.2 and 16.2; filter gradient, 20 steps 12.6 and 9.3, 32 level, 56 steps 12.6 and 16.9.
+// gradient, 47 steps 13.5 and 12.1, 52 steps 13.3 and 12.6, 56 steps 13.4 and 14.0, 72 steps 14.2 and 16.2; filter gradient, 20 steps 12.6 and 9.3, 32 level on few
+// workgroups, 34 of them with 41 steps 14.4 and 13.7, 84 with 41 15.0 and 13.6, 8 with 36 12.3 and 12.9, 88 with 42 and 16 rows, most of them absent,
+// 12.2 and 13.6, 56 steps 12.6 and 16.9.
 // Cut launches of less than eight workgroups stay there too: ranges bring more CUs to work (1x1, 512 -> 32, 9x9, batch 4, six of them: 10.3 and 10.4; eight, 5x5,
 // 24 -> 64, 10x10, batch 2: 13.1 and 9.8).
+// `steps` of the longest residue class.
 bool short_applies(int mode, const TileArgs &ta, int64_t steps, int64_t classes, bool fast, bool cut) {
-    const int64_t longest = !cut ? 512 : mode == WGRAD ? 32 : 40, tiles = (ta.Mg + 63) / 64 * ((ta.Ng + 31) / 32) * classes;
+    const int64_t tiles = (ta.Mg + 63) / 64 * ((ta.Ng + 31) / 32) * classes;
+    const int64_t longest = !cut ? 512 : mode == DGRAD ? 52 : mode == WGRAD ? (tiles >= 32 && ta.Mg > 32 ? 44 : 32) : 40;
     return fast && g_cfg_override < 0 && steps >= 4 && steps <= longest && tiles >= (cut ? 8 : 1) && tiles <= NUM_CU;
 }
 template <int MODE>
@@ -1724,9 +1728,10 @@ void gemm_batched(hipStream_t st, const float *a, const float *b, float *out, in
 }
 
 // out[z][m][n] = sum_t a[z][t][m] b[z][t][n]: the reduction runs over the rows of both operands (weight-gradient form);
-// `splits` partial results per GEMM go to ws (splits * batch * m * n floats) and are added in range order
+// `splits` partial results per GEMM go to ws (splits * batch * m * n floats) and are added in range order; accumulate: and to what out
+// holds (the workspace has room for one result at least)
 void gemm_tn_batched(hipStream_t st, const float *a, const float *b, float *out, int batch, int64_t red, int m, int n, int splits,
-                     float *ws, size_t ws_bytes) {
+                     float *ws, size_t ws_bytes, bool accumulate) {
     if (batch < 1 || red < 1 || m < 1 || n < 1 || m % 4 || n % 4) throw KernelError("gemm_tn_batched: bad shape");
     ConvShape cs{1, 1, (int)red, n, m, 1, 1, 1, 0, 1, (int)red};
     check_shape(cs);
@@ -1739,7 +1744,8 @@ void gemm_tn_batched(hipStream_t st, const float *a, const float *b, float *out,
     // the aligned loader addresses each operand plane with 32-bit byte offsets
     if (red * m * 4 >= ((int64_t)1 << 32) - (1 << 20) || red * n * 4 >= ((int64_t)1 << 32) - (1 << 20))
         throw KernelError("gemm_tn_batched: an operand plane of 4 GiB or more");
-    launch_tile<WGRAD, 2, 4, 3>(st, ta, true, batch, out, splits, ws, ws_bytes, (red + BK - 1) / BK, false, "gemm_tn_batched");
+    if (accumulate && (!ws || ws_bytes < (size_t)ta.out_elems * 4)) throw KernelError("gemm_tn_batched: an accumulated result needs a workspace of its size");
+    launch_tile<WGRAD, 2, 4, 3>(st, ta, true, batch, out, splits, ws, ws_bytes, (red + BK - 1) / BK, accumulate, "gemm_tn_batched");
 }
 
 void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const ConvShape &cs, int splits, float *ws, size_t ws_bytes,
@@ -1801,7 +1807,8 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     const int64_t span32 = ((int64_t)1 << 32) - (1 << 20);
     const int64_t reach = ((int64_t)cs.R * cs.Q + cs.S) * cs.K * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
-    if (short_applies(DGRAD, ta, sg.steps, sg.classes, fast, splits > 1 || ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes) > 1)) {
+    const int64_t longest = ((int64_t)((cs.R + cs.stride - 1) / cs.stride) * ((cs.S + cs.stride - 1) / cs.stride) * cs.K + BK - 1) / BK;
+    if (short_applies(DGRAD, ta, longest, sg.classes, fast, splits > 1 || ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes) > 1)) {
         check_splits(splits, sg.steps, ta.out_elems, ws, ws_bytes, "conv_dgrad");
         launch_short<DGRAD>(st, ta, sg.classes, dx, accumulate);
         return;

@@ -69,7 +69,7 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
 void gemm_batched(hipStream_t st, const float *a, const float *b, float *out, int batch, int64_t rows, int cols, int red,
                   bool adjoint_use = false);
 void gemm_tn_batched(hipStream_t st, const float *a, const float *b, float *out, int batch, int64_t red, int m, int n, int splits,
-                     float *ws, size_t ws_bytes);
+                     float *ws, size_t ws_bytes, bool accumulate = false);
 // Winograd F(4x4, 3x3) in one kernel (transformed input and products stay on chip): workspace = the transformed filters
 // only, 36 * round_up(out channels, 64) * reduction channels floats.  Needs reduction channels % 8 == 0.
 bool winograd_fused_applies(const ConvShape &cs, bool adjoint);

@@ -631,9 +631,11 @@ void conv_winograd_wgrad(hipStream_t st, const float *x, const float *dy, float 
         }
         hip_check(hipGetLastError(), "winograd transform launch");
         const int sp = std::min(wp.ranges, wgrad_ranges(cs, gm.T, planes));      // the last chunk may be shorter
-        gemm_tn_batched(st, D, V, img0 == 0 ? dU : share, planes, gm.T, cs.K, cs.C, sp, sp > 1 ? slabs : nullptr,
-                        sp > 1 ? (size_t)sp * wp.filt * sizeof(float) : 0);
-        if (img0 > 0) copy_or_accumulate(st, share, dU, (int64_t)wp.filt, true);
+        // later chunks' shares are added by the kernel that adds their ranges (a launch per chunk less); uncut ones come through `share`
+        const bool add = img0 > 0 && sp > 1;
+        gemm_tn_batched(st, D, V, img0 == 0 || add ? dU : share, planes, gm.T, cs.K, cs.C, sp, sp > 1 ? slabs : nullptr,
+                        sp > 1 ? (size_t)sp * wp.filt * sizeof(float) : 0, add);
+        if (img0 > 0 && !add) copy_or_accumulate(st, share, dU, (int64_t)wp.filt, true);
     }
     const int64_t fe = (int64_t)cs.K * cs.C;
     const dim3 fg((unsigned)((fe + 255) / 256));
