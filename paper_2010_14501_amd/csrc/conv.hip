@@ -339,7 +339,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS, KS == 1 && (WM * WN < 4 || (WM *
     // all indices of work items and reduction steps are 32 bits wide (bounded by the host): a 64-bit division is 150 scalar
     // instructions, and four of them per wave were a microsecond of every tile
     const unsigned tiles = (unsigned)ta.total_tiles;
-    const unsigned item = blockIdx.x % NUM_XCD * (gridDim.x / NUM_XCD) + blockIdx.x / NUM_XCD;
+    // Each GEMM of a batch deals its shares from another XCD on: the shares without an item (12 items in shares of two: the last two) would fall to the same
+    // XCDs 36 times.  Winograd filter gradient, batch 184 of 14x14, 256 -> 256: 230 and 185 us; batch 176 of 56x56, 256 -> 256: 2082 and 2014; where memory bounds
+    // it (112x112, 128 -> 128) level.
+    const unsigned first = MODE == DGRAD ? 0u : blockIdx.z;      // (an input gradient's classes read the same rows: each stays with its XCD)
+    const unsigned item = (blockIdx.x + first) % NUM_XCD * (gridDim.x / NUM_XCD) + blockIdx.x / NUM_XCD;
     if (item >= tiles * (unsigned)nsplit) return;
     const int split = nsplit > 1 ? (int)(item / tiles) : 0;
     const unsigned logical = item - (unsigned)split * tiles;
