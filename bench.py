@@ -18,9 +18,9 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-MFMA_F32_PEAK_TFLOPS = 157.3      # 256 CUs x 256 flop/clk x 2.4 GHz
-# the implicit GEMMs make an fp32 product of six bf16 ones: 256 CUs x 4096 flop/clk x 2.4 GHz / 6
+# the implicit GEMMs make an fp32 product of six bf16 ones: 256 CUs x 4096 flop/clk x 2.4 GHz / 6; the one-kernel Winograd form of three fp16 ones
 MFMA_PIECES_PEAK_TFLOPS = 419.4
+MFMA_F16_PIECES_PEAK_TFLOPS = 838.9
 HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of a kernel class come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs scaled by what the same
 # counters read for a plain copy; counters cannot be read from inside this process, so the figure is the one recorded in
@@ -260,10 +260,10 @@ def main():
         def mfma_entry(c, label):
             # held against the peak: the flop the kernels put on the matrix cores (a Winograd form issues 1/4 to 1/2.25 of
             # the direct form's); `algorithmic` is the direct form's flop per second, the figure the metric counts.
-            # The one-kernel Winograd form runs on fp32 matrix instructions, the workspace form's GEMMs on bf16 pieces: a
-            # Winograd class is held against the lower peak unless it is the filter gradient, which has only the second.
-            fp32 = label in ("conv_fwd_winograd", "conv_dgrad_winograd")
-            peak = MFMA_F32_PEAK_TFLOPS if fp32 else MFMA_PIECES_PEAK_TFLOPS
+            # The one-kernel Winograd form runs on two fp16 pieces per operand, the workspace form's GEMMs on three bf16 pieces: a
+            # Winograd class is held against the higher peak unless it is the filter gradient, which has only the second.
+            two = label in ("conv_fwd_winograd", "conv_dgrad_winograd")
+            peak = MFMA_F16_PIECES_PEAK_TFLOPS if two else MFMA_PIECES_PEAK_TFLOPS
             return {"bound": "mfma", "achieved": c["issued_tflops"], "peak": peak, "unit": "TFLOP/s",
                     "frac": c["issued_tflops"] / peak, "algorithmic": c["tflops"]}
 
