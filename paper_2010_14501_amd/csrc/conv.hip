@@ -279,7 +279,7 @@ __device__ __forceinline__ void write_results(const TileArgs &ta, const floatx16
         }
 }
 
-// TAG only names the use in profiles: 0 a convolution, 1 / 2 / 3 the batched GEMMs of a Winograd forward / input gradient /
+// TAG names the use, in profiles and for the order of a batch's work items: 0 a convolution, 1 / 2 / 3 the batched GEMMs of a Winograd forward / input gradient /
 // filter gradient
 // FAST: 0 element-wise loaders, 1 aligned loaders, 2 aligned loaders of a 1x1 layer whose last reduction step is partly
 // empty (a kernel of its own: the two tests per step would cost the other layers 2 %, measured on ResNet-50), 3 aligned
@@ -342,7 +342,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, KS == 1 && (WM * WN < 4 || (WM *
     // Each GEMM of a batch deals its shares from another XCD on: the shares without an item (12 items in shares of two: the last two) would fall to the same
     // XCDs 36 times.  Winograd filter gradient, batch 184 of 14x14, 256 -> 256: 230 and 185 us; batch 176 of 56x56, 256 -> 256: 2082 and 2014; where memory bounds
     // it (112x112, 128 -> 128) level.
-    const unsigned first = MODE == DGRAD ? 0u : blockIdx.z;      // (an input gradient's classes read the same rows: each stays with its XCD)
+    const unsigned first = MODE == DGRAD || TAG == 0 ? 0u : blockIdx.z;      // (an input gradient's classes read the same rows: each stays with its XCD; a launch
+    // that is no batch has nothing to turn, and without the sum its code is faster: 3x3 stride 2, 128 -> 128, 56x56, batch 184, filter gradient 273 and 269 us)
     const unsigned item = (blockIdx.x + first) % NUM_XCD * (gridDim.x / NUM_XCD) + blockIdx.x / NUM_XCD;
     if (item >= tiles * (unsigned)nsplit) return;
     const int split = nsplit > 1 ? (int)(item / tiles) : 0;
