@@ -18,7 +18,7 @@
 // values are up to a hundred times as large, later chunks may be larger by some tens).  What is left of an operand below 2^-25 in that scale
 // is lost.  Two tests say whether that can show in a result: the 36 sums of a (tile, channel) are all finite (else an operand was an infinity or a
 // NaN, or grew beyond its scale), and the largest of them is at least 2^11 * sqrt(channels) (the lost parts' sum is about 2^-11 * sqrt(channels) at
-// most; random data lie near 2^19 * sqrt(channels)).  A half item that fails is worked once more on the fp32 instruction, with the filters
+// most; random data lie near 2^19 * sqrt(channels)), unless all weights of the channel are zero.  A half item that fails is worked once more on the fp32 instruction, with the filters
 // transformed from the weights on the way.
 //
 // What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512): fp32 form
@@ -49,6 +49,7 @@ constexpr int LDS_WORDS = 36 * FT * MROW;       // 152 064 bytes; the two V buff
 constexpr int WROW = CH + 1;                    // row of the fp32 form's V[z][tile][.]
 static_assert(2 * V_WORDS <= LDS_WORDS && 36 * FT * WROW <= LDS_WORDS, "V buffers must fit");
 constexpr int EMPTY = -1000;                    // scale of a tile without a value other than zero
+constexpr int ZERO_FILTER = -128;               // scale of an output channel without a weight other than zero: its code is 0
 constexpr unsigned CHUNK_BYTES = 2048;          // one (position, 32 output channels, chunk) of the filters: two planes of 64 lanes x 16 bytes
 
 // exponent e of |v| < 2^e for the bits of a float that is not negative (subnormals count as 2^-126)
@@ -77,7 +78,8 @@ __device__ __forceinline__ float max_abs(float m, float a, float b) {
 // Transformed filters in pieces:
 //   Up[z][out / 32][red / 16][piece][lane][j],  lane = 32 * (red % 16 / 8) + out % 32,  j = red % 8
 // `out` runs over the output channels padded to a multiple of 64 (zeros).  The power of two of output channel k, plus 128, lies in the lowest
-// bits of the eight m pieces of (z = 0, chunk 0, channels 0 .. 7): at most 2^-24 of a value of up to 2^14.
+// bits of the eight m pieces of (z = 0, chunk 0, channels 0 .. 7): a unit of m's last place there, 2^-23 of the value or, of values too small for two pieces, 2^-24
+// in the filter's scale.  Code 0 says that the channel has no weight other than zero: its pieces and sums are zeros, and exact.
 // One workgroup: 32 output channels x 16 reduction channels; each finds the largest weight of its channels by itself (a few
 // microseconds; a launch of its own would cost as much, and the workspace has no room for its result).
 // ADJ: forward pass (out = K, red = C) or input gradient (out = C, red = K, filter turned by 180 degrees).
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(512) void wino4_filter_pieces_kernel(const float *_
     if (tid < 32) {
         float mx = 0.0f;
         for (int i = 0; i < 16; ++i) mx = fmaxf(mx, part[i][tid]);
-        scale[tid] = mx > 0.0f ? min(14 - exponent_of(mx), 126) : 0;
+        scale[tid] = mx > 0.0f ? min(14 - exponent_of(mx), 126) : ZERO_FILTER;
     }
     __syncthreads();
     const int ol = tid >> 4, o = ob * 32 + ol, c = ch * CH + (tid & 15);
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(512) void wino4_filter_pieces_kernel(const float *_
     float t[3][6];      // t[s][a] = (G g)[a][s]
 #pragma unroll
     for (int s = 0; s < 3; ++s) f4_g(g[0][s], g[1][s], g[2][s], t[s]);
-    const float sc = power_of_two(scale[ol]);
+    const float sc = scale[ol] == ZERO_FILTER ? 1.0f : power_of_two(scale[ol]);
     const unsigned code = (unsigned)(scale[ol] + 128) >> (c & 7);
     const int lane = 32 * ((c & 15) >> 3) + ol;
 #pragma unroll
@@ -459,7 +461,7 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
         for (int a = 0; a < 4; ++a) sum += (o[a][0] + o[a][1]) + (o[a][2] + o[a][3]);
         const int scale = tinfo[tl].scale;
         const bool exists = kout < gm.outc && tinfo[tl].extent;
-        const bool bad = exists && (!(fabsf(sum) < __builtin_inff()) || (scale != EMPTY && mx < enough));
+        const bool bad = exists && (!(fabsf(sum) < __builtin_inff()) || (scale != EMPTY && fscale != ZERO_FILTER && mx < enough));
         if (__syncthreads_or(bad)) again |= 1u << h;      // the barrier also: everyone has read this half
         else emit(kout, o, (scale == EMPTY ? 0 : scale) + fscale, bn_a, bn_b);
     };

@@ -983,6 +983,36 @@ def test_winograd_on_pieces_with_values_beyond_the_pieces(value):
     assert torch.equal(torch.nan_to_num(fused), torch.nan_to_num(out))
 
 
+def winograd_time(torch, x, w):
+    """Microseconds of the one-kernel forward pass."""
+    dims = (*x.shape, w.shape[0])
+    need = monet.call("monet_conv_winograd_fused_workspace_bytes", *dims, 0)
+    ws, out, xd, wd = torch.empty(need // 4, device="cuda"), torch.empty((*x.shape[:3], w.shape[0]), device="cuda"), dev(x), dev(w)
+    best = float("inf")
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            monet.call("monet_conv_winograd_fused", torch.cuda.current_stream().cuda_stream, xd.data_ptr(), wd.data_ptr(), out.data_ptr(), *dims, 0, 0, ws.data_ptr(), need)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 100)
+    return best
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["zero filters"])
+def test_winograd_on_pieces_takes_ordinary_operands_at_full_speed(kind):
+    """Operands that a network brings do not send work to the second pass: with every part of the launch worked again it takes several times as long."""
+    torch = torch_mod()
+    rng = np.random.default_rng(12)
+    x = np.maximum(rng.standard_normal((64, 28, 28, 64), dtype=np.float32), 0)
+    w = rng.standard_normal((64, 3, 3, 64), dtype=np.float32) * np.float32(0.05)
+    plain = winograd_time(torch, x, w)
+    if kind == "zero filters": w[::32] = 0      # one in each half item
+    assert winograd_time(torch, x, w) < 1.4 * plain + 5
+
+
 IM2COL_CASES = [
     # N, H, W, C, K, R, stride, pad, chunk images (0: the recommended workspace)
     (2, 16, 16, 16, 16, 3, 1, 1, 0),
