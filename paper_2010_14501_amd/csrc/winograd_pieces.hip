@@ -14,11 +14,12 @@
 // 1.0e-6 / 1.1e-6 / 1.7e-6, the fp32 instruction 1.1e-6 / 1.3e-6 / 2.5e-6); below, the pieces' 2^-23 shows and the fp32 form stays.
 //
 // Range.  fp16 reaches from 2^-24 to 2^16, so both operands carry powers of two: a filter one per output channel (its largest weight comes
-// to lie in [2^13, 2^14)), a tile one that its first chunk with a value other than zero sets (that patch's largest value in [2^3, 2^4): transformed
-// values are up to a hundred times as large, later chunks may be larger by some tens).  What is left of an operand below 2^-25 in that scale
+// to lie in [2^13, 2^14)), a tile one that its first chunk with a value other than zero sets (that patch's largest value in [2^5, 2^6); transformed
+// values are up to a hundred times as large).  A later chunk with a value above 2^9 sets it anew, and the waves that multiply take their sums along (a maximum and a flag
+// per chunk: 1301 and 1315 us on the first layer below).  What is left of an operand below 2^-25 in that scale
 // is lost.  Two tests say whether that can show in a result: the 36 sums of a (tile, channel) are all finite (else an operand was an infinity or a
-// NaN, or grew beyond its scale), and the largest of them is at least 2^11 * sqrt(channels) (the lost parts' sum is about 2^-11 * sqrt(channels) at
-// most; random data lie near 2^19 * sqrt(channels)), unless all weights of the channel are zero.  A half item that fails is worked once more on the fp32 instruction, with the filters
+// NaN), and the largest of them is at least 2^11 * sqrt(channels) (the lost parts' sum is about 2^-11 * sqrt(channels) at
+// most; random data lie near 2^21 * sqrt(channels)), unless all weights of the channel are zero.  A half item that fails is worked once more on the fp32 instruction, with the filters
 // transformed from the weights on the way.
 //
 // What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512): fp32 form
@@ -49,6 +50,7 @@ constexpr int LDS_WORDS = 36 * FT * MROW;       // 152 064 bytes; the two V buff
 constexpr int WROW = CH + 1;                    // row of the fp32 form's V[z][tile][.]
 static_assert(2 * V_WORDS <= LDS_WORDS && 36 * FT * WROW <= LDS_WORDS, "V buffers must fit");
 constexpr int EMPTY = -1000;                    // scale of a tile without a value other than zero
+constexpr int TARGET = 6, LIMIT = 9;            // a tile's largest value so far lies in [2^5, 2^6) when its scale is set, and is at most 2^9
 constexpr int ZERO_FILTER = -128;               // scale of an output channel without a weight other than zero: its code is 0
 constexpr unsigned CHUNK_BYTES = 2048;          // one (position, 32 output channels, chunk) of the filters: two planes of 64 lanes x 16 bytes
 
@@ -180,6 +182,13 @@ __device__ __forceinline__ Patch patch_of(const FusedGeom &gm, int64_t tb, int p
 // fours, so that the eight lanes that write a tile's 16 channels meet in no bank.
 __device__ __forceinline__ int v_word(int tile, int half) { return half * (4 * FT) + (tile ^ (half << 2)) * 4; }
 
+// Tiles whose scale a chunk changed, for the waves that multiply it: whether any of the eight tiles of a wave that makes patches, and the power of two by which
+// each one's sums so far are smaller in the new scale.  As many as there are V buffers.
+struct Growth {
+    unsigned any[2][4];
+    float by[2][FT];
+};
+
 struct Ops {      // what a workgroup reads
     __amdgpu_buffer_rsrc_t x, u;
     int nch, o32, ob;
@@ -187,10 +196,10 @@ struct Ops {      // what a workgroup reads
 
 // The reduction loop of a wave that makes the patches of eight tiles: a chunk's patch is transformed, split and left in LDS while the other waves
 // multiply the chunk before.  Returns the scale of the lane's tile.
-__device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, int lane, int pt, const Patch &patch) {
+__device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, Growth &grown, int lane, int pt, const Patch &patch) {
     f2 d[36];
     int scale = EMPTY;
-    float factor = 1.0f;
+    float factor = 1.0f, limit = 0.0f;      // a patch with a value beyond `limit` changes the scale
     auto load_row = [&](const Patch &p, int a, int ch) {
 #pragma unroll
         for (int b = 0; b < 6; ++b)
@@ -198,7 +207,8 @@ __device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, int la
     };
     // Transforms the patch of both channels in place, columns first, and leaves its pieces in V.  A row's registers take the patch of chunk `ch` as
     // soon as its pieces are out: what a load waits for memory passes under the other rows.
-    auto transform_store = [&](unsigned *V, int ch) {
+    auto transform_store = [&](int buf, int ch) {
+        unsigned *V = lds + buf * V_WORDS;
         auto map_row = [&](int i) {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
@@ -208,19 +218,27 @@ __device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, int la
                 for (int k = 0; k < 6; ++k) d[i + k][e] = o[k];
             }
         };
-        if (__any(scale == EMPTY)) {      // uniform over the wave: the first chunk, and tiles that were zero so far
-            float mx = 0.0f;              // the two maps make it a hundred times as large at most
-            asm volatile("" : "+v"(mx));      // behind the branch: the compiler would compute the maximum for every chunk
+        float mx = 0.0f;              // the two maps make it a hundred times as large at most
 #pragma unroll
-            for (int i = 0; i < 36; ++i) mx = max_abs(mx, d[i].x, d[i].y);
+        for (int i = 0; i < 36; ++i) mx = max_abs(mx, d[i].x, d[i].y);
+        unsigned any_grown = 0;
+        if (__any(mx > limit)) {      // uniform over the wave: a tile's first value other than zero, or one that its scale does not hold
             mx = fmaxf(mx, __shfl_xor(mx, 1));      // the eight lanes of a tile
             mx = fmaxf(mx, __shfl_xor(mx, 2));
             mx = fmaxf(mx, __shfl_xor(mx, 4));
-            if (scale == EMPTY && mx > 0.0f) {
-                scale = min(4 - exponent_of(mx), 124);
+            float less = 1.0f;      // what the tile's sums so far are multiplied by
+            if (mx > limit) {
+                const int now = min(TARGET - exponent_of(mx), 124);
+                // (sums that shrink by more than 2^126 are far below the new ones' last place in any case)
+                if (scale != EMPTY) less = power_of_two(max(now - scale, -126));
+                scale = now;
                 factor = power_of_two(scale);
+                limit = power_of_two(min(LIMIT - scale, 127));
             }
+            any_grown = __any(less != 1.0f);
+            if ((lane & 7) == 0) grown.by[buf][pt] = less;
         }
+        if (lane == 0) grown.any[buf][pt >> 3] = any_grown;
         // columns, and the power of two with them: f4_bt with its coefficients times `factor` and three products more
         const float s4 = 4.0f * factor, s5 = -5.0f * factor;
 #pragma unroll
@@ -259,11 +277,11 @@ __device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, int la
 
 #pragma unroll
     for (int a = 0; a < 6; ++a) load_row(patch, a, 0);
-    transform_store(lds, op.nch > 1 ? 1 : 0);
+    transform_store(0, op.nch > 1 ? 1 : 0);
     __syncthreads();
     for (int ch = 0; ch < op.nch; ++ch) {
         // V[next] was last read before the barrier that ended chunk ch - 1
-        if (ch + 1 < op.nch) transform_store(lds + ((ch + 1) & 1) * V_WORDS, ch + 2 < op.nch ? ch + 2 : ch + 1);
+        if (ch + 1 < op.nch) transform_store((ch + 1) & 1, ch + 2 < op.nch ? ch + 2 : ch + 1);
         __syncthreads();
     }
     return scale;
@@ -272,7 +290,7 @@ __device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, int la
 // The reduction loop of a wave that multiplies: NZ positions from z0 on.  HALF: only the block of 32 output channels ob (acc[.][0]), else
 // ob and ob + 1.
 template <bool HALF>
-__device__ __forceinline__ void multiply(const Ops &op, const unsigned *lds, int z0, int lane, floatx16 (&acc)[NZ][2]) {
+__device__ __forceinline__ void multiply(const Ops &op, const unsigned *lds, const Growth &grown, int z0, int lane, floatx16 (&acc)[NZ][2]) {
     const int nch = op.nch;
 #pragma unroll
     for (int zi = 0; zi < NZ; ++zi)
@@ -303,6 +321,27 @@ __device__ __forceinline__ void multiply(const Ops &op, const unsigned *lds, int
     __syncthreads();
     for (int ch = 0; ch < nch; ++ch) {
         const unsigned *V = lds + (ch & 1) * V_WORDS;
+        {
+            // tiles whose scale this chunk changed: rows 8 * wave + 4 * (lane / 32) .. + 3 of the products are registers 4 * wave .. + 3
+            const uint4 a = *(const uint4 *)grown.any[ch & 1];
+            if (__builtin_amdgcn_readfirstlane(a.x | a.y | a.z | a.w)) {
+                const unsigned any[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (__builtin_amdgcn_readfirstlane(any[v])) {
+                        const float4 by = *(const float4 *)&grown.by[ch & 1][8 * v + 4 * (lane >> 5)];
+#pragma unroll
+                        for (int zi = 0; zi < NZ; ++zi)
+#pragma unroll
+                            for (int h = 0; h < (HALF ? 1 : 2); ++h) {
+                                acc[zi][h][4 * v] *= by.x;
+                                acc[zi][h][4 * v + 1] *= by.y;
+                                acc[zi][h][4 * v + 2] *= by.z;
+                                acc[zi][h][4 * v + 3] *= by.w;
+                            }
+                    }
+            }
+        }
         const int nx = ch + 1 < nch ? ch + 1 : ch;      // the last chunk requests filters that exist (its own) instead of branching; nothing reads them
 #pragma unroll
         for (int zi = 0; zi < NZ; ++zi) {
@@ -346,6 +385,7 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
                                                            FusedGeom gm, BnAffine bn) {
     __shared__ __attribute__((aligned(16))) unsigned lds[LDS_WORDS];
     __shared__ TileInfo tinfo[FT];
+    __shared__ __attribute__((aligned(16))) Growth grown;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // the same for the whole wave: kept in a scalar register
     FusedItem it;
@@ -357,14 +397,14 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
     const bool makes = wave >= MUL_WAVES;
     const int z0 = NZ * wave;
     if (!makes) {
-        if (it.nh == 2) multiply<false>(op, lds, z0, lane, acc);
-        else multiply<true>(op, lds, z0, lane, acc);
+        if (it.nh == 2) multiply<false>(op, lds, grown, z0, lane, acc);
+        else multiply<true>(op, lds, grown, z0, lane, acc);
     } else {
         // lane = 8 * (tile % 8) + channel / 2: eight neighbouring lanes read 64 bytes
         const int pt = (wave - MUL_WAVES) * 8 + (lane >> 3);
         const bool first = (lane & 7) == 0;
         const Patch patch = patch_of(gm, it.tb, pt, 2 * (lane & 7), first ? &tinfo[pt] : nullptr);
-        const int scale = make_patches(op, lds, lane, pt, patch);
+        const int scale = make_patches(op, lds, grown, lane, pt, patch);
         if (first) tinfo[pt].scale = scale;      // read behind the first barrier below
     }
 

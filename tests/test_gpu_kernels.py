@@ -1001,7 +1001,7 @@ def winograd_time(torch, x, w):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind", ["zero filters"])
+@pytest.mark.parametrize("kind", ["zero filters", "small channels first", "channels grow"])
 def test_winograd_on_pieces_takes_ordinary_operands_at_full_speed(kind):
     """Operands that a network brings do not send work to the second pass: with every part of the launch worked again it takes several times as long."""
     torch = torch_mod()
@@ -1010,6 +1010,8 @@ def test_winograd_on_pieces_takes_ordinary_operands_at_full_speed(kind):
     w = rng.standard_normal((64, 3, 3, 64), dtype=np.float32) * np.float32(0.05)
     plain = winograd_time(torch, x, w)
     if kind == "zero filters": w[::32] = 0      # one in each half item
+    if kind == "small channels first": x[..., :16] *= np.float32(1 / 200)
+    if kind == "channels grow": x *= np.repeat(np.array([1e-2, 1, 1e2, 1e4], np.float32), 16)
     assert winograd_time(torch, x, w) < 1.4 * plain + 5
 
 
