@@ -18,8 +18,10 @@
 // values are up to a hundred times as large).  A later chunk with a value above 2^9 sets it anew, and the waves that multiply take their sums along (a maximum and a flag
 // per chunk: 1301 and 1315 us on the first layer below).  What is left of an operand below 2^-25 in that scale
 // is lost.  Two tests say whether that can show in a result: the 36 sums of a (tile, channel) are all finite (else an operand was an infinity or a
-// NaN), and the largest of them is at least 2^11 * sqrt(channels) (the lost parts' sum is about 2^-11 * sqrt(channels) at
-// most; random data lie near 2^21 * sqrt(channels)), unless all weights of the channel are zero.  A half item that fails is worked once more on the fp32 instruction, with the filters
+// NaN), and the largest of them is at least 2^20 times what the lost parts can add up to, unless all weights of the channel are zero.  That is, for n channels
+// of which the tile has a value other than zero and a largest value a (scaled): n * 2^-25 * (2^14 + 100 a), all signs alike; dense random data lie near 2^21 * sqrt(n), a
+// hundred times above the bound at 512 channels.  (One bound for all tiles, 2^11 * sqrt(all channels), was one that signs alike could break by sqrt(channels), and sent most
+// launches with less than 0.5 % of the values present to the second pass: a tile with two such values has small sums that nothing is lost from.)  A half item that fails is worked once more on the fp32 instruction, with the filters
 // transformed from the weights on the way.
 //
 // What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512): fp32 form
@@ -149,8 +151,8 @@ struct Patch { unsigned col[6], row[6]; };
 __device__ __forceinline__ unsigned patch_at(const Patch &p, int a, int b) { return __builtin_elementwise_add_sat(p.col[b], p.row[a]); }
 
 // tinfo[tile] = {byte offset of output element (image, 4 * ti, 4 * tj, channel 0), rows | columns << 8 of the 4x4 output tile
-// that lie inside the map (0 for a tile beyond the last one), scale}
-struct TileInfo { unsigned off, extent; int scale; };
+// that lie inside the map (0 for a tile beyond the last one), scale, what a channel's largest sum has to reach}
+struct TileInfo { unsigned off, extent; int scale; float enough; };
 
 __device__ __forceinline__ Patch patch_of(const FusedGeom &gm, int64_t tb, int pt, int channel, TileInfo *info) {
     Patch p;
@@ -195,10 +197,11 @@ struct Ops {      // what a workgroup reads
 };
 
 // The reduction loop of a wave that makes the patches of eight tiles: a chunk's patch is transformed, split and left in LDS while the other waves
-// multiply the chunk before.  Returns the scale of the lane's tile.
-__device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, Growth &grown, int lane, int pt, const Patch &patch) {
+// multiply the chunk before.  Leaves the scale of the lane's tile and what its sums have to reach.
+__device__ __forceinline__ void make_patches(const Ops &op, unsigned *lds, Growth &grown, int lane, int pt, const Patch &patch, TileInfo &info) {
     f2 d[36];
-    int scale = EMPTY;
+    int scale = EMPTY, present = 0;      // `present`: the lane's chunks with a value other than zero
+    float largest = 0.0f;
     float factor = 1.0f, limit = 0.0f;      // a patch with a value beyond `limit` changes the scale
     auto load_row = [&](const Patch &p, int a, int ch) {
 #pragma unroll
@@ -221,6 +224,8 @@ __device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, Growth
         float mx = 0.0f;              // the two maps make it a hundred times as large at most
 #pragma unroll
         for (int i = 0; i < 36; ++i) mx = max_abs(mx, d[i].x, d[i].y);
+        present += mx > 0.0f;
+        largest = fmaxf(largest, mx);
         unsigned any_grown = 0;
         if (__any(mx > limit)) {      // uniform over the wave: a tile's first value other than zero, or one that its scale does not hold
             mx = fmaxf(mx, __shfl_xor(mx, 1));      // the eight lanes of a tile
@@ -284,7 +289,15 @@ __device__ __forceinline__ int make_patches(const Ops &op, unsigned *lds, Growth
         if (ch + 1 < op.nch) transform_store((ch + 1) & 1, ch + 2 < op.nch ? ch + 2 : ch + 1);
         __syncthreads();
     }
-    return scale;
+#pragma unroll
+    for (int i = 1; i < 8; i *= 2) {
+        present += __shfl_xor(present, i);
+        largest = fmaxf(largest, __shfl_xor(largest, i));
+    }
+    if ((lane & 7) == 0) {      // read behind the caller's next barrier
+        info.scale = scale;
+        info.enough = (float)(2 * present) * 0x1p-5f * (0x1p14f + 100.0f * (largest * factor));      // (an infinity fails the other test)
+    }
 }
 
 // The reduction loop of a wave that multiplies: NZ positions from z0 on.  HALF: only the block of 32 output channels ob (acc[.][0]), else
@@ -404,8 +417,7 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
         const int pt = (wave - MUL_WAVES) * 8 + (lane >> 3);
         const bool first = (lane & 7) == 0;
         const Patch patch = patch_of(gm, it.tb, pt, 2 * (lane & 7), first ? &tinfo[pt] : nullptr);
-        const int scale = make_patches(op, lds, grown, lane, pt, patch);
-        if (first) tinfo[pt].scale = scale;      // read behind the first barrier below
+        make_patches(op, lds, grown, lane, pt, patch, tinfo[pt]);
     }
 
     // ---- output transform, 32 channels at a time: thread = (channel ok_ of the half, tile tl).  Output element
@@ -479,7 +491,6 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
         if (EPI == 2 && kout < gm.outc) bn_affine_coeffs(bn.gamma, bn.beta, bn.stats, gm.outc, kout, a, b);
     };
 
-    const float enough = 2048.0f * sqrtf((float)gm.red);
     unsigned again = 0;      // halves whose pieces do not hold their numbers
     auto finish = [&](auto half) {
         constexpr int h = decltype(half)::value;
@@ -501,7 +512,7 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
         for (int a = 0; a < 4; ++a) sum += (o[a][0] + o[a][1]) + (o[a][2] + o[a][3]);
         const int scale = tinfo[tl].scale;
         const bool exists = kout < gm.outc && tinfo[tl].extent;
-        const bool bad = exists && (!(fabsf(sum) < __builtin_inff()) || (scale != EMPTY && fscale != ZERO_FILTER && mx < enough));
+        const bool bad = exists && (!(fabsf(sum) < __builtin_inff()) || (scale != EMPTY && fscale != ZERO_FILTER && mx < tinfo[tl].enough));
         if (__syncthreads_or(bad)) again |= 1u << h;      // the barrier also: everyone has read this half
         else emit(kout, o, (scale == EMPTY ? 0 : scale) + fscale, bn_a, bn_b);
     };

@@ -929,12 +929,18 @@ def pieces_operands(kind):
     if kind == "zero image": x[1] = 0
     if kind == "zero filters": w[3:9] = 0
     if kind == "sparse": x *= rng.random(x.shape) < 0.002
+    if kind == "dominant weight":      # every product but one channel's lies below what the pieces hold, all of one sign
+        x[..., 5] *= np.float32(0.92 * 2.0 ** -5)
+        x[..., :5], x[..., 6:16], x[..., 16:] = 1, 1, 15.99
+        w[...] = 0.999 * 2.0 ** -36
+        w[..., 5] = 0
+        w[:, 2, 2, 5] = 1
     return x, w
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["plain", "tiny", "huge", "tiny filters", "both small", "images apart", "filters apart", "zero chunk first", "growing chunks",
-                                  "channels apart, filters against", "zero image", "zero filters", "sparse"])
+                                  "channels apart, filters against", "zero image", "zero filters", "sparse", "dominant weight"])
 def test_winograd_on_pieces_keeps_the_range_of_fp32(kind):
     """Scales that fp16 pieces cannot hold: every image and every output channel is as close to 64 bits as the fp32 form, whose error
     is relative to the products' sizes: 4e-6 of |x| * |w| for each (image, channel), plus fp32's smallest number per output."""
