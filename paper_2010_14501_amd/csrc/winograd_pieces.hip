@@ -21,8 +21,11 @@
 // NaN), and the largest of them is at least 2^20 times what the lost parts can add up to, unless all weights of the channel are zero.  That is, for n channels
 // of which the tile has a value other than zero and a largest value a (scaled): n * 2^-25 * (2^14 + 100 a), all signs alike; dense random data lie near 2^21 * sqrt(n), a
 // hundred times above the bound at 512 channels.  (One bound for all tiles, 2^11 * sqrt(all channels), was one that signs alike could break by sqrt(channels), and sent most
-// launches with less than 0.5 % of the values present to the second pass: a tile with two such values has small sums that nothing is lost from.)  A half item that fails is worked once more on the fp32 instruction, with the filters
-// transformed from the weights on the way.
+// launches with less than 0.5 % of the values present to the second pass: a tile with two such values has small sums that nothing is lost from.)  A half item that fails is worked once more on the fp32
+// instruction, patches and filters transformed into LDS a chunk at a time.  What that costs with every half item affected: first layer below 1308 -> 3833 us, second
+// 109 -> 333 (the fp32 form, which takes both halves from one transform and its filters from the workspace: 2187 and 206).  Ordinary operands stay clear of it: 0.3 % of the
+// values present, filters of zeros, channels of very different size.  Those that do not: large inputs that meet weights of almost nothing, or of nothing at all (a
+// network with most of its filter planes pruned: sums of zero, which cannot be told from lost ones).
 //
 // What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512): fp32 form
 // 2187 / 206 / 174 / 1926, this one 1344 / 108 / 102 / 1089.  A chunk takes 3.2 us where its matrix instructions alone take 1.3 (measured with the
@@ -49,8 +52,8 @@ constexpr int THREADS = 64 * (MUL_WAVES + 4);
 constexpr int V_WORDS = 36 * 2 * FT * CH / 2;   // one V buffer: [z][piece][channels 8g .. 8g+7][tile][4 words of two channels]
 constexpr int MROW = 33;                        // row of M[z][tile][.] in LDS
 constexpr int LDS_WORDS = 36 * FT * MROW;       // 152 064 bytes; the two V buffers take the first 147 456
-constexpr int WROW = CH + 1;                    // row of the fp32 form's V[z][tile][.]
-static_assert(2 * V_WORDS <= LDS_WORDS && 36 * FT * WROW <= LDS_WORDS, "V buffers must fit");
+constexpr int WROW = 33, WZ = 2 * CH * WROW;    // second pass: row of V[z][channel][tile] and U[z][channel][output channel], one behind the other for each z
+static_assert(2 * V_WORDS <= LDS_WORDS && 36 * WZ <= LDS_WORDS, "V buffers must fit");
 constexpr int EMPTY = -1000;                    // scale of a tile without a value other than zero
 constexpr int TARGET = 6, LIMIT = 9;            // a tile's largest value so far lies in [2^5, 2^6) when its scale is set, and is at most 2^9
 constexpr int ZERO_FILTER = -128;               // scale of an output channel without a weight other than zero: its code is 0
@@ -376,22 +379,6 @@ __device__ __forceinline__ void multiply(const Ops &op, const unsigned *lds, con
     }
 }
 
-// Transformed filter at position (a, b) of the 6x6 tile: one value of G g G^T
-template <bool ADJ>
-__device__ __forceinline__ float filter_at(const float *w, int K, int C, int o, int c, const float (&ga)[3], const float (&gb)[3]) {
-    if (o >= (ADJ ? C : K)) return 0.0f;
-    float u = 0.0f;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        float t = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-            t = __builtin_fmaf(ga[r], ADJ ? w[((int64_t)c * 9 + (2 - r) * 3 + (2 - s)) * C + o] : w[((int64_t)o * 9 + r * 3 + s) * C + c], t);
-        u = __builtin_fmaf(gb[s], t, u);
-    }
-    return u;
-}
-
 // ADJ: input gradient.  EPI: 0 plain store, 1 added to what is there, 2 followed by the BatchNorm multiply-add.
 template <bool ADJ, int EPI>
 __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__restrict__ x, const float *__restrict__ Up, const float *__restrict__ w, float *y,
@@ -520,55 +507,89 @@ __global__ __launch_bounds__(THREADS) void wino4_pieces_kernel(const float *__re
     finish(std::integral_constant<int, 1>{});
     if (!again) return;
 
-    // ---- on the fp32 instruction, one half at a time and nothing overlapped: such tiles are rare
-    static constexpr float G[6][3] = {{0.25f, 0, 0}, {-1.0f / 6, -1.0f / 6, -1.0f / 6}, {-1.0f / 6, 1.0f / 6, -1.0f / 6},
-                                      {1.0f / 24, 1.0f / 12, 1.0f / 6}, {1.0f / 24, -1.0f / 12, 1.0f / 6}, {0, 0, 1}};
-    const int wt = (tid >> 4) & (FT - 1), wc = tid & 15;      // the first half of the threads makes the patch of one (tile, channel) each
-    const Patch patch = patch_of(gm, it.tb, wt, wc, nullptr);
-    for (int h = 0; h < 2; ++h) {
-        if (!((again >> h) & 1u)) continue;
-        const int ob = it.ob + h;
+    // ---- on the fp32 instruction, one half at a time.  Threads 0 .. 511 transform the patch of one (tile, channel) of a chunk each, the others one filter; both
+    // load the next chunk's while twelve waves multiply.
+    const int t512 = tid & (FT * CH - 1);
+    const int pt = t512 >> 4, pc = t512 & 15;                                          // patches: 16 lanes read 64 bytes of a pixel
+    const int uo = ADJ ? t512 & 31 : t512 >> 4, uc = ADJ ? t512 >> 5 : t512 & 15;      // filters: neighbouring lanes read neighbouring weights
+    const unsigned w_ch = ADJ ? 9u * gm.outc * 4u : 4u, w_tap = (ADJ ? gm.outc : gm.red) * 4u;      // bytes from channel to channel and from tap to tap
+    const __amdgpu_buffer_rsrc_t rw = buffer_of(w, 9u * gm.outc * gm.red * 4u);
+    const int put = wave >= FT * CH / 64 ? (CH + uc) * WROW + uo : pc * WROW + pt;
+    auto reduce = [&](auto role, int ob) {      // the chunks of block ob of 32 output channels; every wave passes the same barriers
+        constexpr bool FILTERS = decltype(role)::value;
+        Patch patch;
+        unsigned w_at = 0;
+        if constexpr (!FILTERS) patch = patch_of(gm, it.tb, pt, pc, nullptr);
+        else if (ob * 32 + uo < gm.outc) w_at = (unsigned)(ob * 32 + uo) * (ADJ ? 4u : 9u * gm.red * 4u) + uc * w_ch;
+        else w_at = ABSENT;
+        float d[FILTERS ? 9 : 36];
+        auto load = [&](int ch) {
+            if constexpr (!FILTERS) {
 #pragma unroll
-        for (int zi = 0; zi < NZ; ++zi)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[zi][0][i] = 0.0f;
-        for (int ch = 0; ch < gm.nch; ++ch) {
-            __syncthreads();      // the products of the chunk before, or the outputs of the half before, have been read
-            if (tid < FT * CH) {
-                float d[36];
+                for (int a = 0; a < 6; ++a) asm volatile("" : "+v"(patch.row[a]));      // the 36 sums are made here, as above
 #pragma unroll
                 for (int a = 0; a < 6; ++a)
 #pragma unroll
                     for (int b = 0; b < 6; ++b) d[a * 6 + b] = buffer_load(op.x, patch_at(patch, a, b), ch * (CH * 4));
-                float m[6][6];      // m[b][a] = (B^T d)[a][b]
+            } else {
 #pragma unroll
-                for (int b = 0; b < 6; ++b) f4_bt(d[b], d[6 + b], d[12 + b], d[18 + b], d[24 + b], d[30 + b], m[b]);
+                for (int i = 0; i < 9; ++i) d[i] = buffer_load(rw, w_at, ch * CH * w_ch + (ADJ ? 8 - i : i) * w_tap);
+            }
+        };
+#pragma unroll
+        for (int zi = 0; zi < NZ; ++zi)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[zi][0][i] = 0.0f;
+        load(0);
+        for (int ch = 0; ch < gm.nch; ++ch) {
+            int at = put;
+            asm volatile("" : "+v"(at));      // not an address per position kept over the loop
+            __syncthreads();      // the products of the chunk before, or the outputs of the half before, have been read
+            if constexpr (!FILTERS) {
+                float o[6];
+#pragma unroll
+                for (int b = 0; b < 6; ++b) {
+                    f4_bt(d[b], d[6 + b], d[12 + b], d[18 + b], d[24 + b], d[30 + b], o);
+#pragma unroll
+                    for (int a = 0; a < 6; ++a) d[6 * a + b] = o[a];
+                }
 #pragma unroll
                 for (int a = 0; a < 6; ++a) {
-                    float o[6];
-                    f4_bt(m[0][a], m[1][a], m[2][a], m[3][a], m[4][a], m[5][a], o);
+                    f4_bt(d[6 * a], d[6 * a + 1], d[6 * a + 2], d[6 * a + 3], d[6 * a + 4], d[6 * a + 5], o);
 #pragma unroll
-                    for (int b = 0; b < 6; ++b) M[((6 * a + b) * FT + wt) * WROW + wc] = o[b];
+                    for (int b = 0; b < 6; ++b) M[at + (6 * a + b) * WZ] = o[b];
+                }
+            } else {
+                float t[3][6];      // t[s][a] = (G g)[a][s]
+#pragma unroll
+                for (int s = 0; s < 3; ++s) f4_g(d[s], d[3 + s], d[6 + s], t[s]);
+#pragma unroll
+                for (int a = 0; a < 6; ++a) {
+                    float u[6];
+                    f4_g(t[0][a], t[1][a], t[2][a], u);
+#pragma unroll
+                    for (int b = 0; b < 6; ++b) M[at + (6 * a + b) * WZ] = u[b];
                 }
             }
+            load(ch + 1 < gm.nch ? ch + 1 : ch);      // the last chunk loads its own again instead of branching
             __syncthreads();
+            if (makes) continue;
 #pragma unroll
             for (int zi = 0; zi < NZ; ++zi) {
-                if (makes) continue;
-                const int z = z0 + zi;
-                float ga[3], gb[3];
 #pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    ga[r] = G[z / 6][r];
-                    gb[r] = G[z % 6][r];
-                }
-#pragma unroll 2
                 for (int j = 0; j < CH / 2; ++j) {
-                    const float u = filter_at<ADJ>(w, ADJ ? gm.red : gm.outc, ADJ ? gm.outc : gm.red, ob * 32 + l32, ch * CH + 2 * j + g, ga, gb);
-                    acc[zi][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(M[(z * FT + l32) * WROW + 2 * j + g], u, acc[zi][0], 0, 0, 0);
+                    const float *from = M + (z0 + zi) * WZ + (2 * j + g) * WROW + l32;
+                    acc[zi][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(from[0], from[CH * WROW], acc[zi][0], 0, 0, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+    };
+    for (int h = 0; h < 2; ++h) {
+        if (!((again >> h) & 1u)) continue;
+        const int ob = it.ob + h;
+        if (wave < FT * CH / 64) reduce(std::false_type{}, ob);
+        else reduce(std::true_type{}, ob);
         __syncthreads();
         stage(std::integral_constant<int, 0>{});
         __syncthreads();
