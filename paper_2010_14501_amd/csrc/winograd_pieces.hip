@@ -16,7 +16,7 @@
 // Range.  fp16 reaches from 2^-24 to 2^16, so both operands carry powers of two: a filter one per output channel (its largest weight comes
 // to lie in [2^13, 2^14)), a tile one that its first chunk with a value other than zero sets (that patch's largest value in [2^5, 2^6); transformed
 // values are up to a hundred times as large).  A later chunk with a value above 2^9 sets it anew, and the waves that multiply take their sums along (a maximum and a flag
-// per chunk: 1301 and 1315 us on the first layer below).  What is left of an operand below 2^-25 in that scale
+// per chunk: 1247 and 1261 us on the first layer below, 104.1 and 106.2 on the second).  What is left of an operand below 2^-25 in that scale
 // is lost.  Two tests say whether that can show in a result: the 36 sums of a (tile, channel) are all finite (else an operand was an infinity or a
 // NaN), and the largest of them is at least 2^20 times what the lost parts can add up to, unless all weights of the channel are zero.  That is, for n channels
 // of which the tile has a value other than zero and a largest value a (scaled): n * 2^-25 * (2^14 + 100 a), all signs alike; dense random data lie near 2^21 * sqrt(n), a
@@ -337,26 +337,23 @@ __device__ __forceinline__ void multiply(const Ops &op, const unsigned *lds, con
     __syncthreads();
     for (int ch = 0; ch < nch; ++ch) {
         const unsigned *V = lds + (ch & 1) * V_WORDS;
-        {
-            // tiles whose scale this chunk changed: rows 8 * wave + 4 * (lane / 32) .. + 3 of the products are registers 4 * wave .. + 3
-            const uint4 a = *(const uint4 *)grown.any[ch & 1];
-            if (__builtin_amdgcn_readfirstlane(a.x | a.y | a.z | a.w)) {
-                const unsigned any[4] = {a.x, a.y, a.z, a.w};
+        const unsigned any = grown.any[ch & 1][lane & 3];
+        // tiles whose scale this chunk changed: rows 8 * wave + 4 * (lane / 32) .. + 3 of the products are registers 4 * wave .. + 3
+        if (const unsigned long long changed = __ballot(any != 0)) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (__builtin_amdgcn_readfirstlane(any[v])) {
-                        const float4 by = *(const float4 *)&grown.by[ch & 1][8 * v + 4 * (lane >> 5)];
+            for (int v = 0; v < 4; ++v)
+                if ((changed >> v) & 1u) {
+                    const float4 by = *(const float4 *)&grown.by[ch & 1][8 * v + 4 * (lane >> 5)];
 #pragma unroll
-                        for (int zi = 0; zi < NZ; ++zi)
+                    for (int zi = 0; zi < NZ; ++zi)
 #pragma unroll
-                            for (int h = 0; h < (HALF ? 1 : 2); ++h) {
-                                acc[zi][h][4 * v] *= by.x;
-                                acc[zi][h][4 * v + 1] *= by.y;
-                                acc[zi][h][4 * v + 2] *= by.z;
-                                acc[zi][h][4 * v + 3] *= by.w;
-                            }
-                    }
-            }
+                        for (int h = 0; h < BLOCKS; ++h) {
+                            acc[zi][h][4 * v] *= by.x;
+                            acc[zi][h][4 * v + 1] *= by.y;
+                            acc[zi][h][4 * v + 2] *= by.z;
+                            acc[zi][h][4 * v + 3] *= by.w;
+                        }
+                }
         }
         const int nx = ch + 1 < nch ? ch + 1 : ch;      // the last chunk requests filters that exist (its own) instead of branching; nothing reads them
 #pragma unroll
