@@ -57,6 +57,7 @@ static_assert(2 * V_WORDS <= LDS_WORDS && 36 * WZ <= LDS_WORDS, "V buffers must 
 constexpr int EMPTY = -1000;                    // scale of a tile without a value other than zero
 constexpr int TARGET = 6, LIMIT = 9;            // a tile's largest value so far lies in [2^5, 2^6) when its scale is set, and is at most 2^9
 constexpr int ZERO_FILTER = -128;               // scale of an output channel without a weight other than zero: its code is 0
+constexpr int FILTER_WORKGROUPS = 2 * FUSED_CUS;
 constexpr unsigned CHUNK_BYTES = 2048;          // one (position, 32 output channels, chunk) of the filters: two planes of 64 lanes x 16 bytes
 
 // exponent e of |v| < 2^e for the bits of a float that is not negative (subnormals count as 2^-126)
@@ -88,14 +89,16 @@ __device__ __forceinline__ float max_abs(float m, float a, float b) {
 // bits of the eight m pieces of (z = 0, chunk 0, channels 0 .. 7): a unit of m's last place there, 2^-23 of the value or, of values too small for two pieces, 2^-24
 // in the filter's scale.  Code 0 says that the channel has no weight other than zero: its pieces and sums are zeros, and exact.
 // One workgroup: 32 output channels x 16 reduction channels; each finds the largest weight of its channels by itself (a few
-// microseconds; a launch of its own would cost as much, and the workspace has no room for its result).
+// microseconds; a launch of its own would cost as much, and the workspace has no room for its result).  LONG: `chunks` times as many reduction channels, for layers
+// that give the CUs two workgroups each all the same: the largest weights are read once per workgroup, 19 GB at 2048 -> 2048 channels, 7x7, batch 1, with one chunk each
+// (1371 us; 781 so, the fp32 form 1000; 1024 -> 1024, 26x38, batch 11: 544 and 490).
 // ADJ: forward pass (out = K, red = C) or input gradient (out = C, red = K, filter turned by 180 degrees).
-template <bool ADJ>
-__global__ __launch_bounds__(512) void wino4_filter_pieces_kernel(const float *__restrict__ w, unsigned short *__restrict__ Up, int K, int C, int o32) {
+template <bool ADJ, bool LONG>
+__global__ __launch_bounds__(512) void wino4_filter_pieces_kernel(const float *__restrict__ w, unsigned short *__restrict__ Up, int K, int C, int o32, int chunks) {
     __shared__ float part[16][32];
     __shared__ int scale[32];
-    const int outc = ADJ ? C : K, red = ADJ ? K : C, nch = red / CH;
-    const int ob = blockIdx.x / nch, ch = blockIdx.x - ob * nch, tid = threadIdx.x;
+    const int outc = ADJ ? C : K, red = ADJ ? K : C, nch = red / CH, groups = LONG ? (nch + chunks - 1) / chunks : nch;
+    const int ob = blockIdx.x / groups, first = (blockIdx.x - ob * groups) * (LONG ? chunks : 1), tid = threadIdx.x;
     const int len = 9 * red;      // weights of one output channel
     {
         // forward: a row of w; 16 lanes share it.  Input gradient: a column of w seen as [9 * red][C]; 32 lanes read neighbouring columns.
@@ -116,32 +119,35 @@ __global__ __launch_bounds__(512) void wino4_filter_pieces_kernel(const float *_
         scale[tid] = mx > 0.0f ? min(14 - exponent_of(mx), 126) : ZERO_FILTER;
     }
     __syncthreads();
-    const int ol = tid >> 4, o = ob * 32 + ol, c = ch * CH + (tid & 15);
-    float g[3][3];
+    const int ol = tid >> 4, o = ob * 32 + ol, last = LONG ? min(first + chunks, nch) : first + 1;
+    for (int ch = first; ch < last; ++ch) {
+        const int c = ch * CH + (tid & 15);
+        float g[3][3];
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+        for (int r = 0; r < 3; ++r)
 #pragma unroll
-        for (int s = 0; s < 3; ++s)
-            g[r][s] = o >= outc ? 0.0f : (ADJ ? w[((int64_t)c * 9 + (2 - r) * 3 + (2 - s)) * C + o] : w[((int64_t)o * 9 + r * 3 + s) * C + c]);
-    float t[3][6];      // t[s][a] = (G g)[a][s]
+            for (int s = 0; s < 3; ++s)
+                g[r][s] = o >= outc ? 0.0f : (ADJ ? w[((int64_t)c * 9 + (2 - r) * 3 + (2 - s)) * C + o] : w[((int64_t)o * 9 + r * 3 + s) * C + c]);
+        float t[3][6];      // t[s][a] = (G g)[a][s]
 #pragma unroll
-    for (int s = 0; s < 3; ++s) f4_g(g[0][s], g[1][s], g[2][s], t[s]);
-    const float sc = scale[ol] == ZERO_FILTER ? 1.0f : power_of_two(scale[ol]);
-    const unsigned code = (unsigned)(scale[ol] + 128) >> (c & 7);
-    const int lane = 32 * ((c & 15) >> 3) + ol;
+        for (int s = 0; s < 3; ++s) f4_g(g[0][s], g[1][s], g[2][s], t[s]);
+        const float sc = scale[ol] == ZERO_FILTER ? 1.0f : power_of_two(scale[ol]);
+        const unsigned code = (unsigned)(scale[ol] + 128) >> (c & 7);
+        const int lane = 32 * ((c & 15) >> 3) + ol;
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
-        float u[6];
-        f4_g(t[0][a], t[1][a], t[2][a], u);
+        for (int a = 0; a < 6; ++a) {
+            float u[6];
+            f4_g(t[0][a], t[1][a], t[2][a], u);
 #pragma unroll
-        for (int b = 0; b < 6; ++b) {
-            const int z = 6 * a + b;
-            const Pieces16 p = split16(u[b] * sc, 0.0f);
-            unsigned short m = (unsigned short)word_of(p.m);
-            if (z == 0 && c < 8) m = (unsigned short)((m & ~1u) | (code & 1u));
-            unsigned short *at = Up + ((((int64_t)z * o32 + ob) * nch + ch) * 2 * 64 + lane) * 8 + (c & 7);
-            at[0] = (unsigned short)word_of(p.h);
-            at[64 * 8] = m;
+            for (int b = 0; b < 6; ++b) {
+                const int z = 6 * a + b;
+                const Pieces16 p = split16(u[b] * sc, 0.0f);
+                unsigned short m = (unsigned short)word_of(p.m);
+                if (z == 0 && c < 8) m = (unsigned short)((m & ~1u) | (code & 1u));
+                unsigned short *at = Up + ((((int64_t)z * o32 + ob) * nch + ch) * 2 * 64 + lane) * 8 + (c & 7);
+                at[0] = (unsigned short)word_of(p.h);
+                at[64 * 8] = m;
+            }
         }
     }
 }
@@ -611,13 +617,14 @@ void conv_winograd_pieces(hipStream_t st, const float *in, const float *w, float
     FusedGeom gm;
     const int64_t grid = fused_geometry(gm, cs, adjoint, CH);
     const int o32 = gm.kblocks * 2;
-    const dim3 fg((unsigned)(o32 * gm.nch)), fwg(512), wg(THREADS), gd((unsigned)grid);
+    const int chunks = std::max(1, (int)((int64_t)o32 * gm.nch / FILTER_WORKGROUPS));
+    const dim3 fg((unsigned)(o32 * ((gm.nch + chunks - 1) / chunks))), fwg(512), wg(THREADS), gd((unsigned)grid);
     if (adjoint) {
-        hipLaunchKernelGGL(wino4_filter_pieces_kernel<true>, fg, fwg, 0, st, w, (unsigned short *)ws, cs.K, cs.C, o32);
+        hipLaunchKernelGGL((chunks > 1 ? wino4_filter_pieces_kernel<true, true> : wino4_filter_pieces_kernel<true, false>), fg, fwg, 0, st, w, (unsigned short *)ws, cs.K, cs.C, o32, chunks);
         if (accumulate) hipLaunchKernelGGL((wino4_pieces_kernel<true, 1>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
         else hipLaunchKernelGGL((wino4_pieces_kernel<true, 0>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
     } else {
-        hipLaunchKernelGGL(wino4_filter_pieces_kernel<false>, fg, fwg, 0, st, w, (unsigned short *)ws, cs.K, cs.C, o32);
+        hipLaunchKernelGGL((chunks > 1 ? wino4_filter_pieces_kernel<false, true> : wino4_filter_pieces_kernel<false, false>), fg, fwg, 0, st, w, (unsigned short *)ws, cs.K, cs.C, o32, chunks);
         if (bn.gamma) hipLaunchKernelGGL((wino4_pieces_kernel<false, 2>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
         else if (accumulate) hipLaunchKernelGGL((wino4_pieces_kernel<false, 1>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
         else hipLaunchKernelGGL((wino4_pieces_kernel<false, 0>), gd, wg, 0, st, in, (const float *)ws, w, out, gm, bn);
