@@ -1584,11 +1584,7 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // against narrow: 9016 tiles (56x56), 5 steps 187 and 205 us, 8 steps 282 and 328; 2254 (28x28), 6 steps 57 and 60, 8 steps 66 and 76; 564
 // (14x14), level from 2 to 16 steps.  A reduction cut into
 // ranges fills it anyway.  `straddle`: reduction steps that cross filter taps.
-// Results of up to 32 columns leave half of the 128x64 tile's matrix instructions to columns that do not exist.  6: 128x32, two waves per workgroup, where
-// workgroups are many and the reduction is more than memory: 3x3, 64 -> 32, 90x90, batch 16 (1013 workgroups, 36 steps): 61 and 48 us; its mirror's input gradient 69
-// and 50; 5x5, 32 -> 96, 28x28, batch 320, input gradient 416 and 365; 3x3, 8 -> 32, 112x112, batch 8: 18 and 14.  Half as many waves per workgroup lose where
-// there are few (5x5, 24 -> 64, 14x14, batch 320, input gradient, 490 of them: 91 and 95; 3x3 stride 2, 32 -> 32, 56x56, batch 64, 392: 19 and 22), and 1x1 layers of
-// up to 12 steps, which move memory, are level or lose (192 -> 32, 28x28, batch 272: 39 and 41).
+// Results of up to 32 columns leave half of the 128x64 tile's matrix instructions to columns that do not exist.  6: 128x32, two waves per workgroup (narrow_tile below).
 // 7: 64x128 for cut 1x1 layers of at most 64 rows (a small batch's fully connected layer: half of 128 rows would not exist): 25088 -> 4096, batch 64: forward 153 and
 // 115 us, input gradient 149 and 107; 2048 -> 1000, batch 64: 14.2 and 12.7.  Uncut it has no more workgroups than the 128x128 tile's groups (700 and 734).
 // Element-wise loaders (`fast` false) are bound by loading: a wider tile reads each activation for fewer column tiles.  Forward, 128x64
@@ -1600,7 +1596,21 @@ void launch_tile(hipStream_t st, TileArgs ta, bool fast, int zdim, float *out, i
 // Element-wise filter gradients take 128x64 in place of 128x128, whose 128 registers they exceed: 5x5 stride 3, 438 -> 392, 32x32, batch 38: 501
 // and 756 us; 3x3, 258 -> 514, 14x14, batch 64, ten ranges: 434 and 501; 1x1, 438 -> 391, 32x32, batch 38, 64 ranges: 251 and 287.
 // (It loses where its twice as many tiles just begin a second round: 7x7, 402 -> 304, 16x16, batch 10: 221 and 196.)
-int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int taps, int splits, bool fast, bool straddle) {
+//
+// 128x32: the same workgroups as the 128x64 tile, with half the waves each and four on a CU (1024 in a round) where that has three (768).  Times against the 128x64
+// tile, 5900 launches of up to 32 columns in all: 640 - 768 workgroups 0.92, - 1024 (one round for two) 0.80; 1024 - 1536 (two rounds both) 1.03 - 1.09 forward, 0.97 - 1.01
+// in the input gradient, up to 1.38; from there 0.88 - 0.95 in the input gradient, 0.95 - 1.04 forward, 0.92 - 0.96 from 2560 on.  3x3, 64 -> 32, 90x90, batch 16 (1013, 36 steps): 61
+// and 48 us; 3x3, 8 <- 180, 75x78, batch 26, input gradient (1252): 195 and 236.  Beyond one round 1x1 layers are level or lose (1.01 - 1.03: they move memory), and so do
+// straddling reductions that are long or, forward, strided (0.95 - 0.98, single ones to 1.20: that variant has one register stage of loads here); aligned reductions of less than eight steps are
+// level (0.98 - 1.02).  `workgroups`: of the residue classes that have a filter tap; the others only write zeros.  Cut launches keep the wider tile: their ranges are further
+// workgroups.  Half as many waves per workgroup lose where there are few (5x5, 24 -> 64, 14x14, batch 320, input gradient, 490 of them: 91 and 95).
+bool narrow_tile(int mode, int64_t workgroups, int64_t steps, int taps, int stride, bool straddle) {
+    if (workgroups < 640 || (!straddle && steps < (taps > 1 ? 8 : 16))) return false;
+    if (workgroups <= 4 * NUM_CU) return true;
+    return taps > 1 && workgroups >= (mode == DGRAD ? 6 : 10) * NUM_CU && !(straddle && (steps >= 100 || (mode == FWD && stride > 1)));
+}
+// `busy`: residue classes that have a filter tap
+int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, int64_t busy, int taps, int stride, int splits, bool fast, bool straddle) {
     if (mode == WGRAD) {
         static const int nearest[6] = {0, 3, 4, 3, 4, 5};
         if (g_cfg_override >= 0) return nearest[g_cfg_override] == 0 && !fast ? 3 : nearest[g_cfg_override];
@@ -1608,7 +1618,7 @@ int pick_cfg(int mode, int64_t Mg, int64_t Ng, int64_t steps, int64_t classes, i
         if (Mg <= 64) return (Ng + 127) / 128 * 128 <= (Ng + 63) / 64 * 64 * 9 / 8 ? 4 : 5;
         return fast ? 0 : 3;
     }
-    if (g_cfg_override < 0 && fast && Ng <= 32 && (steps >= 16 || taps > 1) && (Mg + 127) / 128 * classes >= 640) return 6;
+    if (g_cfg_override < 0 && fast && Ng <= 32 && splits == 1 && narrow_tile(mode, (Mg + 127) / 128 * busy, steps, taps, stride, straddle)) return 6;
     if (g_cfg_override < 0 && fast && taps == 1 && splits > 1 && Mg <= 64 && Ng > 64) return 7;      // at most 64 rows
     if (straddle) return 3;      // straddling lanes carry their tap: registers the larger tile does not have
     if (g_cfg_override >= 0) return g_cfg_override == 0 ? 0 : 3;
@@ -1795,7 +1805,7 @@ void conv_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
             return;
         }
     }
-    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, steps, 1, cs.R * cs.S, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, steps, accumulate, "conv_fwd");
+    launch_cfg<FWD>(pick_cfg(FWD, ta.Mg, ta.Ng, steps, 1, 1, cs.R * cs.S, cs.stride, splits, fast, fast && !conv_fwd_aligned(cs)), st, ta, fast, 1, y, splits, ws, ws_bytes, steps, accumulate, "conv_fwd");
 }
 
 void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, const ConvShape &cs, bool accumulate, int splits, float *ws,
@@ -1819,7 +1829,7 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
         return;
     }
     if (splits == 1) splits = ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes);
-    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, cs.R * cs.S, splits, fast, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
+    launch_cfg<DGRAD>(pick_cfg(DGRAD, ta.Mg, ta.Ng, sg.steps, sg.classes, (int64_t)std::min(cs.R, cs.stride) * std::min(cs.S, cs.stride), cs.R * cs.S, cs.stride, splits, fast, fast && cs.K % BK != 0 && cs.R * cs.S > 1), st, ta, fast, sg.classes, dx, splits, ws, ws_bytes, sg.steps, accumulate, "conv_dgrad");
 }
 
 void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, const ConvShape &cs, int splits, float *ws, size_t ws_bytes) {
@@ -1850,7 +1860,7 @@ void conv_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, cons
         launch_short<WGRAD>(st, ta, 1, dw, false);
         return;
     }
-    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, cs.R * cs.S, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, steps, false, "conv_wgrad");
+    launch_cfg<WGRAD>(pick_cfg(WGRAD, ta.Mg, ta.Ng, 0, 1, 1, cs.R * cs.S, cs.stride, splits, fast, false), st, ta, fast, 1, dw, splits, ws, ws_bytes, steps, false, "conv_wgrad");
 }
 
 }  // namespace monet

@@ -839,6 +839,50 @@ def test_convolution_tiles_and_wave_groups_match_64_bits(case, infinite):
         assert (np.abs(got - ref)[sure] <= bound * sz[sure]).all()
 
 
+def times_taken_and_forced(torch, call, runs):
+    """Microseconds of a convolution call by itself and with the 128x64 tile forced, in turn, the least of a few measurements each."""
+    best = [float("inf"), float("inf")]
+    try:
+        for _ in range(8):
+            for forced in (0, 1):
+                monet.call("monet_conv_force_tile", 3 if forced else -1)
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                call()
+                a.record()
+                for _ in range(runs):
+                    call()
+                b.record()
+                torch.cuda.synchronize()
+                best[forced] = min(best[forced], a.elapsed_time(b) * 1e3 / runs)
+    finally:
+        monet.call("monet_conv_force_tile", -1)
+    return best
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # mode, N, H, W, C, K, R, stride, pad
+    ("dgrad", 26, 77, 80, 8, 180, 3, 1, 0),       # 1252 workgroups of 128 rows: two rounds on either tile
+    ("dgrad", 100, 31, 31, 8, 968, 1, 3, 0),      # nine residue classes, one of them with a tap: 95 workgroups that multiply
+    ("fwd", 61, 50, 50, 176, 20, 3, 1, 1),        # 1192 workgroups
+    ("fwd", 32, 69, 72, 312, 8, 2, 1, 0),         # 1207
+    ("fwd", 83, 41, 41, 344, 16, 1, 1, 0),        # 1091, a 1x1 layer
+])
+def test_narrow_results_take_no_slower_tile_than_the_128x64_one(case):
+    torch = torch_mod()
+    mode, N, H, W, C, K, R, st, pad = case
+    P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
+    x, w, y = torch.randn(N, H, W, C, device="cuda"), torch.randn(K, R, R, C, device="cuda"), torch.randn(N, P, Q, K, device="cuda")
+    dims = (N, H, W, C, K, R, R, st, pad)
+
+    def call():
+        if mode == "fwd": monet.call("monet_conv_fwd", None, x.data_ptr(), w.data_ptr(), y.data_ptr(), *dims, 1, None, 0)
+        else: monet.call("monet_conv_dgrad", None, y.data_ptr(), w.data_ptr(), x.data_ptr(), *dims, 0, 1, None, 0)
+
+    taken, wide = times_taken_and_forced(torch, call, 20)
+    assert taken < 1.08 * wide + 0.5
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows, C", [(1, 4), (33, 16), (512, 16), (2047, 16), (4099, 16), (70, 60), (300, 256), (300, 260), (40, 1024)])
 def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
