@@ -1640,16 +1640,17 @@ void launch_cfg(int cfg, Rest... rest) {
 
 // Launches of few results (see conv_short_kernel): at most one workgroup per CU, and from four steps on: up to three, the tile kernel's chain has fewer roundings.
 // A launch that the tile kernel would work uncut takes it up to 512 steps (0.45 us each there; 288 steps: 140 us against 44).  One that it would cut
-// into ranges costs 12 - 14 us there with the second kernel, however long: forward, 34 steps 12.5 and 9.3 us, 64 steps 12.2 and 16.2; input
-// gradient, 47 steps 13.5 and 12.1, 52 steps 13.3 and 12.6, 56 steps 13.4 and 14.0, 72 steps 14.2 and 16.2; filter gradient, 20 steps 12.6 and 9.3, 32 level on few
-// workgroups, 34 of them with 41 steps 14.4 and 13.7, 84 with 41 15.0 and 13.6, 8 with 36 12.3 and 12.9, 88 with 42 and 16 rows, most of them absent,
-// 12.2 and 13.6, 56 steps 12.6 and 16.9.
+// into ranges costs 11 - 15 us there with the second kernel, however long.  Time here over time there, 8000 launches with the ranges that a graph declares, mean and
+// 90th percentile by steps: forward 32 - 39 0.75 / 0.87, 44 - 47 0.84 / 0.97, 52 - 55 0.96 / 1.12; input gradient 40 - 43 0.85 / 0.93, 48 - 51 0.90 / 0.97, 56 - 63 0.99 / 1.10;
+// accumulating, which costs the second kernel nothing there and a read of the result here, 36 - 39 0.88 / 0.99, 44 - 47 0.97 / 1.08, 48 - 51 1.01 / 1.10, with 128 workgroups and
+// more 48 - 51 0.84 / 0.99; filter gradient of more than 64 rows and 32 workgroups and more 36 - 39 0.85 / 0.88, 40 - 43 0.91 / 0.97, 44 - 47 0.99 / 1.03; of at most 64 rows, for which
+// the tile kernel has tiles of 64, 28 - 31 0.85 / 0.90, 32 - 35 0.94 / 1.02, 40 - 43 1.10 / 1.15.
 // Cut launches of less than eight workgroups stay there too: ranges bring more CUs to work (1x1, 512 -> 32, 9x9, batch 4, six of them: 10.3 and 10.4; eight, 5x5,
 // 24 -> 64, 10x10, batch 2: 13.1 and 9.8).
 // `steps` of the longest residue class.
-bool short_applies(int mode, const TileArgs &ta, int64_t steps, int64_t classes, bool fast, bool cut) {
+bool short_applies(int mode, const TileArgs &ta, int64_t steps, int64_t classes, bool fast, bool cut, bool accumulate = false) {
     const int64_t tiles = (ta.Mg + 63) / 64 * ((ta.Ng + 31) / 32) * classes;
-    const int64_t longest = !cut ? 512 : mode == DGRAD ? 52 : mode == WGRAD ? (tiles >= 32 && ta.Mg > 32 ? 44 : 32) : 40;
+    const int64_t longest = !cut ? 512 : mode == DGRAD ? (accumulate && tiles < 128 ? 40 : 52) : mode == WGRAD ? (tiles >= 32 && ta.Mg > 64 ? 44 : 32) : 40;
     return fast && g_cfg_override < 0 && steps >= 4 && steps <= longest && tiles >= (cut ? 8 : 1) && tiles <= NUM_CU;
 }
 template <int MODE>
@@ -1823,7 +1824,7 @@ void conv_dgrad(hipStream_t st, const float *dy, const float *w, float *dx, cons
     const int64_t reach = ((int64_t)cs.R * cs.Q + cs.S) * cs.K * 4;
     bool fast = cs.K % 4 == 0 && cs.C % 4 == 0 && cs.R * cs.S <= 32 && cs.M() * cs.K * 4 + reach < span32 && cs.K * cs.RSC() * 4 < span32;
     const int64_t longest = ((int64_t)((cs.R + cs.stride - 1) / cs.stride) * ((cs.S + cs.stride - 1) / cs.stride) * cs.K + BK - 1) / BK;
-    if (short_applies(DGRAD, ta, longest, sg.classes, fast, splits > 1 || ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes) > 1)) {
+    if (short_applies(DGRAD, ta, longest, sg.classes, fast, splits > 1 || ranges_by_workspace(sg, ta.out_elems, ws, ws_bytes) > 1, accumulate)) {
         check_splits(splits, sg.steps, ta.out_elems, ws, ws_bytes, "conv_dgrad");
         launch_short<DGRAD>(st, ta, sg.classes, dx, accumulate);
         return;

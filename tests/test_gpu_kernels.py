@@ -884,6 +884,28 @@ def test_narrow_results_take_no_slower_tile_than_the_128x64_one(case):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # N, H, W, C, K, R, stride, pad, ranges
+    (3, 17, 17, 56, 712, 1, 1, 0, 5),       # 45 steps, 28 blocks of 64x32
+    (34, 8, 8, 40, 80, 3, 1, 1, 5),         # 45 steps, 68 blocks
+    (1, 16, 16, 48, 32, 5, 1, 2, 6),        # 50 steps, 8 blocks
+])
+def test_cut_input_gradients_that_accumulate_take_the_faster_form(case):
+    """Against the tile kernel with as many ranges."""
+    torch = torch_mod()
+    N, H, W, C, K, R, st, pad, splits = case
+    P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
+    dx, w, dy = torch.zeros(N, H, W, C, device="cuda"), torch.randn(K, R, R, C, device="cuda"), torch.randn(N, P, Q, K, device="cuda")
+    ws = torch.empty(splits * dx.numel(), device="cuda")
+
+    def call():
+        monet.call("monet_conv_dgrad", None, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), N, H, W, C, K, R, R, st, pad, 1, splits, ws.data_ptr(), ws.numel() * 4)
+
+    taken, tile = times_taken_and_forced(torch, call, 60)
+    assert taken < 1.04 * tile + 0.3
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("rows, C", [(1, 4), (33, 16), (512, 16), (2047, 16), (4099, 16), (70, 60), (300, 256), (300, 260), (40, 1024)])
 def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
     """Partial sums that every apply workgroup adds for itself (up to 16 slabs and 256 channels) and beyond.  Sums of `rows` terms in fp32, in slabs: 1e-5 of the terms' sizes."""
