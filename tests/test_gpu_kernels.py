@@ -127,7 +127,7 @@ def test_input_gradient_on_element_wise_loaders(case):
 @pytest.mark.parametrize("tile", range(6))
 @pytest.mark.parametrize("case", [(3, 15, 14, 48, 112, 3, 1, 1), (2, 11, 13, 20, 76, 3, 2, 1), (2, 9, 8, 30, 70, 3, 1, 1), (2, 20, 18, 132, 72, 1, 1, 0)])
 def test_conv_trio_on_every_tile_shape(case, tile):
-    """Each of the shape numbers (every tile shape there is, and those that stand for another), with rows and columns beyond a tile's edge, aligned, straddling and element-wise loaders,
+    """Each of the shape numbers that can be forced (128x128, 128x64, 64x128, 64x64 and those that stand for another), with rows and columns beyond a tile's edge, aligned, straddling and element-wise loaders,
     whole and in ranges, forward and both gradients, plain and accumulating."""
     torch = torch_mod()
     N, H, W, C, K, R, stride, pad = case
@@ -720,15 +720,24 @@ def test_fused_winograd_convolution_matches_oracle(case):
 
 # launches of few results: a 64 x 32 block per workgroup, reduction steps dealt to eight waves
 SHORT_CASES = [
-    # N, H, W, C, K, R, stride, pad
-    (1, 8, 8, 64, 32, 1, 1, 0),        # one block exactly, four steps forward, fewer waves at work than there are
-    (1, 5, 13, 132, 36, 1, 1, 0),      # a row and a column block more; a last step of four indices
-    (2, 9, 7, 20, 44, 3, 1, 1),        # steps that straddle taps
-    (1, 11, 10, 32, 64, 3, 2, 1),      # residue classes of 4, 2, 2 and 1 taps
-    (3, 7, 7, 16, 24, 1, 3, 0),        # classes without a tap
-    (1, 6, 6, 1024, 40, 3, 1, 1),      # 576 steps forward: the tile kernel; 23 in the input gradient
-    (1, 4, 5, 4, 256, 5, 1, 2),        # window as large as the map
+    # N, H, W, C, K, R, stride, pad; the directions that take that form (from four steps and up to 512)
+    (1, 8, 8, 64, 32, 1, 1, 0, "fw"),       # one block exactly, four steps forward, fewer waves at work than there are
+    (1, 5, 13, 132, 36, 1, 1, 0, "fw"),     # a row and a column block more; a last step of four indices
+    (2, 9, 7, 20, 44, 3, 1, 1, "fdw"),      # steps that straddle taps
+    (1, 11, 10, 32, 64, 3, 2, 1, "fd"),     # residue classes of 4, 2, 2 and 1 taps
+    (3, 7, 7, 16, 72, 1, 3, 0, "d"),        # classes without a tap
+    (1, 6, 6, 1024, 40, 3, 1, 1, "d"),      # 576 steps forward: the tile kernel; 23 in the input gradient
+    (1, 4, 5, 4, 256, 5, 1, 2, "fd"),       # window as large as the map
 ]
+
+
+def kernels_of(torch, call):
+    """Names of the kernels that a call launches."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if "monet::" in e.name]
 
 
 def conv_taps(a, R, st, pad, P, Q):
@@ -759,7 +768,7 @@ def test_convolutions_of_few_results_match_64_bits(case, kind):
     of 16 at most: 2e-7 of the sum of the products' sizes bounds it.  Operands near 2^-120 and an infinity go through the fp32 instruction, which rounds after
     every product: n * 2^-24 of it."""
     torch = torch_mod()
-    N, H, W, C, K, R, st, pad = case
+    N, H, W, C, K, R, st, pad, short = case
     P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
     rng = np.random.default_rng(21)
     x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, P, Q, K), dtype=np.float32)
@@ -774,11 +783,14 @@ def test_convolutions_of_few_results_match_64_bits(case, kind):
     want, size = conv64(x, w, dy, st, pad), conv64(np.abs(x), np.abs(w), np.abs(dy), st, pad)
     y = torch.full((N, P, Q, K), float("nan"), device="cuda")
     dx, dw = torch.full((N, H, W, C), float("nan"), device="cuda"), torch.full((K, R, R, C), float("nan"), device="cuda")
-    monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, 1, None, 0)
-    monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), dx.data_ptr(), *dims, 0, 1, None, 0)
+    calls = {"f": lambda: monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, 1, None, 0),
+             "d": lambda: monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), dx.data_ptr(), *dims, 0, 1, None, 0),
+             "w": lambda: monet.call("monet_conv_wgrad", None, xs.data_ptr(), ds.data_ptr(), dw.data_ptr(), *dims, 1, None, 0)}
+    for mode, (direction, call) in enumerate(calls.items()):
+        if kind == "plain": assert any(f"conv_short_kernel<{mode}>" in k for k in kernels_of(torch, call)) == (direction in short), direction
+        else: call()
     twice = dx.clone()
     monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), twice.data_ptr(), *dims, 1, 1, None, 0)
-    monet.call("monet_conv_wgrad", None, xs.data_ptr(), ds.data_ptr(), dw.data_ptr(), *dims, 1, None, 0)
     outs = [t.cpu().numpy() for t in (y, dx, dw)]
     for got, ref, sz, n in zip(outs, want, size, (C * R * R, K * R * R, N * P * Q)):
         if kind == "infinite":
@@ -799,15 +811,19 @@ def test_convolutions_of_few_results_match_64_bits(case, kind):
 
 # tile shapes and wave groups of the forward pass and the input gradient
 GROUP_CASES = [
-    # N, H, W, C, K, R, stride, pad, splits
-    (5, 28, 28, 80, 160, 3, 1, 1, 1),       # two groups on 128x64 tiles, 45 steps forward: one turn more for the first
-    (5, 27, 28, 64, 176, 3, 1, 1, 1),       # 36 and 99 steps, ragged tiles
-    (3, 28, 28, 64, 320, 3, 2, 1, 1),       # residue classes of unequal length
-    (5, 28, 28, 192, 160, 3, 1, 1, 3),      # two groups on 128x128 tiles, cut into three ranges of 36 and 30 steps
-    (2, 208, 200, 16, 24, 3, 1, 1, 1),      # 128x32 tiles: 24 columns forward, 16 in the input gradient
-    (2, 208, 200, 20, 32, 3, 1, 1, 1),      # and steps that straddle taps
-    (1, 5, 11, 512, 132, 1, 1, 0, 4),       # 64x128 tiles: at most 64 rows of a cut 1x1 layer
-    (64, 1, 1, 1284, 516, 1, 1, 0, 8),      # and a last step of four indices
+    # N, H, W, C, K, R, stride, pad, splits; kernel of the forward pass and of the input gradient: rows / 64, columns / 32, loader, groups (None: the form of few results)
+    (5, 28, 28, 80, 160, 3, 1, 1, 1, (2, 2, 1, 2), None),                 # two groups on 128x64 tiles, 45 steps: one turn more for the first
+    (5, 28, 28, 160, 80, 3, 1, 1, 1, None, (2, 2, 1, 2)),                 # the same in the input gradient
+    (9, 27, 28, 176, 176, 3, 1, 1, 1, (2, 2, 1, 2), (2, 2, 1, 2)),        # 99 steps, ragged tiles
+    (4, 28, 28, 192, 512, 3, 2, 1, 1, None, (2, 2, 1, 2)),                # residue classes of 128, 64, 64 and 32 steps
+    (6, 28, 28, 256, 512, 1, 2, 0, 1, (2, 2, 1, 1), (2, 2, 1, 2)),        # three of four classes without a tap
+    (5, 28, 28, 192, 192, 3, 1, 1, 3, (2, 4, 1, 2), (2, 4, 1, 2)),        # two groups on 128x128 tiles, cut into three ranges of 36 steps
+    (2, 208, 200, 16, 24, 3, 1, 1, 1, (2, 1, 1, 1), (2, 1, 3, 1)),        # 128x32 tiles: 24 columns forward; 16 and steps that straddle taps in the input gradient
+    (2, 208, 200, 20, 32, 3, 1, 1, 1, (2, 1, 3, 1), (2, 1, 1, 1)),        # and the other way about
+    (1, 5, 11, 512, 132, 1, 1, 0, 4, (1, 4, 1, 1), None),                 # 64x128 tiles: at most 64 rows of a cut 1x1 layer
+    (1, 5, 11, 132, 512, 1, 1, 0, 4, None, (1, 4, 1, 1)),
+    (64, 1, 1, 1284, 516, 1, 1, 0, 8, (1, 4, 2, 1), None),                # and a last step of four indices
+    (64, 1, 1, 516, 1284, 1, 1, 0, 8, None, (1, 4, 2, 1)),
 ]
 
 
@@ -817,7 +833,7 @@ GROUP_CASES = [
 def test_convolution_tiles_and_wave_groups_match_64_bits(case, infinite):
     """Bounds as above; `infinite`: a tile is worked again on the fp32 instruction, by both groups."""
     torch = torch_mod()
-    N, H, W, C, K, R, st, pad, splits = case
+    N, H, W, C, K, R, st, pad, splits, *kernels = case
     P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
     rng = np.random.default_rng(22)
     x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, P, Q, K), dtype=np.float32)
@@ -829,9 +845,12 @@ def test_convolution_tiles_and_wave_groups_match_64_bits(case, infinite):
     y, dx = torch.full((N, P, Q, K), float("nan"), device="cuda"), torch.full((N, H, W, C), float("nan"), device="cuda")
     room = torch.empty(splits * max(y.numel(), dx.numel()), device="cuda")
     dims = (N, H, W, C, K, R, R, st, pad)
-    monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, splits, room.data_ptr() if splits > 1 else None, room.numel() * 4 if splits > 1 else 0)
-    monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), dx.data_ptr(), *dims, 0, splits, room.data_ptr() if splits > 1 else None,
-               room.numel() * 4 if splits > 1 else 0)
+    wsp, wsb = (room.data_ptr(), room.numel() * 4) if splits > 1 else (None, 0)
+    calls = (lambda: monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), y.data_ptr(), *dims, splits, wsp, wsb),
+             lambda: monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), dx.data_ptr(), *dims, 0, splits, wsp, wsb))
+    for mode, (call, kernel) in enumerate(zip(calls, kernels)):
+        name = f"conv_short_kernel<{mode}>" if kernel is None else "conv_tile_kernel<%d, %d, %d, %d, 0, %d>" % (mode, *kernel)
+        assert any(name in k for k in kernels_of(torch, call)), name
     for got, ref, sz, n in zip((y.cpu().numpy(), dx.cpu().numpy()), want, size, (C * R * R, K * R * R)):
         sure = np.isfinite(got)
         assert sure.all() != infinite and sure.mean() > (0.9 if N * P * Q > 100 else 0.5)
