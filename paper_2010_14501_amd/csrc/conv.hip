@@ -561,7 +561,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, KS == 1 && (WM * WN < 4 || (WM *
         kk0 = (kt0 + group) * BK;
         u_r = u_s = u_c = 0;
         if (MODE != WGRAD && kt0 + group > 0) {  // a later reduction split (or group) starts in the middle: locate it once
-            const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : ns;
+            const int inner = MODE == FWD ? cs.C : cs.K, cols = MODE == FWD ? cs.S : max(ns, 1);      // (a class without a tap has no step, but a second group)
             const int tap = (int)((unsigned)kk0 / (unsigned)inner);
             u_c = kk0 - tap * inner;
             u_r = tap / cols;
