@@ -341,8 +341,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS, KS == 1 && (WM * WN < 4 || (WM *
     const unsigned tiles = (unsigned)ta.total_tiles;
     // Each GEMM of a batch deals its shares from another XCD on: the shares without an item (12 items in shares of two: the last two) would fall to the same
     // XCDs 36 times.  Winograd filter gradient, batch 184 of 14x14, 256 -> 256: 230 and 185 us; batch 176 of 56x56, 256 -> 256: 2082 and 2014; where memory bounds
-    // it (112x112, 128 -> 128) level.
-    const unsigned first = MODE == DGRAD || TAG == 0 ? 0u : blockIdx.z;      // (an input gradient's classes read the same rows: each stays with its XCD; a launch
+    // it (112x112, 128 -> 128) level.  Shares that are even already stay where they are (8, 16, 32 items: 0.6 - 1.0 % slower turned, single ones 10 %;
+    // 9 - 11 items 0.91 of the time, others 0.94 - 1.0).
+    const unsigned first = MODE == DGRAD || TAG == 0 || tiles * (unsigned)nsplit % NUM_XCD == 0 ? 0u : blockIdx.z;      // (an input gradient's classes read the same rows: each stays with its XCD; a launch
     // that is no batch has nothing to turn, and without the sum its code is faster: 3x3 stride 2, 128 -> 128, 56x56, batch 184, filter gradient 273 and 269 us)
     const unsigned item = (blockIdx.x + first) % NUM_XCD * (gridDim.x / NUM_XCD) + blockIdx.x / NUM_XCD;
     if (item >= tiles * (unsigned)nsplit) return;
