@@ -94,9 +94,18 @@ int64_t monet_conv_winograd_workspace_bytes(int N, int H, int W, int C, int K, i
  * transformed tensors ever reaching memory -- the small-workspace end of Appendix D's trade-off.  Workspace: the
  * transformed filters only, 36 * round_up(out channels, 64) * reduction channels floats
  * (monet_conv_winograd_fused_workspace_bytes; out = K, reduction = C for the forward pass, exchanged for adjoint != 0).
- * Needs reduction channels % 8 == 0.  Reads the input once per 64 output channels, so it is the faster form for layers
- * with few channels on large maps and the slower one for many channels.  Same arithmetic as monet_conv_winograd with
- * m = 4 (results agree to rounding; the sums over channels run in the same order). */
+ * Needs reduction channels % 8 == 0.  Reads the input once per 64 output channels: the faster form for layers with few channels or
+ * many tiles (up to 512 channels on 14x14 maps at a batch of 64 and more; level there on 7x7), the slower one for small batches of many channels.
+ * The transforms are those of monet_conv_winograd with m = 4; the products are not: with at least 64 reduction channels in multiples of 16, a
+ * transformed value is held in two fp16 pieces (23 of fp32's 24 bits: to 2^-23 of itself at worst) under powers of two per output channel and per
+ * 4x4 tile, three products are kept, and the sums are fp32; other reductions run on the fp32 matrix instruction.  Results of the two calls agree to
+ * rounding (normwise error of one layer 1e-6 to 4e-6), not bit for bit.  Against the fp32 instruction the pieces' error is 0.65 to 0.8 times as large
+ * on dense operands (64 to 512 channels), 1.1 to 1.25 times where only 30 % of the (image, channel) planes hold anything but zeros, 1.4 to 1.6 times at 10 %
+ * and below.  Where the pieces do not hold the numbers of a block of 32 tiles x 32 channels (infinities and NaNs, which come out as
+ * fp32 arithmetic's; sums that cancel or vanish against the size of the operands, to where parts lost below 2^-25 of their scale could be 2^-20
+ * of the largest sum), it is worked once more with the fp32 matrix instruction.  Operands that do that in every block (large inputs that meet
+ * weights of almost nothing) take three times as long, 1.6 to 1.8 times what the fp32 instruction takes alone; filters of zeros, sparse inputs (down to 0.3 %) and
+ * channels of different size do not. */
 int monet_conv_winograd_fused(void *stream, const float *in, const float *w, float *out, int N, int H, int W, int C, int K,
                               int adjoint, int accumulate, float *ws, size_t ws_bytes);
 int64_t monet_conv_winograd_fused_workspace_bytes(int N, int H, int W, int C, int K, int adjoint);

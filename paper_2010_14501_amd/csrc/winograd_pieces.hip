@@ -1,4 +1,4 @@
-// Winograd F(4x4, 3x3) in one kernel, its products on the fp16 matrix cores at fp32 precision (winograd_fused.hip is the same form on
+// Winograd F(4x4, 3x3) in one kernel, its products on the fp16 matrix cores in two pieces per operand (winograd_fused.hip is the same form on
 // the fp32 instruction, for reductions that are too short or ragged for this one).
 //
 // A workgroup (sixteen waves, four per SIMD) owns 32 tiles x 64 output channels for all 36 positions z of the transformed tile.  The
@@ -8,10 +8,13 @@
 //   * waves 0-11 multiply three positions each (96 accumulators per lane);
 //   * the transformed filters come from the workspace, already in pieces and in lane order.
 //
-// Pieces.  v = h + m with h and m in fp16, each rounded to nearest: 22 bits and a sign.  Of a product the terms m*h, h*m and h*h are kept;
-// every term is exact in the matrix unit, whose sums are fp32: three roundings per 16 products instead of one per two.  Against 64
-// bits that is closer than the fp32 instruction from 64 reduction channels on (normwise, one layer of random numbers, 64 / 128 / 512 channels:
-// 1.0e-6 / 1.1e-6 / 1.7e-6, the fp32 instruction 1.1e-6 / 1.3e-6 / 2.5e-6); below, the pieces' 2^-23 shows and the fp32 form stays.
+// Pieces.  v = h + m with h and m in fp16, each rounded to nearest: 22 bits and the sign of m, one bit less than fp32's 24.  Of a product the terms m*h, h*m and
+// h*h are kept; every term is exact in the matrix unit, whose sums are fp32: three roundings per 16 products instead of one per two.  Against 64
+// bits that is closer than the fp32 instruction on dense operands of at least 64 reduction channels (normwise, 28x28, ReLU'd input, 64 / 128 / 256 / 512 channels:
+// 1.13 / 1.40 / 1.85 / 2.40e-6, the fp32 instruction 1.42 / 1.94 / 2.74 / 3.71e-6; 10 % of the values present 1.29 / 1.59 / 2.09 / 2.78 and 1.44 / 1.94 / 2.69 / 3.74); below, the pieces'
+// 2^-23 shows and the fp32 form stays.  It is the coarser one where most products are of zeros, for which the fp32 instruction rounds nothing: 30 % of the (image, channel)
+// planes present 1.11 / 1.36 / 1.75 / 2.31 and 0.92 / 1.15 / 1.53 / 2.07, 3 % 0.94 / 0.96 / 1.06 / 1.32 and 0.62 / 0.64 / 0.70 / 0.84.  Measured and not taken: the m*m term and filters transformed
+// in 64 bits, 0.86 - 0.99 of the error for 4 - 5 % of the time and 10 us of a call; sums of the small terms apart, which would halve the roundings, need 16 registers of the 8 there are.
 //
 // Range.  fp16 reaches from 2^-24 to 2^16, so both operands carry powers of two: a filter one per output channel (its largest weight comes
 // to lie in [2^13, 2^14)), a tile one that its first chunk with a value other than zero sets (that patch's largest value in [2^5, 2^6); transformed
@@ -23,7 +26,7 @@
 // hundred times above the bound at 512 channels.  (One bound for all tiles, 2^11 * sqrt(all channels), was one that signs alike could break by sqrt(channels), and sent most
 // launches with less than 0.5 % of the values present to the second pass: a tile with two such values has small sums that nothing is lost from.)  A half item that fails is worked once more on the fp32
 // instruction, patches and filters transformed into LDS a chunk at a time.  What that costs with every half item affected: first layer below 1308 -> 3833 us, second
-// 109 -> 333 (the fp32 form, which takes both halves from one transform and its filters from the workspace: 2187 and 206).  Ordinary operands stay clear of it: 0.3 % of the
+// 109 -> 333 (the fp32 form, which takes both halves from one transform and its filters from the workspace: 2080 and 200).  Ordinary operands stay clear of it: 0.3 % of the
 // values present, filters of zeros, channels of very different size.  Those that do not: large inputs that meet weights of almost nothing, or of nothing at all (a
 // network with most of its filter planes pruned: sums of zero, which cannot be told from lost ones).
 //

@@ -133,7 +133,10 @@ class Graph:
         # streams the filters from L2 per 32 tiles, so it wins where maps are large or channels few (measured against the
         # workspace form, forward: x1.9 at 64 channels on 224x224 and 416x608, x1.3-1.5 at 128, x1.1 at 256 on 56x56,
         # level at 28x28x128 and, since the ragged last round of a launch is worked as half items, at 14x14x256, where it also takes the
-        # recomputed ReLU and its mask into its epilogue) and loses on small maps with more channels (14x14x512, 7x7x512).  The library
+        # recomputed ReLU and its mask into its epilogue: all on the fp32 matrix instruction).  On small maps with more channels it lost then (7x7x512, batch
+        # 184: 240 against 185 us) and is withheld.  With its products on fp16 pieces it does not lose there any more: forward 14x14x512, batch 176, 335
+        # against 410 us, batch 64 136 against 160, 7x7x512, batch 184, 130 against 127.  The line has stayed for what is written: an
+        # implementation more would move the ones behind it, which schedules name by their place.  The library
         # addresses the input with 32-bit byte offsets: tensors of 4 GiB and more keep the workspace form.
         wino4f = wino4 and 4 * N * H * W * max(C, K) < (1 << 32) and not (H * W <= 14 * 14 and min(C, K) >= 320)
 
