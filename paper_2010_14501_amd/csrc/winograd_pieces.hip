@@ -30,8 +30,8 @@
 // values present, filters of zeros, channels of very different size.  Those that do not: large inputs that meet weights of almost nothing, or of nothing at all (a
 // network with most of its filter planes pruned: sums of zero, which cannot be told from lost ones).
 //
-// What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512): fp32 form
-// 2187 / 206 / 174 / 1926, this one 1344 / 108 / 102 / 1089.  A chunk takes 3.2 us where its matrix instructions alone take 1.3 (measured with the
+// What it measured (us, batch 176 of 112x112, 128 -> 128 channels / 184 of 14x14, 256 -> 256 / 184 of 28x28, 128 -> 128 / 176 of 28x28, 512 -> 512, on one card): fp32
+// form 2081 / 196 / 171 / 1924, this one 1282 / 109 / 103 / 1047.  A chunk takes 3.2 us where its matrix instructions alone take 1.3 (measured with the
 // other parts left out, at the power limit's clock), and an item another 14 us for its first patch and its outputs.  What the chunk waits for is the vector
 // memory path: 147 KB of filters and 74 KB of patches per chunk (at 64 bytes per clock 1.7 us) and the latency of the patches, whose registers
 // are free again only when the patch before is split.  Eight waves of which four make the patches and multiply less took the same time to 2 %;
