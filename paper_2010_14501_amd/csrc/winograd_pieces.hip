@@ -14,7 +14,7 @@
 // 1.13 / 1.40 / 1.85 / 2.40e-6, the fp32 instruction 1.42 / 1.94 / 2.74 / 3.71e-6; 10 % of the values present 1.29 / 1.59 / 2.09 / 2.78 and 1.44 / 1.94 / 2.69 / 3.74); below, the pieces'
 // 2^-23 shows and the fp32 form stays.  It is the coarser one where most products are of zeros, for which the fp32 instruction rounds nothing: 30 % of the (image, channel)
 // planes present 1.11 / 1.36 / 1.75 / 2.31 and 0.92 / 1.15 / 1.53 / 2.07, 3 % 0.94 / 0.96 / 1.06 / 1.32 and 0.62 / 0.64 / 0.70 / 0.84.  Measured and not taken: the m*m term and filters transformed
-// in 64 bits, 0.86 - 0.99 of the error for 4 - 5 % of the time and 10 us of a call; sums of the small terms apart, which would halve the roundings, need 16 registers of the 8 there are.
+// in 64 bits, 0.86 - 0.99 of the error for 4 - 5 % of the time and 10 us of a call; all four terms in two 16x16x32 instructions, 6 % slower and no closer (it rounds more than once); sums of the small terms apart, which would halve the roundings, need 16 registers of the 8 there are.
 //
 // Range.  fp16 reaches from 2^-24 to 2^16, so both operands carry powers of two: a filter one per output channel (its largest weight comes
 // to lie in [2^13, 2^14)), a tile one that its first chunk with a value other than zero sets (that patch's largest value in [2^5, 2^6); transformed
