@@ -1432,16 +1432,6 @@ void launch_split_reduce(hipStream_t st, const float *ws, float *dw, int64_t n, 
     hip_check(hipGetLastError(), "split reduce launch");
 }
 
-// floor(n / d) = umulhi(n, mul) >> shift for every n < 2^31 (d >= 2): mul = ceil(2^(31 + l) / d) with l = ceil(log2 d)
-// fits 32 bits, and its excess over 2^(31 + l) / d, below d / 2^(31 + l) <= 2^-31, times n stays below one unit
-void magic_of(unsigned d, unsigned &mul, unsigned &shift) {
-    mul = 0; shift = 0;
-    if (d < 2) return;
-    unsigned l = 0;
-    while (((uint64_t)1 << l) < d) ++l;
-    mul = (unsigned)((((uint64_t)1 << (31 + l)) + d - 1) / d);
-    shift = l - 1;
-}
 void set_row_magic(TileArgs &ta) {
     magic_of((unsigned)ta.cs.Q, ta.q_mul, ta.q_shift);
     magic_of((unsigned)ta.cs.P, ta.p_mul, ta.p_shift);
@@ -1688,6 +1678,16 @@ bool conv_epilogue_writes_mask(const ConvShape &cs, bool winograd_fused) {
     return cs.K % 64 == 0;
 }
 
+// floor(n / d) = umulhi(n, mul) >> shift for every n < 2^31 (d >= 2): mul = ceil(2^(31 + l) / d) with l = ceil(log2 d)
+// fits 32 bits, and its excess over 2^(31 + l) / d, below d / 2^(31 + l) <= 2^-31, times n stays below one unit
+void magic_of(unsigned d, unsigned &mul, unsigned &shift) {
+    mul = 0; shift = 0;
+    if (d < 2) return;
+    unsigned l = 0;
+    while (((uint64_t)1 << l) < d) ++l;
+    mul = (unsigned)((((uint64_t)1 << (31 + l)) + d - 1) / d);
+    shift = l - 1;
+}
 void split_reduce(hipStream_t st, const float *ws, float *out, int64_t n, int splits, bool accumulate) {
     launch_split_reduce(st, ws, out, n, splits, accumulate);
 }

@@ -115,6 +115,8 @@ void stem_fwd(hipStream_t st, const float *x, const float *w, float *y, const Co
 bool stem_wgrad_applies(const ConvShape &cs, int splits, size_t ws_bytes);
 void stem_wgrad(hipStream_t st, const float *x, const float *dy, float *dw, const ConvShape &cs, int splits, float *ws, size_t ws_bytes);
 
+// floor(n / d) = umulhi(n, mul) >> shift for every n < 2^31 (d >= 2)
+void magic_of(unsigned d, unsigned &mul, unsigned &shift);
 // out[i] (+)= sum over z < splits of ws[z * n + i], in a fixed order
 void split_reduce(hipStream_t st, const float *ws, float *out, int64_t n, int splits, bool accumulate);
 // Filter gradient of a 1x1 / stride-1 convolution with at most 32 channels on one side and at most 192 on the other

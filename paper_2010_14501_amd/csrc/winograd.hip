@@ -19,6 +19,7 @@
 // 4e-7); both stay far inside the tolerances the parity tests use.
 #include "bn_affine.hpp"
 #include "kernels.hpp"
+#include "winograd_f4.hpp"
 
 namespace monet {
 
@@ -611,8 +612,35 @@ void conv_winograd_wgrad(hipStream_t st, const float *x, const float *dy, float 
         wp = wino_wgrad_plan(cs, m, lo);
     }
     const int planes = (m + 2) * (m + 2), vec = m == 2 ? 4 : 2;
-    float *VD = ws, *dU = VD + (size_t)wp.imgs * wp.per_img, *share = dU + wp.filt, *slabs = share + wp.filt;
     const dim3 blk(256);
+    const int64_t fe = (int64_t)cs.K * cs.C;
+    const dim3 fg((unsigned)((fe + 255) / 256));
+    if (m == 4 && winograd_wgrad_applies(cs)) {
+        // The workspace holds one image's tiles mapped both ways and two transformed gradients, so one image's vertical maps, dU and one partial result.  As few chunks
+        // of images as there can be, or up to three more where the ranges they leave room for make up for them.
+        const size_t have = ws_bytes / sizeof(float), per_img = winograd_wgrad_image_floats(cs);
+        int imgs = 0, most = 0;
+        double best_us = 0;
+        for (int chunks = 1, first = 0; chunks <= cs.N && (first == 0 || chunks <= first + 3); ++chunks) {
+            const int n = (cs.N + chunks - 1) / chunks;
+            if (n > winograd_wgrad_most_images(cs) || n * per_img + 2 * wp.filt > have) continue;
+            if (first == 0) first = chunks;
+            const int room = (int)std::min<size_t>(1024, (have - n * per_img) / wp.filt - 1);
+            const double us = winograd_wgrad_estimate(cs, n, room) * ((cs.N + n - 1) / n);
+            if (imgs == 0 || us < best_us) { imgs = n; most = room; best_us = us; }
+        }
+        if (imgs < 1) throw KernelError("conv_winograd_wgrad: workspace too small");
+        float *dU = ws + imgs * per_img;
+        for (int img0 = 0; img0 < cs.N; img0 += imgs) {
+            ConvShape part = cs;
+            part.N = std::min(imgs, cs.N - img0);
+            conv_winograd_wgrad_maps(st, x + (size_t)img0 * cs.H * cs.W * cs.C, dy + (size_t)img0 * cs.H * cs.W * cs.K, ws, dU, dU + wp.filt, part, most, img0 > 0);
+        }
+        hipLaunchKernelGGL(wino4_filter_back_kernel, fg, blk, 0, st, (const float *)dU, dw, cs.K, cs.C);
+        hip_check(hipGetLastError(), "winograd filter gradient launch");
+        return;
+    }
+    float *VD = ws, *dU = VD + (size_t)wp.imgs * wp.per_img, *share = dU + wp.filt, *slabs = share + wp.filt;
     for (int img0 = 0; img0 < cs.N; img0 += wp.imgs) {
         ConvShape part = cs;
         part.N = std::min(wp.imgs, cs.N - img0);
@@ -637,8 +665,6 @@ void conv_winograd_wgrad(hipStream_t st, const float *x, const float *dy, float 
                         sp > 1 ? (size_t)sp * wp.filt * sizeof(float) : 0, add);
         if (img0 > 0 && !add) copy_or_accumulate(st, share, dU, (int64_t)wp.filt, true);
     }
-    const int64_t fe = (int64_t)cs.K * cs.C;
-    const dim3 fg((unsigned)((fe + 255) / 256));
     if (m == 2) hipLaunchKernelGGL(wino_filter_back_kernel, fg, blk, 0, st, (const float *)dU, dw, cs.K, cs.C);
     else hipLaunchKernelGGL(wino4_filter_back_kernel, fg, blk, 0, st, (const float *)dU, dw, cs.K, cs.C);
     hip_check(hipGetLastError(), "winograd filter gradient launch");

@@ -113,4 +113,12 @@ bool winograd_pieces_applies(const ConvShape &cs, bool adjoint);
 void conv_winograd_pieces(hipStream_t st, const float *in, const float *w, float *out, const ConvShape &cs, bool adjoint, bool accumulate, float *ws,
                           const BnAffine &bn);
 
+// winograd_wgrad.hip: whether a filter gradient's horizontal maps are made on the way into its GEMMs; floats of one image's vertical maps; estimated microseconds of a chunk
+// of images with room for `most` ranges; dU (+)= the transformed filter gradient of the images of `cs`.  `parts`: room for `most` (>= 1) partial results of 36 * K * C floats.
+bool winograd_wgrad_applies(const ConvShape &cs);
+size_t winograd_wgrad_image_floats(const ConvShape &cs);
+int winograd_wgrad_most_images(const ConvShape &cs);      // of one chunk
+double winograd_wgrad_estimate(const ConvShape &cs, int images, int most);
+void conv_winograd_wgrad_maps(hipStream_t st, const float *x, const float *dy, float *maps, float *dU, float *parts, const ConvShape &cs, int most, bool accumulate);
+
 }  // namespace monet

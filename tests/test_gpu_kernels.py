@@ -999,6 +999,80 @@ def test_winograd_on_pieces_matches_64_bits(case):
         assert np.linalg.norm(twice - 2 * want) < 2 * bound * np.linalg.norm(want)
 
 
+# (batch, map, C, K, images that the workspace holds at a time: 0 all of them)
+WGRAD_MAPS_CASES = [
+    (1, 1, 1, 4, 4, 0),            # one tile, four channels
+    (1, 3, 2, 8, 60, 0),           # a map smaller than a tile, channels short of a block
+    (3, 17, 20, 64, 68, 0),        # 75 tiles, one row of which is a quarter full; a second block of four filters
+    (5, 12, 4, 68, 64, 1),         # tiles one above the other; chunks of one image with three tiles
+    (1, 4, 60, 132, 64, 0),        # 15 tiles, one short of a chunk; three blocks of channels
+    (1, 4, 64, 64, 132, 0),        # 16: one chunk
+    (1, 4, 68, 64, 64, 0),         # 17
+    (2, 31, 33, 320, 260, 0),      # 144 tiles and 25 pairs of blocks: not this form
+    (1, 8, 11, 320, 260, 0),       # 6 tiles and 25 pairs of blocks
+    (3, 40, 44, 96, 128, 2),       # four pairs of blocks, several ranges; the last chunk of images is shorter
+    (2, 120, 132, 64, 64, 1),      # 62 chunks of tiles per image in one range: partial sums added in memory
+]
+
+
+def wgrad_maps(torch, x, dy, case):
+    N, H, W, C, K, imgs = case
+    need = monet.call("monet_conv_winograd_wgrad_workspace_bytes", N, H, W, C, K, 4)
+    if imgs:      # what the check of the workspace asks for `imgs` images and one partial result
+        tiles = ((H + 3) // 4) * ((W + 3) // 4)
+        ranges = max(1, min(1024 // (36 * ((K + 127) // 128) * ((C + 127) // 128)), imgs * tiles // 128))
+        need = min(need, 4 * 36 * (imgs * tiles * (C + K) + K * C * (2 + (ranges if ranges > 1 else 0))))
+    ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    dw = torch.full((K, 3, 3, C), float("nan"), dtype=torch.float32, device="cuda")
+    dx, ddy = dev(x), dev(dy)
+    monet.call("monet_conv_winograd_wgrad", None, dx.data_ptr(), ddy.data_ptr(), dw.data_ptr(), N, H, W, C, K, 4, ws.data_ptr(), need)
+    return dw.cpu().numpy()
+
+
+def wgrad64(x, dy):
+    n, h, w, C = x.shape
+    xp = np.pad(x.astype(np.float64), ((0, 0), (1, 1), (1, 1), (0, 0)))
+    g = dy.astype(np.float64).reshape(-1, dy.shape[3])
+    return np.stack([np.stack([g.T @ xp[:, r:r + h, s:s + w, :].reshape(-1, C) for s in range(3)], 1) for r in range(3)], 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", WGRAD_MAPS_CASES)
+def test_winograd_wgrad_with_horizontal_maps_in_the_gemm_matches_64_bits(case):
+    """The transforms' rounding makes the filter gradient of F(4x4, 3x3) 0.5 .. 2.1e-6 normwise (measured, up to 140000 tiles); these have at most
+    2000, whose sums add less: 2e-6.  Twice the same bits."""
+    torch = torch_mod()
+    N, H, W, C, K, _ = case
+    rng = np.random.default_rng(3)
+    x, dy = np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0), rng.standard_normal((N, H, W, K), dtype=np.float32) * np.float32(1e-3)
+    want = wgrad64(x, dy)
+    got = wgrad_maps(torch, x, dy, case)
+    assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want)
+    assert np.abs(got - want).max() <= 50 * 2e-6 * np.sqrt((want ** 2).mean()) + 1e-30
+    assert np.array_equal(got, wgrad_maps(torch, x, dy, case))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["tiny", "huge", "infinity", "nan"])
+def test_winograd_wgrad_with_operands_beyond_the_pieces(kind):
+    """Mapped values below 2^-110 leave bits over in the split, infinities and NaN show in the sums: such a workgroup works its range again on the fp32
+    instruction, to the same bound.  A channel without such a value keeps its gradient."""
+    torch = torch_mod()
+    N, H, W, C, K = 2, 13, 18, 72, 40
+    rng = np.random.default_rng(4)
+    x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, H, W, K), dtype=np.float32)
+    if kind == "tiny": x *= np.float32(1e-34)
+    if kind == "huge": x *= np.float32(1e30)      # x 100 and dy 225 times as large when mapped, sums of 480: up to 1e37 (1e35 would overflow in any order)
+    want = wgrad64(x, dy)
+    keep = np.ones(C, bool)
+    if kind in ("infinity", "nan"):
+        x[1, 6, 7, 70] = np.inf if kind == "infinity" else np.nan
+        keep[70] = False
+    got = wgrad_maps(torch, x, dy, (N, H, W, C, K, 0))
+    assert np.linalg.norm(got[..., keep] - want[..., keep]) <= 2e-6 * np.linalg.norm(want[..., keep])
+    assert not np.isfinite(got[..., ~keep]).any()
+
+
 def pieces_operands(kind):
     rng = np.random.default_rng(11)
     N, H, W, C, K = 4, 9, 10, 64, 40
