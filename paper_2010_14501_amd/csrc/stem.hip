@@ -23,13 +23,13 @@
 // (bf16_pieces.hpp), 48 vector instructions per operand beside six matrix instructions per 32 columns.  7x7, 64 channels, 224x224,
 // batch 184: 568 us on the fp32 instruction, 473 so (76 and 92 TFLOP/s), error against 64 bits 8.5e-7 and 3.1e-7; bound by the chain of LDS reads,
 // splits and matrix instructions of two waves per SIMD (256 registers; the compiler spills 32 of them around the second pass in fp32, none
-// inside the loop over tiles).  The 3x3 filters keep the fp32 instruction, and so does the forward pass,
-// whose eight-value windows cost it more in LDS reads and registers than the instruction saves (529 -> 842 us).  Wave kb of a workgroup owns the 32 output
+// inside the loop over tiles).  The 3x3 filters keep the fp32 instruction.  Wave kb of a workgroup owns the 32 output
 // channels 32 kb .. 32 kb + 31 and all R * 3 S columns; the workgroups' partial results are added in a fixed order by
 // split_reduce.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "bf16_pieces.hpp"
 #include "buffer_addr.hpp"
@@ -211,6 +211,219 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const float *__restric
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();      // every wave has read this tile from LDS
         if (next < gm.tiles) stem_fill_write(lds, staged, gm, tid, nthreads);
+        __syncthreads();
+    }
+}
+
+// Forward pass of the 7x7 / stride 2 filter on bf16 pieces.  The input rows under a tile are split once, on their way to LDS, where the three planes of pieces lie as the
+// rows do in memory; a filter row's 21 values are three groups of eight (the last three with a filter value of zero), and a reduction step of 16 is two groups, one per half wave: eleven
+// steps.  A window begins 6 elements after its neighbour's, on a word boundary, so that a lane's group is four words in a row.  The first two pieces of the filters of a wave's 32 channels stay
+// in registers for all its tiles (88 of them), the third in LDS.
+// 224x224, 64 channels: batch 184 517 us on the fp32 instruction, 412 so; batch 8 36.4 and 25.4; batch 1 19.8 and 15.0; error against 64 bits 2.2e-7 and 7.0e-8.  What bounds it: 3.1e14 flop of matrix
+// instructions (147 products padded to 176), 250 us at the power limit, and 203 us for everything else, which overlap in part: two waves per SIMD.  Stores between the next block's matrix instructions in place of
+// behind the own block's: 455 -> 410; the next tile's loads before this tile's products: 485 -> 451, waited for before the first store, since the number of stores behind them is not known to the
+// compiler; two blocks at a time 473.  Splitting each window on its way into the instruction had been slower than fp32 (842).
+constexpr int STEM7_STEPS = 11;
+constexpr int64_t STEM7_WORKGROUPS = 512;      // two on a CU: 416 us; 768 450, 1024 460, 256 489 (batch 184; each loads its filters once)
+
+struct Stem7Geom {
+    StemGeom g;              // xlead = 0
+    unsigned per_img, img_mul, img_shift, col_mul, col_shift, qn_mul, qn_shift, row4_mul, row4_shift;      // floor(n / d) = umulhi(n, mul) >> shift; d == 1: mul == 0
+    unsigned bytes;          // of an image
+};
+__device__ __forceinline__ unsigned divide(unsigned n, unsigned mul, unsigned shift) { return mul ? __umulhi(n, mul) >> shift : n; }
+struct Stem7Tile { int n, p0, q0; };
+__device__ __forceinline__ Stem7Tile stem7_tile(const Stem7Geom &a, unsigned tile) {
+    const unsigned n = divide(tile, a.img_mul, a.img_shift), t = tile - n * a.per_img, row = divide(t, a.col_mul, a.col_shift);
+    return {(int)n, (int)row * a.g.nrow, (int)(t - row * (unsigned)a.g.col_tiles) * a.g.qn};
+}
+
+// The rows under a tile in pieces of 16 bytes, piece tid + k * nthreads; four floats of a row at any offset, zero where the image ends.
+__device__ __forceinline__ void stem7_fill_load(bf4 (&v)[FILL], const float *__restrict__ x, const Stem7Geom &a, Stem7Tile at, int tid, int nthreads) {
+    const StemGeom &gm = a.g;
+    const int row4 = gm.rowlen / 4, rowf = gm.W * 3;
+    const __amdgpu_buffer_rsrc_t r = buffer_of((const char *)x + (int64_t)at.n * a.bytes, a.bytes);
+    const int h0 = at.p0 * 2 - gm.pad, f0 = (at.q0 * 2 - gm.pad) * 3;
+#pragma unroll
+    for (int k = 0; k < FILL; ++k) {
+        const int idx = tid + k * nthreads, ri = (int)divide((unsigned)idx, a.row4_mul, a.row4_shift), f = f0 + 4 * (idx - ri * row4), h = h0 + ri;
+        const bool row = ri < gm.rows_in && (unsigned)h < (unsigned)gm.H;
+        if (f >= 0 && f + 3 < rowf) v[k] = buffer_load4(r, row ? (unsigned)(h * rowf + f) * 4u : BUFFER_ABSENT, 0u);
+        else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[k][u] = buffer_load(r, row && (unsigned)(f + u) < (unsigned)rowf ? (unsigned)(h * rowf + f + u) * 4u : BUFFER_ABSENT, 0u);
+        }
+    }
+}
+// ... and their three planes of bf16 pieces, `plane` words apart
+__device__ __forceinline__ void stem7_fill_write(unsigned *lds, const bf4 (&v)[FILL], const StemGeom &gm, int plane, int tid, int nthreads, unsigned &lost) {
+    const int total = gm.rows_in * (gm.rowlen / 4);
+#pragma unroll
+    for (int k = 0; k < FILL; ++k) {
+        const int idx = tid + k * nthreads;
+        if (idx < total) {
+            const Pieces a = split_pair(v[k].x, v[k].y, lost), b = split_pair(v[k].z, v[k].w, lost);
+            uint2 *at = (uint2 *)(lds + 2 * idx);
+            at[0] = make_uint2(a.h, b.h);
+            at[plane / 2] = make_uint2(a.m, b.m);
+            at[plane] = make_uint2(a.l, b.l);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void stem7_fwd_kernel(const float *__restrict__ x, const float *__restrict__ w, float *__restrict__ y, Stem7Geom a) {
+    const StemGeom &gm = a.g;
+    extern __shared__ float lds[];
+    constexpr int R = 7, ST = 2, RUN = 21, KP = 11, MBW = 4;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nthreads = blockDim.x;
+    const int nb = wave % (gm.K / 32), mgs = nthreads / 64 / (gm.K / 32);      // as in stem_fwd_kernel
+    const int plane = gm.rows_in * gm.rowlen / 2;                    // words
+    const float *wk = w + (int64_t)(nb * 32 + l32) * (R * RUN);
+    float *rows = lds + gm.K / 32 * (STEM7_STEPS * 64 * 4);
+    unsigned lost_w = 0;
+    struct { bf16x8 h, m; } wr[STEM7_STEPS];
+    bf16x8 *wl = (bf16x8 *)lds + nb * (STEM7_STEPS * 64) + lane;      // the third pieces: every wave of these channels writes and reads the same
+#pragma unroll
+    for (int t = 0; t < STEM7_STEPS; ++t) {
+        const int group = 2 * t + h, r = group / 3, j = 8 * (group - 3 * r);
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = r < R && j + i < RUN ? wk[r * RUN + j + i] : 0.0f;
+        const PieceRow p = split_row(v, lost_w);
+        wr[t] = {p.h, p.m};
+        wl[64 * t] = p.l;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const unsigned *pieces = (const unsigned *)rows;
+    bf4 staged[FILL];
+    unsigned lost = 0;      // of the tile in LDS
+    const unsigned tiles = (unsigned)gm.tiles;
+    if (blockIdx.x < tiles) {
+        stem7_fill_load(staged, x, a, stem7_tile(a, blockIdx.x), tid, nthreads);
+        stem7_fill_write((unsigned *)rows, staged, gm, plane, tid, nthreads, lost);
+    }
+    __syncthreads();
+    int mg = wave / (gm.K / 32);
+    for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        // The wave's group of position blocks: another one for every tile, as the last group has fewer blocks (seven in all on maps of 112 columns).
+        if (++mg >= mgs) mg = 0;
+        // LDS word of this lane's position in every block (positions beyond the tile read position 0)
+        auto word_of = [&](int b) {
+            int m = 32 * (MBW * mg + b) + l32;
+            if (m >= gm.nrow * gm.qn) m = 0;
+            const int pr = gm.nrow == 1 ? 0 : (int)divide((unsigned)m, a.qn_mul, a.qn_shift);
+            return (pr * ST * gm.rowlen + (m - pr * gm.qn) * ST * 3) / 2;
+        };
+        const auto [n, p0, q0] = stem7_tile(a, tile);
+        const int nblk = min(MBW, (gm.nrow * gm.qn + 31) / 32 - MBW * mg);      // position blocks of the nominal tile this wave works on
+        const int rows_here = min(gm.nrow, gm.P - p0), cols_here = min(gm.qn, gm.Q - q0);
+        const int npos = gm.nrow == 1 ? cols_here : rows_here * gm.qn;
+        // the descriptor ends with the tile: a position beyond it is not stored
+        const unsigned kbytes = (unsigned)gm.K * 4u;
+        const __amdgpu_buffer_rsrc_t ry = buffer_of(y + (((int64_t)n * gm.P + p0) * gm.Q + q0) * gm.K, (unsigned)npos * kbytes);
+        const unsigned voff = (unsigned)(32 * MBW * mg + 4 * h) * kbytes + (unsigned)(nb * 32 + l32) * 4u;
+        auto store_one = [&](int b, int i, const floatx16 &v) { buffer_store(ry, voff, (unsigned)(32 * b + 8 * (i / 4) + (i % 4)) * kbytes, v[i]); };
+        auto store = [&](int b, const floatx16 &v) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) store_one(b, i, v);
+        };
+        const unsigned next = tile + gridDim.x;      // fewer than 2^31 tiles
+        if (next < tiles) stem7_fill_load(staged, x, a, stem7_tile(a, next), tid, nthreads);      // uniform over the workgroup
+        float probe = 0.0f;
+        floatx16 prev;      // the block before: its stores go out between the matrix instructions
+        auto block = [&](int b, int words, auto first) {
+            floatx16 acc, low[2];      // the smaller terms in two sums: a product waits for the one before it on the same sum
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = low[0][i] = low[1][i] = 0.0f;
+            bf16x8 ah, am, al, bl;
+            unsigned word;
+            auto place = [&](int t) {
+                // groups 2 t and 2 t + 1: the second eight elements on or, from the third of a row, at the next row's start; the last step has one (its other half's filter
+                // values are zero: that half reads the same group)
+                const int at = (2 * t / 3 * gm.rowlen + 8 * (2 * t % 3)) / 2, step = t == STEM7_STEPS - 1 ? 0 : 2 * t % 3 == 2 ? (gm.rowlen - 16) / 2 : 4;
+                word = (unsigned)(words + h * step + at);
+                asm volatile("" : "+v"(word));      // an address of its own each time: eleven of them would take the registers
+            };
+            auto read = [&](int p) {
+                const unsigned *from = pieces + p * plane + word;
+                return __builtin_bit_cast(bf16x8, uintx4{from[0], from[1], from[2], from[3]});
+            };
+            place(0);
+            ah = read(0);
+            bl = wl[0];
+            am = read(1);
+            al = read(2);
+#pragma unroll
+            for (int t = 0; t < STEM7_STEPS; ++t) {      // a plane of the next step is read as soon as the products of this step's are issued
+                const bool more = t + 1 < STEM7_STEPS;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, wr[t].h, acc, 0, 0, 0);
+                low[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, wr[t].m, low[0], 0, 0, 0);
+                low[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, low[1], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) {
+                    place(t + 1);
+                    ah = read(0);
+                    bl = wl[64 * (t + 1)];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                low[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, wr[t].h, low[0], 0, 0, 0);
+                low[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, wr[t].m, low[1], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) am = read(1);
+                __builtin_amdgcn_sched_barrier(0);
+                low[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, wr[t].h, low[0], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) al = read(2);
+                if constexpr (!decltype(first)::value) {
+#pragma unroll
+                    for (int i = 16 * t / STEM7_STEPS; i < 16 * (t + 1) / STEM7_STEPS; ++i) store_one(b - 1, i, prev);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // The next tile's loads end here, ahead of the stores: waiting for them behind a number of stores that is not known would wait for those as well.
+            if constexpr (decltype(first)::value) {
+#pragma unroll
+                for (int k = 0; k < FILL; ++k) asm volatile("" : "+v"(staged[k].x), "+v"(staged[k].y), "+v"(staged[k].z), "+v"(staged[k].w));
+            }
+            acc += low[0] + low[1];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) probe += acc[i];
+            prev = acc;
+        };
+        block(0, word_of(0), std::true_type{});
+#pragma unroll 1
+        for (int b = 1; b < nblk; ++b) block(b, word_of(b), std::false_type{});      // uniform over the wave
+        store(nblk - 1, prev);
+        // An infinity or a NaN in a result, or an operand below 2^-110: the tile once more on the fp32 instruction.
+        if (__syncthreads_or(!(__builtin_fabsf(probe) < __builtin_inff()) || pieces_lost(lost | lost_w))) {
+            const int total = gm.rows_in * (gm.rowlen / 4);
+            for (int idx = tid; idx < total; idx += nthreads) {      // the rows as they are
+                const int ri = idx / (gm.rowlen / 4), e = 4 * (idx - ri * (gm.rowlen / 4));
+                const int hh = p0 * ST - gm.pad + ri, f = (q0 * ST - gm.pad) * 3 + e;
+                for (int u = 0; u < 4; ++u)
+                    rows[4 * idx + u] = (unsigned)hh < (unsigned)gm.H && (unsigned)(f + u) < (unsigned)(gm.W * 3) ? x[((int64_t)n * gm.H + hh) * gm.W * 3 + f + u] : 0.0f;
+            }
+            __syncthreads();
+            for (int b = 0; b < nblk; ++b) {
+                int m = 32 * (MBW * mg + b) + l32;
+                if (m >= gm.nrow * gm.qn) m = 0;
+                const int pr = gm.nrow == 1 ? 0 : m / gm.qn, at = pr * ST * gm.rowlen + (m - pr * gm.qn) * ST * 3;
+                floatx16 acc;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+                for (int r = 0; r < R; ++r)
+                    for (int t = 0; t < KP; ++t) {      // the padding of the last pair: filter value zero, the window's own value again
+                        const int j = 2 * t + h < RUN ? 2 * t + h : 2 * t;
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(rows[at + r * gm.rowlen + j], 2 * t + h < RUN ? wk[r * RUN + j] : 0.0f, acc, 0, 0, 0);
+                    }
+                store(b, acc);
+            }
+            __syncthreads();
+        }
+        lost = 0;
+        if (next < tiles) stem7_fill_write((unsigned *)rows, staged, gm, plane, tid, nthreads, lost);
         __syncthreads();
     }
 }
@@ -481,6 +694,24 @@ void launch_stem_fwd(hipStream_t st, const float *x, const float *w, float *y, c
     // workgroups of a launch: each keeps its filters for all its tiles (measured on the ResNet-50, MobileNetV2 and VGG-16
     // first layers: 1024 workgroups at or near the best time, 256 and one per tile 10-25 % slower)
     const unsigned grid = (unsigned)std::min<int64_t>(sp.gm.tiles, 1024);
+    if constexpr (R == 7) {
+        Stem7Geom a{};
+        StemGeom &gm = a.g = sp.gm;
+        gm.xlead = 0;
+        gm.rowlen = ((gm.qn - 1) * 6 + 24 + 3) / 4 * 4;      // the last window's third group of eight ends inside
+        a.per_img = (unsigned)(gm.row_tiles * gm.col_tiles);
+        magic_of(a.per_img, a.img_mul, a.img_shift);
+        magic_of((unsigned)gm.col_tiles, a.col_mul, a.col_shift);
+        magic_of((unsigned)gm.qn, a.qn_mul, a.qn_shift);
+        magic_of((unsigned)gm.rowlen / 4, a.row4_mul, a.row4_shift);
+        a.bytes = (unsigned)(gm.H * gm.W * 12);
+        const size_t bytes = (size_t)gm.rows_in * gm.rowlen * 6 + (size_t)gm.K / 32 * STEM7_STEPS * 1024;
+        if (bytes <= 64 * 1024 && (int64_t)gm.H * gm.W < ((int64_t)1 << 28) && gm.tiles < ((int64_t)1 << 30)) {      // (beyond: 96 and 128 channels over many rows)
+            hipLaunchKernelGGL(stem7_fwd_kernel, dim3((unsigned)std::min(sp.gm.tiles, STEM7_WORKGROUPS)), dim3(block), bytes, st, x, w, y, a);
+            hip_check(hipGetLastError(), "stem_fwd launch");
+            return;
+        }
+    }
     hipLaunchKernelGGL((stem_fwd_kernel<R, S, ST>), dim3(grid), dim3(block), sp.lds_bytes, st, x, w, y, sp.gm);
     hip_check(hipGetLastError(), "stem_fwd launch");
 }

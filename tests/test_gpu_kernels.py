@@ -1444,6 +1444,66 @@ def test_first_layer_kernels_refuse_what_they_are_not_for():
                    5 * 64 * 27 * 4 - 4)
 
 
+def stem7_64(x, w, pad):
+    n, h, wd, _ = x.shape
+    P, Q = (h + 2 * pad - 7) // 2 + 1, (wd + 2 * pad - 7) // 2 + 1
+    xp = np.pad(x.astype(np.float64), ((0, 0), (pad, pad), (pad, pad), (0, 0)))
+    return sum(xp[:, r:r + 2 * P - 1:2, s:s + 2 * Q - 1:2, :] @ w[:, r, s, :].astype(np.float64).T for r in range(7) for s in range(7))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # N, H, W, K, pad
+    (1, 7, 7, 32, 0),          # one position
+    (2, 9, 40, 64, 3),         # whole rows, several in a tile
+    (3, 61, 63, 64, 3),        # rows at odd offsets of a 16-byte piece; 224 positions are seven rows of 32
+    (1, 12, 379, 64, 0),       # 187 positions in a row: one row a tile (wider ones are refused: more than eight pieces of 16 bytes per thread)
+    (2, 20, 96, 32, 3),        # one block of channels, the last tile two rows of four
+    (2, 65, 65, 96, 2),        # three blocks of channels, one group of position blocks
+    (12, 224, 224, 64, 3),     # 672 tiles: some workgroups take two, their waves' groups change places
+])
+def test_stem_7x7_on_pieces_matches_64_bits(case):
+    """147 products in eleven steps, one rounding each: 7e-8 measured, bound 3e-7 (the fp32 instruction 2.2e-7)."""
+    torch = torch_mod()
+    N, H, W, K, pad = case
+    rng = np.random.default_rng(6)
+    x, w = rng.standard_normal((N, H, W, 3), dtype=np.float32), rng.standard_normal((K, 7, 7, 3), dtype=np.float32) * np.float32(0.117)
+    want = stem7_64(x, w, pad)
+    y = torch.full(want.shape, float("nan"), dtype=torch.float32, device="cuda")
+    dx, dw = dev(x), dev(w)
+    monet.call("monet_conv_stem_fwd", None, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), N, H, W, K, 7, 7, 2, pad)
+    got = y.cpu().numpy()
+    assert np.linalg.norm(got - want) <= 3e-7 * np.linalg.norm(want)
+    assert np.abs(got - want).max() <= 50 * 3e-7 * np.sqrt((want ** 2).mean())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["tiny image", "tiny filter", "infinity", "nan", "large"])
+def test_stem_7x7_with_operands_beyond_the_pieces(kind):
+    """Tiles that pieces do not hold go through the fp32 instruction: an infinity or a NaN stays in the windows that hold it (a window's padded third group reaches one pixel
+    further, where its filter value is zero), and numbers below 2^-110 or near the largest keep fp32's precision (150 products of up to 5: 1e36 stays finite)."""
+    torch = torch_mod()
+    N, H, W, K = 2, 31, 45, 64
+    rng = np.random.default_rng(7)
+    x, w = rng.standard_normal((N, H, W, 3), dtype=np.float32), rng.standard_normal((K, 7, 7, 3), dtype=np.float32) * np.float32(0.117)
+    if kind == "tiny image": x *= np.float32(1e-35)
+    if kind == "tiny filter": w *= np.float32(1e-35)
+    if kind == "large": x *= np.float32(1e36)
+    want = stem7_64(x, w, 3)
+    hit = np.zeros(want.shape[:3], bool)
+    if kind in ("infinity", "nan"):
+        x[1, 14, 20, 1] = np.inf if kind == "infinity" else np.nan
+        for p in range(want.shape[1]):
+            for q in range(want.shape[2]):
+                hit[1, p, q] = 0 <= 14 - (2 * p - 3) < 7 and 0 <= 20 - (2 * q - 3) < 7
+    y = torch.full(want.shape, float("nan"), dtype=torch.float32, device="cuda")
+    dx, dw = dev(x), dev(w)
+    monet.call("monet_conv_stem_fwd", None, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), N, H, W, K, 7, 7, 2, 3)
+    got = y.cpu().numpy()
+    assert np.linalg.norm(got[~hit] - want[~hit]) <= 1e-6 * np.linalg.norm(want[~hit])
+    assert not np.isfinite(got[hit]).any()
+
+
 POINTWISE_WGRAD_CASES = [
     # N, H, W, C, K, splits: the channel pairs of MobileNetV2's expansion / projection layers (each selects another
     # combination of 16-byte and 4-byte loads of the wide side), position counts that leave a ragged tail, workgroups
