@@ -698,6 +698,96 @@ __global__ __launch_bounds__(512) void bn_bwd_apply(const float *__restrict__ dy
     }
 }
 
+// Both passes in one for tensors of few rows: a workgroup takes 2^gw_shift channel groups and all rows, up to four per thread, which stay in registers between the sums and the apply
+// step.  Threads of a group are added lanes first, then waves in order.
+constexpr int SMALL_THREADS = 1024, SMALL_ROWS = 4;      // rows per thread
+// Below 1024 rows a workgroup reads 64 bytes of a row and more; up to 4096 as few as 16, for which only few channels are worth the launches saved.  us of a call, two or three launches and one:
+// 512 x 16 7.5 and 4.6, 196 x 1024 9.4 and 4.8, 1024 x 256 9.9 and 5.6, 1024 x 2048 12.9 and 9.5; 2048 x 256 10.1 and 7.8, x 512 10.1 and 12.2; 4096 x 64 10.2 and 10.1, x 96 10.5 and 11.8.
+// A step with four layers of 512 x 16: 185.1 -> 173.4 us.  (The kernel counts float4 in 32 bits.)
+bool small_rows(int64_t rows, int C) {
+    return (rows <= 1024 || (rows <= 2048 && C <= 256) || (rows <= 4096 && C <= 64)) && rows * (C / 4) <= INT32_MAX - 4 * SMALL_THREADS * (int64_t)(C / 4);
+}
+template <bool FROM_OUT, int RM>
+__global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, const void *__restrict__ rt, const float *t, const float *__restrict__ gamma,
+                                                              const float *__restrict__ beta, const float *__restrict__ stats, float *dx, int acc, float *side, int side_acc,
+                                                              float *__restrict__ dgamma, float *__restrict__ dbeta, int rows, int C, int gw_shift) {
+    __shared__ float red[SMALL_THREADS / 64][8][8], sums[8][8];
+    const int C4 = C / 4, gw = 1 << gw_shift, tid = threadIdx.x, gl = tid & (gw - 1), cg = blockIdx.x * gw + gl, r0 = tid >> gw_shift, step = SMALL_THREADS >> gw_shift;
+    const bool here = cg < C4;
+    const uint64_t *mask = (const uint64_t *)rt;
+    f4 g[SMALL_ROWS], v[SMALL_ROWS], rv[SMALL_ROWS];
+    unsigned bits[SMALL_ROWS];
+    float sc[4], sh[4], a[4];
+#pragma unroll
+    for (int u = 0; u < SMALL_ROWS; ++u) {
+        const int row = r0 + u * step, i = row * C4 + cg;
+        g[u] = v[u] = rv[u] = f4{0, 0, 0, 0};
+        bits[u] = 0;
+        if (!here || row >= rows) continue;
+        g[u] = *((const f4 *)dy + i);
+        v[u] = *((const f4 *)t + i);
+        if (RM == 1) bits[u] = (unsigned)(mask[i >> 4] >> ((i & 15) * 4)) & 15u;
+        if (RM >= 2) rv[u] = *((const f4 *)rt + i);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = here ? cg * 4 + j : 0;
+        if (FROM_OUT) { sc[j] = 1.0f / gamma[c]; sh[j] = -beta[c] * sc[j]; }
+        else { sc[j] = stats[C + c]; sh[j] = -stats[c] * sc[j]; }
+        a[j] = gamma[c] * stats[C + c];
+    }
+    float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < SMALL_ROWS; ++u) {
+        if (!here || r0 + u * step >= rows) continue;
+        float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w}, vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        relu_gate<RM>(gg, bits[u], rv[u]);
+        g[u] = f4{gg[0], gg[1], gg[2], gg[3]};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sum[2 * j] += gg[j];
+            sum[2 * j + 1] += gg[j] * (vv[j] * sc[j] + sh[j]);
+        }
+    }
+    for (int o = gw; o < 64; o *= 2)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[j] += __shfl_xor(sum[j], o);
+    if ((tid & 63) < gw) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) red[tid >> 6][gl][j] = sum[j];
+    }
+    __syncthreads();
+    if (tid < 8 * gw) {
+        const int k = tid >> 3, j = tid & 7;
+        double in_order = 0;
+#pragma unroll
+        for (int w = 0; w < SMALL_THREADS / 64; ++w) in_order += (double)red[w][k][j];
+        const float s = (float)in_order;
+        sums[k][j] = s / (float)rows;
+        const int c = (blockIdx.x * gw + k) * 4 + (j >> 1);
+        if (c < C) (j & 1 ? dgamma : dbeta)[c] = s;
+    }
+    __syncthreads();
+    float mb[4], mg[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        mb[j] = sums[gl][2 * j];
+        mg[j] = sums[gl][2 * j + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < SMALL_ROWS; ++u) {
+        const int row = r0 + u * step, i = row * C4 + cg;
+        if (!here || row >= rows) continue;
+        if (side) *((f4 *)side + i) = side_acc ? g[u] + *((const f4 *)side + i) : g[u];
+        const float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w}, vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        f4 r;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[j] = a[j] * (gg[j] - mb[j] - (vv[j] * sc[j] + sh[j]) * mg[j]);
+        if (acc) r += *((const f4 *)dx + i);
+        *((f4 *)dx + i) = r;
+    }
+}
+
 void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, const float *gamma, const float *beta,
             const float *stats, float *dx, float *dgamma, float *dbeta, int64_t rows, int C, bool accumulate, float *scratch,
             size_t scratch_bytes, const void *relu_t, int relu_mode, bool six, float *side, bool side_acc) {
@@ -726,6 +816,15 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
         if (from_output) { switch (rm) { case 0: STEP(true, 0); break; case 1: STEP(true, 1); break; case 2: STEP(true, 2); break; default: STEP(true, 3); } } \
         else             { switch (rm) { case 0: STEP(false, 0); break; case 1: STEP(false, 1); break; case 2: STEP(false, 2); break; default: STEP(false, 3); } } \
     } while (0)
+    if (small_rows(rows, C)) {
+        int gw_shift = 3;
+        while (gw_shift > 0 && (rows > (int64_t)SMALL_ROWS * (SMALL_THREADS >> gw_shift) || (1 << (gw_shift - 1)) >= C4)) --gw_shift;
+#define BS(F, RM) hipLaunchKernelGGL((bn_bwd_small<F, RM>), dim3((C4 + (1 << gw_shift) - 1) >> gw_shift), dim3(SMALL_THREADS), 0, st, dy, relu_t, t, gamma, beta, stats, dx, acc, side, sacc, dgamma, dbeta, (int)rows, C, gw_shift)
+        BOTH(BS);
+#undef BS
+        hip_check(hipGetLastError(), "bn_bwd launch");
+        return;
+    }
     // channel groups that leave lanes of the row-shared mapping idle take the flat mapping (same thread count as the apply pass)
     int slabs = g.G;
     if (g.C4 % g.TPR != 0 && apply_threads % C4 == 0) {
@@ -740,8 +839,8 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
         BOTH(BP);
     }
     const BwdSums sums{scratch, dgamma, dbeta, rows, slabs};
-    // Few slabs and channels (small tensors): no launch of its own for their sums (a step with four such layers, 512 x 16: 190.6 -> 185.3 us).  Beyond 16
-    // slabs or 256 channels every workgroup would read more than a launch takes.
+    // Few slabs and channels: no launch of its own for their sums (512 x 16, before bn_bwd_small took it: a step with four such layers 190.6 -> 185.3 us).  Beyond 16
+    // slabs or 256 channels every workgroup would read more than a launch takes.  Reached by four channels of up to 8192 rows, and where scratch holds few slabs.
     if (slabs <= FEW_SLABS && C <= FEW_CHANNELS) {
         BOTH(BAF);
     } else {

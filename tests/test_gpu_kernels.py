@@ -951,6 +951,41 @@ def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
     assert (np.abs(dx.cpu().numpy() - want_dx) <= bound).all()
 
 
+# the edges of what one launch takes (1024 rows, 2048 of up to 256 channels, 4096 of up to 64) and of the rows and channel groups a workgroup is given
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows, C", [(1, 4), (2, 36), (49, 1028), (512, 32), (513, 20), (1024, 48), (1024, 2048), (1025, 260), (2048, 256), (2049, 64), (4096, 60), (4097, 8)])
+def test_bn_backward_in_one_launch_matches_64_bits(rows, C):
+    """From the input and from the output, written and accumulated.  Sums as above: 1e-5 of the terms' sizes."""
+    torch = torch_mod()
+    rng = np.random.default_rng(rows + C)
+    dy, x = rng.standard_normal((rows, C), dtype=np.float32), rng.standard_normal((rows, C), dtype=np.float32) + np.float32(0.5)
+    gamma, beta = rng.uniform(0.5, 1.5, C).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+    mean, inv = x.astype(np.float64).mean(0), 1 / np.sqrt(x.astype(np.float64).var(0) + 1e-5)
+    stats = np.concatenate([mean, inv]).astype(np.float32)
+    xhat = (x - stats[:C].astype(np.float64)) * stats[C:].astype(np.float64)
+    y = (gamma * xhat + beta).astype(np.float32)
+    dyd, gd, bd, sd = dev(dy), dev(gamma), dev(beta), dev(stats)
+    scratch = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    scale = gamma.astype(np.float64) * stats[C:]
+    g = dy.astype(np.float64)
+    want_b, want_g = g.sum(0), (g * xhat).sum(0)
+    want_dx = scale * (g - want_b / rows - xhat * (want_g / rows))
+    for from_output in (0, 1):
+        # an xhat taken from the output carries the output's rounding, and what beta takes from it
+        size_x = np.abs(xhat) + (np.abs(stats[:C]) * stats[C:] if not from_output else (np.abs(y) + np.abs(beta)) / gamma)
+        size_b, size_g = np.abs(g).sum(0), (np.abs(g) * size_x).sum(0)
+        bound = 1e-5 * scale * (np.abs(g) + size_b / rows + size_x * (1 + size_g / rows))
+        for acc in (0, 1):
+            dx = dev(x) if acc else torch.full((rows, C), float("nan"), device="cuda")
+            dgamma, dbeta = torch.full((C,), float("nan"), device="cuda"), torch.full((C,), float("nan"), device="cuda")
+            td = dev(y if from_output else x)
+            monet.call("monet_bn_bwd", None, dyd.data_ptr(), td.data_ptr(), from_output, gd.data_ptr(), bd.data_ptr(), sd.data_ptr(), dx.data_ptr(), dgamma.data_ptr(),
+                       dbeta.data_ptr(), rows, C, acc, scratch.data_ptr(), scratch.numel())
+            assert (np.abs(dbeta.cpu().numpy() - want_b) <= 1e-5 * size_b).all()
+            assert (np.abs(dgamma.cpu().numpy() - want_g) <= 1e-5 * size_g).all()
+            assert (np.abs(dx.cpu().numpy() - (want_dx + (x if acc else 0))) <= bound + 1e-7 * acc * np.abs(x)).all()
+
+
 # one-kernel Winograd form on fp16 pieces: reductions of 64 channels and more, in chunks of 16
 PIECES_CASES = [
     # N, H, W, C, K
