@@ -1165,27 +1165,28 @@ __global__ __launch_bounds__(64 * WM * WN * KS, KS == 1 && (WM * WN < 4 || (WM *
     write_results<MODE, FAST != 0>(ta, acc, stage, at, lane);
 }
 
-// Launches of few results: a workgroup of eight waves per 64 x 32 of them, the reduction steps dealt to the waves in turn.  Each wave loads its operands straight
-// into the matrix instruction's lanes (eight reduction indices of a row or column), splits them there and adds up a 64 x 32 block of its own; the
+// Launches of few results: a workgroup of eight waves per 64 x 32 or 32 x 32 of them, the reduction steps dealt to the waves in turn.  Each wave loads its operands straight
+// into the matrix instruction's lanes (eight reduction indices of a row or column), splits them there and adds up a block of its own; the
 // eight blocks are added in wave order through LDS, and the first wave writes the result.  No operand passes through LDS, no wave waits for
 // another before the end, and all loads of a wave's first two steps are on their way at once: such launches are bound by latency.  The tile kernel
 // takes 0.7 us for each of the steps it works one after another, and needs a second kernel where its reduction is cut.
 // Measured against it (us; the tile kernel with the ranges a graph declares, cut where it says so): 3x3, 16 -> 16, 16x16, batch 2: forward 8.9 and 6.2, input gradient 9.7
 // and 6.9; 1x1, 1024 -> 256, 14x14, batch 1: input gradient (cut) 12.9 and 7.7, filter gradient 14.9 and 7.7; 3x3, 60 -> 92, 13x17, batch 3: forward (cut)
-// 12.5 and 9.3, uncut 23.2 and 9.3; 3x3, 512 -> 512, 7x7, batch 1, uncut: 140 and 44.
-// Per step of a wave 1.2 us forward and in the input gradient, 1.7 in the filter gradient (vector instructions of two waves per SIMD, loads that touch a cache
-// line per row), so that long reductions over few tiles are better spread over the GPU.
+// 12.5 and 9.3, uncut 23.2 and 9.3; 3x3, 512 -> 512, 7x7, batch 1, uncut: 140 and 44.  (All with 64 rows.)
+// Per step of a wave 1.2 us forward and in the input gradient, 1.7 in the filter gradient with 64 rows (vector instructions of two waves per SIMD, loads that touch a cache
+// line per row), 0.6 to 0.8 and 1.1 with 32, so that long reductions over few tiles are better spread over the GPU.
 constexpr int SHORT_WAVES = 8;
 
-template <int MODE>
-__global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs ta) {
-    __shared__ float part[SHORT_WAVES][32][64];
+// BLOCKS: blocks of 32 rows
+template <int MODE, int BLOCKS>
+__device__ __forceinline__ void short_tile(const TileArgs &ta) {
+    __shared__ float part[SHORT_WAVES][16 * BLOCKS][64];
     __shared__ int redo;
     const ConvShape &cs = ta.cs;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned tile_m = blockIdx.x / (unsigned)ta.tiles_n;
-    const int64_t row0 = (int64_t)tile_m * 64;
+    const int64_t row0 = (int64_t)tile_m * (32 * BLOCKS);
     const int col0 = (int)(blockIdx.x - tile_m * (unsigned)ta.tiles_n) * 32, col = col0 + l32;
     const int RSC = (int)cs.RSC();
     if (tid == 0) redo = 0;
@@ -1217,9 +1218,9 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
     const int64_t reach = MODE == WGRAD ? 0 : ((int64_t)(nr > 0 ? nr - 1 : 0) * row + (ns > 0 ? ns - 1 : 0)) * inner;
     const int64_t back = ((int64_t)cs.pad * cs.W + cs.pad) * cs.C;      // how far before its image a window begins
     const int64_t a_shift = MODE == FWD ? (back > reach ? back : reach) : reach, b_shift = MODE == WGRAD ? back : 0;
-    unsigned a_voff[2], a_taps[2], b_voff = 0, b_tapbit = 0;
+    unsigned a_voff[BLOCKS], a_taps[BLOCKS], b_voff = 0, b_tapbit = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < BLOCKS; ++i) {
         const int64_t m = row0 + 32 * i + l32;
         const bool ok = m < Mg;
         if (MODE == WGRAD) {
@@ -1256,7 +1257,7 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
     const __amdgpu_buffer_rsrc_t ra = buffer_of(ta.a - a_shift, ta.a_bytes + (unsigned)a_shift * 4u), rb = buffer_of(ta.b - b_shift, ta.b_bytes + (unsigned)b_shift * 4u);
     const unsigned by_cols = taps_n > 0 ? (1024u + taps_n - 1) / taps_n : 0u;      // tap / taps_n for tap < 32
 
-    struct Step { float a[2][8], b[8]; };      // reduction indices 16 t + 8 g .. + 7
+    struct Step { float a[BLOCKS][8], b[8]; };      // reduction indices 16 t + 8 g .. + 7
     auto load = [&](Step &s, int t) {
         if constexpr (MODE == WGRAD) {
             const unsigned m0 = (unsigned)t * BK + 8u * g, q0 = m0 < (unsigned)Kg ? m0 : 0u;
@@ -1271,7 +1272,7 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
                 const unsigned pix = (((n * (unsigned)cs.H + (unsigned)h0) * (unsigned)cs.W + (unsigned)w0) * (unsigned)cs.C + (unsigned)b_shift) * 4u;
                 s.b[e] = buffer_load(rb, here ? pix + b_voff : BUFFER_ABSENT, 0u);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) s.a[i][e] = buffer_load(ra, in && a_taps[i] ? (m0 + e) * (unsigned)cs.K * 4u + a_voff[i] : BUFFER_ABSENT, 0u);
+                for (int i = 0; i < BLOCKS; ++i) s.a[i][e] = buffer_load(ra, in && a_taps[i] ? (m0 + e) * (unsigned)cs.K * 4u + a_voff[i] : BUFFER_ABSENT, 0u);
                 if (++q == (unsigned)cs.Q) {
                     q = 0;
                     if (++p == (unsigned)cs.P) { p = 0; ++n; }
@@ -1286,7 +1287,7 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
                 const unsigned r = (tap * by_cols) >> 10, ss = tap - r * (unsigned)taps_n;
                 const unsigned step = MODE == FWD ? ((r * cs.W + ss) * cs.C + c) * 4u : (unsigned)((int)c - (int)((r * cs.Q + ss) * cs.K)) * 4u;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
+                for (int i = 0; i < BLOCKS; ++i) {
                     const bf4 v = buffer_load4(ra, in && ((a_taps[i] >> tap) & 1u) ? a_voff[i] + step : BUFFER_ABSENT, 0u);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) s.a[i][4 * f + e] = v[e];
@@ -1311,7 +1312,7 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
         if constexpr (decltype(pieces)::value) {
             const PieceRow b = split_row(s.b, lost);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < BLOCKS; ++i) {
                 const PieceRow a = split_row(s.a[i], lost);
                 acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc[i], 0, 0, 0);
                 low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, low[i], 0, 0, 0);
@@ -1324,7 +1325,7 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
 #pragma unroll
             for (int e = 0; e < 8; ++e)
 #pragma unroll
-                for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[i][e], s.b[e], acc[i], 0, 0, 0);
+                for (int i = 0; i < BLOCKS; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[i][e], s.b[e], acc[i], 0, 0, 0);
         }
     };
     auto clear = [&] {
@@ -1351,7 +1352,7 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
     // once more on the fp32 instruction where the pieces do not hold an operand, as in the tile kernel
     float probe = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < BLOCKS; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             acc[i][v] += low[i][v];
@@ -1369,13 +1370,13 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < BLOCKS; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) part[wave][16 * i + v][lane] = acc[i][v];
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 32 / SHORT_WAVES; ++k) {
-        const int v = wave * (32 / SHORT_WAVES) + k;
+    for (int k = 0; k < 16 * BLOCKS / SHORT_WAVES; ++k) {
+        const int v = wave * (16 * BLOCKS / SHORT_WAVES) + k;
         double sum = 0;      // rounded once: fp32 sums in turn would be further from 64 bits than the tile kernel's one chain
 #pragma unroll
         for (int w = 0; w < SHORT_WAVES; ++w) sum += (double)part[w][v][lane];
@@ -1384,12 +1385,28 @@ __global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs t
     __syncthreads();
     if (wave > 0) return;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < BLOCKS; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][v] = part[0][16 * i + v][lane];
-    const TilePlace at{row0, Mg, col0, Hc, Wc, ph, pw, row0 + 64 <= Mg && col0 + 32 <= ta.Ng, true, ta.out};
+    const TilePlace at{row0, BLOCKS == 2 ? Mg : std::min(Mg, row0 + 32), col0, Hc, Wc, ph, pw, BLOCKS == 2 && row0 + 64 <= Mg && col0 + 32 <= ta.Ng, true, ta.out};
     write_results<MODE, true>(ta, acc, &part[1][0][0], at, lane);
 }
+
+// 64 rows of results a workgroup, or 32: half the vector and matrix instructions per step, and twice the workgroups, where the launch leaves at least half of the CUs idle (see
+// short_halves).  The same bits.  us with 64 and with 32 rows: 3x3, 32 -> 64, 12x12, batch 2: 8.3 and 6.3, input gradient 8.1 and 6.2; 1x1, 384 -> 64, 9x9, batch 4 9.0 and 6.9; filter
+// gradient of 3x3, 24 -> 64, 14x14 7.6 and 5.9.  (Both in one kernel cost the one of 64 rows 0.3 us; 32 rows with up to 256 workgroups of 64, two on a CU: forward 1.15 of the time.)
+namespace rows64 {
+template <int MODE>
+__global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs ta) {
+    short_tile<MODE, 2>(ta);
+}
+}  // namespace rows64
+namespace rows32 {
+template <int MODE>
+__global__ __launch_bounds__(64 * SHORT_WAVES) void conv_short_kernel(TileArgs ta) {
+    short_tile<MODE, 1>(ta);
+}
+}  // namespace rows32
 
 // Sums `splits` partial results in a fixed order.  Block = SL waves; wave sl adds splits sl, sl+SL, ...
 // of 64 consecutive elements (four independent partial sums per lane to keep loads in flight),
@@ -1636,13 +1653,20 @@ void launch_cfg(int cfg, Rest... rest) {
 // accumulating, which costs the second kernel nothing there and a read of the result here, 36 - 39 0.88 / 0.99, 44 - 47 0.97 / 1.08, 48 - 51 1.01 / 1.10, with 128 workgroups and
 // more 48 - 51 0.84 / 0.99; filter gradient of more than 64 rows and 32 workgroups and more 36 - 39 0.85 / 0.88, 40 - 43 0.91 / 0.97, 44 - 47 0.99 / 1.03; of at most 64 rows, for which
 // the tile kernel has tiles of 64, 28 - 31 0.85 / 0.90, 32 - 35 0.94 / 1.02, 40 - 43 1.10 / 1.15.
-// Cut launches of less than eight workgroups stay there too: ranges bring more CUs to work (1x1, 512 -> 32, 9x9, batch 4, six of them: 10.3 and 10.4; eight, 5x5,
-// 24 -> 64, 10x10, batch 2: 13.1 and 9.8).
+// With a workgroup per 32 rows (short_halves) it is faster: 3000 launches of either kind, uncut 0.81 / 0.87 of the time of the 64-row form.  Cut, time here over time there: forward
+// 66 - 71 steps 0.73 / 0.76, 72 - 77 0.83 / 0.97, 90 - 95 0.91 / 1.04; input gradient 60 - 65 0.80 / 0.85, 78 - 83 0.94 / 0.98, 90 - 95 1.02 / 1.07; accumulating 60 - 65 0.86 / 0.91,
+// 66 - 71 0.93 / 1.00, 72 - 77 1.00 / 1.04; filter gradient of more than 64 rows 54 - 59 0.88 / 0.92, 60 - 65 0.95 / 1.02; of at most 64 36 - 41 0.84 / 0.95, 42 - 47 0.96 / 1.01.
+// Below eight workgroups of 64 rows a cut forward or input-gradient launch is the tile kernel's: it is given its ranges there.
 // `steps` of the longest residue class.
+bool short_halves(int mode, const TileArgs &ta, int64_t classes) {
+    return (ta.Mg + 63) / 64 * ((ta.Ng + 31) / 32) * classes <= NUM_CU / 2 && !(mode == FWD && ta.stats_part);      // BatchNorm's partial statistics are of 64 rows
+}
 bool short_applies(int mode, const TileArgs &ta, int64_t steps, int64_t classes, bool fast, bool cut, bool accumulate = false) {
     const int64_t tiles = (ta.Mg + 63) / 64 * ((ta.Ng + 31) / 32) * classes;
-    const int64_t longest = !cut ? 512 : mode == DGRAD ? (accumulate && tiles < 128 ? 40 : 52) : mode == WGRAD ? (tiles >= 32 && ta.Mg > 64 ? 44 : 32) : 40;
-    return fast && g_cfg_override < 0 && steps >= 4 && steps <= longest && tiles >= (cut ? 8 : 1) && tiles <= NUM_CU;
+    int64_t longest = 512;
+    if (cut && short_halves(mode, ta, classes)) longest = mode == WGRAD ? (ta.Mg > 64 ? 58 : 40) : accumulate ? 68 : 80;
+    else if (cut) longest = mode == DGRAD ? (accumulate && tiles < 128 ? 40 : 52) : mode == WGRAD ? (tiles >= 32 && ta.Mg > 64 ? 44 : 32) : 40;
+    return fast && g_cfg_override < 0 && steps >= 4 && steps <= longest && tiles >= (cut && mode != WGRAD ? 8 : 1) && tiles <= NUM_CU;
 }
 template <int MODE>
 void launch_short(hipStream_t st, TileArgs ta, int classes, float *out, bool accumulate) {
@@ -1653,8 +1677,10 @@ void launch_short(hipStream_t st, TileArgs ta, int classes, float *out, bool acc
     ta.splits = 1;
     ta.accumulate = accumulate ? 1 : 0;
     ta.stream = 0;
-    const dim3 grid((unsigned)((ta.Mg + 63) / 64 * ta.tiles_n), 1, (unsigned)classes);
-    hipLaunchKernelGGL((conv_short_kernel<MODE>), grid, dim3(64 * SHORT_WAVES), 0, st, ta);
+    const bool halves = short_halves(MODE, ta, classes);
+    const dim3 grid((unsigned)((halves ? (ta.Mg + 31) / 32 : (ta.Mg + 63) / 64) * ta.tiles_n), 1, (unsigned)classes);
+    if (halves) hipLaunchKernelGGL((rows32::conv_short_kernel<MODE>), grid, dim3(64 * SHORT_WAVES), 0, st, ta);
+    else hipLaunchKernelGGL((rows64::conv_short_kernel<MODE>), grid, dim3(64 * SHORT_WAVES), 0, st, ta);
     hip_check(hipGetLastError(), "conv launch");
 }
 

@@ -809,6 +809,57 @@ def test_convolutions_of_few_results_match_64_bits(case, kind):
         assert (torch.abs(twice - 2 * dx) <= 1e-6 * torch.abs(dx) + 2.0 ** -148).all()
 
 
+# launches of few results with a workgroup per 32 rows, and the edges of that rule
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # direction, N, H, W, C, K, R, stride, pad, ranges, form (rows per workgroup, 0: the tile kernel)
+    ("f", 1, 1, 1, 64, 4, 1, 1, 0, 1, 32),           # one row
+    ("f", 1, 4, 8, 64, 36, 1, 1, 0, 1, 32),          # 32 rows, two blocks of columns
+    ("f", 1, 3, 11, 20, 32, 3, 1, 1, 1, 32),         # 33
+    ("f", 128, 8, 8, 64, 32, 1, 1, 0, 1, 32),        # 128 blocks of 64 rows
+    ("f", 129, 8, 8, 64, 32, 1, 1, 0, 1, 64),        # 129
+    ("f", 8, 8, 8, 1280, 32, 1, 1, 0, 8, 32),        # cut, 80 steps
+    ("f", 8, 8, 8, 1284, 32, 1, 1, 0, 8, 0),         # 81
+    ("f", 7, 8, 8, 640, 32, 1, 1, 0, 4, 0),          # seven blocks, cut
+    ("d", 5, 13, 11, 36, 28, 3, 2, 1, 1, 32),        # residue classes of different sizes
+    ("d", 8, 8, 8, 32, 1280, 1, 1, 0, 8, 32),
+    ("d", 8, 8, 8, 32, 1284, 1, 1, 0, 8, 0),
+    ("a", 8, 8, 8, 32, 1088, 1, 1, 0, 8, 32),        # accumulating: 68 steps
+    ("a", 8, 8, 8, 32, 1092, 1, 1, 0, 8, 0),
+    ("w", 1, 8, 8, 64, 33 * 4, 3, 1, 1, 1, 32),      # 132 rows
+    ("w", 2, 16, 20, 48, 32, 3, 1, 1, 4, 32),        # cut, at most 64 rows, 40 steps
+    ("w", 2, 16, 21, 48, 32, 3, 1, 1, 4, 0),         # 42
+    ("w", 2, 16, 29, 48, 68, 3, 1, 1, 4, 32),        # more than 64 rows, 58
+    ("w", 2, 16, 30, 48, 68, 3, 1, 1, 4, 0),         # 60
+])
+def test_convolutions_of_few_results_in_blocks_of_32_rows_match_64_bits(case):
+    """Bounds as above."""
+    torch = torch_mod()
+    direction, N, H, W, C, K, R, st, pad, splits, form = case
+    P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
+    rng = np.random.default_rng(23)
+    x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, P, Q, K), dtype=np.float32)
+    w = rng.standard_normal((K, R, R, C), dtype=np.float32)
+    i = {"f": 0, "d": 1, "a": 1, "w": 2}[direction]
+    want, size = conv64(x, w, dy, st, pad)[i], conv64(np.abs(x), np.abs(w), np.abs(dy), st, pad)[i]
+    before = x if direction == "a" else np.full(want.shape, np.nan, dtype=np.float32)
+    xs, ws, ds, out = dev(x), dev(w), dev(dy), dev(before)
+    room = torch.empty(splits * out.numel(), device="cuda")
+    dims, tail = (N, H, W, C, K, R, R, st, pad), (splits, room.data_ptr() if splits > 1 else None, room.numel() * 4 if splits > 1 else 0)
+
+    def call():
+        out.copy_(dev(before))
+        if i == 0: monet.call("monet_conv_fwd", None, xs.data_ptr(), ws.data_ptr(), out.data_ptr(), *dims, *tail)
+        elif i == 1: monet.call("monet_conv_dgrad", None, ds.data_ptr(), ws.data_ptr(), out.data_ptr(), *dims, int(direction == "a"), *tail)
+        else: monet.call("monet_conv_wgrad", None, xs.data_ptr(), ds.data_ptr(), out.data_ptr(), *dims, *tail)
+
+    name = f"rows{form}::conv_short_kernel<{i}>" if form else f"conv_tile_kernel<{i},"
+    assert any(name in k for k in kernels_of(torch, call)), name
+    if direction == "a":
+        want, size = want + x, size + np.abs(x)
+    assert (np.abs(out.cpu().numpy() - want) <= 2e-7 * size).all()
+
+
 # tile shapes and wave groups of the forward pass and the input gradient
 GROUP_CASES = [
     # N, H, W, C, K, R, stride, pad, splits; kernel of the forward pass and of the input gradient: rows / 64, columns / 32, loader, groups (None: the form of few results)
