@@ -699,35 +699,49 @@ __global__ __launch_bounds__(512) void bn_bwd_apply(const float *__restrict__ dy
 }
 
 // Both passes in one for tensors of few rows: a workgroup takes 2^gw_shift channel groups and all rows, up to four per thread, which stay in registers between the sums and the apply
-// step.  Threads of a group are added lanes first, then waves in order.
-constexpr int SMALL_THREADS = 1024, SMALL_ROWS = 4;      // rows per thread
-// Below 1024 rows a workgroup reads 64 bytes of a row and more; up to 4096 as few as 16, for which only few channels are worth the launches saved.  us of a call, two or three launches and one:
-// 512 x 16 7.5 and 4.6, 196 x 1024 9.4 and 4.8, 1024 x 256 9.9 and 5.6, 1024 x 2048 12.9 and 9.5; 2048 x 256 10.1 and 7.8, x 512 10.1 and 12.2; 4096 x 64 10.2 and 10.1, x 96 10.5 and 11.8.
-// A step with four layers of 512 x 16: 185.1 -> 173.4 us.  (The kernel counts float4 in 32 bits.)
-bool small_rows(int64_t rows, int C) {
-    return (rows <= 1024 || (rows <= 2048 && C <= 256) || (rows <= 4096 && C <= 64)) && rows * (C / 4) <= INT32_MAX - 4 * SMALL_THREADS * (int64_t)(C / 4);
+// step, together with what is accumulated on.  Threads of a group are added lanes first, then waves in order.  Every XCD has one contiguous share of the channels, in whole 128-byte lines,
+// since pieces of 16 to 64 bytes of a line that belong to different XCDs cost more than the pass saved (1024 x 16384, us: 63 in two passes, 58 with neighbours on different XCDs, 37 so;
+// accumulating 73, 75 and 46).
+constexpr int SMALL_THREADS = 1024, SMALL_ROWS = 4, SMALL_GROUPS = 8;      // rows per thread; channel groups at most
+// What bounds it: the cache lines that one CU can ask for, one per row and operand, where two passes over many workgroups cost two or three launches.  Its time over theirs (launches of
+// a graph): ungated, with a ReLU's gradient, with that written to a second tensor, and added to one: 512 x 16 0.75 / 0.75 / 0.79 / 0.80, 980 x 2048 0.56 / 0.50 / 0.61 / 0.56,
+// 1600 x 128 0.83 / 0.87 / 0.97 / 1.02, 2048 x 128 0.89 / 0.93 / 1.06 / 1.11, 4096 x 64 1.31 / 1.30 / 1.58 / 1.81; rows that begin inside a line: 900 x 132 0.68 / 0.73 / 0.79 / 0.98,
+// 1024 x 132 0.71 / 0.75 / 0.82 / 1.06, 512 x 72 0.79 / 0.84 / 0.92 / 1.13, 392 x 72 0.77 / 0.82 / 0.87 / 1.01.  Added to what dx holds, without and with all of that: 1024 x 128 0.75 and 0.90,
+// 512 x 64 0.90 and 1.06; 512 x 132 0.87 and 1.02.  Few rows of very many channels leave most threads idle (1 x 20000 0.99, 1 x 25088 1.16, 49 x 65536 0.98), beyond 512 rows lines are shared
+// (1024 x 20000 0.66 / 0.65 / 0.92 / 0.81, 980 x 25088 0.95 / 0.98 / 1.08 / 1.06).  The second tensor must not be asked for here: unfused, a step calls this without it, and has the same bits.
+bool small_rows(int64_t rows, int C, bool accumulate) {
+    if (rows > 1600 || rows * (C / 4) > INT32_MAX - 4 * SMALL_THREADS * (int64_t)(C / 4)) return false;      // (the kernel counts float4 in 32 bits)
+    const bool lines = C % 32 == 0 || C < 32;      // rows begin at a line (or are less than one)
+    if (rows > 1024) return !accumulate && C <= 256 && lines;
+    if (accumulate && rows > (!lines ? 256 : C > 64 ? 1024 : 392)) return false;
+    if (!lines && rows > (C % 16 == 0 || C > 100 ? 900 : 392)) return false;
+    return (rows >= 64 && rows <= 512) || C <= 20000;
 }
 template <bool FROM_OUT, int RM>
 __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, const void *__restrict__ rt, const float *t, const float *__restrict__ gamma,
                                                               const float *__restrict__ beta, const float *__restrict__ stats, float *dx, int acc, float *side, int side_acc,
                                                               float *__restrict__ dgamma, float *__restrict__ dbeta, int rows, int C, int gw_shift) {
-    __shared__ float red[SMALL_THREADS / 64][8][8], sums[8][8];
-    const int C4 = C / 4, gw = 1 << gw_shift, tid = threadIdx.x, gl = tid & (gw - 1), cg = blockIdx.x * gw + gl, r0 = tid >> gw_shift, step = SMALL_THREADS >> gw_shift;
+    __shared__ float red[SMALL_THREADS / 64][SMALL_GROUPS][8], sums[SMALL_GROUPS][8];
+    const int C4 = C / 4, gw = 1 << gw_shift, tid = threadIdx.x, gl = tid & (gw - 1), r0 = tid >> gw_shift, step = SMALL_THREADS >> gw_shift;
+    const int block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3), cg = block * gw + gl;
+    if (block * gw >= C4) return;      // the shares are rounded up
     const bool here = cg < C4;
     const uint64_t *mask = (const uint64_t *)rt;
-    f4 g[SMALL_ROWS], v[SMALL_ROWS], rv[SMALL_ROWS];
+    f4 g[SMALL_ROWS], v[SMALL_ROWS], rv[SMALL_ROWS], o[SMALL_ROWS], so[SMALL_ROWS];
     unsigned bits[SMALL_ROWS];
     float sc[4], sh[4], a[4];
 #pragma unroll
     for (int u = 0; u < SMALL_ROWS; ++u) {
         const int row = r0 + u * step, i = row * C4 + cg;
-        g[u] = v[u] = rv[u] = f4{0, 0, 0, 0};
+        g[u] = v[u] = rv[u] = o[u] = so[u] = f4{0, 0, 0, 0};
         bits[u] = 0;
         if (!here || row >= rows) continue;
         g[u] = *((const f4 *)dy + i);
         v[u] = *((const f4 *)t + i);
         if (RM == 1) bits[u] = (unsigned)(mask[i >> 4] >> ((i & 15) * 4)) & 15u;
         if (RM >= 2) rv[u] = *((const f4 *)rt + i);
+        if (acc) o[u] = *((const f4 *)dx + i);
+        if (side && side_acc) so[u] = *((const f4 *)side + i);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -764,7 +778,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, c
         for (int w = 0; w < SMALL_THREADS / 64; ++w) in_order += (double)red[w][k][j];
         const float s = (float)in_order;
         sums[k][j] = s / (float)rows;
-        const int c = (blockIdx.x * gw + k) * 4 + (j >> 1);
+        const int c = (block * gw + k) * 4 + (j >> 1);
         if (c < C) (j & 1 ? dgamma : dbeta)[c] = s;
     }
     __syncthreads();
@@ -778,12 +792,12 @@ __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, c
     for (int u = 0; u < SMALL_ROWS; ++u) {
         const int row = r0 + u * step, i = row * C4 + cg;
         if (!here || row >= rows) continue;
-        if (side) *((f4 *)side + i) = side_acc ? g[u] + *((const f4 *)side + i) : g[u];
+        if (side) *((f4 *)side + i) = side_acc ? g[u] + so[u] : g[u];
         const float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w}, vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
         f4 r;
 #pragma unroll
         for (int j = 0; j < 4; ++j) r[j] = a[j] * (gg[j] - mb[j] - (vv[j] * sc[j] + sh[j]) * mg[j]);
-        if (acc) r += *((const f4 *)dx + i);
+        if (acc) r += o[u];
         *((f4 *)dx + i) = r;
     }
 }
@@ -816,10 +830,10 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
         if (from_output) { switch (rm) { case 0: STEP(true, 0); break; case 1: STEP(true, 1); break; case 2: STEP(true, 2); break; default: STEP(true, 3); } } \
         else             { switch (rm) { case 0: STEP(false, 0); break; case 1: STEP(false, 1); break; case 2: STEP(false, 2); break; default: STEP(false, 3); } } \
     } while (0)
-    if (small_rows(rows, C)) {
-        int gw_shift = 3;
+    if (small_rows(rows, C, accumulate)) {
+        int gw_shift = 3;      // and a grid of whole shares: eight XCDs, lines of eight groups
         while (gw_shift > 0 && (rows > (int64_t)SMALL_ROWS * (SMALL_THREADS >> gw_shift) || (1 << (gw_shift - 1)) >= C4)) --gw_shift;
-#define BS(F, RM) hipLaunchKernelGGL((bn_bwd_small<F, RM>), dim3((C4 + (1 << gw_shift) - 1) >> gw_shift), dim3(SMALL_THREADS), 0, st, dy, relu_t, t, gamma, beta, stats, dx, acc, side, sacc, dgamma, dbeta, (int)rows, C, gw_shift)
+#define BS(F, RM) hipLaunchKernelGGL((bn_bwd_small<F, RM>), dim3((C4 + 63) / 64 * (64 >> gw_shift)), dim3(SMALL_THREADS), 0, st, dy, relu_t, t, gamma, beta, stats, dx, acc, side, sacc, dgamma, dbeta, (int)rows, C, gw_shift)
         BOTH(BS);
 #undef BS
         hip_check(hipGetLastError(), "bn_bwd launch");
@@ -840,7 +854,8 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
     }
     const BwdSums sums{scratch, dgamma, dbeta, rows, slabs};
     // Few slabs and channels: no launch of its own for their sums (512 x 16, before bn_bwd_small took it: a step with four such layers 190.6 -> 185.3 us).  Beyond 16
-    // slabs or 256 channels every workgroup would read more than a launch takes.  Reached by four channels of up to 8192 rows, and where scratch holds few slabs.
+    // slabs or 256 channels every workgroup would read more than a launch takes.  Reached by tensors that small_rows leaves here, up to 1344 rows of 36 channels, 2048 of 16 and 8192 of four,
+    // and where scratch holds few slabs.
     if (slabs <= FEW_SLABS && C <= FEW_CHANNELS) {
         BOTH(BAF);
     } else {

@@ -1002,10 +1002,17 @@ def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
     assert (np.abs(dx.cpu().numpy() - want_dx) <= bound).all()
 
 
-# the edges of what one launch takes (1024 rows, 2048 of up to 256 channels, 4096 of up to 64) and of the rows and channel groups a workgroup is given
+# the edges of what one launch takes and of the rows and channel groups a workgroup is given: rows, channels, whether one launch takes them written and accumulated
+ONE_LAUNCH_CASES = [
+    (1, 4, 1, 1), (2, 36, 1, 1), (49, 1028, 1, 1), (512, 32, 1, 0), (392, 64, 1, 1), (393, 64, 1, 0), (393, 68, 0, 0), (257, 100, 1, 0), (256, 100, 1, 1), (513, 20, 1, 0), (900, 48, 1, 0),
+    (901, 48, 0, 0), (900, 104, 1, 0), (901, 104, 0, 0), (1024, 48, 0, 0), (1024, 96, 1, 1), (1024, 2048, 1, 1), (1025, 96, 1, 0), (1025, 260, 0, 0), (1600, 256, 1, 0), (1600, 288, 0, 0),
+    (1601, 32, 0, 0), (1600, 28, 1, 0), (2048, 256, 0, 0), (2049, 64, 0, 0), (4096, 60, 0, 0), (4097, 8, 0, 0), (1024, 25088, 0, 0), (63, 20004, 0, 0), (64, 20004, 1, 1), (1, 65536, 0, 0),
+]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows, C", [(1, 4), (2, 36), (49, 1028), (512, 32), (513, 20), (1024, 48), (1024, 2048), (1025, 260), (2048, 256), (2049, 64), (4096, 60), (4097, 8)])
-def test_bn_backward_in_one_launch_matches_64_bits(rows, C):
+@pytest.mark.parametrize("rows, C, written, accumulated", ONE_LAUNCH_CASES)
+def test_bn_backward_in_one_launch_matches_64_bits(rows, C, written, accumulated):
     """From the input and from the output, written and accumulated.  Sums as above: 1e-5 of the terms' sizes."""
     torch = torch_mod()
     rng = np.random.default_rng(rows + C)
@@ -1030,8 +1037,9 @@ def test_bn_backward_in_one_launch_matches_64_bits(rows, C):
             dx = dev(x) if acc else torch.full((rows, C), float("nan"), device="cuda")
             dgamma, dbeta = torch.full((C,), float("nan"), device="cuda"), torch.full((C,), float("nan"), device="cuda")
             td = dev(y if from_output else x)
-            monet.call("monet_bn_bwd", None, dyd.data_ptr(), td.data_ptr(), from_output, gd.data_ptr(), bd.data_ptr(), sd.data_ptr(), dx.data_ptr(), dgamma.data_ptr(),
-                       dbeta.data_ptr(), rows, C, acc, scratch.data_ptr(), scratch.numel())
+            names = kernels_of(torch, lambda: monet.call("monet_bn_bwd", None, dyd.data_ptr(), td.data_ptr(), from_output, gd.data_ptr(), bd.data_ptr(), sd.data_ptr(), dx.data_ptr(),
+                                                         dgamma.data_ptr(), dbeta.data_ptr(), rows, C, acc, scratch.data_ptr(), scratch.numel()))
+            assert any("bn_bwd_small" in k for k in names) == bool(accumulated if acc else written), names
             assert (np.abs(dbeta.cpu().numpy() - want_b) <= 1e-5 * size_b).all()
             assert (np.abs(dgamma.cpu().numpy() - want_g) <= 1e-5 * size_g).all()
             assert (np.abs(dx.cpu().numpy() - (want_dx + (x if acc else 0))) <= bound + 1e-7 * acc * np.abs(x)).all()

@@ -232,6 +232,31 @@ def test_fused_neighbours_give_identical_bits():
     assert recomputed_bn > 0 and apply_launches < recomputed_bn
 
 
+@pytest.mark.parametrize("n, h, w, c", [(1, 14, 28, 72), (1, 15, 27, 72), (1, 28, 32, 48), (1, 29, 32, 48), (1, 32, 32, 64), (1, 25, 41, 64), (4, 20, 20, 128), (1, 41, 40, 64)])
+def test_fused_batchnorm_backward_of_few_rows_gives_identical_bits(n, h, w, c):
+    """On either side of the lines between the kernels of BatchNorm's backward pass, which a residual block calls with the other branch's gradient to write or without, fused or not."""
+    g = graphs.Graph()
+    a = g.ext("x", "f32", (n, h, w, c))
+    g.begin_block("before")
+    a = g.relu(g.bn(g.conv(a, c, 1, name="before"), name="before.bn"))
+    g.end_block()
+    g.begin_block("block")
+    b = g.relu(g.bn(g.conv(a, c, 1, name="first"), name="first.bn"))
+    a = g.relu(g.add(g.bn(g.conv(b, c, 1, name="second"), name="second.bn"), a))
+    g.end_block()
+    g.sumloss(a)
+    exts, params = tensors.make_inputs(g, seed=4, gamma_beta="random")
+    run = StepRunner(g.text(), schedules.block_output_schedule(g).text(), exts, params)
+    labels = {l[0] for l in run.plan.launches()}
+    assert {"relu_bn_bwd", "relu_add_bn_bwd"} <= labels, labels
+    run.step()
+    fused = run.grads_numpy()
+    run.plan.set_fusion(False)
+    run.step()
+    plain = run.grads_numpy()
+    assert all(np.array_equal(fused[p], plain[p]) for p in fused)
+
+
 def test_layers_with_a_workspace_and_one_range_cut_their_reduction_in_a_plan(monkeypatch):
     """Convolutions that declare a workspace with splits = 1 cut a reduction of few tiles by themselves.  Statistics, BatchNorm and ReLU that ride
     in the epilogue otherwise then follow it: the same bits with fused launches as one by one, and the loss and
