@@ -976,9 +976,19 @@ def test_cut_input_gradients_that_accumulate_take_the_faster_form(case):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows, C", [(1, 4), (33, 16), (512, 16), (2047, 16), (4099, 16), (70, 60), (300, 256), (300, 260), (40, 1024)])
-def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
-    """Partial sums that every apply workgroup adds for itself (up to 16 slabs and 256 channels) and beyond.  Sums of `rows` terms in fp32, in slabs: 1e-5 of the terms' sizes."""
+@pytest.mark.parametrize("rows, C, slabs, kernel", [
+    # slabs: partial results that the scratch holds (0: 4 MiB of them)
+    (1, 4, 0, "small"), (33, 16, 0, "small"), (512, 16, 0, "small"), (2047, 16, 0, "few"), (4099, 16, 0, "final"), (70, 60, 0, "small"), (300, 256, 0, "small"),
+    (300, 260, 0, "small"), (40, 1024, 0, "small"),
+    (8192, 4, 0, "few"), (8193, 4, 0, "final"),                          # 16 and 17 slabs of 512 rows
+    (2048, 16, 0, "few"), (2049, 16, 0, "final"),                        # of 128
+    (1000, 36, 0, "few"), (1344, 36, 0, "few"), (1345, 36, 0, "final"),      # nine channel groups: of 64, rounded up to three sweeps of 28
+    (1700, 256, 16, "few"), (1700, 256, 17, "final"), (1700, 260, 16, "final"),
+    (5000, 20, 1, "few"),
+])
+def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C, slabs, kernel):
+    """Partial sums that every apply workgroup adds for itself (up to 16 slabs and 256 channels) and beyond; tensors of few rows go through one kernel.  Sums of `rows` terms in
+    fp32, in slabs: 1e-5 of the terms' sizes."""
     torch = torch_mod()
     rng = np.random.default_rng(9)
     dy, x = rng.standard_normal((rows, C), dtype=np.float32), rng.standard_normal((rows, C), dtype=np.float32) + np.float32(0.5)
@@ -991,10 +1001,11 @@ def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C):
     want_dx = scale * (g - want_b / rows - xhat * (want_g / rows))
     dx = torch.full((rows, C), float("nan"), device="cuda")
     dgamma, dbeta = torch.full((C,), float("nan"), device="cuda"), torch.full((C,), float("nan"), device="cuda")
-    scratch = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    scratch = torch.empty((slabs + 1) * 8 * C if slabs else 4 << 20, dtype=torch.uint8, device="cuda")
     dyd, xd, gd, bd, sd = dev(dy), dev(x), dev(gamma), dev(beta), dev(stats)
-    monet.call("monet_bn_bwd", None, dyd.data_ptr(), xd.data_ptr(), 0, gd.data_ptr(), bd.data_ptr(), sd.data_ptr(), dx.data_ptr(), dgamma.data_ptr(), dbeta.data_ptr(),
-               rows, C, 0, scratch.data_ptr(), scratch.numel())
+    names = kernels_of(torch, lambda: monet.call("monet_bn_bwd", None, dyd.data_ptr(), xd.data_ptr(), 0, gd.data_ptr(), bd.data_ptr(), sd.data_ptr(), dx.data_ptr(), dgamma.data_ptr(),
+                                                 dbeta.data_ptr(), rows, C, 0, scratch.data_ptr(), scratch.numel()))
+    assert any({"small": "bn_bwd_small<", "few": "bn_bwd_apply<false, 0, true>", "final": "bn_bwd_final"}[kernel] in k for k in names), names
     size_b, size_g = np.abs(g).sum(0), (np.abs(g) * (np.abs(xhat) + np.abs(stats[:C]) * stats[C:])).sum(0)
     assert (np.abs(dbeta.cpu().numpy() - want_b) <= 1e-5 * size_b).all()
     assert (np.abs(dgamma.cpu().numpy() - want_g) <= 1e-5 * size_g).all()
@@ -1717,8 +1728,10 @@ def test_batchnorm_matches_oracle(rows, C):
 
 
 # edges of the ranges small tensors are cut into: one sweep of 256 16-byte elements per workgroup (64 rows of 16 channels), 512
-# workgroups, slabs of two sweeps, the 256th slab; channel groups that are no power of two, and more than 512 of them
-@pytest.mark.parametrize("rows,C", [(3, 4), (63, 16), (64, 16), (65, 16), (127, 16), (129, 16), (32767, 16), (32769, 16), (300, 24), (9, 2052)])
+# workgroups, slabs of two sweeps, the 256th slab; channel groups that are no power of two, and more than 512 of them.  (The backward pass of up to 1024 rows and some more goes through one
+# kernel, which leaves the scratch alone.)
+@pytest.mark.parametrize("rows,C", [(3, 4), (63, 16), (64, 16), (65, 16), (127, 16), (129, 16), (32767, 16), (32769, 16), (300, 24), (9, 2052),
+                                    (1601, 16), (1663, 16), (1664, 16), (1665, 16), (4099, 24), (1100, 2052), (8191, 4), (8193, 4)])
 @pytest.mark.parametrize("slabs", [1, 3, 1024])
 def test_batchnorm_backward_on_small_tensors(rows, C, slabs):
     torch = torch_mod()
