@@ -345,11 +345,20 @@ int winograd_wgrad_most_images(const ConvShape &cs) {
     return (int)std::min<int64_t>({(int64_t)cs.N, PLANE_FLOATS / (th * (int64_t)columns_of(cs) * std::max(cs.C, cs.K)), ((1 << 24) - 1) / (th * tw)});
 }
 
-// Measured against the workspace form on 300 layers of 64 - 512 channels and the networks' (us, that form and this): up to six pairs of blocks 1.03 - 1.7 times as fast (176x112x112
-// 64 -> 128 2412 and 1671, 128 -> 128 3105 and 2807, 320x28x28 96 -> 128 317 and 307, 9x88x88 256 -> 64 156 and 108).  Every further pair reads and splits the vertical maps
-// once more, while the workspace form's 128 x 128 tiles do with fewer of both: from eight on 0.6 - 1.05 (184x14x14 256 -> 256 189 and 230, 176x28x28 512 -> 512 1667 and 1800), except
-// for few tiles, where two launches less and smaller blocks count (1x14x14 304 -> 192 22.7 and 19.4; 2x11x10 368 -> 448 33 and 30; from 150 tiles on 0.94 - 1.0).
-bool winograd_wgrad_applies(const ConvShape &cs) { return (blocks_of(cs) <= 6 * 6 || tiles_of(cs) <= 128) && winograd_wgrad_most_images(cs) >= 1; }
+// Measured against the workspace form (us in a launched graph, that form and this).  Its tiles of 128 x 128 leave half of themselves empty where one side has no more than 64 channels: up to five
+// pairs of blocks 0.42 - 0.97 of its time at any number of tiles (176x112x112 64 -> 128 2417 and 1665, 8x28x28 320 -> 64 41 and 31).  With two blocks and more on both sides, four or six pairs,
+// 0.76 - 0.99 from 256 to 900 tiles and from 3000 on (176x112x112 128 -> 128 3099 and 2750); in between the ranges that fill the CUs cost more to add up than they save (1568 tiles
+// 128 -> 128 47.4 and 53.4, 2048 192 -> 128 73.4 and 78.2), from 129 to 255 that form works uncut (196 tiles 36.3 and 39.6).  Every further pair reads and splits the vertical maps
+// once more, while those tiles do with fewer of both: from eight on 1.0 - 1.7 (184x14x14 256 -> 256 189 and 230, 176x28x28 512 -> 512 1667 and 1800), except for few tiles, where
+// two launches less count, as long as one round of workgroups does it: up to 128 tiles and 42 pairs 0.83 - 1.0 (1x14x14 320 -> 256 23.8 and 21.2), with 49 pairs and more 1.0 - 1.48
+// (32x7x7 1024 -> 1024 118 and 160).
+bool winograd_wgrad_applies(const ConvShape &cs) {
+    const int64_t pairs = blocks_of(cs) / 6, tiles = tiles_of(cs);
+    const bool wide = cs.K > BLOCK && cs.C > BLOCK;
+    if (winograd_wgrad_most_images(cs) < 1) return false;
+    if (tiles <= 128) return blocks_of(cs) <= FUSED_CUS;
+    return pairs <= (wide ? 0 : 5) || (pairs <= 6 && ((tiles >= 256 && tiles <= 900) || tiles >= 3000));
+}
 
 double winograd_wgrad_estimate(const ConvShape &cs, int images, int most) {
     ConvShape part = cs;

@@ -1158,6 +1158,29 @@ def test_winograd_wgrad_with_horizontal_maps_in_the_gemm_matches_64_bits(case):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("case, taken", [
+    # batch, map, C, K: blocks of 64 channels and filters, tiles
+    ((1, 4, 4, 448, 384), True), ((1, 4, 4, 448, 448), False), ((1, 4, 4, 64, 2752), False),      # 42, 49 and 43 pairs of blocks
+    ((1, 64, 32, 68, 68), True), ((1, 172, 12, 68, 68), False),                                   # 128 and 129 tiles, two blocks on either side
+    ((1, 60, 68, 68, 68), False), ((1, 64, 64, 68, 68), True),                                    # 255, 256
+    ((1, 120, 120, 68, 132), True), ((1, 68, 212, 68, 68), False),                                # 900, 901
+    ((1, 116, 412, 68, 68), False), ((1, 200, 240, 68, 68), True),                                # 2987, 3000
+    ((1, 68, 212, 64, 320), True), ((1, 68, 212, 64, 324), False), ((1, 64, 64, 448, 64), False),      # one block on one side: five, six, seven pairs
+])
+def test_winograd_wgrad_takes_the_faster_form(case, taken):
+    """Horizontal maps in the GEMM, or tiles mapped both ways in the workspace: the form on either side of its lines, and that it is right there.  Bound as above."""
+    torch = torch_mod()
+    N, H, W, C, K = case
+    rng = np.random.default_rng(5)
+    x, dy = rng.standard_normal((N, H, W, C), dtype=np.float32), rng.standard_normal((N, H, W, K), dtype=np.float32)
+    got = []
+    names = kernels_of(torch, lambda: got.append(wgrad_maps(torch, x, dy, case + (0,))))
+    assert any("wino4_wgrad_kernel" in k for k in names) == taken, names
+    want = wgrad64(x, dy)
+    assert np.linalg.norm(got[0] - want) <= 2e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["tiny", "huge", "infinity", "nan"])
 def test_winograd_wgrad_with_operands_beyond_the_pieces(kind):
     """Mapped values below 2^-110 leave bits over in the split, infinities and NaN show in the sums: such a workgroup works its range again on the fp32
