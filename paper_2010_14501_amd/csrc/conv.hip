@@ -1181,7 +1181,7 @@ constexpr int SHORT_WAVES = 8;
 template <int MODE, int BLOCKS>
 __device__ __forceinline__ void short_tile(const TileArgs &ta) {
     __shared__ float part[SHORT_WAVES][16 * BLOCKS][64];
-    __shared__ int redo;
+    __shared__ int redo[BLOCKS];      // blocks of 32 rows one by one: both forms of the kernel then give a row the same bits
     const ConvShape &cs = ta.cs;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1189,7 +1189,7 @@ __device__ __forceinline__ void short_tile(const TileArgs &ta) {
     const int64_t row0 = (int64_t)tile_m * (32 * BLOCKS);
     const int col0 = (int)(blockIdx.x - tile_m * (unsigned)ta.tiles_n) * 32, col = col0 + l32;
     const int RSC = (int)cs.RSC();
-    if (tid == 0) redo = 0;
+    if (tid < BLOCKS) redo[tid] = 0;
 
     // residue class of an input gradient, as in the tile kernel
     int64_t Mg = ta.Mg, Kg = ta.Kg;
@@ -1307,13 +1307,15 @@ __device__ __forceinline__ void short_tile(const TileArgs &ta) {
     };
 
     floatx16 acc[2], low[2];      // the h * h terms and the rest, as in the tile kernel
-    unsigned lost = 0;
+    constexpr int COLUMN = BLOCKS == 1 ? 0 : BLOCKS;      // both blocks share the column operand
+    unsigned lost[COLUMN + 1] = {};
+    bool again[BLOCKS] = {};
     auto multiply = [&](const Step &s, auto pieces) {
         if constexpr (decltype(pieces)::value) {
-            const PieceRow b = split_row(s.b, lost);
+            const PieceRow b = split_row(s.b, lost[COLUMN]);
 #pragma unroll
             for (int i = 0; i < BLOCKS; ++i) {
-                const PieceRow a = split_row(s.a[i], lost);
+                const PieceRow a = split_row(s.a[i], lost[i]);
                 acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc[i], 0, 0, 0);
                 low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, low[i], 0, 0, 0);
                 low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, low[i], 0, 0, 0);
@@ -1323,18 +1325,17 @@ __device__ __forceinline__ void short_tile(const TileArgs &ta) {
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int i = 0; i < BLOCKS; ++i)
+                if (BLOCKS == 1 || again[i]) {      // uniform over the workgroup
 #pragma unroll
-                for (int i = 0; i < BLOCKS; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[i][e], s.b[e], acc[i], 0, 0, 0);
+                    for (int e = 0; e < 8; ++e) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[i][e], s.b[e], acc[i], 0, 0, 0);
+                }
         }
     };
-    auto clear = [&] {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][v] = low[i][v] = 0.0f;
-    };
-    clear();
+        for (int v = 0; v < 16; ++v) acc[i][v] = low[i][v] = 0.0f;
     {
         Step s0, s1;
         int t = wave;
@@ -1350,19 +1351,30 @@ __device__ __forceinline__ void short_tile(const TileArgs &ta) {
         }
     }
     // once more on the fp32 instruction where the pieces do not hold an operand, as in the tile kernel
-    float probe = 0.0f;
+    float probe[BLOCKS] = {};
 #pragma unroll
     for (int i = 0; i < BLOCKS; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             acc[i][v] += low[i][v];
-            probe += acc[i][v];
+            probe[i] += acc[i][v];
         }
     __syncthreads();
-    if (!(__builtin_fabsf(probe) < __builtin_inff()) || pieces_lost(lost)) redo = 1;
+#pragma unroll
+    for (int i = 0; i < BLOCKS; ++i)
+        if (!(__builtin_fabsf(probe[i]) < __builtin_inff()) || pieces_lost(lost[i] | lost[COLUMN])) redo[i] = 1;
     __syncthreads();
-    if (redo) {
-        clear();
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < BLOCKS; ++i) {
+        again[i] = __builtin_amdgcn_readfirstlane(redo[i]) != 0;
+        any |= again[i];
+    }
+    if (any) {
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = BLOCKS == 1 || again[i] ? 0.0f : acc[i][v];
         for (int t = wave; t < steps; t += SHORT_WAVES) {
             Step s;
             load(s, t);
@@ -1393,7 +1405,7 @@ __device__ __forceinline__ void short_tile(const TileArgs &ta) {
 }
 
 // 64 rows of results a workgroup, or 32: half the vector and matrix instructions per step, and twice the workgroups, where the launch leaves at least half of the CUs idle (see
-// short_halves).  The same bits.  us with 64 and with 32 rows: 3x3, 32 -> 64, 12x12, batch 2: 8.3 and 6.3, input gradient 8.1 and 6.2; 1x1, 384 -> 64, 9x9, batch 4 9.0 and 6.9; filter
+// short_halves).  The same bits, also beside a row that is worked once more in fp32.  us with 64 and with 32 rows: 3x3, 32 -> 64, 12x12, batch 2: 8.3 and 6.3, input gradient 8.1 and 6.2; 1x1, 384 -> 64, 9x9, batch 4 9.0 and 6.9; filter
 // gradient of 3x3, 24 -> 64, 14x14 7.6 and 5.9.  (Both in one kernel cost the one of 64 rows 0.3 us; 32 rows with up to 256 workgroups of 64, two on a CU: forward 1.15 of the time.)
 namespace rows64 {
 template <int MODE>

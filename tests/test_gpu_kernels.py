@@ -860,6 +860,37 @@ def test_convolutions_of_few_results_in_blocks_of_32_rows_match_64_bits(case):
     assert (np.abs(out.cpu().numpy() - want) <= 2e-7 * size).all()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [1.2345678 * 2.0 ** -122, float("inf"), float("nan")])
+@pytest.mark.parametrize("R", [1, 3])
+def test_convolution_of_few_results_has_the_same_bits_with_and_without_statistics(R, value):
+    """The first run of a layer leaves the statistics of its output and works 64 rows at a time, its recomputation 32: rows that hold nothing special must not be worked on
+    another instruction in one of them because of a neighbour that the pieces cannot hold."""
+    torch = torch_mod()
+    N, H, W, C, K = 2, 12, 12, 64, 64
+    g = torch.Generator().manual_seed(3)
+    x, w = torch.randn(N, H, W, C, generator=g), torch.randn(K, R, R, C, generator=g) * 0.1
+    x[0, 0, 5, 7] = value
+    x[1, 7, 11, 60] = value
+    x, w = x.cuda(), w.cuda()
+    gamma, beta = torch.rand(K, generator=g).cuda() + 0.5, torch.randn(K, generator=g).cuda()
+    first, plain, again = (torch.full((N, H, W, K), -1.0, device="cuda") for _ in range(3))
+    stats, scratch = torch.empty(2 * K, device="cuda"), torch.empty(1 << 20, device="cuda")
+    dims = (N, H, W, C, K, R, R, 1, R // 2)
+    runs = {
+        "rows64": lambda: monet.call("monet_conv_fwd_bn_stats", None, x.data_ptr(), w.data_ptr(), first.data_ptr(), *dims, None, 0, stats.data_ptr(), 1e-5, scratch.data_ptr(), scratch.numel() * 4),
+        "rows32": lambda: monet.call("monet_conv_fwd", None, x.data_ptr(), w.data_ptr(), plain.data_ptr(), *dims, 1, None, 0),
+    }
+    for form, call in runs.items():
+        assert any(form + "::conv_short_kernel<0>" in k for k in kernels_of(torch, call))
+    stats = torch.cat([torch.randn(K, generator=g), torch.rand(K, generator=g) + 0.5]).cuda()      # of finite values
+    monet.call("monet_bn_apply", None, first.data_ptr(), first.data_ptr(), gamma.data_ptr(), beta.data_ptr(), stats.data_ptr(), N * H * W, K)
+    monet.call("monet_bn_apply", None, plain.data_ptr(), plain.data_ptr(), gamma.data_ptr(), beta.data_ptr(), stats.data_ptr(), N * H * W, K)
+    monet.call("monet_conv_fwd_bn_apply", None, x.data_ptr(), w.data_ptr(), again.data_ptr(), *dims, 0, None, 0, gamma.data_ptr(), beta.data_ptr(), stats.data_ptr())
+    bits = [t.view(torch.int32).cpu() for t in (first, plain, again)]
+    assert torch.equal(bits[0], bits[1]) and torch.equal(bits[0], bits[2])
+
+
 # tile shapes and wave groups of the forward pass and the input gradient
 GROUP_CASES = [
     # N, H, W, C, K, R, stride, pad, splits; kernel of the forward pass and of the input gradient: rows / 64, columns / 32, loader, groups (None: the form of few results)
