@@ -227,15 +227,15 @@ constexpr int STEM7_STEPS = 11;
 constexpr int64_t STEM7_WORKGROUPS = 512;      // two on a CU: 416 us; 768 450, 1024 460, 256 489 (batch 184; each loads its filters once)
 
 struct Stem7Geom {
-    StemGeom g;              // xlead = 0
-    unsigned per_img, img_mul, img_shift, col_mul, col_shift, qn_mul, qn_shift, row4_mul, row4_shift;      // floor(n / d) = umulhi(n, mul) >> shift; d == 1: mul == 0
+    StemGeom g;              // xlead = 0, whole rows (col_tiles == 1)
+    unsigned img_mul, img_shift, qn_mul, qn_shift, row4_mul, row4_shift;      // floor(n / d) = umulhi(n, mul) >> shift; d == 1: mul == 0
     unsigned bytes;          // of an image
 };
 __device__ __forceinline__ unsigned divide(unsigned n, unsigned mul, unsigned shift) { return mul ? __umulhi(n, mul) >> shift : n; }
-struct Stem7Tile { int n, p0, q0; };
+struct Stem7Tile { int n, p0; };
 __device__ __forceinline__ Stem7Tile stem7_tile(const Stem7Geom &a, unsigned tile) {
-    const unsigned n = divide(tile, a.img_mul, a.img_shift), t = tile - n * a.per_img, row = divide(t, a.col_mul, a.col_shift);
-    return {(int)n, (int)row * a.g.nrow, (int)(t - row * (unsigned)a.g.col_tiles) * a.g.qn};
+    const unsigned n = divide(tile, a.img_mul, a.img_shift);
+    return {(int)n, (int)(tile - n * (unsigned)a.g.row_tiles) * a.g.nrow};
 }
 
 // The rows under a tile in pieces of 16 bytes, piece tid + k * nthreads; four floats of a row at any offset, zero where the image ends.
@@ -243,7 +243,9 @@ __device__ __forceinline__ void stem7_fill_load(bf4 (&v)[FILL], const float *__r
     const StemGeom &gm = a.g;
     const int row4 = gm.rowlen / 4, rowf = gm.W * 3;
     const __amdgpu_buffer_rsrc_t r = buffer_of((const char *)x + (int64_t)at.n * a.bytes, a.bytes);
-    const int h0 = at.p0 * 2 - gm.pad, f0 = (at.q0 * 2 - gm.pad) * 3;
+    int f0 = -gm.pad * 3;
+    asm volatile("" : "+s"(f0));      // anew for every tile: kept from tile to tile, the places in a row would spill (0.4 us a launch)
+    const int h0 = at.p0 * 2 - gm.pad;
 #pragma unroll
     for (int k = 0; k < FILL; ++k) {
         const int idx = tid + k * nthreads, ri = (int)divide((unsigned)idx, a.row4_mul, a.row4_shift), f = f0 + 4 * (idx - ri * row4), h = h0 + ri;
@@ -316,13 +318,11 @@ __global__ __launch_bounds__(256, 2) void stem7_fwd_kernel(const float *__restri
             const int pr = gm.nrow == 1 ? 0 : (int)divide((unsigned)m, a.qn_mul, a.qn_shift);
             return (pr * ST * gm.rowlen + (m - pr * gm.qn) * ST * 3) / 2;
         };
-        const auto [n, p0, q0] = stem7_tile(a, tile);
+        const auto [n, p0] = stem7_tile(a, tile);
         const int nblk = min(MBW, (gm.nrow * gm.qn + 31) / 32 - MBW * mg);      // position blocks of the nominal tile this wave works on
-        const int rows_here = min(gm.nrow, gm.P - p0), cols_here = min(gm.qn, gm.Q - q0);
-        const int npos = gm.nrow == 1 ? cols_here : rows_here * gm.qn;
         // the descriptor ends with the tile: a position beyond it is not stored
         const unsigned kbytes = (unsigned)gm.K * 4u;
-        const __amdgpu_buffer_rsrc_t ry = buffer_of(y + (((int64_t)n * gm.P + p0) * gm.Q + q0) * gm.K, (unsigned)npos * kbytes);
+        const __amdgpu_buffer_rsrc_t ry = buffer_of(y + ((int64_t)n * gm.P + p0) * gm.Q * gm.K, (unsigned)(min(gm.nrow, gm.P - p0) * gm.Q) * kbytes);
         const unsigned voff = (unsigned)(32 * MBW * mg + 4 * h) * kbytes + (unsigned)(nb * 32 + l32) * 4u;
         auto store_one = [&](int b, int i, const floatx16 &v) { buffer_store(ry, voff, (unsigned)(32 * b + 8 * (i / 4) + (i % 4)) * kbytes, v[i]); };
         auto store = [&](int b, const floatx16 &v) {
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256, 2) void stem7_fwd_kernel(const float *__restri
             const int total = gm.rows_in * (gm.rowlen / 4);
             for (int idx = tid; idx < total; idx += nthreads) {      // the rows as they are
                 const int ri = idx / (gm.rowlen / 4), e = 4 * (idx - ri * (gm.rowlen / 4));
-                const int hh = p0 * ST - gm.pad + ri, f = (q0 * ST - gm.pad) * 3 + e;
+                const int hh = p0 * ST - gm.pad + ri, f = e - gm.pad * 3;
                 for (int u = 0; u < 4; ++u)
                     rows[4 * idx + u] = (unsigned)hh < (unsigned)gm.H && (unsigned)(f + u) < (unsigned)(gm.W * 3) ? x[((int64_t)n * gm.H + hh) * gm.W * 3 + f + u] : 0.0f;
             }
@@ -699,14 +699,14 @@ void launch_stem_fwd(hipStream_t st, const float *x, const float *w, float *y, c
         StemGeom &gm = a.g = sp.gm;
         gm.xlead = 0;
         gm.rowlen = ((gm.qn - 1) * 6 + 24 + 3) / 4 * 4;      // the last window's third group of eight ends inside
-        a.per_img = (unsigned)(gm.row_tiles * gm.col_tiles);
-        magic_of(a.per_img, a.img_mul, a.img_shift);
-        magic_of((unsigned)gm.col_tiles, a.col_mul, a.col_shift);
+        magic_of((unsigned)gm.row_tiles, a.img_mul, a.img_shift);
         magic_of((unsigned)gm.qn, a.qn_mul, a.qn_shift);
         magic_of((unsigned)gm.rowlen / 4, a.row4_mul, a.row4_shift);
-        a.bytes = (unsigned)(gm.H * gm.W * 12);
+        const int64_t image = (int64_t)gm.H * gm.W * 12;
+        a.bytes = (unsigned)image;
         const size_t bytes = (size_t)gm.rows_in * gm.rowlen * 6 + (size_t)gm.K / 32 * STEM7_STEPS * 1024;
-        if (bytes <= 64 * 1024 && (int64_t)gm.H * gm.W < ((int64_t)1 << 28) && gm.tiles < ((int64_t)1 << 30)) {      // (beyond: 96 and 128 channels over many rows)
+        // Beyond 64 KiB (64 channels and 168 positions in a row or more, 96 and 123, 128 and 78, rows cut into segments among them) the fp32 instruction stays.
+        if (gm.col_tiles == 1 && bytes <= 64 * 1024 && image < 12ll << 28 && gm.tiles < ((int64_t)1 << 30)) {
             hipLaunchKernelGGL(stem7_fwd_kernel, dim3((unsigned)std::min(sp.gm.tiles, STEM7_WORKGROUPS)), dim3(block), bytes, st, x, w, y, a);
             hip_check(hipGetLastError(), "stem_fwd launch");
             return;

@@ -1611,17 +1611,24 @@ def stem7_64(x, w, pad):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case", [
-    # N, H, W, K, pad
-    (1, 7, 7, 32, 0),          # one position
-    (2, 9, 40, 64, 3),         # whole rows, several in a tile
-    (3, 61, 63, 64, 3),        # rows at odd offsets of a 16-byte piece; 224 positions are seven rows of 32
-    (1, 12, 379, 64, 0),       # 187 positions in a row: one row a tile (wider ones are refused: more than eight pieces of 16 bytes per thread)
-    (2, 20, 96, 32, 3),        # one block of channels, the last tile two rows of four
-    (2, 65, 65, 96, 2),        # three blocks of channels, one group of position blocks
-    (12, 224, 224, 64, 3),     # 672 tiles: some workgroups take two, their waves' groups change places
+@pytest.mark.parametrize("case, pieces", [
+    # N, H, W, K, pad; whether LDS holds the rows in pieces (64 KiB)
+    ((1, 7, 7, 32, 0), True),          # one position
+    ((2, 9, 40, 64, 3), True),         # whole rows, several in a tile
+    ((3, 61, 63, 64, 3), True),        # rows at odd offsets of a 16-byte piece; 224 positions are seven rows of 32
+    ((2, 12, 300, 64, 3), True),       # 150 positions in a row: one row a tile
+    ((1, 12, 339, 64, 0), True),       # 167
+    ((1, 12, 341, 64, 0), False),      # 168
+    ((1, 12, 379, 64, 0), False),      # 187 (wider ones are refused: more than eight pieces of 16 bytes per thread)
+    ((2, 20, 96, 32, 3), True),        # one block of channels, the last tile two rows of four
+    ((2, 65, 65, 96, 2), True),        # three blocks of channels, one group of position blocks
+    ((2, 33, 65, 128, 3), True),       # four
+    ((1, 20, 154, 128, 3), True),      # 77 positions in a row, one row a tile
+    ((1, 20, 156, 128, 3), False),     # 78
+    ((1, 20, 300, 128, 3), False),     # 150: a segment of 128 and one of 22
+    ((12, 224, 224, 64, 3), True),     # 672 tiles: some workgroups take two, their waves' groups change places
 ])
-def test_stem_7x7_on_pieces_matches_64_bits(case):
+def test_stem_7x7_on_pieces_matches_64_bits(case, pieces):
     """147 products in eleven steps, one rounding each: 7e-8 measured, bound 3e-7 (the fp32 instruction 2.2e-7)."""
     torch = torch_mod()
     N, H, W, K, pad = case
@@ -1630,7 +1637,8 @@ def test_stem_7x7_on_pieces_matches_64_bits(case):
     want = stem7_64(x, w, pad)
     y = torch.full(want.shape, float("nan"), dtype=torch.float32, device="cuda")
     dx, dw = dev(x), dev(w)
-    monet.call("monet_conv_stem_fwd", None, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), N, H, W, K, 7, 7, 2, pad)
+    names = kernels_of(torch, lambda: monet.call("monet_conv_stem_fwd", None, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), N, H, W, K, 7, 7, 2, pad))
+    assert any(("stem7_fwd_kernel" if pieces else "stem_fwd_kernel<7, 7, 2>") in k for k in names), names
     got = y.cpu().numpy()
     assert np.linalg.norm(got - want) <= 3e-7 * np.linalg.norm(want)
     assert np.abs(got - want).max() <= 50 * 3e-7 * np.sqrt((want ** 2).mean())
