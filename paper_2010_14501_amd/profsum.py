@@ -25,18 +25,19 @@ def short(name):
 
 # launch classes of bench.py -> the kernels their launches consist of (regular expressions on the short kernel name).
 # conv_tile_kernel<MODE, WM, WN, FAST, USE, groups>: MODE 0 forward, 1 input gradient, 2 filter gradient; USE 0 implicit GEMM,
-# 1 / 2 / 3 the batched GEMMs of a Winograd forward pass / input gradient / filter gradient; conv_short_kernel<MODE>.  Linear and transposed
+# 1 / 2 / 3 the batched GEMMs of a Winograd forward pass / input gradient / filter gradient; rows32:: and rows64::conv_short_kernel<MODE>.  Linear and transposed
 # convolution layers run on the same kernels, so their launches are counted with the class that shares the kernel.
 GROUPS = [
-    (("conv_fwd", "linear_fwd", "tconv_dgrad"), [r"^conv_tile_kernel<0, \d+, \d+, \w+, 0, \d+>$", r"^conv_short_kernel<0>$"]),
-    (("conv_dgrad", "linear_dgrad", "tconv_fwd"), [r"^conv_tile_kernel<1, \d+, \d+, \w+, 0, \d+>$", r"^conv_short_kernel<1>$"]),
-    (("conv_wgrad", "linear_wgrad", "tconv_wgrad"), [r"^conv_tile_kernel<2, \d+, \d+, \w+, 0, \d+>$", r"^conv_short_kernel<2>$"]),
+    (("conv_fwd", "linear_fwd", "tconv_dgrad"), [r"^conv_tile_kernel<0, \d+, \d+, \w+, 0, \d+>$", r"^(rows\d+::)?conv_short_kernel<0>$", r"^stem7?_fwd_kernel"]),
+    (("conv_dgrad", "linear_dgrad", "tconv_fwd"), [r"^conv_tile_kernel<1, \d+, \d+, \w+, 0, \d+>$", r"^(rows\d+::)?conv_short_kernel<1>$"]),
+    (("conv_wgrad", "linear_wgrad", "tconv_wgrad"), [r"^conv_tile_kernel<2, \d+, \d+, \w+, 0, \d+>$", r"^(rows\d+::)?conv_short_kernel<2>$", r"^stem7?_wgrad_kernel",
+                                                      r"^pw_wgrad_kernel"]),
     (("conv_fwd_winograd",), [r"^wino4?_filter_kernel<false>$", r"^wino4?_input_kernel<0>$", r"^conv_tile_kernel<0, \d+, \d+, \w+, 1, \d+>$",
                               r"^wino4?_output_kernel<false>$", r"^wino4_fused_kernel<false", r"^wino4_pieces_kernel<false", r"^wino4_filter_(fused|pieces)_kernel<false"]),
     (("conv_dgrad_winograd",), [r"^wino4?_filter_kernel<true>$", r"^wino4?_input_kernel<1>$", r"^conv_tile_kernel<0, \d+, \d+, \w+, 2, \d+>$",
                                 r"^wino4?_output_kernel<true>$", r"^wino4_fused_kernel<true", r"^wino4_pieces_kernel<true", r"^wino4_filter_(fused|pieces)_kernel<true"]),
     (("conv_wgrad_winograd",), [r"^wino4?_input_kernel<2>$", r"^wino4?_dy_kernel$", r"^conv_tile_kernel<2, \d+, \d+, \w+, 3, \d+>$",
-                                r"^wino4?_filter_back_kernel$"]),
+                                r"^wino4?_filter_back_kernel$", r"^wino4_vertical_kernel$", r"^wino4_wgrad_kernel$"]),
     (("bn_bwd", "relu_bn_bwd", "relu_add_bn_bwd"), [r"^bn_bwd_"]),
     (("bn_relu_fwd", "bn_add_relu_fwd", "bn_relu_apply", "bn_add_relu_apply", "add_relu_fwd"), [r"^fwd_chain_kernel"]),
     (("dwconv_fwd", "dwconv_dgrad"), [r"^dw3_row_kernel", r"^dw3_dgrad_s2_kernel", r"^dw_fwd_kernel", r"^dw_dgrad_kernel"]),
