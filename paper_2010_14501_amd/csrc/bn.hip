@@ -700,24 +700,24 @@ __global__ __launch_bounds__(512) void bn_bwd_apply(const float *__restrict__ dy
 
 // Both passes in one for tensors of few rows: a workgroup takes 2^gw_shift channel groups and all rows, up to four per thread, which stay in registers between the sums and the apply
 // step, together with what is accumulated on.  Threads of a group are added lanes first, then waves in order.  Every XCD has one contiguous share of the channels, in whole 128-byte lines,
-// since pieces of 16 to 64 bytes of a line that belong to different XCDs cost more than the pass saved (1024 x 16384, us: 63 in two passes, 58 with neighbours on different XCDs, 37 so;
+// since pieces of 16 to 64 bytes of a line that belong to different XCDs cost more than the pass saved (1024 x 16384, us: 64 in two passes, 58 with neighbours on different XCDs, 37 so;
 // accumulating 73, 75 and 46).
 constexpr int SMALL_THREADS = 1024, SMALL_ROWS = 4, SMALL_GROUPS = 8;      // rows per thread; channel groups at most
 // What bounds it: the cache lines that one CU can ask for, one per row and operand, where two passes over many workgroups cost two or three launches.  Its time over theirs (launches of
-// a graph): ungated, with a ReLU's gradient, with that written to a second tensor, and added to one: 512 x 16 0.75 / 0.75 / 0.79 / 0.80, 980 x 2048 0.56 / 0.50 / 0.61 / 0.56,
-// 1600 x 128 0.83 / 0.87 / 0.97 / 1.02, 2048 x 128 0.89 / 0.93 / 1.06 / 1.11, 4096 x 64 1.31 / 1.30 / 1.58 / 1.81; rows that begin inside a line: 900 x 132 0.68 / 0.73 / 0.79 / 0.98,
-// 1024 x 132 0.71 / 0.75 / 0.82 / 1.06, 512 x 72 0.79 / 0.84 / 0.92 / 1.13, 392 x 72 0.77 / 0.82 / 0.87 / 1.01.  Added to what dx holds, without and with all of that: 1024 x 128 0.75 and 0.90,
-// 512 x 64 0.90 and 1.06; 512 x 132 0.87 and 1.02.  Few rows of very many channels leave most threads idle (1 x 20000 0.99, 1 x 25088 1.16, 49 x 65536 0.98), beyond 512 rows lines are shared
-// (1024 x 20000 0.66 / 0.65 / 0.92 / 0.81, 980 x 25088 0.95 / 0.98 / 1.08 / 1.06).  The second tensor must not be asked for here: unfused, a step calls this without it, and has the same bits.
+// a graph): ungated, with a ReLU's gradient, with that written to a second tensor, and added to one: 512 x 16 0.69 / 0.72 / 0.74 / 0.81, 980 x 2048 0.49 / 0.43 / 0.55 / 0.51,
+// 2048 x 64 0.78 / 0.80 / 0.91 / 1.00, x 128 0.79 / 0.81 / 0.95 / 1.04, 2304 x 128 0.95 / 0.96 / 1.14 / 1.30, 4096 x 64 1.30 / 1.29 / 1.61 / 1.79; rows that begin inside a line: 1024 x 48
+// 0.67 / 0.70 / 0.76 / 0.99, x 100 0.64 / 0.65 / 0.73 / 1.02, 1400 x 100 0.69 / 0.73 / 0.81 / 1.09, 784 x 60 0.69 / 0.72 / 0.79 / 1.00, 900 x 60 0.70 / 0.74 / 0.83 / 1.10.  Added to what dx holds, without and with
+// all of that: 1400 x 64 0.79 and 0.96, 1568 x 128 0.81 and 1.02; 320 x 72 0.78 and 0.97, 392 x 100 0.85 and 1.03, 512 x 72 0.93 and 1.15.  Few rows of very many
+// channels leave most threads idle (1 x 16384 0.71 / 0.83 / 0.80 / 0.90, 1 x 20000 0.88 / 1.03 / 1.02 / 1.17, 64 x 65536 0.82 / 0.91 / 0.87 / 0.95), beyond 512 rows lines are shared
+// (1024 x 20000 0.61 / 0.58 / 0.88 / 0.79, 980 x 25088 0.85 / 0.89 / 1.05 / 1.02).  The second tensor must not be asked for here: unfused, a step calls this without it, and has the same bits.
 bool small_rows(int64_t rows, int C, bool accumulate) {
-    if (rows > 1600 || rows * (C / 4) > INT32_MAX - 4 * SMALL_THREADS * (int64_t)(C / 4)) return false;      // (the kernel counts float4 in 32 bits)
-    const bool lines = C % 32 == 0 || C < 32;      // rows begin at a line (or are less than one)
-    if (rows > 1024) return !accumulate && C <= 256 && lines;
-    if (accumulate && rows > (!lines ? 256 : C > 64 ? 1024 : 392)) return false;
-    if (!lines && rows > (C % 16 == 0 || C > 100 ? 900 : 392)) return false;
-    return (rows >= 64 && rows <= 512) || C <= 20000;
+    if (rows > 2048 || rows * (C / 4) > INT32_MAX - 4 * SMALL_THREADS * (int64_t)(C / 4)) return false;      // (the kernel counts float4 in 32 bits)
+    if ((rows < 64 && C > 16384) || (rows > 512 && C > 20000) || (rows > 1024 && C > 256)) return false;
+    if (C % 32 == 0 || C < 32) return rows <= (accumulate ? 1400 : 2048);      // rows begin at a line (or are less than one)
+    return rows <= (accumulate ? 320 : C % 16 == 0 || C > 64 ? 1024 : 784);
 }
-template <bool FROM_OUT, int RM>
+// ADDS: dx or the second tensor is accumulated on.  N: rows per thread, SMALL_ROWS or one (where rows are few, loads of rows that do not exist cost 5 - 10 %)
+template <bool FROM_OUT, int RM, bool ADDS, int N>
 __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, const void *__restrict__ rt, const float *t, const float *__restrict__ gamma,
                                                               const float *__restrict__ beta, const float *__restrict__ stats, float *dx, int acc, float *side, int side_acc,
                                                               float *__restrict__ dgamma, float *__restrict__ dbeta, int rows, int C, int gw_shift) {
@@ -727,35 +727,48 @@ __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, c
     if (block * gw >= C4) return;      // the shares are rounded up
     const bool here = cg < C4;
     const uint64_t *mask = (const uint64_t *)rt;
-    f4 g[SMALL_ROWS], v[SMALL_ROWS], rv[SMALL_ROWS], o[SMALL_ROWS], so[SMALL_ROWS];
-    unsigned bits[SMALL_ROWS];
-    float sc[4], sh[4], a[4];
-#pragma unroll
-    for (int u = 0; u < SMALL_ROWS; ++u) {
-        const int row = r0 + u * step, i = row * C4 + cg;
-        g[u] = v[u] = rv[u] = o[u] = so[u] = f4{0, 0, 0, 0};
-        bits[u] = 0;
-        if (!here || row >= rows) continue;
-        g[u] = *((const f4 *)dy + i);
-        v[u] = *((const f4 *)t + i);
-        if (RM == 1) bits[u] = (unsigned)(mask[i >> 4] >> ((i & 15) * 4)) & 15u;
-        if (RM >= 2) rv[u] = *((const f4 *)rt + i);
-        if (acc) o[u] = *((const f4 *)dx + i);
-        if (side && side_acc) so[u] = *((const f4 *)side + i);
-    }
+    // Loads without a branch among them (rows and groups that do not exist read the last one) and coefficients read before any is used: the compiler otherwise waits for some of them one by one
+    // (1024 x 256 5.7 and 4.9 us; 512 x 16 from the output, with a ReLU, 5.6 and 4.8).
+    f4 g[N], v[N], rv[N], o[N], so[N];
+    uint64_t word[N];
+    float first[4], scale[4], inv[4];
+    const int group = here ? cg : C4 - 1;
+    auto place = [&](int u) { return min(r0 + u * step, rows - 1) * C4 + group; };
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int c = here ? cg * 4 + j : 0;
-        if (FROM_OUT) { sc[j] = 1.0f / gamma[c]; sh[j] = -beta[c] * sc[j]; }
-        else { sc[j] = stats[C + c]; sh[j] = -stats[c] * sc[j]; }
-        a[j] = gamma[c] * stats[C + c];
+        const int c = group * 4 + j;
+        scale[j] = gamma[c];
+        inv[j] = stats[C + c];
+        first[j] = FROM_OUT ? beta[c] : stats[c];
     }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int i = place(u);
+        g[u] = *((const f4 *)dy + i);
+        v[u] = *((const f4 *)t + i);
+        if (RM == 1) word[u] = mask[i >> 4];
+        if (RM >= 2) rv[u] = *((const f4 *)rt + i);
+        else rv[u] = f4{0, 0, 0, 0};
+        if (ADDS && acc) o[u] = *((const f4 *)dx + i);
+        if (ADDS && side && side_acc) so[u] = *((const f4 *)side + i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float sc[4], sh[4], a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        sc[j] = FROM_OUT ? 1.0f / scale[j] : inv[j];
+        sh[j] = -first[j] * sc[j];
+        a[j] = scale[j] * inv[j];
+    }
+    if (RM == 1)
+#pragma unroll
+        for (int u = 0; u < N; ++u) asm volatile("" : "+v"(word[u]));      // or the first one is read where it is used
     float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int u = 0; u < SMALL_ROWS; ++u) {
+    for (int u = 0; u < N; ++u) {
         if (!here || r0 + u * step >= rows) continue;
         float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w}, vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-        relu_gate<RM>(gg, bits[u], rv[u]);
+        relu_gate<RM>(gg, RM == 1 ? (unsigned)(word[u] >> ((place(u) & 15) * 4)) & 15u : 0u, rv[u]);
         g[u] = f4{gg[0], gg[1], gg[2], gg[3]};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -763,9 +776,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, c
             sum[2 * j + 1] += gg[j] * (vv[j] * sc[j] + sh[j]);
         }
     }
-    for (int o = gw; o < 64; o *= 2)
+    for (int d = gw; d < 64; d *= 2) {      // all eight on their way at once, and the sixteen below
+        float other[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sum[j] += __shfl_xor(sum[j], o);
+        for (int j = 0; j < 8; ++j) other[j] = __shfl_xor(sum[j], d);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[j] += other[j];
+    }
     if ((tid & 63) < gw) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) red[tid >> 6][gl][j] = sum[j];
@@ -773,9 +791,13 @@ __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, c
     __syncthreads();
     if (tid < 8 * gw) {
         const int k = tid >> 3, j = tid & 7;
+        float part[SMALL_THREADS / 64];
+#pragma unroll
+        for (int w = 0; w < SMALL_THREADS / 64; ++w) part[w] = red[w][k][j];
+        __builtin_amdgcn_sched_barrier(0);
         double in_order = 0;
 #pragma unroll
-        for (int w = 0; w < SMALL_THREADS / 64; ++w) in_order += (double)red[w][k][j];
+        for (int w = 0; w < SMALL_THREADS / 64; ++w) in_order += (double)part[w];
         const float s = (float)in_order;
         sums[k][j] = s / (float)rows;
         const int c = (block * gw + k) * 4 + (j >> 1);
@@ -789,15 +811,15 @@ __global__ __launch_bounds__(SMALL_THREADS) void bn_bwd_small(const float *dy, c
         mg[j] = sums[gl][2 * j + 1];
     }
 #pragma unroll
-    for (int u = 0; u < SMALL_ROWS; ++u) {
+    for (int u = 0; u < N; ++u) {
         const int row = r0 + u * step, i = row * C4 + cg;
         if (!here || row >= rows) continue;
-        if (side) *((f4 *)side + i) = side_acc ? g[u] + so[u] : g[u];
+        if (side) *((f4 *)side + i) = ADDS && side_acc ? g[u] + so[u] : g[u];
         const float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w}, vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
         f4 r;
 #pragma unroll
         for (int j = 0; j < 4; ++j) r[j] = a[j] * (gg[j] - mb[j] - (vv[j] * sc[j] + sh[j]) * mg[j]);
-        if (acc) r += o[u];
+        if (ADDS && acc) r += o[u];
         *((f4 *)dx + i) = r;
     }
 }
@@ -833,9 +855,17 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
     if (small_rows(rows, C, accumulate)) {
         int gw_shift = 3;      // and a grid of whole shares: eight XCDs, lines of eight groups
         while (gw_shift > 0 && (rows > (int64_t)SMALL_ROWS * (SMALL_THREADS >> gw_shift) || (1 << (gw_shift - 1)) >= C4)) --gw_shift;
-#define BS(F, RM) hipLaunchKernelGGL((bn_bwd_small<F, RM>), dim3((C4 + 63) / 64 * (64 >> gw_shift)), dim3(SMALL_THREADS), 0, st, dy, relu_t, t, gamma, beta, stats, dx, acc, side, sacc, dgamma, dbeta, (int)rows, C, gw_shift)
+        const int groups = C4 <= 1 << gw_shift ? 1 : (C4 + 63) / 64 * (64 >> gw_shift);
+        const bool one = rows <= SMALL_THREADS >> gw_shift, adds = accumulate || (side && side_acc);
+#define SMALL(F, RM, ADDS, N) hipLaunchKernelGGL((bn_bwd_small<F, RM, ADDS, N>), dim3(groups), dim3(SMALL_THREADS), 0, st, dy, relu_t, t, gamma, beta, stats, dx, acc, side, sacc, dgamma, dbeta, (int)rows, C, gw_shift)
+#define BS(F, RM)                                                                                                   \
+    do {                                                                                                            \
+        if (adds) { if (one) SMALL(F, RM, true, 1); else SMALL(F, RM, true, SMALL_ROWS); }                          \
+        else { if (one) SMALL(F, RM, false, 1); else SMALL(F, RM, false, SMALL_ROWS); }                             \
+    } while (0)
         BOTH(BS);
 #undef BS
+#undef SMALL
         hip_check(hipGetLastError(), "bn_bwd launch");
         return;
     }
@@ -854,7 +884,7 @@ void bn_bwd(hipStream_t st, const float *dy, const float *t, bool from_output, c
     }
     const BwdSums sums{scratch, dgamma, dbeta, rows, slabs};
     // Few slabs and channels: no launch of its own for their sums (512 x 16, before bn_bwd_small took it: a step with four such layers 190.6 -> 185.3 us).  Beyond 16
-    // slabs or 256 channels every workgroup would read more than a launch takes.  Reached by tensors that small_rows leaves here, up to 1344 rows of 36 channels, 2048 of 16 and 8192 of four,
+    // slabs or 256 channels every workgroup would read more than a launch takes.  Reached by tensors that small_rows leaves here, up to 1344 rows of 36 channels and 8192 of four, 2048 of 16 accumulating,
     // and where scratch holds few slabs.
     if (slabs <= FEW_SLABS && C <= FEW_CHANNELS) {
         BOTH(BAF);

@@ -1009,12 +1009,11 @@ def test_cut_input_gradients_that_accumulate_take_the_faster_form(case):
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows, C, slabs, kernel", [
     # slabs: partial results that the scratch holds (0: 4 MiB of them)
-    (1, 4, 0, "small"), (33, 16, 0, "small"), (512, 16, 0, "small"), (2047, 16, 0, "few"), (4099, 16, 0, "final"), (70, 60, 0, "small"), (300, 256, 0, "small"),
+    (1, 4, 0, "small"), (33, 16, 0, "small"), (512, 16, 0, "small"), (2047, 16, 0, "small"), (4099, 16, 0, "final"), (70, 60, 0, "small"), (300, 256, 0, "small"),
     (300, 260, 0, "small"), (40, 1024, 0, "small"),
     (8192, 4, 0, "few"), (8193, 4, 0, "final"),                          # 16 and 17 slabs of 512 rows
-    (2048, 16, 0, "few"), (2049, 16, 0, "final"),                        # of 128
-    (1000, 36, 0, "few"), (1344, 36, 0, "few"), (1345, 36, 0, "final"),      # nine channel groups: of 64, rounded up to three sweeps of 28
-    (1700, 256, 16, "few"), (1700, 256, 17, "final"), (1700, 260, 16, "final"),
+    (1025, 36, 0, "few"), (1344, 36, 0, "few"), (1345, 36, 0, "final"),      # nine channel groups: of 64, rounded up to three sweeps of 28
+    (2500, 256, 16, "few"), (2500, 256, 17, "final"), (2500, 260, 16, "final"),
     (5000, 20, 1, "few"),
 ])
 def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C, slabs, kernel):
@@ -1046,9 +1045,10 @@ def test_bn_backward_of_few_and_many_slabs_matches_64_bits(rows, C, slabs, kerne
 
 # the edges of what one launch takes and of the rows and channel groups a workgroup is given: rows, channels, whether one launch takes them written and accumulated
 ONE_LAUNCH_CASES = [
-    (1, 4, 1, 1), (2, 36, 1, 1), (49, 1028, 1, 1), (512, 32, 1, 0), (392, 64, 1, 1), (393, 64, 1, 0), (393, 68, 0, 0), (257, 100, 1, 0), (256, 100, 1, 1), (513, 20, 1, 0), (900, 48, 1, 0),
-    (901, 48, 0, 0), (900, 104, 1, 0), (901, 104, 0, 0), (1024, 48, 0, 0), (1024, 96, 1, 1), (1024, 2048, 1, 1), (1025, 96, 1, 0), (1025, 260, 0, 0), (1600, 256, 1, 0), (1600, 288, 0, 0),
-    (1601, 32, 0, 0), (1600, 28, 1, 0), (2048, 256, 0, 0), (2049, 64, 0, 0), (4096, 60, 0, 0), (4097, 8, 0, 0), (1024, 25088, 0, 0), (63, 20004, 0, 0), (64, 20004, 1, 1), (1, 65536, 0, 0),
+    (1, 4, 1, 1), (2, 36, 1, 1), (49, 1028, 1, 1), (512, 32, 1, 1), (1400, 64, 1, 1), (1401, 64, 1, 0), (2048, 256, 1, 0), (2049, 32, 0, 0), (2048, 28, 1, 0), (513, 20, 1, 1), (1025, 288, 0, 0),
+    (320, 68, 1, 1), (321, 68, 1, 0), (320, 36, 1, 1), (784, 60, 1, 0), (785, 60, 0, 0), (1024, 68, 1, 0), (1025, 68, 0, 0), (1024, 48, 1, 0), (1025, 48, 0, 0), (128, 132, 1, 1), (129, 132, 1, 1),
+    (1024, 2048, 1, 1), (1025, 260, 0, 0), (2049, 64, 0, 0), (4096, 60, 0, 0), (4097, 8, 0, 0), (1024, 25088, 0, 0), (63, 16388, 0, 0), (63, 16384, 1, 1), (64, 20004, 1, 1),
+    (1, 65536, 0, 0),
 ]
 
 
@@ -1799,10 +1799,10 @@ def test_batchnorm_matches_oracle(rows, C):
 
 
 # edges of the ranges small tensors are cut into: one sweep of 256 16-byte elements per workgroup (64 rows of 16 channels), 512
-# workgroups, slabs of two sweeps, the 256th slab; channel groups that are no power of two, and more than 512 of them.  (The backward pass of up to 1024 rows and some more goes through one
+# workgroups, slabs of two sweeps, the 256th slab; channel groups that are no power of two, and more than 512 of them.  (The backward pass of up to 2048 rows goes through one
 # kernel, which leaves the scratch alone.)
 @pytest.mark.parametrize("rows,C", [(3, 4), (63, 16), (64, 16), (65, 16), (127, 16), (129, 16), (32767, 16), (32769, 16), (300, 24), (9, 2052),
-                                    (1601, 16), (1663, 16), (1664, 16), (1665, 16), (4099, 24), (1100, 2052), (8191, 4), (8193, 4)])
+                                    (2111, 16), (2112, 16), (2113, 16), (4099, 24), (1100, 2052), (8191, 4), (8193, 4)])
 @pytest.mark.parametrize("slabs", [1, 3, 1024])
 def test_batchnorm_backward_on_small_tensors(rows, C, slabs):
     torch = torch_mod()
