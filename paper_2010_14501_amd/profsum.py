@@ -59,7 +59,7 @@ def cmd_stats(a):
     with open(a.csv[0]) as fh:
         rows = list(csv.DictReader(fh))
     lines = [f"# {a.title}", "", "Command (run from the repo root on the MI355X box):", ""] + [f"    {c}" for c in a.cmd] + [
-        "", "rocprofv3 kernel statistics (all launches of the run: warm-up, timed steps and the per-launch-timed pass):", "",
+        "", "rocprofv3 kernel statistics (all launches of the run):", "",
         f"{'kernel':<92} {'calls':>6} {'total ms':>10} {'avg us':>10} {'%':>6} {'min us':>9} {'max us':>9}"]
     for r in rows[:a.top]:
         lines.append(f"{short(r['Name']):<92} {int(r['Calls']):>6} {int(r['TotalDurationNs']) / 1e6:>10.3f} "
