@@ -133,7 +133,11 @@ int64_t monet_conv_im2col_workspace_bytes(int N, int H, int W, int C, int K, int
  * what the forward kernel stages per workgroup (the 7x7 filter with 32 output channels, or on rows wider than about 380
  * pixels).  Filter gradient: splits >= 2 and a device
  * workspace of min(splits, 1024, tiles) * K * R * S * 3 floats, tiles = N * ceil(P / rows per tile) * segments (partial
- * results of the workgroups, added in a fixed order: two calls agree bit for bit).  monet_conv_fwd (splits == 1, no
+ * results of the workgroups, added in a fixed order: two calls agree bit for bit).  The 7x7 filter's products are worked in six terms of
+ * bf16 pieces as in monet_conv_fwd, to 2^-24 of a product at worst; normwise error of a layer 7e-8 forward and 3e-7 in the filter
+ * gradient (the fp32 matrix instruction: 2.2e-7 and 8.5e-7), and a workgroup's tile or, in the filter gradient, all its tiles are worked once
+ * more on that instruction where the pieces do not hold the numbers.  On it stay the 3x3 filters and the 7x7 forward pass over
+ * output rows of more than 167, 122 and 77 positions with 64, 96 and 128 channels (128: of 60 to 64 as well).  monet_conv_fwd (splits == 1, no
  * accumulation) and monet_conv_wgrad take these forms by themselves where they apply. */
 int monet_conv_stem_fwd(void *stream, const float *x, const float *w, float *y, int N, int H, int W, int K, int R, int S, int stride, int pad);
 int monet_conv_stem_wgrad(void *stream, const float *x, const float *dy, float *dw, int N, int H, int W, int K, int R, int S, int stride,
@@ -152,7 +156,11 @@ int monet_conv_pointwise_wgrad(void *stream, const float *x, const float *dy, fl
  * two buffers of P*K*C floats (the transformed filter gradient and one chunk's share of it, added chunk after chunk)
  * and up to 1024 / (P * ceil(K/128) * ceil(C/128)) more of them for the partial sums of a chunk's reduction ranges;
  * monet_conv_winograd_wgrad_workspace_bytes returns the size for chunks of about half a GiB, smaller sizes down to one
- * image per chunk are accepted (the result then differs by rounding: another order of the sum over images). */
+ * image per chunk are accepted (the result then differs by rounding: another order of the sum over images).
+ * m = 4, few blocks of 64 channels or few tiles (at most five pairs of blocks where K or C is at most 64, at most six with 256 to 900 or at
+ * least 3000 tiles of 4x4; up to 128 tiles, at most 42 pairs): only the vertical half of the transforms goes through the same workspace, per image of a chunk
+ * 6 * ceil(H/4) * ((4 ceil(W/4) + 2) * C + 4 ceil(W/4) * K) floats, beside the P*K*C floats of the transformed filter gradient and between
+ * one and 1024 partial results of as many, one per reduction range.  Chunks and ranges follow the size given, and every size accepted above is. */
 int monet_conv_winograd_wgrad(void *stream, const float *x, const float *dy, float *dw, int N, int H, int W, int C, int K,
                               int m, float *ws, size_t ws_bytes);
 int64_t monet_conv_winograd_wgrad_workspace_bytes(int N, int H, int W, int C, int K, int m);

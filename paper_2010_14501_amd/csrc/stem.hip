@@ -11,19 +11,20 @@
 // filter row is padded from 3 S to the next even number (the matrix instruction takes two reduction indices; the filter
 // value of the padding is zero, its input value a float of the position's own window read a second time).
 //
-// Forward: mfma_f32_32x32x2f32 with A = positions x reduction (lane (m, h) reads LDS[off(m) + r * rowlen + 2 t + h]),
+// Forward, 3x3 filters and 7x7 ones whose rows in pieces exceed LDS (stem7_fwd_kernel below takes the others): mfma_f32_32x32x2f32 with A = positions x reduction
+// (lane (m, h) reads LDS[off(m) + r * rowlen + 2 t + h]),
 // B = the filters of 32 output channels, resident in registers for the whole launch (R * ceil(3 S / 2) values per lane).
 // A wave takes four blocks of 32 consecutive positions and 32 output channels; a workgroup (K / 32 waves per group of
 // four blocks, at most four waves) one tile of up to 224 positions: whole output rows if they fit, else a segment of
 // one row.  Workgroups loop over tiles.
 //
-// Filter gradient: dw[k][r][j] = sum_m dy[m][k] * x_row(m, r)[j]: A = dy (positions are the reduction index now, read
+// Filter gradient, 7x7: dw[k][r][j] = sum_m dy[m][k] * x_row(m, r)[j]: A = dy (positions are the reduction index now, read
 // from memory in the layout of v_mfma_f32_32x32x16_bf16: lane (k, h) loads dy[m + 8 h + i][k], i < 8), B = lane (col, h) reads
 // LDS[off(m + 8 h + i) + r(col) * rowlen + j(col)] with col = (r, j) flattened; both are split into bf16 pieces in registers
 // (bf16_pieces.hpp), 48 vector instructions per operand beside six matrix instructions per 32 columns.  7x7, 64 channels, 224x224,
 // batch 184: 568 us on the fp32 instruction, 473 so (76 and 92 TFLOP/s), error against 64 bits 8.5e-7 and 3.1e-7; bound by the chain of LDS reads,
 // splits and matrix instructions of two waves per SIMD (256 registers; the compiler spills 32 of them around the second pass in fp32, none
-// inside the loop over tiles).  The 3x3 filters keep the fp32 instruction.  Wave kb of a workgroup owns the 32 output
+// inside the loop over tiles).  The 3x3 filters keep the fp32 instruction in both directions.  Wave kb of a workgroup owns the 32 output
 // channels 32 kb .. 32 kb + 31 and all R * 3 S columns; the workgroups' partial results are added in a fixed order by
 // split_reduce.
 #include <hip/hip_runtime.h>
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const float *__restric
 // rows do in memory; a filter row's 21 values are three groups of eight (the last three with a filter value of zero), and a reduction step of 16 is two groups, one per half wave: eleven
 // steps.  A window begins 6 elements after its neighbour's, on a word boundary, so that a lane's group is four words in a row.  The first two pieces of the filters of a wave's 32 channels stay
 // in registers for all its tiles (88 of them), the third in LDS.
-// 224x224, 64 channels: batch 184 517 us on the fp32 instruction, 412 so; batch 8 36.4 and 25.4; batch 1 19.8 and 15.0; error against 64 bits 2.2e-7 and 7.0e-8.  What bounds it: 3.1e14 flop of matrix
+// 224x224, 64 channels: batch 184 517 us on the fp32 instruction, 412 so; batch 8 36.4 and 25.4; batch 1 19.8 and 15.0; error against 64 bits 2.2e-7 and 7.0e-8.  What bounds it: 3.1e11 flop of matrix
 // instructions (147 products padded to 176), 250 us at the power limit, and 203 us for everything else, which overlap in part: two waves per SIMD.  Stores between the next block's matrix instructions in place of
 // behind the own block's: 455 -> 410; the next tile's loads before this tile's products: 485 -> 451, waited for before the first store, since the number of stores behind them is not known to the
 // compiler; two blocks at a time 473.  Splitting each window on its way into the instruction had been slower than fp32 (842).
@@ -705,7 +706,7 @@ void launch_stem_fwd(hipStream_t st, const float *x, const float *w, float *y, c
         const int64_t image = (int64_t)gm.H * gm.W * 12;
         a.bytes = (unsigned)image;
         const size_t bytes = (size_t)gm.rows_in * gm.rowlen * 6 + (size_t)gm.K / 32 * STEM7_STEPS * 1024;
-        // Beyond 64 KiB (64 channels and 168 positions in a row or more, 96 and 123, 128 and 78, rows cut into segments among them) the fp32 instruction stays.
+        // Beyond 64 KiB (64 channels and 168 positions in a row or more, 96 and 123, 128 and 78, or two rows of 60 to 64, rows cut into segments among them) the fp32 instruction stays.
         if (gm.col_tiles == 1 && bytes <= 64 * 1024 && image < 12ll << 28 && gm.tiles < ((int64_t)1 << 30)) {
             hipLaunchKernelGGL(stem7_fwd_kernel, dim3((unsigned)std::min(sp.gm.tiles, STEM7_WORKGROUPS)), dim3(block), bytes, st, x, w, y, a);
             hip_check(hipGetLastError(), "stem_fwd launch");

@@ -9,7 +9,7 @@
 //     three bf16 pieces per float (bf16_pieces.hpp) and leaves words of two tiles in LDS;
 //   * eight waves multiply the chunk before, three blocks of 32 x 32 each of the 24 (six positions, 2 x 2 blocks), on v_mfma_f32_32x32x16_bf16 as in conv.hip: six per
 //     fp32 product, the h * h terms and the rest in sums of their own.
-// What bounds it (176x112x112, 128 -> 128: 1.1 ms of vertical maps at 6 TB/s, 1.6 ms of GEMMs): the waves that map, 200 vector instructions a chunk each, of which 144 split; 1.5 us a chunk,
+// What bounds it (176x112x112, 128 -> 128: in eight chunks of images 1.09 ms of vertical maps at 5.2 TB/s, 1.72 ms of GEMMs, 0.05 ms of range sums): the waves that map, 200 vector instructions a chunk each, of which 144 split; 1.5 us a chunk,
 // 1.0 without their loads, 0.9 for the matrix instructions alone.  Words of two tiles keep their LDS reads and writes free of conflicts (a quarter of the LDS cycles with the channels in
 // order).  Measured and not taken: both maps of either operand in this kernel, which reads every patch once for each of its six rows (3390 us against 3105 of the workspace form, 2807 this way);
 // loads four chunks ahead (3 % slower); every partial sum in a place of its own for the range sum to add (1 - 10 % slower than adding to the range's).

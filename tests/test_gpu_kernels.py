@@ -1632,6 +1632,9 @@ def stem7_64(x, w, pad):
     ((2, 20, 96, 32, 3), True),        # one block of channels, the last tile two rows of four
     ((2, 65, 65, 96, 2), True),        # three blocks of channels, one group of position blocks
     ((2, 33, 65, 128, 3), True),       # four
+    ((1, 20, 117, 128, 3), True),      # two rows of 59 positions
+    ((1, 20, 119, 128, 3), False),     # 60
+    ((1, 20, 129, 128, 3), True),      # one row of 65
     ((1, 20, 154, 128, 3), True),      # 77 positions in a row, one row a tile
     ((1, 20, 156, 128, 3), False),     # 78
     ((1, 20, 300, 128, 3), False),     # 150: a segment of 128 and one of 22
