@@ -58,7 +58,7 @@ def load_counters(path):
 def cmd_stats(a):
     with open(a.csv[0]) as fh:
         rows = list(csv.DictReader(fh))
-    lines = [f"# {a.title}", "", "Command (run from the repo root on the MI355X box):", ""] + [f"    {c}" for c in a.cmd] + [
+    lines = [f"# {a.title}", "", "Command (run from the repo root on an MI355X):", ""] + [f"    {c}" for c in a.cmd] + [
         "", "rocprofv3 kernel statistics (all launches of the run):", "",
         f"{'kernel':<92} {'calls':>6} {'total ms':>10} {'avg us':>10} {'%':>6} {'min us':>9} {'max us':>9}"]
     for r in rows[:a.top]:
@@ -87,7 +87,7 @@ def cmd_traffic(a):
     for (k, c), (n, v) in write.items():
         if c == "WRITE_SIZE":
             per_kernel.setdefault(k, [n, 0.0, 0.0])[2] = v * 1024.0 / wf
-    lines = [f"# {a.title}", "", "Commands (run from the repo root on the MI355X box; one counter per run):", ""]
+    lines = [f"# {a.title}", "", "Commands (run from the repo root on an MI355X; one counter per run):", ""]
     lines += [f"    {c}" for c in a.cmd]
     lines += ["", f"Calibration: a plain copy of {a.copy_mib} MiB (reads and writes that much per launch) reads",
               f"FETCH_SIZE = {fraw:.0f} KiB and WRITE_SIZE = {wraw:.0f} KiB per dispatch,",
@@ -122,7 +122,7 @@ def cmd_counters(a):
             agg[k][c] = v
             disp[k] = n
     names = sorted({c for v in agg.values() for c in v})
-    lines = [f"# {a.title}", "", "Commands (run from the repo root on the MI355X box; one counter group per run):", ""]
+    lines = [f"# {a.title}", "", "Commands (run from the repo root on an MI355X; one counter group per run):", ""]
     lines += [f"    {c}" for c in a.cmd]
     lines += ["", "Counter sums over all dispatches of the kernel in the run (counters are per shader engine / XCD summed by rocprofv3):", ""]
     for k in sorted(agg, key=lambda k: -max(agg[k].values())):
